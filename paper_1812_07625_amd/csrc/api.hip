@@ -47,46 +47,55 @@ bool ws_ok(void* ws, size_t have, size_t need)
 
 namespace w2l {
 
-int conv_fwd(const ConvDesc& d, const void* x, const void* w, const float* bias, void* y, int dt, int ydt,
-             hipStream_t st)
+bool conv_fwd_is_generic(const ConvDesc& d, int dt) { return !(dt == W2L_BF16 && conv_fwd_mfma_ok(d)); }
+bool conv_dgrad_is_generic(const ConvDesc& d, int dt, int dydt) { return !(dt == W2L_BF16 && dydt == W2L_BF16 && conv_dgrad_mfma_ok(d)); }
+static bool wgrad_is_generic(const ConvDesc& d, int dt, int dydt)
 {
-    if (dt == W2L_BF16 && conv_fwd_mfma_ok(d)) return conv_fwd_mfma(d, x, w, bias, y, ydt, st);
-    return conv_fwd_generic(d, x, w, bias, y, dt, ydt, st);
+    return d.Cout > 32 && !(dt == W2L_BF16 && dydt == W2L_BF16 && conv_wgrad_mfma_ok(d));
+}
+
+int conv_fwd(const ConvDesc& d, const void* x, const void* w, const float* bias, void* y, int dt, int ydt,
+             hipStream_t st, void* scratch, size_t scratch_bytes)
+{
+    if (!conv_fwd_is_generic(d, dt)) return conv_fwd_mfma(d, x, w, bias, y, ydt, st);
+    return conv_fwd_generic(d, x, w, bias, y, dt, ydt, st, scratch, scratch_bytes);
 }
 
 int conv_dgrad(const ConvDesc& d, const void* dy, const void* w, void* dx, int dt, int dydt, hipStream_t st,
                void* scratch, size_t scratch_bytes)
 {
-    if (dt == W2L_BF16 && dydt == W2L_BF16 && conv_dgrad_mfma_ok(d))
-        return conv_dgrad_mfma(d, dy, w, dx, scratch, scratch_bytes, st);
-    return conv_dgrad_generic(d, dy, w, dx, dt, dydt, st);
+    if (!conv_dgrad_is_generic(d, dt, dydt)) return conv_dgrad_mfma(d, dy, w, dx, scratch, scratch_bytes, st);
+    return conv_dgrad_generic(d, dy, w, dx, dt, dydt, st, scratch, scratch_bytes);
 }
 
-size_t conv_wgrad_scratch_bytes(int Cin, int Cout, int k)
+// scratch of a weight gradient: column sums, then what the kernel of the shape needs
+static size_t wgrad_dbias_scratch(const ConvDesc& d) { return round_up((size_t)DBIAS_CHUNKS * d.Cout * 4, 256); }
+size_t conv_wgrad_scratch_bytes(const ConvDesc& d)
 {
-    return round_up((size_t)DBIAS_CHUNKS * Cout * 4, 256) + conv_wgrad_skinny_scratch(Cin, Cout, k);
+    return wgrad_dbias_scratch(d) + (d.Cout <= 32 ? conv_wgrad_skinny_scratch(d.Cin, d.Cout, d.k) : conv_wgrad_generic_scratch(d));
 }
 
 bool conv_wgrad_fuses_dbias(const ConvDesc& d, int dt, int dydt)
 {
-    return d.Cout > 32 && dt == W2L_BF16 && dydt == W2L_BF16 && conv_wgrad_mfma_takes_dbias(d);
+    return wgrad_is_generic(d, dt, dydt) ||
+           (d.Cout > 32 && dt == W2L_BF16 && dydt == W2L_BF16 && conv_wgrad_mfma_takes_dbias(d));
 }
 
 int conv_wgrad(const ConvDesc& d, const void* x, const void* dy, float* dw, float* dbias, int dt, int dydt,
                int accumulate, void* scratch, hipStream_t st)
 {
     float* dbias_scratch = static_cast<float*>(scratch);
-    float* skinny_scratch =
-        reinterpret_cast<float*>(static_cast<unsigned char*>(scratch) + round_up((size_t)DBIAS_CHUNKS * d.Cout * 4, 256));
+    unsigned char* rest = static_cast<unsigned char*>(scratch) + wgrad_dbias_scratch(d);
+    if (wgrad_is_generic(d, dt, dydt))
+        return conv_wgrad_generic(d, x, dy, dw, dbias, dt, dydt, accumulate, st, rest, conv_wgrad_generic_scratch(d));
     if (dbias && conv_wgrad_fuses_dbias(d, dt, dydt)) return conv_wgrad_mfma(d, x, dy, dw, dbias, accumulate, st);
     if (dbias) {
         // halo frames hold zeros, so summing every frame of the allocation is the same sum
         const int rc = dbias_reduce(dy, dbias, (long long)d.B * d.y_pitch, d.Cout, dydt, accumulate, dbias_scratch, st);
         if (rc) return rc;
     }
-    if (d.Cout <= 32) return conv_wgrad_skinny(d, x, dy, dw, dt, dydt, accumulate, skinny_scratch, st);
-    if (dt == W2L_BF16 && dydt == W2L_BF16 && conv_wgrad_mfma_ok(d)) return conv_wgrad_mfma(d, x, dy, dw, nullptr, accumulate, st);
-    return conv_wgrad_generic(d, x, dy, dw, dt, dydt, accumulate, st);
+    if (d.Cout <= 32) return conv_wgrad_skinny(d, x, dy, dw, dt, dydt, accumulate, reinterpret_cast<float*>(rest), st);
+    return conv_wgrad_mfma(d, x, dy, dw, nullptr, accumulate, st);
 }
 
 }  // namespace w2l
@@ -99,6 +108,11 @@ constexpr int ABI_HALO = LAYOUT_HALO, ABI_SLACK = LAYOUT_SLACK, ABI_SLACK_ZERO =
 size_t haloed_bytes(int B, int frames, int C) { return round_up(((size_t)B * (frames + 2 * ABI_HALO) + ABI_SLACK) * C * 2, 256); }
 bool stage_fwd(int Cin, int Cout, int k, int s, int dt) { return dt == W2L_BF16 && k > 1 && (k - 1) / 2 <= ABI_HALO && Cin % 64 == 0 && Cout >= 16 && s >= 1; }
 bool stage_wgrad(int Cin, int Cout, int k, int s, int dt) { return dt == W2L_BF16 && s == 1 && (k - 1) / 2 <= ABI_HALO && Cin % 8 == 0 && Cout % 8 == 0 && Cout >= 64 && (long long)k * Cin >= 64; }
+// The same for fp32, for the kernels of conv_generic.hip: a copy of 16-byte chunks, i.e. of twice the channels in bf16
+bool stage_f32(int k, int s, int dt) { return dt == W2L_F32 && k > 1 && (k - 1) / 2 <= ABI_HALO && s == 1; }
+bool stage_fwd_f32(int Cin, int k, int s, int dt) { return stage_f32(k, s, dt) && k * Cin % 32 == 0 && Cin % 4 == 0; }
+bool stage_dgrad_f32(int Cin, int Cout, int k, int s, int dt) { return stage_f32(k, s, dt) && Cout % 32 == 0 && Cin % 4 == 0; }
+bool stage_wgrad_f32(int Cin, int Cout, int k, int s, int dt) { return stage_f32(k, s, dt) && Cin % 4 == 0 && Cout % 4 == 0 && Cout > 32; }
 // a strided layer whose stride folds into the channels (fold_stride) is staged as the stride-1 layer it folds to
 bool stage_wgrad_folded(int B, int T, int Cin, int Cout, int k, int s, int dt, ConvDesc& f)
 {
@@ -109,7 +123,10 @@ bool stage_wgrad_folded(int B, int T, int Cin, int Cout, int k, int s, int dt, C
 extern "C" size_t w2l_conv1d_fwd_workspace_bytes(int B, int T, int Cin, int Cout, int k, int stride, int dtype)
 {
     if (check_conv_shape(B, T, Cin, Cout, k, stride)) return 0;
-    return stage_fwd(Cin, Cout, k, stride, dtype) ? haloed_bytes(B, T, Cin) : 0;
+    const ConvDesc d = dense_desc(B, T, Cin, Cout, k, stride);
+    if (stage_fwd(Cin, Cout, k, stride, dtype)) return haloed_bytes(B, T, Cin);
+    if (stage_fwd_f32(Cin, k, stride, dtype)) return haloed_bytes(B, T, 2 * Cin) + conv_fwd_generic_scratch(d);
+    return valid_dtype(dtype) && conv_fwd_is_generic(d, dtype) ? conv_fwd_generic_scratch(d) : 0;
 }
 
 extern "C" int w2l_conv1d_fwd(const void* x, const void* w, const float* bias, void* y, int B, int T, int Cin,
@@ -126,15 +143,18 @@ extern "C" int w2l_conv1d_fwd(const void* x, const void* w, const float* bias, v
     if (workspace && !ws_ok(workspace, ws_bytes, need)) return W2L_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     ConvDesc d = dense_desc(B, T, Cin, Cout, k, stride);
-    if (workspace && need) {
-        rc = pad_layout_bf16(x, workspace, B, T, Cin, T + 2 * ABI_HALO, ABI_HALO, ABI_SLACK_ZERO, st);
+    const bool f32 = stage_fwd_f32(Cin, k, stride, dtype);
+    if (workspace && (f32 || stage_fwd(Cin, Cout, k, stride, dtype))) {
+        const int C = f32 ? 2 * Cin : Cin;
+        rc = pad_layout_bf16(x, workspace, B, T, C, T + 2 * ABI_HALO, ABI_HALO, ABI_SLACK_ZERO, st);
         if (rc) return rc;
         d.x_pitch = T + 2 * ABI_HALO;
         d.x_halo = ABI_HALO;
         d.slack = ABI_SLACK;
-        x = workspace;
+        const size_t copy = haloed_bytes(B, T, C);
+        return conv_fwd(d, workspace, w, bias, y, dtype, y_dtype, st, static_cast<unsigned char*>(workspace) + copy, need - copy);
     }
-    return conv_fwd(d, x, w, bias, y, dtype, y_dtype, st);
+    return conv_fwd(d, x, w, bias, y, dtype, y_dtype, st, workspace, workspace ? need : 0);
 }
 
 namespace w2l {
@@ -186,7 +206,10 @@ extern "C" size_t w2l_conv1d_bwd_data_workspace_bytes(int B, int T, int Cin, int
 {
     if (check_conv_shape(B, T, Cin, Cout, k, stride)) return 0;
     const DgradPrep p = dgrad_prep(B, T, Cin, Cout, k, stride, dtype);
-    return p.ok ? p.total() : 0;
+    if (p.ok) return p.total();
+    if (!valid_dtype(dtype)) return 0;
+    const size_t copy = stage_dgrad_f32(Cin, Cout, k, stride, dtype) ? haloed_bytes(B, T, 2 * Cout) : 0;
+    return copy + conv_dgrad_generic_scratch(dense_desc(B, T, Cin, Cout, k, stride));
 }
 
 extern "C" int w2l_conv1d_bwd_data(const void* dy, const void* w, void* dx, int B, int T, int Cin, int Cout,
@@ -208,7 +231,18 @@ extern "C" int w2l_conv1d_bwd_data(const void* dy, const void* w, void* dx, int 
         // (A 1x1 layer with bf16 dy and whole channel blocks needs none of it: the kernels read its dense dy as it is.)
         const DgradPrep p = dgrad_prep(B, T, Cin, Cout, k, stride, dtype);
         const bool plain_1x1 = k == 1 && stride == 1 && dy_dtype == W2L_BF16 && !p.copy_w;
-        if (!plain_1x1) return conv_dgrad_prepared(p, dy, dy_dtype, w, dx, workspace, st);
+        if (p.ok && !plain_1x1) return conv_dgrad_prepared(p, dy, dy_dtype, w, dx, workspace, st);
+        if (!p.ok) {
+            ConvDesc d = dense_desc(B, T, Cin, Cout, k, stride);
+            if (!stage_dgrad_f32(Cin, Cout, k, stride, dtype)) return conv_dgrad(d, dy, w, dx, dtype, dy_dtype, st, workspace, need);
+            rc = pad_layout_bf16(dy, workspace, B, T, 2 * Cout, T + 2 * ABI_HALO, ABI_HALO, ABI_SLACK_ZERO, st);
+            if (rc) return rc;
+            d.y_pitch = T + 2 * ABI_HALO;
+            d.y_halo = ABI_HALO;
+            d.slack = ABI_SLACK;
+            const size_t copy = haloed_bytes(B, T, 2 * Cout);
+            return conv_dgrad(d, workspace, w, dx, dtype, dy_dtype, st, static_cast<unsigned char*>(workspace) + copy, need - copy);
+        }
     }
     return conv_dgrad(dense_desc(B, T, Cin, Cout, k, stride), dy, w, dx, dtype, dy_dtype, st);
 }
@@ -217,9 +251,10 @@ extern "C" size_t w2l_conv1d_bwd_weight_workspace_bytes(int B, int T, int Cin, i
                                                         int dtype)
 {
     if (check_conv_shape(B, T, Cin, Cout, k, stride)) return 0;
-    size_t n = conv_wgrad_scratch_bytes(Cin, Cout, k);
+    size_t n = conv_wgrad_scratch_bytes(dense_desc(B, T, Cin, Cout, k, stride));
     ConvDesc f;
     if (stage_wgrad(Cin, Cout, k, stride, dtype)) n += haloed_bytes(B, T, Cin) + haloed_bytes(B, T, Cout);
+    else if (stage_wgrad_f32(Cin, Cout, k, stride, dtype)) n += haloed_bytes(B, T, 2 * Cin) + haloed_bytes(B, T, 2 * Cout);
     else if (stage_wgrad_folded(B, T, Cin, Cout, k, stride, dtype, f)) n += haloed_bytes(B, f.T, f.Cin) + haloed_bytes(B, f.T, Cout);
     return n;
 }
@@ -241,7 +276,7 @@ extern "C" int w2l_conv1d_bwd_weight(const void* x, const void* dy, float* dw, f
     unsigned char* ws = static_cast<unsigned char*>(workspace);
     ConvDesc f;
     if (dy_dtype == W2L_BF16 && stage_wgrad_folded(B, T, Cin, Cout, k, stride, dtype, f)) {
-        unsigned char* xp = ws + conv_wgrad_scratch_bytes(Cin, Cout, k);
+        unsigned char* xp = ws + conv_wgrad_scratch_bytes(d);
         unsigned char* dyp = xp + haloed_bytes(B, f.T, f.Cin);
         rc = pad_layout2_bf16(x, xp, f.Cin, dy, dyp, Cout, B, f.T, f.T + 2 * ABI_HALO, ABI_HALO, ABI_SLACK_ZERO, st);
         if (rc) return rc;
@@ -250,10 +285,12 @@ extern "C" int w2l_conv1d_bwd_weight(const void* x, const void* dy, float* dw, f
         f.slack = ABI_SLACK;
         return conv_wgrad(f, xp, dyp, dw, dbias, dtype, dy_dtype, accumulate, workspace, st);
     }
-    if (dy_dtype == W2L_BF16 && stage_wgrad(Cin, Cout, k, stride, dtype)) {
-        unsigned char* xp = ws + conv_wgrad_scratch_bytes(Cin, Cout, k);
-        unsigned char* dyp = xp + haloed_bytes(B, T, Cin);
-        rc = pad_layout2_bf16(x, xp, Cin, dy, dyp, Cout, B, T, T + 2 * ABI_HALO, ABI_HALO, ABI_SLACK_ZERO, st);
+    const bool f32 = stage_wgrad_f32(Cin, Cout, k, stride, dtype);
+    if (f32 || (dy_dtype == W2L_BF16 && stage_wgrad(Cin, Cout, k, stride, dtype))) {
+        const int e = f32 ? 2 : 1;
+        unsigned char* xp = ws + conv_wgrad_scratch_bytes(d);
+        unsigned char* dyp = xp + haloed_bytes(B, T, e * Cin);
+        rc = pad_layout2_bf16(x, xp, e * Cin, dy, dyp, e * Cout, B, T, T + 2 * ABI_HALO, ABI_HALO, ABI_SLACK_ZERO, st);
         if (rc) return rc;
         d.x_pitch = d.y_pitch = T + 2 * ABI_HALO;
         d.x_halo = d.y_halo = ABI_HALO;

@@ -94,26 +94,40 @@ inline bool fold_stride(const ConvDesc& d, ConvDesc& f)
     return true;
 }
 
-// dispatchers (api.hip): MFMA kernels where the shape allows, shape-agnostic kernels otherwise
+// dispatchers (api.hip): bf16 MFMA kernels where the type and shape allow, the kernels for any shape otherwise
+// (*_is_generic).  scratch (optional): for a generic problem the *_generic_scratch() bytes below, for a bf16 data
+// gradient conv_dgrad_scratch_bytes(d); given it, shapes that would leave CUs idle split their reduction
+bool conv_fwd_is_generic(const ConvDesc& d, int dt);
+bool conv_dgrad_is_generic(const ConvDesc& d, int dt, int dydt);
 int conv_fwd(const ConvDesc& d, const void* x, const void* w, const float* bias, void* y, int dt, int ydt,
-             hipStream_t st);
-// scratch (optional): conv_dgrad_scratch_bytes(d) bytes of device memory; given it, shapes that would
-// leave CUs idle split their reduction over two workgroups per tile
+             hipStream_t st, void* scratch = nullptr, size_t scratch_bytes = 0);
 int conv_dgrad(const ConvDesc& d, const void* dy, const void* w, void* dx, int dt, int dydt, hipStream_t st,
                void* scratch = nullptr, size_t scratch_bytes = 0);
 size_t conv_dgrad_scratch_bytes(const ConvDesc& d);
 // scratch: conv_wgrad_scratch_bytes() bytes of device memory
-size_t conv_wgrad_scratch_bytes(int Cin, int Cout, int k);
+size_t conv_wgrad_scratch_bytes(const ConvDesc& d);
 // true where conv_wgrad() produces dbias inside the weight-gradient launch (no separate column-sum kernels)
 bool conv_wgrad_fuses_dbias(const ConvDesc& d, int dt, int dydt);
 int conv_wgrad(const ConvDesc& d, const void* x, const void* dy, float* dw, float* dbias, int dt, int dydt,
                int accumulate, void* scratch, hipStream_t st);
 
+// kernels for any shape and type (conv_generic.hip).  scratch (optional): *_scratch() bytes; given them, a problem
+// with too few tiles for the chip splits its reduction and adds the fp32 sums in a finishing launch
+size_t conv_fwd_generic_scratch(const ConvDesc& d);
+size_t conv_dgrad_generic_scratch(const ConvDesc& d);
+size_t conv_wgrad_generic_scratch(const ConvDesc& d);
 int conv_fwd_generic(const ConvDesc& d, const void* x, const void* w, const float* bias, void* y, int dt, int ydt,
-                     hipStream_t st);
-int conv_dgrad_generic(const ConvDesc& d, const void* dy, const void* w, void* dx, int dt, int dydt, hipStream_t st);
-int conv_wgrad_generic(const ConvDesc& d, const void* x, const void* dy, float* dw, int dt, int dydt, int accumulate,
-                       hipStream_t st);
+                     hipStream_t st, void* scratch = nullptr, size_t scratch_bytes = 0);
+int conv_dgrad_generic(const ConvDesc& d, const void* dy, const void* w, void* dx, int dt, int dydt, hipStream_t st,
+                       void* scratch = nullptr, size_t scratch_bytes = 0);
+int conv_wgrad_generic(const ConvDesc& d, const void* x, const void* dy, float* dw, float* dbias, int dt, int dydt, int accumulate,
+                       hipStream_t st, void* scratch = nullptr, size_t scratch_bytes = 0);
+// The same, leaving the *_parts() planes of fp32 sums ([parts][B * frames][channels], dense) to the finish_* pass that
+// the caller fuses with its next elementwise step.
+int conv_fwd_generic_parts(const ConvDesc& d);
+int conv_dgrad_generic_parts(const ConvDesc& d);
+int conv_fwd_generic_partial(const ConvDesc& d, const void* x, const void* w, int dt, float* part, hipStream_t st);
+int conv_dgrad_generic_partial(const ConvDesc& d, const void* dy, const void* w, int dt, int dydt, float* part, hipStream_t st);
 // narrow outputs (Cout <= 32): row-chunked reduction, SKINNY_CHUNKS partials summed in a fixed order
 enum { SKINNY_CHUNKS = 64 };
 size_t conv_wgrad_skinny_scratch(int Cin, int Cout, int k);
@@ -164,6 +178,19 @@ int glu_fwd_layout(const void* y, void* h, int B, int Tp, int Cout, int dtype, i
                    hipStream_t st);
 int glu_bwd_layout(const void* y, const void* dh, void* dy, int B, int Tp, int Cout, int dtype, int pitch, int halo,
                    int slack, hipStream_t st);
+
+// Finishing passes of a split reduction: part holds `parts` planes of fp32 sums, added in order (elementwise.hip).
+//   rows: + bias -> y in the given layout;  glu_fwd: + bias -> y (dense) and h = GLU(y) as in glu_fwd_layout;
+//   glu_bwd: dh = sums (rounded as the stored dh would be) -> dy as in glu_bwd_layout;
+//   sums: flat, n values -> out (accumulate: added to it) and, from bpart, nb values -> bout (nullable)
+int finish_rows(const float* part, int parts, const float* bias, void* y, int dtype, int B, int frames, int N, int pitch, int halo,
+                hipStream_t st);
+int finish_glu_fwd(const float* part, int parts, const float* bias, void* y, void* h, int B, int Tp, int Cout, int dtype, int pitch,
+                   int halo, int slack, hipStream_t st);
+int finish_glu_bwd(const float* part, int parts, const void* y, void* dy, int B, int Tp, int Cout, int dtype, int pitch, int halo,
+                   int slack, hipStream_t st);
+int finish_sums(const float* part, int parts, long long n, float* out, const float* bpart, int nb, float* bout, int accumulate,
+                hipStream_t st);
 
 // dense bf16 [B*Tp, C] (C % 8 == 0) -> layout with the given pitch / halo / slack, zeros outside the real frames
 // (and `nclear` integers at `clear` set to zero on the way)

@@ -1,184 +1,691 @@
-// Shape-agnostic temporal-convolution kernels (fp32 or bf16 operands, fp32 accumulation).
+// Temporal-convolution kernels for any shape and type, on the fp32 matrix instruction
+// (v_mfma_f32_32x32x2_f32: fp32 operands, fp32 accumulation).
 //
-// These back every shape the MFMA kernels do not take (fp32 tensors, channel counts
-// that are not multiples of 8, strided data gradients).  Each of the three passes is
-// the GEMM C[m,n] = sum_r A(m,r) * B(r,n) over a 64x64 output tile per workgroup,
-// 16-deep LDS panels, 4x4 outputs per thread; the operand functors fold the
-// convolution's indexing (tap offset, stride, zero padding) into the loads, so no
-// unfolded copy of the input is ever made.
-//
-// Definitions (the paper names the op in Sec. 2.3 without a formula):
+// These take every problem that the bf16 kernels do not: fp32 tensors, channel counts that are not multiples of 8,
+// strides that do not fold, calls without workspace.  bf16 operands are widened on their way into LDS, so their
+// products stay exact.  Each of the three passes is the GEMM C[m,n] = sum_r A(m,r) * B(r,n) over the convolution's
+// own tensors -- no unfolded copy of the input is made:
 //   fwd   y[b,t',co]  = bias[co] + sum_{j,ci} w[co,j,ci] * x[b, s t' + j - p, ci]
 //   dgrad dx[b,t,ci]  = sum_{j,co} w[co,j,ci] * dy[b,(t+p-j)/s,co]   (divisible, in range)
 //   wgrad dw[co,j,ci] = sum_{b,t'} dy[b,t',co] * x[b, s t' + j - p, ci]
+// (the paper names the op in Sec. 2.3 without a formula).
+//
+// What bounds them: the fp32 matrix pipe, 256 FLOP per cycle and CU, a sixteenth of the bf16 rate.  A wavefront
+// multiplies for 64 cycles on one dword per lane of either operand, so the operands' way costs little as long as it
+// costs no vector instructions (fp32 matrix instructions run on the vector units), and what is worth something is
+// work for all 1024 SIMDs: the reduction is split over workgroups (any_plan) whose fp32 sums a finishing pass adds in
+// a fixed order -- inside the train step that pass is the layer's GLU, which would be launched anyway.
+// Measured inside the train step of the 10M-parameter network in fp32 (4 x 400 frames, k = 11, 256 -> 512, 4.6 GFLOP
+// a pass; 30 us at the pipe's rate), before (64 x 64 tiles of scalar FMAs, one workgroup per tile) and now: forward
+// 476 -> 46 us, data gradient 1190 -> 58, weight gradient 325 -> 70 (the last two side by side), step 11.4 -> 1.02 ms.
+#include <type_traits>
 #include "common.h"
 
 namespace w2l {
 namespace {
 
-constexpr int TM = 64, TN = 64, TK = 16;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x4a __attribute__((ext_vector_type(4)));
 
-template <class AF, class BF, class EP, bool A_RFAST, bool B_RFAST>
-__global__ __launch_bounds__(256) void gemm_tiled(AF af, BF bf, EP ep, int M, int N, int R)
+// ---- operands ------------------------------------------------------------------------
+// A line is a run of memory: element c of line i is base[off + c], real where lo <= c < hi and zero elsewhere.
+// K_LINES: the lines are the rows (columns) of the output and c runs along the reduction; otherwise the lines are
+// the steps of the reduction and c runs along the output.
+struct Line { long long off; int lo, hi; };
+__device__ __forceinline__ Line no_line() { return Line{0, 0, 0}; }
+
+template <typename T>
+struct XWindow {  // fwd A: m = (b,t') -> x[b, s t' - p ..], r = (j,ci)
+    static constexpr bool K_LINES = true;
+    typedef T type;
+    const T* base; int M, T_, Tp, Cin, k, s, p, pitch, halo;
+    // every line starts and ends on a 16-byte chunk of fp32
+    bool chunks() const { return aligned16(base) && Cin % 4 == 0; }
+    bool fast() const { return chunks() && k * Cin % 32 == 0 && (p == 0 || halo >= p); }
+    __device__ __forceinline__ long long fast_line(int m) const { return line(m < M ? m : M - 1).off; }
+    __device__ __forceinline__ Line line(int m) const
+    {
+        if (m >= M) return no_line();
+        const int b = (unsigned)m / (unsigned)Tp, t0 = s * (m - b * Tp) - p, last = T_ - t0;
+        return Line{((long long)b * pitch + halo + t0) * Cin, (t0 < 0 ? -t0 : 0) * Cin, (last < k ? last : k) * Cin};
+    }
+};
+template <typename T>
+struct WRows {  // fwd B: n = co -> w[co], r = (j,ci)
+    static constexpr bool K_LINES = true;
+    typedef T type;
+    const T* base; int N, KC;
+    bool chunks() const { return aligned16(base) && KC % 4 == 0; }
+    bool fast() const { return chunks() && KC % 32 == 0; }
+    __device__ __forceinline__ long long fast_line(int n) const { return (long long)(n < N ? n : N - 1) * KC; }
+    __device__ __forceinline__ Line line(int n) const { return n < N ? Line{(long long)n * KC, 0, KC} : no_line(); }
+};
+// The frames t of the data gradient with the same (t + p) mod s = ph meet the same taps j = ph, ph + s, .. (taps of
+// them) and read taps consecutive frames of dy, the last tap first: each such phase is a stride-1 problem of its own.
+struct Phase { int ph, taps, first, count; };  // first frame of the phase, frames per utterance
+__host__ __device__ inline Phase phase_of(int ph, int T, int k, int s, int p)
 {
-    __shared__ float As[TK][TM + 1];
-    __shared__ float Bs[TK][TN + 1];
-    const int tid = threadIdx.x;
-    const int tx = tid % 16, ty = tid / 16;
-    const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
-    float acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-
-    for (int r0 = 0; r0 < R; r0 += TK) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int e = tid + i * 256;
-            int rr, mm;
-            if (A_RFAST) { rr = e % TK; mm = e / TK; } else { mm = e % TM; rr = e / TM; }
-            const int m = m0 + mm, r = r0 + rr;
-            As[rr][mm] = (m < M && r < R) ? af(m, r) : 0.f;
-            int nn;
-            if (B_RFAST) { rr = e % TK; nn = e / TK; } else { nn = e % TN; rr = e / TN; }
-            const int n = n0 + nn;
-            const int r2 = r0 + rr;
-            Bs[rr][nn] = (n < N && r2 < R) ? bf(r2, n) : 0.f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int rr = 0; rr < TK; ++rr) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[rr][ty * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = Bs[rr][tx * 4 + j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-            if (m < M && n < N) ep(m, n, acc[i][j]);
-        }
+    Phase q;
+    q.ph = ph;
+    q.taps = ph < k ? (k - ph + s - 1) / s : 0;
+    q.first = ((ph - p) % s + s) % s;
+    q.count = q.first < T ? (T - q.first + s - 1) / s : 0;
+    return q;
 }
+template <typename T>
+struct DyWindow {  // dgrad A: m = (b, frame of the phase) -> its dy frames, r = (q,co), q-th frame <-> tap ph + s (taps-1-q)
+    static constexpr bool K_LINES = true;
+    typedef T type;
+    const T* base; int B, Tp, Cout, s, p, pitch, halo; Phase q;
+    bool chunks() const { return aligned16(base) && Cout % 4 == 0; }
+    bool fast() const { return chunks() && s == 1 && Cout % 32 == 0 && (p == 0 || halo >= p); }
+    __device__ __forceinline__ long long fast_line(int m) const { return line(m < B * q.count ? m : B * q.count - 1).off; }
+    __device__ __forceinline__ Line line(int m) const
+    {
+        if (m >= B * q.count) return no_line();
+        const int b = (unsigned)m / (unsigned)q.count, t = q.first + s * (m - b * q.count);
+        const int u0 = (t + p - q.ph) / s - q.taps + 1, last = Tp - u0;
+        return Line{((long long)b * pitch + halo + u0) * Cout, (u0 < 0 ? -u0 : 0) * Cout, (last < q.taps ? last : q.taps) * Cout};
+    }
+};
+template <typename T>
+struct WCols {  // dgrad B: r = (q,co) -> w[co, tap], n = ci
+    static constexpr bool K_LINES = false;
+    typedef T type;
+    const T* base; int Cin, Cout, k, s; Phase q;
+    // every line starts and ends on a 16-byte chunk of fp32
+    bool chunks() const { return aligned16(base) && Cin % 4 == 0; }
+    bool fast() const { return chunks() && s == 1 && Cout % 32 == 0; }  // the 32 lines of a panel lie in one tap
+    __device__ __forceinline__ long long fast_base(int r) const { return line(r).off; }
+    __device__ __forceinline__ int fast_pitch() const { return k * Cin; }
+    __device__ __forceinline__ int width() const { return Cin; }
+    __device__ __forceinline__ Line line(int r) const
+    {
+        const int t = (unsigned)r / (unsigned)Cout, co = r - t * Cout;
+        return Line{((long long)co * k + q.ph + s * (q.taps - 1 - t)) * Cin, 0, Cin};
+    }
+};
+template <typename T>
+struct DyT {  // wgrad A: r = (b,t') -> dy[b,t'], m = co
+    static constexpr bool K_LINES = false;
+    typedef T type;
+    const T* base; int Tp, Cout, pitch, halo;
+    bool chunks() const { return aligned16(base) && Cout % 4 == 0; }
+    // (the walk of wgrad_t through the frames of a haloed layout)
+    __device__ __forceinline__ long long fast_base(int r) const { return (long long)(halo + r) * Cout; }
+    __device__ __forceinline__ int fast_pitch() const { return Cout; }
+    __device__ __forceinline__ int width() const { return Cout; }
+    __device__ __forceinline__ Line line(int r) const
+    {
+        const int b = (unsigned)r / (unsigned)Tp, tp = r - b * Tp;
+        return Line{((long long)b * pitch + halo + tp) * Cout, 0, Cout};
+    }
+};
+template <typename T>
+struct XShift {  // wgrad B: r = (b,t') -> x[b, s t' - p ..], n = (j,ci)
+    static constexpr bool K_LINES = false;
+    typedef T type;
+    const T* base; int T_, Tp, Cin, k, s, p, pitch, halo;
+    // every line starts and ends on a 16-byte chunk of fp32
+    bool chunks() const { return aligned16(base) && Cin % 4 == 0; }
+    __device__ __forceinline__ long long fast_base(int r) const { return (long long)(halo - p + r) * Cin; }
+    __device__ __forceinline__ int fast_pitch() const { return Cin; }
+    __device__ __forceinline__ int width() const { return k * Cin; }
+    __device__ __forceinline__ Line line(int r) const
+    {
+        const int b = (unsigned)r / (unsigned)Tp, t0 = s * (r - b * Tp) - p, last = T_ - t0;
+        return Line{((long long)b * pitch + halo + t0) * Cin, (t0 < 0 ? -t0 : 0) * Cin, (last < k ? last : k) * Cin};
+    }
+};
 
-// ---- operand functors (time-axis layout: element ((b*pitch + halo + t) * C + c)) ---------
+// ---- outputs -------------------------------------------------------------------------
+// row(m) = element offset of output row m; sums of split z go one plane further each
 template <typename T>
-struct XWindow {  // A(m=(b,t'), r=(j,ci)) = x[b, s t' + j - p, ci]
-    const T* x; int T_, Tp, Cin, s, p, pitch, halo;
-    __device__ float operator()(int m, int r) const {
-        const int b = m / Tp, tp = m - b * Tp;
-        const int j = r / Cin, ci = r - j * Cin;
-        const int t = s * tp + j - p;
-        if (t < 0 || t >= T_) return 0.f;
-        return Elem<T>::load(x, ((size_t)b * pitch + halo + t) * Cin + ci);
+struct StoreRows {  // m = (b, i): frame first + step * i of utterance b
+    T* y; const float* bias; int N, count, first, step, pitch, halo; long long plane;
+    __device__ __forceinline__ long long row(int m) const
+    {
+        const int b = (unsigned)m / (unsigned)count;
+        return ((long long)b * pitch + halo + first + (long long)step * (m - b * count)) * N;
     }
-};
-template <typename T>
-struct WRows {  // B(r=(j,ci), n=co) = w[co, j, ci]
-    const T* w; int KC;
-    __device__ float operator()(int r, int n) const { return Elem<T>::load(w, (size_t)n * KC + r); }
-};
-template <typename T>
-struct DyWindow {  // A(m=(b,t), r=(j,co)) = dy[b, (t+p-j)/s, co]
-    const T* dy; int T_, Tp, Cout, s, p, pitch, halo;
-    __device__ float operator()(int m, int r) const {
-        const int b = m / T_, t = m - b * T_;
-        const int j = r / Cout, co = r - j * Cout;
-        const int u = t + p - j;
-        if (u < 0) return 0.f;
-        const int tp = u / s;
-        if (tp * s != u || tp >= Tp) return 0.f;
-        return Elem<T>::load(dy, ((size_t)b * pitch + halo + tp) * Cout + co);
-    }
-};
-template <typename T>
-struct WCols {  // B(r=(j,co), n=ci) = w[co, j, ci]
-    const T* w; int Cin, Cout, k;
-    __device__ float operator()(int r, int n) const {
-        const int j = r / Cout, co = r - j * Cout;
-        return Elem<T>::load(w, ((size_t)co * k + j) * Cin + n);
-    }
-};
-template <typename T>
-struct DyT {  // A(m=co, r=(b,t')) = dy[b,t',co]
-    const T* dy; int Tp, Cout, pitch, halo;
-    __device__ float operator()(int m, int r) const {
-        const int b = r / Tp, tp = r - b * Tp;
-        return Elem<T>::load(dy, ((size_t)b * pitch + halo + tp) * Cout + m);
-    }
-};
-template <typename T>
-struct XShift {  // B(r=(b,t'), n=(j,ci)) = x[b, s t' + j - p, ci]
-    const T* x; int T_, Tp, Cin, s, p, pitch, halo;
-    __device__ float operator()(int r, int n) const {
-        const int b = r / Tp, tp = r - b * Tp;
-        const int j = n / Cin, ci = n - j * Cin;
-        const int t = s * tp + j - p;
-        if (t < 0 || t >= T_) return 0.f;
-        return Elem<T>::load(x, ((size_t)b * pitch + halo + t) * Cin + ci);
-    }
-};
-template <typename T>
-struct StoreRows {  // out[b, t, n] = v (+ bias[n]); m = (b,t) over `frames` frames per utterance
-    T* y; const float* bias; int N, frames, pitch, halo;
-    __device__ void operator()(int m, int n, float v) const {
-        const int b = m / frames, t = m - b * frames;
-        Elem<T>::store(y, ((size_t)b * pitch + halo + t) * N + n, v + (bias ? bias[n] : 0.f));
-    }
+    __device__ __forceinline__ float add(int n) const { return bias ? bias[n] : 0.f; }
+    __device__ __forceinline__ void store(long long i, float v, int split) const { Elem<T>::store(y + split * plane, (size_t)i, v); }
 };
 struct StoreAcc {
-    float* d; int N; int accumulate;
-    __device__ void operator()(int m, int n, float v) const {
-        const size_t i = (size_t)m * N + n;
-        d[i] = accumulate ? d[i] + v : v;
+    float* d; int N, accumulate; long long plane;
+    __device__ __forceinline__ long long row(int m) const { return (long long)m * N; }
+    __device__ __forceinline__ float add(int) const { return 0.f; }
+    __device__ __forceinline__ void store(long long i, float v, int split) const
+    {
+        float* q = d + split * plane + i;
+        *q = accumulate ? *q + v : v;
     }
 };
 
-template <class AF, class BF, class EP, bool AR, bool BR>
-int launch(AF af, BF bf, EP ep, long long M, long long N, long long R, hipStream_t st)
+// four consecutive elements from c on
+template <typename T>
+__device__ __forceinline__ void load4(const T* base, const Line& l, int c, float (&v)[4])
 {
-    const long long gy = (M + TM - 1) / TM, gx = (N + TN - 1) / TN;
-    if (gy > 65535 || gx > 2147483647LL || M * 1 > 2147483647LL || R > 2147483647LL) return W2L_ERR_SHAPE;
-    hipLaunchKernelGGL((gemm_tiled<AF, BF, EP, AR, BR>), dim3((unsigned)gx, (unsigned)gy), dim3(256), 0, st,
-                       af, bf, ep, (int)M, (int)N, (int)R);
+    const T* q = base + l.off + c;
+    if (c >= l.lo && c + 4 <= l.hi) {
+        if constexpr (sizeof(T) == 4) {
+            const f32x4u u = *reinterpret_cast<const f32x4u*>(q);  // lines start at any element: dword alignment
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = u[e];
+        } else {
+            if ((reinterpret_cast<uintptr_t>(q) & 7) == 0) {
+                const uint2 u = *reinterpret_cast<const uint2*>(q);
+                v[0] = __uint_as_float(u.x << 16);
+                v[1] = __uint_as_float(u.x & 0xffff0000u);
+                v[2] = __uint_as_float(u.y << 16);
+                v[3] = __uint_as_float(u.y & 0xffff0000u);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = Elem<T>::load(q, e);
+            }
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = (c + e >= l.lo && c + e < l.hi) ? Elem<T>::load(q, e) : 0.f;
+    }
+}
+
+constexpr int TILE = 64, PANEL = 32;  // a workgroup's outputs in either direction; steps of the reduction per panel
+
+// One operand's share of a panel: W rows of the output by BK steps of the reduction.
+template <class OP, int W, int BK>
+struct AnyPanel {
+    static constexpr bool KL = OP::K_LINES;
+    // LDS image: [W][BK + 4] (a row pitch of 36 dwords starts 16 consecutive rows on distinct banks) or
+    // [BK][W + 8] (the two halves of a wavefront read lines four apart: 32 banks apart)
+    static constexpr int PITCH = KL ? BK + 4 : W + 8;
+    static constexpr int FLOATS = KL ? W * PITCH : BK * PITCH;
+    static constexpr int CPL = (KL ? BK : W) / 4;  // 4-element chunks per line
+    static constexpr int LPP = 256 / CPL;          // lines that the workgroup's threads cover at once
+    static constexpr int NC = W * BK / 1024;       // chunks per thread
+    static_assert(W * BK % 1024 == 0 && 256 % CPL == 0, "a panel splits evenly over 256 threads");
+    Line ln[KL ? NC : 1];
+    float v[NC][4];
+    static __device__ __forceinline__ int l_of(int i) { return threadIdx.x / CPL + i * LPP; }
+    static __device__ __forceinline__ int c_of() { return threadIdx.x % CPL * 4; }
+    __device__ __forceinline__ void init(const OP& op, int w0, int r_end)
+    {
+        if constexpr (KL) {
+#pragma unroll
+            for (int i = 0; i < NC; ++i) {
+                ln[i] = op.line(w0 + l_of(i));
+                if (ln[i].hi > r_end) ln[i].hi = r_end;
+            }
+        }
+    }
+    __device__ __forceinline__ void load(const OP& op, int w0, int r0, int r_end)
+    {
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            if constexpr (KL) load4(op.base, ln[i], r0 + c_of(), v[i]);
+            else {
+                const int r = r0 + l_of(i);
+                const Line l = r < r_end ? op.line(r) : no_line();
+                load4(op.base, l, w0 + c_of(), v[i]);
+            }
+        }
+    }
+    __device__ __forceinline__ void store(float* lds) const
+    {
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            const f32x4a u = {v[i][0], v[i][1], v[i][2], v[i][3]};
+            *reinterpret_cast<f32x4a*>(lds + l_of(i) * PITCH + c_of()) = u;
+        }
+    }
+    // Operand registers of NB blocks of 32 rows from row w on, for the four instructions of reduction steps
+    // r .. r + 7: instruction q takes step r + q from lanes 0..31 and step r + 4 + q from lanes 32..63, so that a
+    // lane's four values are consecutive in a [W][BK] image.  In a [BK][W] image the NB values of a line are taken
+    // from consecutive rows instead: block i, lane c is row NB * c + i there and 32 * i + c here (at()).
+    template <int NB>
+    static __device__ __forceinline__ void frags(const float* lds, int w, int r, int lane, float (&f)[NB][4])
+    {
+        const int c = lane & 31, h = lane >> 5;
+        if constexpr (KL) {
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                const f32x4a u = *reinterpret_cast<const f32x4a*>(lds + (w + 32 * i + c) * PITCH + r + 4 * h);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) f[i][q] = u[q];
+            }
+        } else {
+            typedef float vec __attribute__((ext_vector_type(NB)));
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const vec u = *reinterpret_cast<const vec*>(lds + (r + 4 * h + q) * PITCH + w + NB * c);
+#pragma unroll
+                for (int i = 0; i < NB; ++i) f[i][q] = u[i];
+            }
+        }
+    }
+    template <int NB> static __device__ __forceinline__ int at(int i, int c) { return KL ? 32 * i + c : NB * c + i; }
+};
+
+// TILE x TILE outputs per workgroup of four wavefronts (2 x 2).  grid.z = splits.  colsum (A by reduction lines, i.e. the weight gradient): the sums of A over the reduction -- the bias
+// gradient -- from the values that pass through the first column of workgroups anyway.
+template <class OA, class OB, class EP>
+__global__ __launch_bounds__(256, 4) void gemm_any_k(OA oa, OB ob, EP ep, int M, int N, int R, int per, int splits, float* colsum, int colsum_acc)
+{
+    constexpr int BM = TILE, BN = TILE, BK = PANEL;
+    using PA = AnyPanel<OA, BM, BK>;
+    using PB = AnyPanel<OB, BN, BK>;
+    constexpr int STAGE = PA::FLOATS + PB::FLOATS, NA = BM / 64, NB = BN / 64;
+    __shared__ __align__(16) float lds[2 * STAGE];
+    const int split = blockIdx.z % splits;
+    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
+    const int r_begin = split * per, r_end = R < r_begin + per ? R : r_begin + per;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wm = (wave >> 1) * (BM / 2), wn = (wave & 1) * (BN / 2);
+    const bool sum_a = !PA::KL && colsum && blockIdx.x == 0;
+    PA pa;
+    PB pb;
+    pa.init(oa, m0, r_end);
+    pb.init(ob, n0, r_end);
+    f32x16 acc[NA][NB];
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    float asum[4] = {0.f, 0.f, 0.f, 0.f};
+    auto fetch = [&](int r0) {
+        pa.load(oa, m0, r0, r_end);
+        pb.load(ob, n0, r0, r_end);
+    };
+    auto put = [&](float* q) {
+        pa.store(q);
+        pb.store(q + PA::FLOATS);
+        if (sum_a) {
+#pragma unroll
+            for (int i = 0; i < PA::NC; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) asum[e] += pa.v[i][e];
+        }
+    };
+    const int steps = r_end > r_begin ? (r_end - r_begin + BK - 1) / BK : 0;
+    if (steps > 0) {
+        fetch(r_begin);
+        put(lds);
+    }
+    __syncthreads();
+    for (int st = 0; st < steps; ++st) {
+        if (st + 1 < steps) fetch(r_begin + (st + 1) * BK);
+        const float* la = lds + (st & 1) * STAGE;
+        const float* lb = la + PA::FLOATS;
+#pragma unroll
+        for (int r = 0; r < BK; r += 8) {
+            float fa[NA][4], fb[NB][4];
+            PA::template frags<NA>(la, wm, r, lane, fa);
+            PB::template frags<NB>(lb, wn, r, lane, fb);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int i = 0; i < NA; ++i)
+#pragma unroll
+                    for (int j = 0; j < NB; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][q], fb[j][q], acc[i][j], 0, 0, 0);
+        }
+        if (st + 1 < steps) put(lds + ((st + 1) & 1) * STAGE);
+        __syncthreads();
+    }
+    float addn[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+        const int n = n0 + wn + PB::template at<NB>(j, lane & 31);
+        addn[j] = n < N ? ep.add(n) : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int m = m0 + wm + PA::template at<NA>(i, 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3));
+            if (m >= M) continue;
+            const long long row = ep.row(m);
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                const int n = n0 + wn + PB::template at<NB>(j, lane & 31);
+                if (n < N) ep.store(row + n, acc[i][j][e] + addn[j], split);
+            }
+        }
+    if (sum_a) {  // thread (line, column chunk) partial sums, added over the lines in order
+        float* red = lds;  // every wavefront is past its last read of the panels
+#pragma unroll
+        for (int e = 0; e < 4; ++e) red[PA::l_of(0) * BM + PA::c_of() + e] = asum[e];
+        __syncthreads();
+        for (int c = threadIdx.x; c < BM; c += 256) {
+            float v = 0.f;
+            for (int l = 0; l < PA::LPP; ++l) v += red[l * BM + c];
+            const int m = m0 + c;
+            if (m < M) {
+                float* q = colsum + (long long)split * M + m;
+                *q = colsum_acc ? *q + v : v;
+            }
+        }
+    }
+}
+
+// ---- fp32 operands in 16-byte chunks: global -> LDS directly -------------------------
+// Where every line starts and ends on a multiple of four elements, a panel needs no registers on its way: each lane
+// asks for its 16-byte chunk (or for a block of zeros), the chunk lands in LDS at 16 bytes times the lane.  The loads
+// of a panel and the LDS reads of the next eight steps are placed between the matrix instructions (64 cycles each,
+// so a dozen other instructions pass in the shadow of one): a wavefront alone on its SIMD keeps the pipe busy.
+// FAST: tensors in the haloed time layout (the train step's, and what the entry points stage).  Every window is then
+// plain memory: a lane's offset from the first line of its panel never changes and the loads cost no vector
+// instruction at all, which counts, because fp32 matrix instructions run on the vector units (the two do not overlap).
+__device__ __align__(16) const float g_zero_chunk[4] = {0.f, 0.f, 0.f, 0.f};
+typedef __attribute__((address_space(3))) unsigned char lds_byte;
+
+__device__ __forceinline__ void dma16(const void* g, unsigned lds_addr)
+{
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds_addr) : "memory");
+}
+
+// address = uniform 64-bit base + per-lane 32-bit byte offset
+__device__ __forceinline__ void dma16s(unsigned voff, const void* sbase, unsigned lds_addr)
+{
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_addr) : "memory");
+}
+
+template <class OP, int W, bool FAST>
+struct DmaPanel {
+    static constexpr int BK = PANEL;
+    static constexpr bool KL = OP::K_LINES;
+    // [W][32] with the 16-byte chunks of a row permuted (16 consecutive rows read at one chunk index lie on all
+    // banks), or [32][W]: a half wavefront reads consecutive columns of one line, nothing to permute
+    static constexpr int FLOATS = W * BK;
+    static constexpr int CPL = (KL ? BK : W) / 4;     // chunks per line
+    static constexpr int NI = FLOATS * 4 / 1024 / 4;  // 1 KB load instructions per wavefront
+    Line ln[KL && !FAST ? NI : 1];
+    unsigned voff[FAST ? NI : 1];
+    const typename OP::type* sbase;
+    static __device__ __forceinline__ int swz(int row) { return KL ? (row & 7) ^ ((row >> 3) & 1) : 0; }
+    static __device__ __forceinline__ int chunk(int i) { return ((threadIdx.x >> 6) + 4 * i) * 64 + (threadIdx.x & 63); }
+    static __device__ __forceinline__ int l_of(int i) { return chunk(i) / CPL; }
+    static __device__ __forceinline__ int c_of(int i) { return ((chunk(i) % CPL) ^ swz(l_of(i))) * 4; }
+    __device__ __forceinline__ void init(const OP& op, int w0, int r_end)
+    {
+        if constexpr (FAST && KL) {
+            const long long first = op.fast_line(w0);
+            sbase = op.base + first;
+#pragma unroll
+            for (int i = 0; i < NI; ++i) voff[i] = (unsigned)((op.fast_line(w0 + l_of(i)) - first + c_of(i)) * 4);
+        } else if constexpr (FAST) {
+            sbase = op.base + w0;
+            const int cols = op.width() - w0;  // columns past the end read the first ones: outputs nobody stores
+#pragma unroll
+            for (int i = 0; i < NI; ++i) voff[i] = (unsigned)((l_of(i) * op.fast_pitch() + (c_of(i) < cols ? c_of(i) : 0)) * 4);
+        } else if constexpr (KL) {
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                ln[i] = op.line(w0 + l_of(i));
+                if (ln[i].hi > r_end) ln[i].hi = r_end;
+            }
+        }
+    }
+    __device__ __forceinline__ void issue(const OP& op, int i, int w0, int r0, int r_end, unsigned lds_panel) const
+    {
+        const unsigned dst = __builtin_amdgcn_readfirstlane(lds_panel + (threadIdx.x >> 6) * 1024) + i * 4096;
+        if constexpr (FAST) {
+            if constexpr (KL) dma16s(voff[i], sbase + r0, dst);
+            else dma16s(voff[i], sbase + op.fast_base(r0), dst);
+            return;
+        }
+        Line l;
+        int c;
+        if constexpr (KL) {
+            l = ln[i];
+            c = r0 + c_of(i);
+        } else {
+            const int r = r0 + l_of(i);
+            l = r < r_end ? op.line(r) : no_line();
+            c = w0 + c_of(i);
+        }
+        dma16(c >= l.lo && c < l.hi ? (const void*)(op.base + l.off + c) : (const void*)g_zero_chunk, dst);
+    }
+    // as AnyPanel::frags
+    template <int NB>
+    static __device__ __forceinline__ void frags(const float* lds, int w, int r, int lane, float (&f)[NB][4])
+    {
+        const int c = lane & 31, h = lane >> 5;
+        if constexpr (KL) {
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                const int row = w + 32 * i + c;
+                const f32x4a u = *reinterpret_cast<const f32x4a*>(lds + row * BK + (((r >> 2) + h) ^ swz(row)) * 4);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) f[i][q] = u[q];
+            }
+        } else {
+            typedef float vec __attribute__((ext_vector_type(NB)));
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const vec u = *reinterpret_cast<const vec*>(lds + (r + 4 * h + q) * W + w + NB * c);
+#pragma unroll
+                for (int i = 0; i < NB; ++i) f[i][q] = u[i];
+            }
+        }
+    }
+    template <int NB> static __device__ __forceinline__ int at(int i, int c) { return KL ? 32 * i + c : NB * c + i; }
+};
+
+// Same tiles, splits and results as gemm_any_k.  The next panel is requested under the first matrix instructions of a
+// panel, into the other of two slots; before the last eight steps every wavefront waits for its share of it and the
+// barrier makes it everybody's, so that its first operands are read under those last instructions.  (Three slots are
+// no faster for 64 x 64 tiles -- 2.33 against 2.18 ms for the forward pass of 16 x 1600 frames, k = 11, 512 -> 1024 --
+// because their 48 KB leave room for three workgroups on a CU instead of four.)
+template <class OA, class OB, class EP, bool FAST>
+__global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M, int N, int R, int per, int splits,
+                                                                   float* colsum, int colsum_acc)
+{
+    constexpr int BM = TILE, BN = TILE, BK = PANEL;
+    using PA = DmaPanel<OA, BM, FAST>;
+    using PB = DmaPanel<OB, BN, FAST>;
+    constexpr int STAGE = PA::FLOATS + PB::FLOATS, NA = BM / 64, NB = BN / 64, NL = PA::NI + PB::NI;
+    constexpr int GROUPS = BK / 8, MPG = 4 * NA * NB;        // groups of eight steps, matrix instructions per group
+    static_assert(NL <= (GROUPS - 1) * MPG, "a load after every instruction: all of them before the hand-over");
+    __shared__ __align__(1024) float lds[2 * STAGE];
+    const int split = blockIdx.z % splits;
+    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
+    const int r_begin = split * per, r_end = R < r_begin + per ? R : r_begin + per;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wm = (wave >> 1) * (BM / 2), wn = (wave & 1) * (BN / 2);
+    const bool sum_a = !PA::KL && colsum && blockIdx.x == 0;
+    const unsigned lds0 = (unsigned)(size_t)(lds_byte*)lds;
+    PA pa;
+    PB pb;
+    pa.init(oa, m0, r_end);
+    pb.init(ob, n0, r_end);
+    f32x16 acc[NA][NB];
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    float asum[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) asum[i] = 0.f;
+    const int steps = r_end > r_begin ? (r_end - r_begin + BK - 1) / BK : 0;
+    // (past the last panel the loads fetch zeros, or that panel again: the number in flight never changes)
+    auto issue = [&](int i, int st) {
+        const unsigned dst = lds0 + (st & 1) * (STAGE * 4);
+        const int r0 = r_begin + (FAST && st >= steps ? steps - 1 : st) * BK;
+        if (i < PA::NI) pa.issue(oa, i, m0, r0, r_end, dst);
+        else pb.issue(ob, i - PA::NI, n0, r0, r_end, dst + PA::FLOATS * 4);
+    };
+    float fa[2][NA][4], fb[2][NB][4];
+    if (steps > 0) {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) issue(i, 0);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        PA::template frags<NA>(lds, wm, 0, lane, fa[0]);
+        PB::template frags<NB>(lds + PA::FLOATS, wn, 0, lane, fb[0]);
+    }
+    for (int st = 0; st < steps; ++st) {
+        const float* cur = lds + (st & 1) * STAGE;
+        const float* nxt = lds + ((st + 1) & 1) * STAGE;
+#pragma unroll
+        for (int g = 0; g < GROUPS; ++g) {
+            const int u = g & 1;
+            const float* src = g + 1 < GROUPS ? cur : nxt;
+            if (g + 1 == GROUPS) {
+                asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // my share of panel st + 1
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+            }
+            PA::template frags<NA>(src, wm, (g + 1) % GROUPS * 8, lane, fa[1 - u]);
+            PB::template frags<NB>(src + PA::FLOATS, wn, (g + 1) % GROUPS * 8, lane, fb[1 - u]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int i = 0; i < NA; ++i)
+#pragma unroll
+                    for (int j = 0; j < NB; ++j) {
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[u][i][q], fb[u][j][q], acc[i][j], 0, 0, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        const int t = (g * 4 + q) * NA * NB + i * NB + j;
+                        if (t < NL) issue(t, st + 1);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+            if (sum_a) {
+                asm volatile("");  // a branch: without it every workgroup would add, and select
+#pragma unroll
+                for (int i = 0; i < NA; ++i) asum[i] += (fa[u][i][0] + fa[u][i][1]) + (fa[u][i][2] + fa[u][i][3]);
+            }
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing may land in LDS once it is used otherwise
+    float addn[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+        const int n = n0 + wn + PB::template at<NB>(j, lane & 31);
+        addn[j] = n < N ? ep.add(n) : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int m = m0 + wm + PA::template at<NA>(i, 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3));
+            if (m >= M) continue;
+            const long long row = ep.row(m);
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                const int n = n0 + wn + PB::template at<NB>(j, lane & 31);
+                if (n < N) ep.store(row + n, acc[i][j][e] + addn[j], split);
+            }
+        }
+    if (sum_a && (wave & 1) == 0) {  // the two wavefronts of a row of the tile hold the same values: one writes
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            const float v = asum[i] + __shfl_xor(asum[i], 32, 64);  // lanes 0..31 and 32..63 took different steps
+            const int m = m0 + wm + PA::template at<NA>(i, lane & 31);
+            if (lane < 32 && m < M) {
+                float* q = colsum + (long long)split * M + m;
+                *q = colsum_acc ? *q + v : v;
+            }
+        }
+    }
+}
+
+// How many workgroups share the reduction of an M x N x R problem's tiles.  The candidates' times are added up from
+// cycles: panels at 16 instructions of 64 cycles, one after the other for the workgroups that share a CU (at 0.67 of
+// the rate if there is one, 0.76 from three on: measured, 4 x 400 frames, k = 11, 256 -> 512, forward: 200 workgroups
+// of 88 panels 61 us, 1000 of 18 panels 46 us), about 12000 to fill and to drain, and for a split the partial sums'
+// way to memory and back (2500 bytes per cycle) plus the finishing launch.  64 x 64 outputs per workgroup everywhere:
+// 128 x 128 was slower on the largest problems as well (16 x 1600 frames, k = 11, 512 -> 1024: forward 2.30 against
+// 2.18 ms, data gradient 2.69 against 2.38, weight gradient 3.06 against 2.45), four small workgroups on a CU
+// covering each other's barriers better than two large ones.
+struct AnyPlan { int splits, per; };
+AnyPlan any_plan(long long M, long long N, long long R, size_t budget, double finish_cycles)
+{
+    const long long tiles = ((M + TILE - 1) / TILE) * ((N + TILE - 1) / TILE), panels = (R + PANEL - 1) / PANEL;
+    AnyPlan best{1, 0};
+    double best_t = -1;
+    for (int s = 1; s <= 16; ++s) {
+        const long long per = (panels + s - 1) / s;
+        if (s > 1 && (per * (s - 1) >= panels || per < 2 || (size_t)s * M * N * 4 > budget)) continue;
+        const long long load = (tiles * s + 255) / 256;
+        double t = load * per * 1024.0 / (load > 2 ? 0.76 : load > 1 ? 0.72 : 0.67) + 12000;
+        if (s > 1) t += 8.0 * s * M * N / 2500 + finish_cycles;
+        if (best_t < 0 || t < best_t) {
+            best_t = t;
+            best = AnyPlan{s, (int)(per * PANEL)};
+        }
+    }
+    return best;
+}
+
+template <class OA, class OB, class EP>
+int launch_any(const AnyPlan& pl, OA oa, OB ob, EP ep, long long M, long long N, long long R, hipStream_t st, float* colsum = nullptr,
+               int colsum_acc = 0, bool fast = false)
+{
+    const long long gy = (M + TILE - 1) / TILE, gx = (N + TILE - 1) / TILE;
+    if (M > 2147483647LL || R > 2147483647LL - 4096 || gy > 65535 || gx > 2147483647LL) return W2L_ERR_SHAPE;
+    if (M <= 0) return W2L_OK;
+    const dim3 g((unsigned)gx, (unsigned)gy, (unsigned)pl.splits);
+#define W2L_ANY(KERN) hipLaunchKernelGGL(KERN, g, dim3(256), 0, st, oa, ob, ep, (int)M, (int)N, (int)R, pl.per, pl.splits, colsum, colsum_acc)
+    if constexpr (std::is_same<typename OA::type, float>::value && std::is_same<typename OB::type, float>::value) {
+        if (oa.chunks() && ob.chunks()) {
+            if (fast) W2L_ANY((gemm_f32_k<OA, OB, EP, true>));
+            else W2L_ANY((gemm_f32_k<OA, OB, EP, false>));
+            return launch_status();
+        }
+    }
+    W2L_ANY((gemm_any_k<OA, OB, EP>));
+#undef W2L_ANY
     return launch_status();
 }
 
-template <typename TI, typename TO>
-int fwd_t(const ConvDesc& d, const void* x, const void* w, const float* bias, void* y, hipStream_t st)
+bool wgrad_walks(const ConvDesc& d)
 {
-    XWindow<TI> af{(const TI*)x, d.T, d.Tp, d.Cin, d.s, d.p, d.x_pitch, d.x_halo};
-    WRows<TI> bf{(const TI*)w, d.k * d.Cin};
-    StoreRows<TO> ep{(TO*)y, bias, d.Cout, d.Tp, d.y_pitch, d.y_halo};
-    return launch<XWindow<TI>, WRows<TI>, StoreRows<TO>, true, true>(af, bf, ep, (long long)d.B * d.Tp, d.Cout,
-                                                                      (long long)d.k * d.Cin, st);
+    return d.s == 1 && d.x_pitch == d.y_pitch && d.x_halo == d.y_halo && d.x_halo >= d.p && d.slack >= 64 &&
+           (d.B == 1 || d.x_halo > 0 || d.p == 0);
 }
-template <typename TW, typename TDY>
-int dgrad_t(const ConvDesc& d, const void* dy, const void* w, void* dx, hipStream_t st)
+
+template <typename TI, typename TO>
+int fwd_t(const ConvDesc& d, const AnyPlan& pl, const void* x, const void* w, const float* bias, TO* y, int pitch, int halo,
+          long long plane, hipStream_t st)
 {
-    DyWindow<TDY> af{(const TDY*)dy, d.T, d.Tp, d.Cout, d.s, d.p, d.y_pitch, d.y_halo};
-    WCols<TW> bf{(const TW*)w, d.Cin, d.Cout, d.k};
-    StoreRows<TW> ep{(TW*)dx, nullptr, d.Cin, d.T, d.x_pitch, d.x_halo};
-    return launch<DyWindow<TDY>, WCols<TW>, StoreRows<TW>, true, false>(af, bf, ep, (long long)d.B * d.T, d.Cin,
-                                                                         (long long)d.k * d.Cout, st);
+    const long long M = (long long)d.B * d.Tp;
+    XWindow<TI> a{(const TI*)x, (int)M, d.T, d.Tp, d.Cin, d.k, d.s, d.p, d.x_pitch, d.x_halo};
+    WRows<TI> b{(const TI*)w, d.Cout, d.k * d.Cin};
+    StoreRows<TO> ep{y, bias, d.Cout, d.Tp, 0, 1, pitch, halo, plane};
+    return launch_any(pl, a, b, ep, M, d.Cout, (long long)d.k * d.Cin, st, nullptr, 0, a.fast() && b.fast());
+}
+template <typename TW, typename TDY, typename TO>
+int dgrad_t(const ConvDesc& d, const AnyPlan& pl, const void* dy, const void* w, TO* dx, int pitch, int halo, long long plane, hipStream_t st)
+{
+    for (int ph = 0; ph < d.s; ++ph) {
+        const Phase q = phase_of(ph, d.T, d.k, d.s, d.p);
+        DyWindow<TDY> a{(const TDY*)dy, d.B, d.Tp, d.Cout, d.s, d.p, d.y_pitch, d.y_halo, q};
+        WCols<TW> b{(const TW*)w, d.Cin, d.Cout, d.k, d.s, q};
+        StoreRows<TO> ep{dx, nullptr, d.Cin, q.count, q.first, d.s, pitch, halo, plane};
+        const int rc = launch_any(pl, a, b, ep, (long long)d.B * q.count, d.Cin, (long long)q.taps * d.Cout, st, nullptr, 0, a.fast() && b.fast());
+        if (rc) return rc;
+    }
+    return W2L_OK;
 }
 template <typename TX, typename TDY>
-int wgrad_t(const ConvDesc& d, const void* x, const void* dy, float* dw, int accumulate, hipStream_t st)
+int wgrad_t(const ConvDesc& d, const AnyPlan& pl, const void* x, const void* dy, float* dw, float* dbias, int accumulate, long long plane,
+            hipStream_t st)
 {
-    DyT<TDY> af{(const TDY*)dy, d.Tp, d.Cout, d.y_pitch, d.y_halo};
-    XShift<TX> bf{(const TX*)x, d.T, d.Tp, d.Cin, d.s, d.p, d.x_pitch, d.x_halo};
-    StoreAcc ep{dw, d.k * d.Cin, accumulate};
-    return launch<DyT<TDY>, XShift<TX>, StoreAcc, false, false>(af, bf, ep, d.Cout, (long long)d.k * d.Cin,
-                                                                 (long long)d.B * d.Tp, st);
+    DyT<TDY> a{(const TDY*)dy, d.Tp, d.Cout, d.y_pitch, d.y_halo};
+    XShift<TX> b{(const TX*)x, d.T, d.Tp, d.Cin, d.k, d.s, d.p, d.x_pitch, d.x_halo};
+    StoreAcc ep{dw, d.k * d.Cin, accumulate, plane};
+    // with x and dy in one haloed layout the reduction runs straight through its frames: dy is zero in the halo
+    // frames, and in the slack that the last panel reads into
+    const long long walk = (long long)(d.B - 1) * d.y_pitch + d.Tp;
+    const bool fast = wgrad_walks(d) && walk <= (long long)pl.per * pl.splits;
+    const long long R = fast ? walk : (long long)d.B * d.Tp;
+    return launch_any(pl, a, b, ep, d.Cout, (long long)d.k * d.Cin, R, st, dbias, accumulate, fast);
 }
 
 // ---- weight gradient for narrow outputs (Cout <= 32, e.g. the 29 grapheme classes) ---------
@@ -334,28 +841,108 @@ __global__ void colsum_stage2(const float* part, float* dbias, int chunks, int C
 
 }  // namespace
 
+namespace {
+// a finishing launch of its own costs about 5 us; inside the train step it is the layer's GLU, launched in any case
+constexpr double FINISH_OWN = 12000, FINISH_FREE = 2000;
+constexpr size_t MAX_PARTIALS = 96u << 20;
+AnyPlan fwd_plan(const ConvDesc& d, size_t budget, double fin) { return any_plan((long long)d.B * d.Tp, d.Cout, (long long)d.k * d.Cin, budget, fin); }
+AnyPlan dgrad_plan(const ConvDesc& d, size_t budget, double fin)
+{
+    // of a stride's phases, the one with the most taps (they are launched one after the other)
+    return any_plan((long long)d.B * ((d.T + d.s - 1) / d.s), d.Cin, (long long)((d.k + d.s - 1) / d.s) * d.Cout, budget, fin);
+}
+AnyPlan wgrad_plan(const ConvDesc& d, size_t budget)
+{
+    // the reduction as long as the walk through the haloed layout makes it
+    return any_plan(d.Cout, (long long)d.k * d.Cin, (long long)d.B * (d.Tp + 2 * LAYOUT_HALO), budget, FINISH_OWN);
+}
+size_t part_bytes(int splits, long long rows, long long cols) { return splits > 1 ? round_up((size_t)splits * rows * cols * 4, 256) : 0; }
+}  // namespace
+
+size_t conv_fwd_generic_scratch(const ConvDesc& d)
+{
+    return part_bytes(fwd_plan(d, MAX_PARTIALS, FINISH_OWN).splits, (long long)d.B * d.Tp, d.Cout);
+}
+size_t conv_dgrad_generic_scratch(const ConvDesc& d)
+{
+    return part_bytes(dgrad_plan(d, MAX_PARTIALS, FINISH_OWN).splits, (long long)d.B * d.T, d.Cin);
+}
+size_t conv_wgrad_generic_scratch(const ConvDesc& d)
+{
+    return part_bytes(wgrad_plan(d, MAX_PARTIALS).splits, d.Cout, (long long)d.k * d.Cin + 1);
+}
+int conv_fwd_generic_parts(const ConvDesc& d) { return fwd_plan(d, MAX_PARTIALS, FINISH_FREE).splits; }
+int conv_dgrad_generic_parts(const ConvDesc& d) { return dgrad_plan(d, MAX_PARTIALS, FINISH_FREE).splits; }
+
+int conv_fwd_generic_partial(const ConvDesc& d, const void* x, const void* w, int dt, float* part, hipStream_t st)
+{
+    const AnyPlan pl = fwd_plan(d, MAX_PARTIALS, FINISH_FREE);
+    const long long plane = (long long)d.B * d.Tp * d.Cout;
+    if (dt == W2L_F32) return fwd_t<float, float>(d, pl, x, w, nullptr, part, d.Tp, 0, plane, st);
+    return fwd_t<bf16_t, float>(d, pl, x, w, nullptr, part, d.Tp, 0, plane, st);
+}
+int conv_dgrad_generic_partial(const ConvDesc& d, const void* dy, const void* w, int dt, int dydt, float* part, hipStream_t st)
+{
+    const AnyPlan pl = dgrad_plan(d, MAX_PARTIALS, FINISH_FREE);
+    const long long plane = (long long)d.B * d.T * d.Cin;
+    if (dt == W2L_F32) return dgrad_t<float, float, float>(d, pl, dy, w, part, d.T, 0, plane, st);
+    if (dydt == W2L_BF16) return dgrad_t<bf16_t, bf16_t, float>(d, pl, dy, w, part, d.T, 0, plane, st);
+    return dgrad_t<bf16_t, float, float>(d, pl, dy, w, part, d.T, 0, plane, st);
+}
+
 int conv_fwd_generic(const ConvDesc& d, const void* x, const void* w, const float* bias, void* y, int dt, int ydt,
-                     hipStream_t st)
+                     hipStream_t st, void* scratch, size_t scratch_bytes)
 {
-    if (dt == W2L_F32 && ydt == W2L_F32) return fwd_t<float, float>(d, x, w, bias, y, st);
-    if (dt == W2L_BF16 && ydt == W2L_BF16) return fwd_t<bf16_t, bf16_t>(d, x, w, bias, y, st);
-    if (dt == W2L_BF16 && ydt == W2L_F32) return fwd_t<bf16_t, float>(d, x, w, bias, y, st);
-    return W2L_ERR_DTYPE;
+    if (dt == W2L_F32 && ydt != W2L_F32) return W2L_ERR_DTYPE;
+    const AnyPlan pl = fwd_plan(d, scratch ? (scratch_bytes < MAX_PARTIALS ? scratch_bytes : MAX_PARTIALS) : 0, FINISH_OWN);
+    if (pl.splits > 1) {
+        float* part = static_cast<float*>(scratch);
+        const long long rows = (long long)d.B * d.Tp, plane = rows * d.Cout;
+        const int rc = dt == W2L_F32 ? fwd_t<float, float>(d, pl, x, w, nullptr, part, d.Tp, 0, plane, st)
+                                     : fwd_t<bf16_t, float>(d, pl, x, w, nullptr, part, d.Tp, 0, plane, st);
+        return rc ? rc : finish_rows(part, pl.splits, bias, y, ydt, d.B, d.Tp, d.Cout, d.y_pitch, d.y_halo, st);
+    }
+    if (dt == W2L_F32) return fwd_t<float, float>(d, pl, x, w, bias, (float*)y, d.y_pitch, d.y_halo, 0, st);
+    if (ydt == W2L_BF16) return fwd_t<bf16_t, bf16_t>(d, pl, x, w, bias, (bf16_t*)y, d.y_pitch, d.y_halo, 0, st);
+    return fwd_t<bf16_t, float>(d, pl, x, w, bias, (float*)y, d.y_pitch, d.y_halo, 0, st);
 }
-int conv_dgrad_generic(const ConvDesc& d, const void* dy, const void* w, void* dx, int dt, int dydt, hipStream_t st)
+int conv_dgrad_generic(const ConvDesc& d, const void* dy, const void* w, void* dx, int dt, int dydt, hipStream_t st, void* scratch,
+                       size_t scratch_bytes)
 {
-    if (dt == W2L_F32 && dydt == W2L_F32) return dgrad_t<float, float>(d, dy, w, dx, st);
-    if (dt == W2L_BF16 && dydt == W2L_BF16) return dgrad_t<bf16_t, bf16_t>(d, dy, w, dx, st);
-    if (dt == W2L_BF16 && dydt == W2L_F32) return dgrad_t<bf16_t, float>(d, dy, w, dx, st);
-    return W2L_ERR_DTYPE;
+    if (dt == W2L_F32 && dydt != W2L_F32) return W2L_ERR_DTYPE;
+    const AnyPlan pl = dgrad_plan(d, scratch ? (scratch_bytes < MAX_PARTIALS ? scratch_bytes : MAX_PARTIALS) : 0, FINISH_OWN);
+    if (pl.splits > 1) {
+        float* part = static_cast<float*>(scratch);
+        const long long plane = (long long)d.B * d.T * d.Cin;
+        int rc;
+        if (dt == W2L_F32) rc = dgrad_t<float, float, float>(d, pl, dy, w, part, d.T, 0, plane, st);
+        else if (dydt == W2L_BF16) rc = dgrad_t<bf16_t, bf16_t, float>(d, pl, dy, w, part, d.T, 0, plane, st);
+        else rc = dgrad_t<bf16_t, float, float>(d, pl, dy, w, part, d.T, 0, plane, st);
+        return rc ? rc : finish_rows(part, pl.splits, nullptr, dx, dt, d.B, d.T, d.Cin, d.x_pitch, d.x_halo, st);
+    }
+    if (dt == W2L_F32) return dgrad_t<float, float, float>(d, pl, dy, w, (float*)dx, d.x_pitch, d.x_halo, 0, st);
+    if (dydt == W2L_BF16) return dgrad_t<bf16_t, bf16_t, bf16_t>(d, pl, dy, w, (bf16_t*)dx, d.x_pitch, d.x_halo, 0, st);
+    return dgrad_t<bf16_t, float, bf16_t>(d, pl, dy, w, (bf16_t*)dx, d.x_pitch, d.x_halo, 0, st);
 }
-int conv_wgrad_generic(const ConvDesc& d, const void* x, const void* dy, float* dw, int dt, int dydt, int accumulate,
-                       hipStream_t st)
+int conv_wgrad_generic(const ConvDesc& d, const void* x, const void* dy, float* dw, float* dbias, int dt, int dydt, int accumulate,
+                       hipStream_t st, void* scratch, size_t scratch_bytes)
 {
-    if (dt == W2L_F32 && dydt == W2L_F32) return wgrad_t<float, float>(d, x, dy, dw, accumulate, st);
-    if (dt == W2L_BF16 && dydt == W2L_BF16) return wgrad_t<bf16_t, bf16_t>(d, x, dy, dw, accumulate, st);
-    if (dt == W2L_BF16 && dydt == W2L_F32) return wgrad_t<bf16_t, float>(d, x, dy, dw, accumulate, st);
-    return W2L_ERR_DTYPE;
+    if (dt == W2L_F32 && dydt != W2L_F32) return W2L_ERR_DTYPE;
+    // (the bias sums of the splits lie behind the weight sums: one more column)
+    const long long n = (long long)d.k * d.Cin, plane = d.Cout * n;
+    AnyPlan pl = wgrad_plan(d, MAX_PARTIALS);
+    if (!scratch || scratch_bytes < part_bytes(pl.splits, d.Cout, n + 1)) pl = wgrad_plan(d, 0);
+    float* part = static_cast<float*>(scratch);
+    const bool split = pl.splits > 1;
+    float* const out = split ? part : dw;
+    float* const bout = !dbias ? nullptr : split ? part + pl.splits * plane : dbias;
+    const int acc = split ? 0 : accumulate;
+    int rc;
+    if (dt == W2L_F32) rc = wgrad_t<float, float>(d, pl, x, dy, out, bout, acc, plane, st);
+    else if (dydt == W2L_BF16) rc = wgrad_t<bf16_t, bf16_t>(d, pl, x, dy, out, bout, acc, plane, st);
+    else rc = wgrad_t<bf16_t, float>(d, pl, x, dy, out, bout, acc, plane, st);
+    if (rc || !split) return rc;
+    return finish_sums(part, pl.splits, plane, dw, bout, d.Cout, dbias, accumulate, st);
 }
 size_t conv_wgrad_skinny_scratch(int Cin, int Cout, int k)
 {

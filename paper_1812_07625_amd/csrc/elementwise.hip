@@ -142,6 +142,154 @@ __global__ __launch_bounds__(256) void glu_bwd_k(const T* __restrict__ y, const 
     }
 }
 
+// ---- finishing passes of a split reduction --------------------------------------------
+// A convolution whose tiles do not fill the chip is cut along its reduction (conv_generic.hip, conv_mfma.hip); the
+// planes of fp32 sums are added here, in order, by the pass that would have read the result next.  V consecutive
+// values a thread (4 where the row length allows: 16-byte loads); the planes were written by the launch before and
+// mostly still lie in the memory-side cache, so what bounds these is the number of loads in flight: a thread's loads
+// of up to four planes are issued together.
+template <int V> struct FVec { float v[V]; };
+template <int V>
+__device__ __forceinline__ FVec<V> sum_parts(const float* __restrict__ q, long long plane, int parts)
+{
+    typedef float vec __attribute__((ext_vector_type(V)));
+    FVec<V> o;
+#pragma unroll
+    for (int j = 0; j < V; ++j) o.v[j] = 0.f;
+    int p = 0;
+    for (; p + 4 <= parts; p += 4) {
+        vec u[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) u[e] = *reinterpret_cast<const vec*>(q + (p + e) * plane);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int j = 0; j < V; ++j) o.v[j] += u[e][j];
+    }
+    for (; p < parts; ++p) {
+        const vec u = *reinterpret_cast<const vec*>(q + p * plane);
+#pragma unroll
+        for (int j = 0; j < V; ++j) o.v[j] += u[j];
+    }
+    return o;
+}
+// v rounded to T and back
+template <typename T> __device__ __forceinline__ float as_stored(float v) { return v; }
+template <> __device__ __forceinline__ float as_stored<bf16_t>(float v) { return bf16_to_f32(f32_to_bf16(v)); }
+template <typename T, int V>
+__device__ __forceinline__ void store_vec(T* p, const float (&v)[V])
+{
+    if constexpr (V == 1) Elem<T>::store(p, 0, v[0]);
+    else if constexpr (sizeof(T) == 4) *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+    else *reinterpret_cast<uint2*>(p) = make_uint2((unsigned)f32_to_bf16(v[0]) | ((unsigned)f32_to_bf16(v[1]) << 16),
+                                                   (unsigned)f32_to_bf16(v[2]) | ((unsigned)f32_to_bf16(v[3]) << 16));
+}
+template <typename T, int V>
+__device__ __forceinline__ void load_vec(const T* p, float (&v)[V])
+{
+    if constexpr (V == 1) v[0] = Elem<T>::load(p, 0);
+    else if constexpr (sizeof(T) == 4) {
+        const float4 u = *reinterpret_cast<const float4*>(p);
+        v[0] = u.x; v[1] = u.y; v[2] = u.z; v[3] = u.w;
+    } else {
+        const uint2 u = *reinterpret_cast<const uint2*>(p);
+        v[0] = __uint_as_float(u.x << 16); v[1] = __uint_as_float(u.x & 0xffff0000u);
+        v[2] = __uint_as_float(u.y << 16); v[3] = __uint_as_float(u.y & 0xffff0000u);
+    }
+}
+
+template <typename T, int V>
+__global__ __launch_bounds__(256) void finish_rows_k(const float* __restrict__ part, int parts, const float* __restrict__ bias,
+                                                     T* __restrict__ y, unsigned rows, int N, int frames, int pitch, int halo)
+{
+    const unsigned nv = N / V, total = rows * nv;
+    const long long plane = (long long)rows * N;
+    for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
+        const unsigned r = i / nv, b = r / (unsigned)frames;
+        const int c = (int)(i - r * nv) * V;
+        FVec<V> s = sum_parts<V>(part + (long long)r * N + c, plane, parts);
+        if (bias) {
+#pragma unroll
+            for (int j = 0; j < V; ++j) s.v[j] += bias[c + j];
+        }
+        store_vec<T, V>(y + ((long long)b * pitch + halo + (r - b * frames)) * N + c, s.v);
+    }
+}
+template <typename T, int V>
+__global__ __launch_bounds__(256) void finish_glu_fwd_k(const float* __restrict__ part, int parts, const float* __restrict__ bias,
+                                                        T* __restrict__ y, T* __restrict__ h, unsigned out_rows, int H, RowMap map,
+                                                        long long plane)
+{
+    const unsigned hv = H / V, total = out_rows * hv;
+    for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
+        const unsigned f = i / hv;
+        const int c = (int)(i - f * hv) * V;
+        const long long r = map.src(f);
+        float o[V];
+        if (r >= 0) {
+            FVec<V> a = sum_parts<V>(part + r * 2 * H + c, plane, parts), g = sum_parts<V>(part + r * 2 * H + H + c, plane, parts);
+#pragma unroll
+            for (int j = 0; j < V; ++j) {
+                if (bias) { a.v[j] += bias[c + j]; g.v[j] += bias[H + c + j]; }
+                o[j] = as_stored<T>(a.v[j]) * sigmoidf_(as_stored<T>(g.v[j]));
+            }
+            store_vec<T, V>(y + r * 2 * H + c, a.v);
+            store_vec<T, V>(y + r * 2 * H + H + c, g.v);
+        } else {
+#pragma unroll
+            for (int j = 0; j < V; ++j) o[j] = 0.f;
+        }
+        store_vec<T, V>(h + (size_t)f * H + c, o);
+    }
+}
+template <typename T, int V>
+__global__ __launch_bounds__(256) void finish_glu_bwd_k(const float* __restrict__ part, int parts, const T* __restrict__ y,
+                                                        T* __restrict__ dy, unsigned out_rows, int H, RowMap map, long long plane)
+{
+    const unsigned hv = H / V, total = out_rows * hv;
+    for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
+        const unsigned f = i / hv;
+        const int c = (int)(i - f * hv) * V;
+        const long long r = map.src(f);
+        float da[V], dg[V];
+        if (r >= 0) {
+            const FVec<V> s = sum_parts<V>(part + r * H + c, plane, parts);
+            float a[V], g[V];
+            load_vec<T, V>(y + r * 2 * H + c, a);
+            load_vec<T, V>(y + r * 2 * H + H + c, g);
+#pragma unroll
+            for (int j = 0; j < V; ++j) {
+                const float d = as_stored<T>(s.v[j]), sg = sigmoidf_(g[j]);
+                da[j] = d * sg;
+                dg[j] = d * a[j] * sg * (1.f - sg);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < V; ++j) { da[j] = 0.f; dg[j] = 0.f; }
+        }
+        store_vec<T, V>(dy + (size_t)f * 2 * H + c, da);
+        store_vec<T, V>(dy + (size_t)f * 2 * H + H + c, dg);
+    }
+}
+template <int V>
+__global__ __launch_bounds__(256) void finish_sums_k(const float* __restrict__ part, int parts, long long n, float* __restrict__ out,
+                                                     const float* __restrict__ bpart, int nb, float* __restrict__ bout, int accumulate)
+{
+    const long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x, nv = n / V;
+    if (t < nv) {
+        FVec<V> s = sum_parts<V>(part + t * V, n, parts);
+        if (accumulate) {
+#pragma unroll
+            for (int j = 0; j < V; ++j) s.v[j] += out[t * V + j];
+        }
+        store_vec<float, V>(out + t * V, s.v);
+    } else if (bout && t - nv < nb) {
+        const int c = (int)(t - nv);
+        const FVec<1> s = sum_parts<1>(bpart + c, nb, parts);
+        bout[c] = accumulate ? bout[c] + s.v[0] : s.v[0];
+    }
+}
+
 // dense [B*Tp, C] -> haloed layout (zeros in halo and slack frames); C % 8 == 0, bf16
 __global__ __launch_bounds__(256) void pad_layout_k(const bf16_t* __restrict__ src, bf16_t* __restrict__ dst,
                                                     long long out_rows, int C, RowMap map, int* __restrict__ clear,
@@ -368,6 +516,60 @@ int glu_bwd_layout(const void* y, const void* dh, void* dy, int B, int Tp, int C
 }  // namespace w2l
 
 namespace w2l {
+int finish_rows(const float* part, int parts, const float* bias, void* y, int dtype, int B, int frames, int N, int pitch, int halo,
+                hipStream_t st)
+{
+    const unsigned rows = (unsigned)B * frames;
+    const bool vec = N % 4 == 0;
+    const dim3 g(grid_for((long long)rows * (vec ? N / 4 : N))), b(256);
+#define W2L_FIN(T_, V_) hipLaunchKernelGGL((finish_rows_k<T_, V_>), g, b, 0, st, part, parts, bias, (T_*)y, rows, N, frames, pitch, halo)
+    if (dtype == W2L_BF16) { if (vec) W2L_FIN(bf16_t, 4); else W2L_FIN(bf16_t, 1); }
+    else { if (vec) W2L_FIN(float, 4); else W2L_FIN(float, 1); }
+#undef W2L_FIN
+    return launch_status();
+}
+int finish_glu_fwd(const float* part, int parts, const float* bias, void* y, void* h, int B, int Tp, int Cout, int dtype, int pitch,
+                   int halo, int slack, hipStream_t st)
+{
+    const int H = Cout / 2;
+    const bool vec = H % 4 == 0;
+    const unsigned out_rows = (unsigned)B * pitch + slack;
+    const RowMap map{Tp, pitch, halo, (long long)B * pitch};
+    const long long plane = (long long)B * Tp * Cout;
+    const dim3 g(grid_for((long long)out_rows * (vec ? H / 4 : H))), b(256);
+#define W2L_FIN(T_, V_) hipLaunchKernelGGL((finish_glu_fwd_k<T_, V_>), g, b, 0, st, part, parts, bias, (T_*)y, (T_*)h, out_rows, H, map, plane)
+    if (dtype == W2L_BF16) { if (vec) W2L_FIN(bf16_t, 4); else W2L_FIN(bf16_t, 1); }
+    else { if (vec) W2L_FIN(float, 4); else W2L_FIN(float, 1); }
+#undef W2L_FIN
+    return launch_status();
+}
+int finish_glu_bwd(const float* part, int parts, const void* y, void* dy, int B, int Tp, int Cout, int dtype, int pitch, int halo,
+                   int slack, hipStream_t st)
+{
+    const int H = Cout / 2;
+    const bool vec = H % 4 == 0;
+    const unsigned out_rows = (unsigned)B * pitch + slack;
+    const RowMap map{Tp, pitch, halo, (long long)B * pitch};
+    const long long plane = (long long)B * Tp * H;
+    const dim3 g(grid_for((long long)out_rows * (vec ? H / 4 : H))), b(256);
+#define W2L_FIN(T_, V_) hipLaunchKernelGGL((finish_glu_bwd_k<T_, V_>), g, b, 0, st, part, parts, (const T_*)y, (T_*)dy, out_rows, H, map, plane)
+    if (dtype == W2L_BF16) { if (vec) W2L_FIN(bf16_t, 4); else W2L_FIN(bf16_t, 1); }
+    else { if (vec) W2L_FIN(float, 4); else W2L_FIN(float, 1); }
+#undef W2L_FIN
+    return launch_status();
+}
+int finish_sums(const float* part, int parts, long long n, float* out, const float* bpart, int nb, float* bout, int accumulate,
+                hipStream_t st)
+{
+    if (!bout) nb = 0;
+    const bool vec = n % 4 == 0;
+    const long long items = (vec ? n / 4 : n) + nb, blocks = (items + 255) / 256;
+    if (blocks > 2147483647LL) return W2L_ERR_SHAPE;
+    if (vec) hipLaunchKernelGGL(finish_sums_k<4>, dim3((unsigned)blocks), dim3(256), 0, st, part, parts, n, out, bpart, nb, bout, accumulate);
+    else hipLaunchKernelGGL(finish_sums_k<1>, dim3((unsigned)blocks), dim3(256), 0, st, part, parts, n, out, bpart, nb, bout, accumulate);
+    return launch_status();
+}
+
 int pad_layout_bf16(const void* src, void* dst, int B, int Tp, int C, int pitch, int halo, int slack, hipStream_t st,
                     int* clear, int nclear)
 {

@@ -58,8 +58,8 @@ struct Plan {
     int n = 0, C = 0, Tlast = 0, tot_stride = 1;
     std::vector<int> Tin, Tout, outch;
     std::vector<size_t> pre, post;  // workspace offsets of conv output (dense) and GLU output (haloed) per layer
-    size_t dlogits = 0, crit_len = 0, gdy[3] = {0, 0, 0}, gdh[2] = {0, 0}, ctc = 0, conv = 0, conv0 = 0, dbias = 0, dgs = 0, total = 0;
-    size_t ctc_bytes = 0, conv_bytes = 0, dgs_bytes = 0;
+    size_t dlogits = 0, crit_len = 0, gdy[3] = {0, 0, 0}, gdh[2] = {0, 0}, ctc = 0, conv = 0, conv0 = 0, dbias = 0, dgs = 0, part = 0, total = 0;
+    size_t ctc_bytes = 0, conv_bytes = 0, dgs_bytes = 0, part_bytes = 0;  // part: sums of split reductions on the caller's stream
     size_t xfold = 0;      // haloed copy of x with the first layer's stride folded into the channels (0 bytes if unused)
     bool fold0 = false;
     size_t cls = 0;        // operands of the last layer's data gradient prepared for the MFMA kernels (its dy is fp32)
@@ -67,6 +67,7 @@ struct Plan {
     int status = W2L_OK;
 };
 
+size_t max_of(size_t a, size_t b) { return a > b ? a : b; }
 size_t haloed_bytes(int B, int frames, int ch, size_t es) { return ((size_t)B * (frames + 2 * HALO) + SLACK) * ch * es; }
 
 Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int criterion)
@@ -107,8 +108,14 @@ Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int
         }
         const size_t g2 = (size_t)B * t * l.cin * es;
         dhmax = g2 > dhmax ? g2 : dhmax;
-        const size_t cw = w2l_conv1d_bwd_weight_workspace_bytes(B, t, l.cin, l.cout, l.k, l.stride, dtype);
-        p.conv_bytes = cw > p.conv_bytes ? cw : p.conv_bytes;
+        ConvDesc dd = dense_desc(B, t, l.cin, l.cout, l.k, l.stride);
+        if (i > 0) { dd.x_pitch = t + 2 * HALO; dd.x_halo = HALO; dd.slack = SLACK; }
+        if (l.glu) { dd.y_pitch = to + 2 * HALO; dd.y_halo = HALO; dd.slack = SLACK; }
+        p.conv_bytes = max_of(p.conv_bytes, conv_wgrad_scratch_bytes(dd));
+        if (conv_fwd_is_generic(dd, dtype))
+            p.part_bytes = max_of(p.part_bytes, l.glu ? (size_t)conv_fwd_generic_parts(dd) * B * to * l.cout * 4 : conv_fwd_generic_scratch(dd));
+        if (i > 0 && conv_dgrad_is_generic(dd, dtype, i == n - 1 ? W2L_F32 : dtype))
+            p.part_bytes = max_of(p.part_bytes, L[i - 1].glu ? (size_t)conv_dgrad_generic_parts(dd) * B * t * l.cin * 4 : conv_dgrad_generic_scratch(dd));
         if (i > 0 && L[i - 1].glu) {
             // scratch of a split-reduction data gradient (tickets and the fp32 sums of both halves)
             ConvDesc sd = dense_desc(B, t, l.cin, l.cout, l.k, l.stride);
@@ -131,11 +138,12 @@ Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int
     p.ctc = off; off += round_up(p.ctc_bytes, 256);
     p.conv = off; off += round_up(p.conv_bytes, 256);
     // layer 0's weight gradient runs on the caller's stream next to the helper stream's launches: its own scratch
-    p.conv0 = off; off += round_up(conv_wgrad_scratch_bytes(L[0].cin, L[0].cout, L[0].k), 256);
+    p.conv0 = off; off += round_up(conv_wgrad_scratch_bytes(dense_desc(B, T, L[0].cin, L[0].cout, L[0].k, L[0].stride)), 256);
     int cmax = 0;
     for (int i = 0; i < n; ++i) cmax = L[i].cout > cmax ? L[i].cout : cmax;
     p.dbias = off; off += round_up((size_t)DBIAS_CHUNKS * cmax * 4, 256);
     p.dgs = off; off += round_up(p.dgs_bytes, 256);
+    p.part = off; off += round_up(p.part_bytes, 256);
     {
         // a strided first layer with GLU (its dy is haloed): the weight gradient reads x folded and haloed
         ConvDesc d0 = dense_desc(B, T, L[0].cin, L[0].cout, L[0].k, L[0].stride), f0;
@@ -224,7 +232,17 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
             h = ws + p.post[i];
             continue;
         }
-        rc = conv_fwd(fd, h, weights[i], biases[i], ws + p.pre[i], dtype, ydt, st);
+        float* const part = reinterpret_cast<float*>(ws + p.part);
+        if (l.glu && conv_fwd_is_generic(fd, dtype) && conv_fwd_generic_parts(fd) > 1) {
+            rc = conv_fwd_generic_partial(fd, h, weights[i], dtype, part, st);  // the GLU pass adds the parts up
+            if (rc) return rc;
+            rc = finish_glu_fwd(part, conv_fwd_generic_parts(fd), biases[i], ws + p.pre[i], ws + p.post[i], B, p.Tout[i], l.cout, dtype,
+                                p.Tout[i] + 2 * HALO, HALO, SLACK_ZERO, st);
+            if (rc) return rc;
+            h = ws + p.post[i];
+            continue;
+        }
+        rc = conv_fwd(fd, h, weights[i], biases[i], ws + p.pre[i], dtype, ydt, st, part, p.part_bytes);
         if (rc) return rc;
         if (l.glu) {
             rc = glu_fwd_layout(ws + p.pre[i], ws + p.post[i], B, p.Tout[i], l.cout, dtype, p.Tout[i] + 2 * HALO, HALO,
@@ -347,6 +365,18 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
                 dy_ready = true;
                 continue;
             }
+            const bool prepared = i == n - 1 && dy_dt == W2L_F32 && p.cls_prep.ok;
+            if (layers[i - 1].glu && !prepared && conv_dgrad_is_generic(d, dtype, dy_dt) && conv_dgrad_generic_parts(d) > 1) {
+                float* const part = reinterpret_cast<float*>(ws + p.part);
+                if (!wait_wgrad(i + 2)) return W2L_ERR_LAUNCH;
+                rc = conv_dgrad_generic_partial(d, dy, weights[i], dtype, dy_dt, part, st);
+                if (rc) return rc;
+                rc = finish_glu_bwd(part, conv_dgrad_generic_parts(d), ws + p.pre[i - 1], ws + p.gdy[(i - 1) % 3], B, p.Tout[i - 1],
+                                    layers[i - 1].cout, dtype, p.Tout[i - 1] + 2 * HALO, HALO, SLACK_ZERO, st);
+                if (rc) return rc;
+                dy_ready = true;
+                continue;
+            }
             ConvDesc dd = d;   // dx = dh_{i-1} is written dense
             dd.x_pitch = p.Tin[i];
             dd.x_halo = 0;
@@ -355,10 +385,11 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
                 if (!wait_wgrad(gdh_reader[q])) return W2L_ERR_LAUNCH;
                 gdh_reader[q] = -1;
             }
-            if (i == n - 1 && dy_dt == W2L_F32 && p.cls_prep.ok)  // the criterion's fp32 gradient: cast, pad, MFMA
+            if (prepared)  // the criterion's fp32 gradient: cast, pad, MFMA
                 rc = conv_dgrad_prepared(p.cls_prep, dy, dy_dt, weights[i], gdhb[q], ws + p.cls, st);
             else
-                rc = conv_dgrad(dd, dy, weights[i], gdhb[q], dtype, dy_dt, st);
+                rc = conv_dgrad(dd, dy, weights[i], gdhb[q], dtype, dy_dt, st,
+                                conv_dgrad_is_generic(dd, dtype, dy_dt) ? ws + p.part : nullptr, p.part_bytes);
             if (rc) return rc;
             dh = gdhb[q];
             cur = q;

@@ -1,0 +1,86 @@
+"""The convolution kernels for any shape and type (fp32 matrix instruction, 64 x 64 tiles, panels of 32 steps, reductions
+split over workgroups) against the oracle at the edges of tiles, panels and splits, with and without workspace.
+
+fp32 outputs: products exact or rounded once, fp32 sums -- every element within 1e-5 |ref| + 1e-5 rms(ref) and relative
+L2 <= 1e-5 (a sum of K <= 4000 terms in any order: about sqrt(K) 2^-24 = 4e-6 of the rms of the result).  bf16 outputs
+add one rounding."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+from gpu_util import BF16_ABS, BF16_L2, BF16_REL, assert_elementwise, empty, rel_l2, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    # B, T, Cin, Cout, k, s
+    (1, 64, 32, 64, 1, 1),       # one whole tile
+    (1, 63, 32, 65, 1, 1),       # a row short, a column over
+    (2, 65, 64, 66, 3, 1),       # lines of whole chunks, staged into the haloed layout
+    (5, 128, 32, 192, 17, 1),    # the widest window the layout's halo takes
+    (2, 100, 36, 68, 5, 1),      # whole chunks, but panels that straddle taps
+    (3, 50, 32, 64, 19, 1),      # window wider than the halo: not staged
+    (2, 90, 30, 33, 3, 1),       # lines that start anywhere
+    (4, 130, 256, 128, 11, 1),   # few tiles, long reduction: split forward and data gradient
+    (2, 1500, 40, 64, 3, 1),     # few tiles, many frames: split weight gradient
+    (2, 131, 40, 64, 13, 2),     # strides: phases with unequal taps and frames
+    (3, 70, 24, 48, 3, 4),       # a stride wider than the window: phases without taps
+    (1, 7, 5, 40, 5, 3),
+]
+
+
+def _check(got, ref, bf16, what):
+    if bf16:
+        assert rel_l2(got, ref) <= BF16_L2, what
+        assert_elementwise(got, ref, BF16_REL, BF16_ABS, what=what)
+    else:
+        assert rel_l2(got, ref) <= 1e-5, what
+        assert_elementwise(got, ref, 1e-5, 1e-5, what=what)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_conv_any_edges(shape, dtype):
+    import paper_1812_07625_amd as P
+    B, T, Cin, Cout, k, s = shape
+    if dtype == "bf16":
+        Cin, Cout = Cin + 1, Cout + 3      # channel counts that the bf16 kernels do not take
+    rng = np.random.default_rng(sum(shape))
+    Tp = oracle.out_len(T, s)
+    grid = lambda a: W.round_to_bf16(a.astype(np.float32)) if dtype == "bf16" else a.astype(np.float32)
+    x, dy = grid(rng.standard_normal((B, T, Cin))), grid(rng.standard_normal((B, Tp, Cout)))
+    w = grid(rng.standard_normal((Cout, k, Cin)) / np.sqrt(k * Cin))
+    bias = rng.standard_normal(Cout).astype(np.float32)
+    code = P.W2L_BF16 if dtype == "bf16" else P.W2L_F32
+    xd, wd, bd, dyd = to_dev(x, dtype), to_dev(w, dtype), to_dev(bias), to_dev(dy, dtype)
+    y_o, dx_o = oracle.conv1d_fwd(x, w, bias, s), oracle.conv1d_bwd_data(dy, w, T, s)
+    dw_o, db_o = oracle.conv1d_bwd_weight(x, dy, k, s)
+    ws = lambda q, use: P.workspace(q(B, T, Cin, Cout, k, s, code)) if use else None
+    for use in (False, True):
+        y = P.w2l_conv1d_fwd(xd, wd, bd, empty((B, Tp, Cout), dtype), s, ws(P.w2l_conv1d_fwd_workspace_bytes, use))
+        _check(to_host(y), y_o, dtype == "bf16", "y")
+        dx = P.w2l_conv1d_bwd_data(dyd, wd, empty((B, T, Cin), dtype), s, ws(P.w2l_conv1d_bwd_data_workspace_bytes, use))
+        _check(to_host(dx), dx_o, dtype == "bf16", "dx")
+    wsw = ws(P.w2l_conv1d_bwd_weight_workspace_bytes, True)
+    dw, db = P.w2l_conv1d_bwd_weight(xd, dyd, empty((Cout, k, Cin)), empty((Cout,)), s, False, wsw)
+    _check(to_host(dw), dw_o, False, "dw")
+    _check(to_host(db), db_o, False, "db")
+    P.w2l_conv1d_bwd_weight(xd, dyd, dw, db, s, True, wsw)
+    _check(to_host(dw), 2 * dw_o, False, "dw accumulated")
+    _check(to_host(db), 2 * db_o, False, "db accumulated")
+    P.w2l_conv1d_bwd_weight(xd, dyd, dw, None, s, False, wsw)
+    _check(to_host(dw), dw_o, False, "dw without db")
+
+
+def test_fp32_train_step_split_and_ragged():
+    """An fp32 network whose layers take every form of the kernels inside a step: a strided first layer over dense
+    features, split reductions finished by the GLU passes, channel counts off the chunks."""
+    import paper_1812_07625_amd as P
+    from test_gpu_parity import check_train_step, oracle_train_step
+    from workloads.device import run_train_step
+    layers = [dict(k=5, stride=2, cin=40, cout=256, glu=1), dict(k=9, stride=1, cin=128, cout=256, glu=1),
+              dict(k=3, stride=1, cin=128, cout=140, glu=1), dict(k=3, stride=1, cin=70, cout=64, glu=0),
+              dict(k=1, stride=1, cin=64, cout=40, glu=0)]
+    cfg = W.small_model(51, 3, 120, 201, 40, layers, False, 4, 20)
+    check_train_step(run_train_step(P, cfg), oracle_train_step(cfg), "f32")
