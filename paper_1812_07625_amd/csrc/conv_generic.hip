@@ -683,7 +683,9 @@ int wgrad_t(const ConvDesc& d, const AnyPlan& pl, const void* x, const void* dy,
     // with x and dy in one haloed layout the reduction runs straight through its frames: dy is zero in the halo
     // frames, and in the slack that the last panel reads into
     const long long walk = (long long)(d.B - 1) * d.y_pitch + d.Tp;
-    const bool fast = wgrad_walks(d) && walk <= (long long)pl.per * pl.splits;
+    // (only the kernel that launch_any takes for fp32 operands in whole chunks walks; the others count real frames)
+    const bool fast = std::is_same<TX, float>::value && std::is_same<TDY, float>::value && a.chunks() && b.chunks() && wgrad_walks(d) &&
+                      walk <= (long long)pl.per * pl.splits;
     const long long R = fast ? walk : (long long)d.B * d.Tp;
     return launch_any(pl, a, b, ep, d.Cout, (long long)d.k * d.Cin, R, st, dbias, accumulate, fast);
 }

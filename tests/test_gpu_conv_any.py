@@ -84,3 +84,16 @@ def test_fp32_train_step_split_and_ragged():
               dict(k=1, stride=1, cin=64, cout=40, glu=0)]
     cfg = W.small_model(51, 3, 120, 201, 40, layers, False, 4, 20)
     check_train_step(run_train_step(P, cfg), oracle_train_step(cfg), "f32")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_train_step_haloed_layers_off_the_chunks(dtype):
+    """Gated layers on either side of 70 channels: x and dy of the weight gradient share the step's haloed layout, but
+    their lines are no whole chunks, so the reduction counts real frames (of several utterances)."""
+    import paper_1812_07625_amd as P
+    from test_gpu_parity import check_train_step, oracle_train_step
+    from workloads.device import run_train_step
+    layers = [dict(k=5, stride=1, cin=40, cout=140, glu=1), dict(k=5, stride=1, cin=70, cout=140, glu=1),
+              dict(k=3, stride=1, cin=70, cout=140, glu=1), dict(k=1, stride=1, cin=70, cout=40, glu=0)]
+    cfg = W.small_model(52, 3, 120, 201, 40, layers, dtype == "bf16", 4, 20)
+    check_train_step(run_train_step(P, cfg), oracle_train_step(cfg), dtype)
