@@ -57,7 +57,7 @@ static bool wgrad_is_generic(const ConvDesc& d, int dt, int dydt)
 int conv_fwd(const ConvDesc& d, const void* x, const void* w, const float* bias, void* y, int dt, int ydt,
              hipStream_t st, void* scratch, size_t scratch_bytes)
 {
-    if (!conv_fwd_is_generic(d, dt)) return conv_fwd_mfma(d, x, w, bias, y, ydt, st);
+    if (!conv_fwd_is_generic(d, dt)) return conv_fwd_mfma(d, x, w, bias, y, ydt, st, scratch, scratch_bytes);
     return conv_fwd_generic(d, x, w, bias, y, dt, ydt, st, scratch, scratch_bytes);
 }
 
@@ -68,11 +68,33 @@ int conv_dgrad(const ConvDesc& d, const void* dy, const void* w, void* dx, int d
     return conv_dgrad_generic(d, dy, w, dx, dt, dydt, st, scratch, scratch_bytes);
 }
 
+int conv_fwd_parts(const ConvDesc& d, int dt) { return conv_fwd_is_generic(d, dt) ? conv_fwd_generic_parts(d) : conv_fwd_mfma_parts(d); }
+int conv_dgrad_parts(const ConvDesc& d, int dt, int dydt)
+{
+    return conv_dgrad_is_generic(d, dt, dydt) ? conv_dgrad_generic_parts(d) : conv_dgrad_mfma_parts(d);
+}
+int conv_fwd_partial(const ConvDesc& d, const void* x, const void* w, int dt, float* part, hipStream_t st)
+{
+    return conv_fwd_is_generic(d, dt) ? conv_fwd_generic_partial(d, x, w, dt, part, st) : conv_fwd_mfma_partial(d, x, w, part, st);
+}
+int conv_dgrad_partial(const ConvDesc& d, const void* dy, const void* w, int dt, int dydt, float* part, hipStream_t st)
+{
+    return conv_dgrad_is_generic(d, dt, dydt) ? conv_dgrad_generic_partial(d, dy, w, dt, dydt, part, st) : conv_dgrad_mfma_partial(d, dy, w, part, st);
+}
+size_t conv_fwd_scratch(const ConvDesc& d, int dt) { return conv_fwd_is_generic(d, dt) ? conv_fwd_generic_scratch(d) : conv_fwd_mfma_scratch(d); }
+size_t conv_dgrad_scratch(const ConvDesc& d, int dt, int dydt)
+{
+    return conv_dgrad_is_generic(d, dt, dydt) ? conv_dgrad_generic_scratch(d) : conv_dgrad_scratch_bytes(d);
+}
+
 // scratch of a weight gradient: column sums, then what the kernel of the shape needs
 static size_t wgrad_dbias_scratch(const ConvDesc& d) { return round_up((size_t)DBIAS_CHUNKS * d.Cout * 4, 256); }
-size_t conv_wgrad_scratch_bytes(const ConvDesc& d)
+size_t conv_wgrad_scratch_bytes(const ConvDesc& d, int dt, int dydt)
 {
-    return wgrad_dbias_scratch(d) + (d.Cout <= 32 ? conv_wgrad_skinny_scratch(d.Cin, d.Cout, d.k) : conv_wgrad_generic_scratch(d));
+    const size_t rest = d.Cout <= 32                  ? conv_wgrad_skinny_scratch(d.Cin, d.Cout, d.k)
+                        : wgrad_is_generic(d, dt, dydt) ? conv_wgrad_generic_scratch(d)
+                                                        : conv_wgrad_mfma_scratch(d);
+    return wgrad_dbias_scratch(d) + rest;
 }
 
 bool conv_wgrad_fuses_dbias(const ConvDesc& d, int dt, int dydt)
@@ -82,20 +104,21 @@ bool conv_wgrad_fuses_dbias(const ConvDesc& d, int dt, int dydt)
 }
 
 int conv_wgrad(const ConvDesc& d, const void* x, const void* dy, float* dw, float* dbias, int dt, int dydt,
-               int accumulate, void* scratch, hipStream_t st)
+               int accumulate, void* scratch, size_t scratch_bytes, hipStream_t st)
 {
     float* dbias_scratch = static_cast<float*>(scratch);
     unsigned char* rest = static_cast<unsigned char*>(scratch) + wgrad_dbias_scratch(d);
+    const size_t rest_bytes = scratch_bytes - wgrad_dbias_scratch(d);
     if (wgrad_is_generic(d, dt, dydt))
-        return conv_wgrad_generic(d, x, dy, dw, dbias, dt, dydt, accumulate, st, rest, conv_wgrad_generic_scratch(d));
-    if (dbias && conv_wgrad_fuses_dbias(d, dt, dydt)) return conv_wgrad_mfma(d, x, dy, dw, dbias, accumulate, st);
+        return conv_wgrad_generic(d, x, dy, dw, dbias, dt, dydt, accumulate, st, rest, rest_bytes);
+    if (dbias && conv_wgrad_fuses_dbias(d, dt, dydt)) return conv_wgrad_mfma(d, x, dy, dw, dbias, accumulate, st, rest, rest_bytes);
     if (dbias) {
         // halo frames hold zeros, so summing every frame of the allocation is the same sum
         const int rc = dbias_reduce(dy, dbias, (long long)d.B * d.y_pitch, d.Cout, dydt, accumulate, dbias_scratch, st);
         if (rc) return rc;
     }
     if (d.Cout <= 32) return conv_wgrad_skinny(d, x, dy, dw, dt, dydt, accumulate, reinterpret_cast<float*>(rest), st);
-    return conv_wgrad_mfma(d, x, dy, dw, nullptr, accumulate, st);
+    return conv_wgrad_mfma(d, x, dy, dw, nullptr, accumulate, st, rest, rest_bytes);
 }
 
 }  // namespace w2l
@@ -124,9 +147,9 @@ extern "C" size_t w2l_conv1d_fwd_workspace_bytes(int B, int T, int Cin, int Cout
 {
     if (check_conv_shape(B, T, Cin, Cout, k, stride)) return 0;
     const ConvDesc d = dense_desc(B, T, Cin, Cout, k, stride);
-    if (stage_fwd(Cin, Cout, k, stride, dtype)) return haloed_bytes(B, T, Cin);
-    if (stage_fwd_f32(Cin, k, stride, dtype)) return haloed_bytes(B, T, 2 * Cin) + conv_fwd_generic_scratch(d);
-    return valid_dtype(dtype) && conv_fwd_is_generic(d, dtype) ? conv_fwd_generic_scratch(d) : 0;
+    if (!valid_dtype(dtype)) return 0;
+    const bool f32 = stage_fwd_f32(Cin, k, stride, dtype);
+    return (f32 || stage_fwd(Cin, Cout, k, stride, dtype) ? haloed_bytes(B, T, f32 ? 2 * Cin : Cin) : 0) + conv_fwd_scratch(d, dtype);
 }
 
 extern "C" int w2l_conv1d_fwd(const void* x, const void* w, const float* bias, void* y, int B, int T, int Cin,
@@ -209,7 +232,9 @@ extern "C" size_t w2l_conv1d_bwd_data_workspace_bytes(int B, int T, int Cin, int
     if (p.ok) return p.total();
     if (!valid_dtype(dtype)) return 0;
     const size_t copy = stage_dgrad_f32(Cin, Cout, k, stride, dtype) ? haloed_bytes(B, T, 2 * Cout) : 0;
-    return copy + conv_dgrad_generic_scratch(dense_desc(B, T, Cin, Cout, k, stride));
+    const ConvDesc d = dense_desc(B, T, Cin, Cout, k, stride);
+    const size_t a = conv_dgrad_scratch(d, dtype, dtype), b = conv_dgrad_scratch(d, dtype, W2L_F32);
+    return copy + (a > b ? a : b);
 }
 
 extern "C" int w2l_conv1d_bwd_data(const void* dy, const void* w, void* dx, int B, int T, int Cin, int Cout,
@@ -232,6 +257,7 @@ extern "C" int w2l_conv1d_bwd_data(const void* dy, const void* w, void* dx, int 
         const DgradPrep p = dgrad_prep(B, T, Cin, Cout, k, stride, dtype);
         const bool plain_1x1 = k == 1 && stride == 1 && dy_dtype == W2L_BF16 && !p.copy_w;
         if (p.ok && !plain_1x1) return conv_dgrad_prepared(p, dy, dy_dtype, w, dx, workspace, st);
+        if (plain_1x1 && p.ok) return conv_dgrad(dense_desc(B, T, Cin, Cout, k, stride), dy, w, dx, dtype, dy_dtype, st, workspace, need);
         if (!p.ok) {
             ConvDesc d = dense_desc(B, T, Cin, Cout, k, stride);
             if (!stage_dgrad_f32(Cin, Cout, k, stride, dtype)) return conv_dgrad(d, dy, w, dx, dtype, dy_dtype, st, workspace, need);
@@ -251,7 +277,8 @@ extern "C" size_t w2l_conv1d_bwd_weight_workspace_bytes(int B, int T, int Cin, i
                                                         int dtype)
 {
     if (check_conv_shape(B, T, Cin, Cout, k, stride)) return 0;
-    size_t n = conv_wgrad_scratch_bytes(dense_desc(B, T, Cin, Cout, k, stride));
+    if (!valid_dtype(dtype)) return 0;
+    size_t n = conv_wgrad_scratch_bytes(dense_desc(B, T, Cin, Cout, k, stride), dtype, dtype);
     ConvDesc f;
     if (stage_wgrad(Cin, Cout, k, stride, dtype)) n += haloed_bytes(B, T, Cin) + haloed_bytes(B, T, Cout);
     else if (stage_wgrad_f32(Cin, Cout, k, stride, dtype)) n += haloed_bytes(B, T, 2 * Cin) + haloed_bytes(B, T, 2 * Cout);
@@ -274,21 +301,22 @@ extern "C" int w2l_conv1d_bwd_weight(const void* x, const void* dy, float* dw, f
     hipStream_t st = (hipStream_t)stream;
     ConvDesc d = dense_desc(B, T, Cin, Cout, k, stride);
     unsigned char* ws = static_cast<unsigned char*>(workspace);
+    const size_t scratch = conv_wgrad_scratch_bytes(d, dtype, dtype);  // (an fp32 dy of bf16 operands splits as far as this takes it)
     ConvDesc f;
     if (dy_dtype == W2L_BF16 && stage_wgrad_folded(B, T, Cin, Cout, k, stride, dtype, f)) {
-        unsigned char* xp = ws + conv_wgrad_scratch_bytes(d);
+        unsigned char* xp = ws + scratch;
         unsigned char* dyp = xp + haloed_bytes(B, f.T, f.Cin);
         rc = pad_layout2_bf16(x, xp, f.Cin, dy, dyp, Cout, B, f.T, f.T + 2 * ABI_HALO, ABI_HALO, ABI_SLACK_ZERO, st);
         if (rc) return rc;
         f.x_pitch = f.y_pitch = f.T + 2 * ABI_HALO;
         f.x_halo = f.y_halo = ABI_HALO;
         f.slack = ABI_SLACK;
-        return conv_wgrad(f, xp, dyp, dw, dbias, dtype, dy_dtype, accumulate, workspace, st);
+        return conv_wgrad(f, xp, dyp, dw, dbias, dtype, dy_dtype, accumulate, workspace, scratch, st);
     }
     const bool f32 = stage_wgrad_f32(Cin, Cout, k, stride, dtype);
     if (f32 || (dy_dtype == W2L_BF16 && stage_wgrad(Cin, Cout, k, stride, dtype))) {
         const int e = f32 ? 2 : 1;
-        unsigned char* xp = ws + conv_wgrad_scratch_bytes(d);
+        unsigned char* xp = ws + scratch;
         unsigned char* dyp = xp + haloed_bytes(B, T, e * Cin);
         rc = pad_layout2_bf16(x, xp, e * Cin, dy, dyp, e * Cout, B, T, T + 2 * ABI_HALO, ABI_HALO, ABI_SLACK_ZERO, st);
         if (rc) return rc;
@@ -298,7 +326,7 @@ extern "C" int w2l_conv1d_bwd_weight(const void* x, const void* dy, float* dw, f
         x = xp;
         dy = dyp;
     }
-    return conv_wgrad(d, x, dy, dw, dbias, dtype, dy_dtype, accumulate, workspace, st);
+    return conv_wgrad(d, x, dy, dw, dbias, dtype, dy_dtype, accumulate, workspace, scratch, st);
 }
 
 // ---- measurement aid: what the matrix pipe sustains with nothing else going on -----------

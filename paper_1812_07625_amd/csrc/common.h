@@ -105,11 +105,22 @@ int conv_dgrad(const ConvDesc& d, const void* dy, const void* w, void* dx, int d
                void* scratch = nullptr, size_t scratch_bytes = 0);
 size_t conv_dgrad_scratch_bytes(const ConvDesc& d);
 // scratch: conv_wgrad_scratch_bytes() bytes of device memory
-size_t conv_wgrad_scratch_bytes(const ConvDesc& d);
+size_t conv_wgrad_scratch_bytes(const ConvDesc& d, int dt, int dydt);
 // true where conv_wgrad() produces dbias inside the weight-gradient launch (no separate column-sum kernels)
 bool conv_wgrad_fuses_dbias(const ConvDesc& d, int dt, int dydt);
 int conv_wgrad(const ConvDesc& d, const void* x, const void* dy, float* dw, float* dbias, int dt, int dydt,
-               int accumulate, void* scratch, hipStream_t st);
+               int accumulate, void* scratch, size_t scratch_bytes, hipStream_t st);
+
+constexpr size_t MAX_PARTIALS = 96u << 20;  // bytes of partial sums that a split reduction may leave (they stay in the memory-side cache)
+// Planes of fp32 sums that the pass leaves in front of the GLU pass that adds them up (1: the pass is not split), the
+// bytes they take, and the launch: whichever kernels the type and shape take (api.hip)
+int conv_fwd_parts(const ConvDesc& d, int dt);
+int conv_dgrad_parts(const ConvDesc& d, int dt, int dydt);
+int conv_fwd_partial(const ConvDesc& d, const void* x, const void* w, int dt, float* part, hipStream_t st);
+int conv_dgrad_partial(const ConvDesc& d, const void* dy, const void* w, int dt, int dydt, float* part, hipStream_t st);
+// scratch of conv_fwd / conv_dgrad
+size_t conv_fwd_scratch(const ConvDesc& d, int dt);
+size_t conv_dgrad_scratch(const ConvDesc& d, int dt, int dydt);
 
 // kernels for any shape and type (conv_generic.hip).  scratch (optional): *_scratch() bytes; given them, a problem
 // with too few tiles for the chip splits its reduction and adds the fp32 sums in a finishing launch
@@ -140,7 +151,16 @@ int dbias_reduce(const void* dy, float* dbias, long long rows, int Cout, int dyd
 
 // MFMA (bf16 operands, fp32 accumulate) paths; *_ok() says whether a shape is taken
 bool conv_fwd_mfma_ok(const ConvDesc& d);
-int conv_fwd_mfma(const ConvDesc& d, const void* x, const void* w, const float* bias, void* y, int ydt, hipStream_t st);
+int conv_fwd_mfma(const ConvDesc& d, const void* x, const void* w, const float* bias, void* y, int ydt, hipStream_t st,
+                  void* scratch = nullptr, size_t scratch_bytes = 0);
+// scratch (optional) of a pass that splits its reduction: conv_*_mfma_scratch(d) bytes (data gradient:
+// conv_dgrad_scratch_bytes); *_parts() > 1: planes of sums for the finish_glu_* pass, as the *_generic_* functions
+size_t conv_fwd_mfma_scratch(const ConvDesc& d);
+int conv_fwd_mfma_parts(const ConvDesc& d);
+int conv_fwd_mfma_partial(const ConvDesc& d, const void* x, const void* w, float* part, hipStream_t st);
+int conv_dgrad_mfma_parts(const ConvDesc& d);
+int conv_dgrad_mfma_partial(const ConvDesc& d, const void* dy, const void* w, float* part, hipStream_t st);
+size_t conv_wgrad_mfma_scratch(const ConvDesc& d);
 bool conv_dgrad_mfma_ok(const ConvDesc& d);
 // tickets_zeroed: the first DGRAD_TICKET_BYTES of scratch are already zero on the stream (the caller's staging
 // launch cleared them), so the launch that would clear them is left out
@@ -164,7 +184,8 @@ bool dgrad_split_ok(const ConvDesc& d);
 bool conv_wgrad_mfma_ok(const ConvDesc& d);
 // dbias (nullable): only where conv_wgrad_mfma_takes_dbias(d) -- the bias gradient comes out of the same launch
 bool conv_wgrad_mfma_takes_dbias(const ConvDesc& d);
-int conv_wgrad_mfma(const ConvDesc& d, const void* x, const void* dy, float* dw, float* dbias, int accumulate, hipStream_t st);
+int conv_wgrad_mfma(const ConvDesc& d, const void* x, const void* dy, float* dw, float* dbias, int accumulate, hipStream_t st,
+                    void* scratch = nullptr, size_t scratch_bytes = 0);
 
 // w2l_ctc_fwd_bwd with in_len counted before a total stride len_div (ctc.hip): the criterion sees ceil(in_len / len_div)
 int ctc_fwd_bwd_strided(const float* input, int is_logits, const int* targets, const int* in_len, const int* tgt_len,

@@ -846,7 +846,6 @@ __global__ void colsum_stage2(const float* part, float* dbias, int chunks, int C
 namespace {
 // a finishing launch of its own costs about 5 us; inside the train step it is the layer's GLU, launched in any case
 constexpr double FINISH_OWN = 12000, FINISH_FREE = 2000;
-constexpr size_t MAX_PARTIALS = 96u << 20;
 AnyPlan fwd_plan(const ConvDesc& d, size_t budget, double fin) { return any_plan((long long)d.B * d.Tp, d.Cout, (long long)d.k * d.Cin, budget, fin); }
 AnyPlan dgrad_plan(const ConvDesc& d, size_t budget, double fin)
 {
@@ -933,7 +932,10 @@ int conv_wgrad_generic(const ConvDesc& d, const void* x, const void* dy, float* 
     // (the bias sums of the splits lie behind the weight sums: one more column)
     const long long n = (long long)d.k * d.Cin, plane = d.Cout * n;
     AnyPlan pl = wgrad_plan(d, MAX_PARTIALS);
-    if (!scratch || scratch_bytes < part_bytes(pl.splits, d.Cout, n + 1)) pl = wgrad_plan(d, 0);
+    if (!scratch || scratch_bytes < part_bytes(pl.splits, d.Cout, n + 1)) {
+        const size_t bias = (size_t)17 * d.Cout * 4;  // (room for the bias sums of 16 splits, rounded up)
+        pl = wgrad_plan(d, scratch && scratch_bytes > bias ? scratch_bytes - bias : 0);
+    }
     float* part = static_cast<float*>(scratch);
     const bool split = pl.splits > 1;
     float* const out = split ? part : dw;

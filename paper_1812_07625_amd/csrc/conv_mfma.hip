@@ -38,6 +38,7 @@
 // (k-1)/2 frames around every utterance (the train step keeps its activations that way): every
 // window is then plain in-bounds memory, the per-lane byte offsets are loop invariants, the
 // panel advance is a scalar add on the base pointer, and a load costs three instructions.
+#include <cmath>
 #include <map>
 #include <type_traits>
 #include <mutex>
@@ -740,7 +741,7 @@ __device__ __forceinline__ long long out_row(int m, int frames, int pitch, int h
 // =============================== forward ================================================
 template <int BM, int BN, int BKT, int STAGES, int KG, int GN, bool FAST, typename TO>
 __global__ __launch_bounds__(256 * KG * GN) void conv_fwd_k(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w,
-                                                 const float* __restrict__ bias, TO* __restrict__ y, ConvGeom g)
+                                                 const float* __restrict__ bias, TO* __restrict__ y, ConvGeom g, int per, long long plane)
 {
     using PA = PanelK<BM, BKT, 4 * KG * GN>;
     using PB = PanelK<BN, BKT, 4 * KG * GN>;
@@ -789,7 +790,13 @@ __global__ __launch_bounds__(256 * KG * GN) void conv_fwd_k(const bf16_t* __rest
     }
     Core<BM, BN, BKT, KG, GN, PA, PB> core;
     core.zero();
-    const int nsteps = (K + BKT - 1) / BKT;  // FAST requires K % BKT == 0
+    const int total = (K + BKT - 1) / BKT, st0 = blockIdx.y * per;  // FAST requires K % BKT == 0
+    const int nsteps = total - st0 < per ? total - st0 : per;       // this split's panels
+    y += blockIdx.y * plane;
+    if (FAST) {
+        x += st0 * BKT;
+        w += st0 * BKT;
+    }
     run_ring<STAGES, KG * GN, PA::NI + PB::NI, STAGE, PA::BYTES>(
         core, lds, nsteps,
         [&](int i, int st, unsigned dst) {
@@ -798,8 +805,8 @@ __global__ __launch_bounds__(256 * KG * GN) void conv_fwd_k(const bf16_t* __rest
                 if (i < PA::NI) pa.issue_fast(i, x + r0, dst);
                 else pb.issue_fast(i - PA::NI, w + r0, dst + PA::BYTES);
             } else {
-                if (i < PA::NI) pa.issue(i, st * BKT, dst);
-                else pb.issue(i - PA::NI, st * BKT, dst + PA::BYTES);
+                if (i < PA::NI) pa.issue(i, (st0 + st) * BKT, dst);
+                else pb.issue(i - PA::NI, (st0 + st) * BKT, dst + PA::BYTES);
             }
         },
         grp, kg, wm, wn, lane);
@@ -949,9 +956,9 @@ __global__ __launch_bounds__(256 * KG) void conv_fwd_slab_k(const bf16_t* __rest
 
 // =============================== data gradient (stride 1) =============================
 // dx[b,t,ci] = sum_{j',co} dy[b, t-p+j', co] * w[co, k-1-j', ci]
-template <int BM, int BN, int BKT, int STAGES, int KG, int GN, bool FAST>
+template <int BM, int BN, int BKT, int STAGES, int KG, int GN, bool FAST, typename TO>
 __global__ __launch_bounds__(256 * KG * GN) void conv_dgrad_k(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ w,
-                                                   bf16_t* __restrict__ dx, ConvGeom g)
+                                                   TO* __restrict__ dx, ConvGeom g, int per, long long plane)
 {
     using PA = PanelK<BM, BKT, 4 * KG * GN>;
     using PB = PanelMN<BN, BKT, 4 * KG * GN>;
@@ -989,12 +996,14 @@ __global__ __launch_bounds__(256 * KG * GN) void conv_dgrad_k(const bf16_t* __re
     }
     Core<BM, BN, BKT, KG, GN, PA, PB> core;
     core.zero();
-    const int nsteps = K / BKT;  // Cout is a multiple of BKT: a panel stays inside one tap
+    const int total = K / BKT, st0 = blockIdx.y * per;  // Cout is a multiple of BKT: a panel stays inside one tap
+    const int nsteps = total - st0 < per ? total - st0 : per;  // this split's panels
+    dx += blockIdx.y * plane;
     run_ring<STAGES, KG * GN, PA::NI + PB::NI, STAGE, PA::BYTES>(
         core, lds, nsteps,
         [&](int i, int st, unsigned dst) {
             const int stc = (FAST && st >= nsteps) ? nsteps - 1 : st;
-            const int r0 = stc * BKT;
+            const int r0 = (st0 + stc) * BKT;
             if (i < PA::NI) {
                 if (FAST) pa.issue_fast(i, dy + r0, dst);
                 else pa.issue(i, r0, dst);
@@ -1017,11 +1026,18 @@ __global__ __launch_bounds__(256 * KG * GN) void conv_dgrad_k(const bf16_t* __re
         },
         grp, kg, wm, wn, lane);
     core.reduce_groups(lds, kg, w4, lane);
+    if constexpr (sizeof(TO) == 4) {  // a split's sums
+        core.for_each(kg, wm, wn, lane, [&](int mm, int nn, float v, int) {
+            const int m = m0 + mm, n = n0 + nn;
+            if (m < M && n < N) dx[(size_t)m * N + n] = v;
+        });
+        return;
+    }
     float zero[core.TN];
 #pragma unroll
     for (int j = 0; j < core.TN; ++j) zero[j] = 0.f;
     store_tile_bf16<BM, BN, 256 * KG * GN, STAGES * STAGE>(
-        core, lds, zero, dx, n0, N, kg, wm, wn, lane,
+        core, lds, zero, reinterpret_cast<bf16_t*>(dx), n0, N, kg, wm, wn, lane,
         [&](int r) { return m0 + r < M ? out_row(m0 + r, g.T, g.x_pitch, g.x_halo) : -1LL; });
 }
 
@@ -1187,7 +1203,8 @@ __global__ __launch_bounds__(256) void zero_rows_k(bf16_t* __restrict__ p, long 
 // gradient -- computed by the same pipeline with the same loads per phase, in a fixed order.
 template <int BM, int BN, int BKT, int STAGES, int KG, int GN, bool FAST, bool BIAS>
 __global__ __launch_bounds__(256 * KG * GN) void conv_wgrad_k(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dy,
-                                                   float* __restrict__ dw, float* __restrict__ dbias, ConvGeom g, int accumulate)
+                                                   float* __restrict__ dw, float* __restrict__ dbias, ConvGeom g, int accumulate,
+                                                   int per)
 {
     static_assert(FAST || !BIAS, "the bias column rides on the dense walk through the frames");
     using PA = PanelMN<BM, BKT, 4 * KG * GN>;
@@ -1219,7 +1236,14 @@ __global__ __launch_bounds__(256 * KG * GN) void conv_wgrad_k(const bf16_t* __re
     }
     const int spb = (g.Tp + BKT - 1) / BKT;  // CHECKED: panels per utterance
     const int frames = (g.B - 1) * g.y_pitch + g.Tp;  // FAST: first real frame of utterance 0 .. last real frame
-    const int nsteps = FAST ? (frames + BKT - 1) / BKT : g.B * spb;
+    const int total = FAST ? (frames + BKT - 1) / BKT : g.B * spb, st0 = blockIdx.y * per;
+    const int nsteps = total - st0 < per ? total - st0 : per;  // this split's panels
+    dw += (size_t)blockIdx.y * M * N;                          // (splits leave planes of sums)
+    if (BIAS) dbias += (size_t)blockIdx.y * M;
+    if (FAST) {
+        dy += (size_t)st0 * BKT * g.Cout;
+        x += (size_t)st0 * BKT * g.Cin;
+    }
     Core<BM, BN, BKT, KG, GN, PA, PB> core;
     core.zero();
     run_ring<STAGES, KG * GN, PA::NI + PB::NI, STAGE, PA::BYTES>(
@@ -1231,7 +1255,7 @@ __global__ __launch_bounds__(256 * KG * GN) void conv_wgrad_k(const bf16_t* __re
                 else pb.issue_fast(i - PA::NI, bias_tile ? ones : x + (g.x_halo - g.p + f0) * g.Cin + n0, dst + PA::BYTES);
                 return;
             }
-            const int b = st / spb, tp0 = (st - b * spb) * BKT;
+            const int b = (st0 + st) / spb, tp0 = (st0 + st - b * spb) * BKT;
             const int left = (st < nsteps) ? g.Tp - tp0 : 0;  // past the end: every row masked
             if (i < PA::NI) {
                 const long long boff = ((long long)b * g.y_pitch + g.y_halo + tp0) * g.Cout + m0;
@@ -1264,6 +1288,13 @@ __global__ __launch_bounds__(256 * KG * GN) void conv_wgrad_k(const bf16_t* __re
         core.for_each(kg, wm, wn, lane, [&](int mm, int nn, float v, int) {
             const int m = m0 + mm;
             if (nn == 0 && m < M) dbias[m] = accumulate ? dbias[m] + v : v;
+        });
+        return;
+    }
+    if (gridDim.y > 1) {  // read again by the next launch
+        core.for_each(kg, wm, wn, lane, [&](int mm, int nn, float v, int) {
+            const int m = m0 + mm, n = n0 + nn;
+            if (m < M && n < N) dw[(size_t)m * N + n] = v;
         });
         return;
     }
@@ -1376,6 +1407,63 @@ bool slab_ok(const ConvDesc& d, int bm, int srows, int C, int frames, int pitch,
     else if (tc.bm == 128 && tc.bn == 256) { CALL(128, 256, 64, 3, 2, 1); }    \
     else { CALL(128, 128, 64, 3, 2, 1); }
 
+// ---- reductions split over workgroups
+// A problem whose tiles do not fill the 256 CUs (each holds one workgroup of these kernels) lasts as long as one tile's
+// reduction whatever the idle CUs could do, so the reduction is cut into runs of panels: a workgroup per tile and run,
+// a plane of fp32 sums per run, and the pass that reads the result next adds the planes up in order (finish_*).
+// Times in us, on which the choice of tile and cut rests, measured on 8 x 128 .. 16 x 1600 frames, 64 .. 2048 channels:
+//   64 steps of the reduction on one CU 0.55 (128 x 128), 0.80 (256 x 128), 0.88 (192 x 192), 1.50 (256 x 256);
+//   a workgroup's first panels and its way out 4; the sums' way to memory and back 4 TB/s;
+//   a finishing pass of its own with its launch 6, where a GLU pass does it about as long as that takes anyway.
+// 16 x 800 frames, k = 11, 256 -> 512, weight gradient beside the data gradient 121 -> 93 us (46 tiles of 256 x 128, five
+// runs, instead of 92 of 128 x 128), 1x1 256 -> 1024 121 -> 46 us; 4 x 619 frames, data gradient 53 -> 32 us.
+constexpr double FINISH_OWN = 6.0, FINISH_FREE = 0.5, GLU_PASS = 5.0;
+double tile_us(int bm, int bn)
+{
+    return bm * bn == 128 * 128 ? 0.55 : bm * bn == 256 * 128 ? 0.80 : bm * bn == 192 * 192 ? 0.88 : 1.50;
+}
+constexpr double ROUND_US = 4.0, PLANE_US = 8.0 / 4e6;  // (per workgroup in turn; per value of a plane)
+double whole_us(long long M, long long N, long long panels, TileChoice tc, int extra = 0)
+{
+    const long long tiles = ((M + tc.bm - 1) / tc.bm) * ((N + tc.bn - 1) / tc.bn + extra);
+    return (double)((tiles + 255) / 256) * (panels * tile_us(tc.bm, tc.bn) + ROUND_US);
+}
+struct SplitPlan { TileChoice tc; int splits; };
+// splits = 1: not worth it against whole (the time of the unsplit path)
+SplitPlan split_plan(long long M, long long N, long long panels, double whole, double finish, int extra = 0)
+{
+    const TileChoice cand[] = {{256, 256}, {192, 192}, {256, 128}, {128, 256}, {128, 128}};
+    SplitPlan best{{0, 0}, 1};
+    double best_t = 0.92 * whole;
+    const double plane = PLANE_US * M * N;
+    if (panels < 4 || panels > 1 << 20 || ROUND_US + 2 * plane + finish >= best_t) return best;
+    const int most = (int)(MAX_PARTIALS / 4.0 / ((double)M * N)), np = (int)panels;
+    for (const TileChoice& c : cand) {
+        const double tiles = (double)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn + extra), us = tile_us(c.bm, c.bn);
+        // as many runs as fill the chip once or twice, or as balance the panels' time and the planes'
+        const double want[] = {256 / tiles, 512 / tiles, std::sqrt(np * us / plane)};
+        for (const double wnt : want) {
+            int s = wnt < 16 ? (int)wnt : 16;
+            s = s < most ? s : most;
+            s = s < np / 2 ? s : np / 2;
+            if (s < 2) continue;
+            const int per = (np + s - 1) / s;
+            s = (np + per - 1) / per;  // (no run without panels)
+            const double t = std::ceil(tiles * s / 256) * (per * us + ROUND_US) + s * plane + finish;
+            if (s > 1 && t < best_t) { best_t = t; best = SplitPlan{c, s}; }
+        }
+    }
+    return best;
+}
+// a split's launch: panels of a tile's depth per split, and the splits that then have any
+struct SplitRun { int per, splits; };
+SplitRun split_run(long long steps, int splits)
+{
+    const int per = (int)((steps + splits - 1) / splits);
+    return SplitRun{per, (int)((steps + per - 1) / per)};
+}
+size_t split_bytes(const SplitPlan& pl, long long M, long long N) { return pl.splits > 1 ? round_up((size_t)pl.splits * M * N * 4, 256) : 0; }
+
 }  // namespace
 
 bool conv_fwd_mfma_ok(const ConvDesc& d)
@@ -1393,48 +1481,75 @@ static int fwd_slab_xcd(const ConvDesc& g, long long tiles_m, long long tiles_n)
     return xcd_split(tiles_m, tiles_n, (double)(192 + g.k - 1) * g.Cin, 192.0 * g.k * g.Cin);
 }
 
-int conv_fwd_mfma(const ConvDesc& g0, const void* x, const void* w, const float* bias, void* y, int ydt, hipStream_t st)
-{
-    ConvDesc g = g0;
-    const long long M = (long long)g.B * g.Tp, N = g.Cout;
-    const TileChoice tc = choose_tile(M, N);
-    const bool fast = halo_ok_x(g) && ((long long)g.k * g.Cin) % 64 == 0;
-    int rc = W2L_OK;
-    if (fast && tc.bm == 192 && tc.bn == 192 && slab_ok(g, 192, 256, g.Cin, g.T, g.x_pitch, g.x_halo)) {
-        constexpr int bytes = slab_lds_bytes(192, 192, 256, 2);
-        const long long F = (long long)(g.B - 1) * g.x_pitch + g.T;
-        const unsigned grid = (unsigned)(((F + 191) / 192) * ((N + 191) / 192));
-        g.xcd_m = fwd_slab_xcd(g, (F + 191) / 192, (N + 191) / 192);
-        if (ydt == W2L_BF16) {
-            rc = set_lds(conv_fwd_slab_k<192, 192, 256, 2, bf16_t, false>, bytes);
-            if (!rc) hipLaunchKernelGGL((conv_fwd_slab_k<192, 192, 256, 2, bf16_t, false>), dim3(grid), dim3(512), bytes, st, (const bf16_t*)x, (const bf16_t*)w, bias, (bf16_t*)y, (bf16_t*)nullptr, g);
-        } else {
-            rc = set_lds(conv_fwd_slab_k<192, 192, 256, 2, float, false>, bytes);
-            if (!rc) hipLaunchKernelGGL((conv_fwd_slab_k<192, 192, 256, 2, float, false>), dim3(grid), dim3(512), bytes, st, (const bf16_t*)x, (const bf16_t*)w, bias, (float*)y, (bf16_t*)nullptr, g);
-        }
-        return rc ? rc : launch_status();
-    }
-#define LAUNCH(KERN, BYTES, ...)                                                          \
+#define W2L_LAUNCH(KERN, BYTES, NTHR, ...)                                                \
     {                                                                                     \
         rc = set_lds(KERN, BYTES);                                                        \
-        if (!rc) hipLaunchKernelGGL(KERN, dim3(grid), dim3(nthreads), BYTES, st, __VA_ARGS__);  \
+        if (!rc) hipLaunchKernelGGL(KERN, grid, dim3(NTHR), BYTES, st, __VA_ARGS__);      \
     }
+
+// splits > 1: y takes a plane of fp32 sums [B * Tp][Cout] per split (bias: nullptr, g's y dense)
+template <typename TO>
+static int launch_fwd(const ConvDesc& g, TileChoice tc, int splits, const void* x, const void* w, const float* bias, TO* y, hipStream_t st)
+{
+    const long long M = (long long)g.B * g.Tp, N = g.Cout;
+    const bool fast = halo_ok_x(g) && ((long long)g.k * g.Cin) % 64 == 0;
+    int rc = W2L_OK;
 #define CALL(BM_, BN_, BK_, ST_, KG_, GN_)                                                                         \
     {                                                                                                         \
         constexpr int bytes = ST_ * (BM_ + BN_) * BK_ * 2;                                                    \
-        const unsigned nthreads = 256 * KG_ * GN_;                                                                  \
-        const unsigned grid = (unsigned)(((M + BM_ - 1) / BM_) * ((N + BN_ - 1) / BN_));                      \
-        if (ydt == W2L_BF16) {                                                                                \
-            if (fast) LAUNCH((conv_fwd_k<BM_, BN_, BK_, ST_, KG_, GN_, true, bf16_t>), bytes, (const bf16_t*)x, (const bf16_t*)w, bias, (bf16_t*)y, g) \
-            else LAUNCH((conv_fwd_k<BM_, BN_, BK_, ST_, KG_, GN_, false, bf16_t>), bytes, (const bf16_t*)x, (const bf16_t*)w, bias, (bf16_t*)y, g)     \
-        } else {                                                                                              \
-            if (fast) LAUNCH((conv_fwd_k<BM_, BN_, BK_, ST_, KG_, GN_, true, float>), bytes, (const bf16_t*)x, (const bf16_t*)w, bias, (float*)y, g)   \
-            else LAUNCH((conv_fwd_k<BM_, BN_, BK_, ST_, KG_, GN_, false, float>), bytes, (const bf16_t*)x, (const bf16_t*)w, bias, (float*)y, g)       \
-        }                                                                                                     \
+        const SplitRun sr = split_run(((long long)g.k * g.Cin + BK_ - 1) / BK_, splits);                      \
+        const dim3 grid((unsigned)(((M + BM_ - 1) / BM_) * ((N + BN_ - 1) / BN_)), (unsigned)sr.splits);      \
+        if (fast) W2L_LAUNCH((conv_fwd_k<BM_, BN_, BK_, ST_, KG_, GN_, true, TO>), bytes, 256 * KG_ * GN_, (const bf16_t*)x, (const bf16_t*)w, bias, y, g, sr.per, M * N) \
+        else W2L_LAUNCH((conv_fwd_k<BM_, BN_, BK_, ST_, KG_, GN_, false, TO>), bytes, 256 * KG_ * GN_, (const bf16_t*)x, (const bf16_t*)w, bias, y, g, sr.per, M * N)     \
     }
     W2L_TILE_DISPATCH(CALL)
 #undef CALL
     return rc ? rc : launch_status();
+}
+
+static SplitPlan fwd_split(const ConvDesc& d, double finish)
+{
+    const long long M = (long long)d.B * d.Tp, N = d.Cout, panels = ((long long)d.k * d.Cin + 63) / 64;
+    return split_plan(M, N, panels, whole_us(M, N, panels, choose_tile(M, N)), finish);
+}
+// in front of a GLU pass that adds the planes up: free, unless the unsplit path has none
+static SplitPlan fwd_split_glu(const ConvDesc& d) { return fwd_split(d, conv_fwd_glu_ok(d) ? GLU_PASS : FINISH_FREE); }
+int conv_fwd_mfma_parts(const ConvDesc& d) { return fwd_split_glu(d).splits; }
+int conv_fwd_mfma_partial(const ConvDesc& d, const void* x, const void* w, float* part, hipStream_t st)
+{
+    const SplitPlan pl = fwd_split_glu(d);
+    ConvDesc g = d;
+    g.y_pitch = g.Tp;
+    g.y_halo = 0;
+    return pl.splits > 1 ? launch_fwd<float>(g, pl.tc, pl.splits, x, w, nullptr, part, st) : W2L_ERR_SHAPE;
+}
+size_t conv_fwd_mfma_scratch(const ConvDesc& d) { return split_bytes(fwd_split(d, FINISH_OWN), (long long)d.B * d.Tp, d.Cout); }
+
+int conv_fwd_mfma(const ConvDesc& g0, const void* x, const void* w, const float* bias, void* y, int ydt, hipStream_t st, void* scratch,
+                  size_t scratch_bytes)
+{
+    ConvDesc g = g0;
+    const long long M = (long long)g.B * g.Tp, N = g.Cout;
+    const SplitPlan pl = fwd_split(g, FINISH_OWN);
+    if (scratch && pl.splits > 1 && scratch_bytes >= split_bytes(pl, M, N)) {
+        g.y_pitch = g.Tp;
+        g.y_halo = 0;
+        const int rc = launch_fwd<float>(g, pl.tc, pl.splits, x, w, nullptr, (float*)scratch, st);
+        return rc ? rc : finish_rows((const float*)scratch, pl.splits, bias, y, ydt, g.B, g.Tp, g.Cout, g0.y_pitch, g0.y_halo, st);
+    }
+    const TileChoice tc = choose_tile(M, N);
+    const bool fast = halo_ok_x(g) && ((long long)g.k * g.Cin) % 64 == 0;
+    if (fast && tc.bm == 192 && tc.bn == 192 && slab_ok(g, 192, 256, g.Cin, g.T, g.x_pitch, g.x_halo)) {
+        constexpr int bytes = slab_lds_bytes(192, 192, 256, 2);
+        const long long F = (long long)(g.B - 1) * g.x_pitch + g.T;
+        const dim3 grid((unsigned)(((F + 191) / 192) * ((N + 191) / 192)));
+        g.xcd_m = fwd_slab_xcd(g, (F + 191) / 192, (N + 191) / 192);
+        int rc = W2L_OK;
+        if (ydt == W2L_BF16) W2L_LAUNCH((conv_fwd_slab_k<192, 192, 256, 2, bf16_t, false>), bytes, 512, (const bf16_t*)x, (const bf16_t*)w, bias, (bf16_t*)y, (bf16_t*)nullptr, g)
+        else W2L_LAUNCH((conv_fwd_slab_k<192, 192, 256, 2, float, false>), bytes, 512, (const bf16_t*)x, (const bf16_t*)w, bias, (float*)y, (bf16_t*)nullptr, g)
+        return rc ? rc : launch_status();
+    }
+    return ydt == W2L_BF16 ? launch_fwd<bf16_t>(g, tc, 1, x, w, bias, (bf16_t*)y, st) : launch_fwd<float>(g, tc, 1, x, w, bias, (float*)y, st);
 }
 
 bool conv_fwd_glu_ok(const ConvDesc& d)
@@ -1479,12 +1594,54 @@ bool dgrad_split_ok(const ConvDesc& g)
     const long long t2 = ((F + 191) / 192) * ((N + 191) / 192);
     return t1 <= 170 && 2 * t2 <= 256 && 2 * t2 > t1;
 }
-size_t conv_dgrad_scratch_bytes(const ConvDesc& g)
+// its scratch
+static size_t dgrad_pair_bytes(const ConvDesc& g)
 {
-    if (!dgrad_split_ok(g)) return 0;
     const long long F = (long long)(g.B - 1) * g.y_pitch + g.Tp;
     const size_t tiles = (size_t)((F + 191) / 192) * ((g.Cin + 191) / 192);
     return DGRAD_TICKET_BYTES + tiles * 2 * 192 * 192 * 4;
+}
+
+template <typename TO>
+static int launch_dgrad(const ConvDesc& g, TileChoice tc, int splits, const void* dy, const void* w, TO* dx, hipStream_t st)
+{
+    const long long M = (long long)g.B * g.T, N = g.Cin;
+    const bool fast = halo_ok_y(g);
+    int rc = W2L_OK;
+#define CALL(BM_, BN_, BK_, ST_, KG_, GN_)                                                                     \
+    {                                                                                                     \
+        constexpr int bytes = ST_ * (BM_ + BN_) * BK_ * 2;                                                \
+        const SplitRun sr = split_run((long long)g.k * g.Cout / BK_, splits);                             \
+        const dim3 grid((unsigned)(((M + BM_ - 1) / BM_) * ((N + BN_ - 1) / BN_)), (unsigned)sr.splits);  \
+        if (fast) W2L_LAUNCH((conv_dgrad_k<BM_, BN_, BK_, ST_, KG_, GN_, true, TO>), bytes, 256 * KG_ * GN_, (const bf16_t*)dy, (const bf16_t*)w, dx, g, sr.per, M * N) \
+        else W2L_LAUNCH((conv_dgrad_k<BM_, BN_, BK_, ST_, KG_, GN_, false, TO>), bytes, 256 * KG_ * GN_, (const bf16_t*)dy, (const bf16_t*)w, dx, g, sr.per, M * N)     \
+    }
+    W2L_TILE_DISPATCH(CALL)
+#undef CALL
+    return rc ? rc : launch_status();
+}
+
+// planes of sums against the paths of one or two workgroups a tile
+static SplitPlan dgrad_split(const ConvDesc& d, double finish)
+{
+    const long long M = (long long)d.B * d.T, N = d.Cin, panels = (long long)d.k * d.Cout / 64;
+    const double pair = panels / 2 * tile_us(192, 192) + ROUND_US + 6;
+    return split_plan(M, N, panels, dgrad_split_ok(d) ? pair : whole_us(M, N, panels, choose_tile(M, N)), finish);
+}
+// in front of a GLU backward pass that adds the planes up: free, unless the unsplit path has none
+static SplitPlan dgrad_split_glu(const ConvDesc& d) { return dgrad_split(d, conv_dgrad_glu_ok(d) ? GLU_PASS : FINISH_FREE); }
+int conv_dgrad_mfma_parts(const ConvDesc& d) { return dgrad_split_glu(d).splits; }
+int conv_dgrad_mfma_partial(const ConvDesc& d, const void* dy, const void* w, float* part, hipStream_t st)
+{
+    const SplitPlan pl = dgrad_split_glu(d);
+    return pl.splits > 1 ? launch_dgrad<float>(d, pl.tc, pl.splits, dy, w, part, st) : W2L_ERR_SHAPE;
+}
+
+size_t conv_dgrad_scratch_bytes(const ConvDesc& g)
+{
+    const size_t a = conv_dgrad_mfma_ok(g) ? split_bytes(dgrad_split(g, FINISH_OWN), (long long)g.B * g.T, g.Cin) : 0;
+    const size_t b = dgrad_split_ok(g) ? dgrad_pair_bytes(g) : 0;
+    return a > b ? a : b;
 }
 
 // grid and XCD cut of the split data gradient's launch (two workgroups per 192x192 tile)
@@ -1501,9 +1658,13 @@ int conv_dgrad_mfma(const ConvDesc& g0, const void* dy, const void* w, void* dx,
     ConvDesc g = g0;
     const long long M = (long long)g.B * g.T, N = g.Cin;
     const TileChoice tc = choose_tile(M, N);
-    const bool fast = halo_ok_y(g);
     int rc = W2L_OK;
-    if (scratch && dgrad_split_ok(g) && scratch_bytes >= conv_dgrad_scratch_bytes(g)) {
+    const SplitPlan pl = dgrad_split(g, FINISH_OWN);
+    if (scratch && pl.splits > 1 && scratch_bytes >= split_bytes(pl, M, N)) {
+        rc = launch_dgrad<float>(g, pl.tc, pl.splits, dy, w, (float*)scratch, st);
+        return rc ? rc : finish_rows((const float*)scratch, pl.splits, nullptr, dx, W2L_BF16, g.B, g.T, g.Cin, g.x_pitch, g.x_halo, st);
+    }
+    if (scratch && dgrad_split_ok(g) && scratch_bytes >= dgrad_pair_bytes(g)) {
         constexpr int bytes = slab_lds_bytes(192, 192, 256, 2);
         const long long F = (long long)(g.B - 1) * g.y_pitch + g.Tp;
         const int tiles = (int)(((F + 191) / 192) * ((N + 191) / 192));
@@ -1514,32 +1675,18 @@ int conv_dgrad_mfma(const ConvDesc& g0, const void* dy, const void* w, void* dx,
             rc = launch_status();
             if (rc) return rc;
         }
-        rc = set_lds(conv_dgrad_slab_k<192, 192, 256, 2, false>, bytes);
-        if (rc) return rc;
         const dim3 grid = dgrad_split_grid(g, (F + 191) / 192, (N + 191) / 192);
-        hipLaunchKernelGGL((conv_dgrad_slab_k<192, 192, 256, 2, false>), grid, dim3(512), bytes, st, (const bf16_t*)dy, (const bf16_t*)w, (bf16_t*)dx, (const bf16_t*)nullptr, part, tickets, g);
-        g.xcd_m = 0;
-        return launch_status();
-    }
-    if (fast && tc.bm == 256 && tc.bn == 128 && slab_ok(g, 256, 320, g.Cout, g.Tp, g.y_pitch, g.y_halo)) {
-        constexpr int bytes = slab_lds_bytes(256, 128, 320, 2);
-        const long long F = (long long)(g.B - 1) * g.y_pitch + g.Tp;
-        const unsigned grid = (unsigned)(((F + 255) / 256) * ((N + 127) / 128));
-        rc = set_lds(conv_dgrad_slab_k<256, 128, 320, 2, false>, bytes);
-        if (!rc) hipLaunchKernelGGL((conv_dgrad_slab_k<256, 128, 320, 2, false>), dim3(grid), dim3(512), bytes, st, (const bf16_t*)dy, (const bf16_t*)w, (bf16_t*)dx, (const bf16_t*)nullptr, (float*)nullptr, (int*)nullptr, g);
+        W2L_LAUNCH((conv_dgrad_slab_k<192, 192, 256, 2, false>), bytes, 512, (const bf16_t*)dy, (const bf16_t*)w, (bf16_t*)dx, (const bf16_t*)nullptr, part, tickets, g)
         return rc ? rc : launch_status();
     }
-#define CALL(BM_, BN_, BK_, ST_, KG_, GN_)                                                                     \
-    {                                                                                                     \
-        constexpr int bytes = ST_ * (BM_ + BN_) * BK_ * 2;                                                \
-        const unsigned nthreads = 256 * KG_ * GN_;                                                              \
-        const unsigned grid = (unsigned)(((M + BM_ - 1) / BM_) * ((N + BN_ - 1) / BN_));                  \
-        if (fast) LAUNCH((conv_dgrad_k<BM_, BN_, BK_, ST_, KG_, GN_, true>), bytes, (const bf16_t*)dy, (const bf16_t*)w, (bf16_t*)dx, g) \
-        else LAUNCH((conv_dgrad_k<BM_, BN_, BK_, ST_, KG_, GN_, false>), bytes, (const bf16_t*)dy, (const bf16_t*)w, (bf16_t*)dx, g)     \
+    if (halo_ok_y(g) && tc.bm == 256 && tc.bn == 128 && slab_ok(g, 256, 320, g.Cout, g.Tp, g.y_pitch, g.y_halo)) {
+        constexpr int bytes = slab_lds_bytes(256, 128, 320, 2);
+        const long long F = (long long)(g.B - 1) * g.y_pitch + g.Tp;
+        const dim3 grid((unsigned)(((F + 255) / 256) * ((N + 127) / 128)));
+        W2L_LAUNCH((conv_dgrad_slab_k<256, 128, 320, 2, false>), bytes, 512, (const bf16_t*)dy, (const bf16_t*)w, (bf16_t*)dx, (const bf16_t*)nullptr, (float*)nullptr, (int*)nullptr, g)
+        return rc ? rc : launch_status();
     }
-    W2L_TILE_DISPATCH(CALL)
-#undef CALL
-    return rc ? rc : launch_status();
+    return launch_dgrad<bf16_t>(g, tc, 1, dy, w, (bf16_t*)dx, st);
 }
 
 bool conv_dgrad_glu_ok(const ConvDesc& d)
@@ -1556,7 +1703,7 @@ int conv_dgrad_glu(const ConvDesc& g0, const void* dy, const void* w, const void
     ConvDesc g = g0;
     const long long F = (long long)(g.B - 1) * g.y_pitch + g.Tp;
     const long long z_end = (long long)g.B * g.y_pitch + LAYOUT_SLACK_ZERO;
-    if (scratch && dgrad_split_ok(g) && scratch_bytes >= conv_dgrad_scratch_bytes(g)) {
+    if (scratch && dgrad_split_ok(g) && scratch_bytes >= dgrad_pair_bytes(g)) {
         // two workgroups per 192x192 tile; the one that finishes a tile applies the GLU backward in its epilogue
         constexpr int bytes = slab_lds_bytes(192, 192, 256, 2);
         const long long tiles_m = (F + 191) / 192;
@@ -1604,28 +1751,51 @@ static bool wgrad_fast(const ConvDesc& g)
 
 bool conv_wgrad_mfma_takes_dbias(const ConvDesc& d) { return conv_wgrad_mfma_ok(d) && wgrad_fast(d); }
 
-int conv_wgrad_mfma(const ConvDesc& g, const void* x, const void* dy, float* dw, float* dbias, int accumulate, hipStream_t st)
+// (the reduction as long as the walk through the haloed layout makes it: the same plan for every layout)
+static SplitPlan wgrad_split(const ConvDesc& d)
+{
+    const long long M = d.Cout, N = d.w_cols ? d.w_cols : (long long)d.k * d.Cin, panels = ((long long)d.B * (d.Tp + 2 * LAYOUT_HALO) + 63) / 64;
+    return split_plan(M, N, panels, whole_us(M, N, panels, choose_tile(M, N), 1), FINISH_OWN, 1);
+}
+size_t conv_wgrad_mfma_scratch(const ConvDesc& d)
+{
+    return split_bytes(wgrad_split(d), d.Cout, (d.w_cols ? d.w_cols : (long long)d.k * d.Cin) + 1);
+}
+
+int conv_wgrad_mfma(const ConvDesc& g, const void* x, const void* dy, float* dw, float* dbias, int accumulate, hipStream_t st, void* scratch,
+                    size_t scratch_bytes)
 {
     const long long M = g.Cout, N = g.w_cols ? g.w_cols : (long long)g.k * g.Cin;
-    const TileChoice tc = choose_tile(M, N);
     const bool fast = wgrad_fast(g);
     if (g.w_cols && !fast) return W2L_ERR_SHAPE;  // a folded layer exists only in the dense walk through the frames
     if (dbias && !fast) return W2L_ERR_SHAPE;  // callers ask conv_wgrad_mfma_takes_dbias() first
     const long long extra = dbias ? 1 : 0;     // the column of tiles that yields the bias gradient
+    TileChoice tc = choose_tile(M, N);
+    int splits = 1;
+    const SplitPlan pl = wgrad_split(g);
+    if (scratch && pl.splits > 1 && scratch_bytes >= conv_wgrad_mfma_scratch(g)) { tc = pl.tc; splits = pl.splits; }
     int rc = W2L_OK;
 #define CALL(BM_, BN_, BK_, ST_, KG_, GN_)                                                                     \
     {                                                                                                     \
         constexpr int bytes = ST_ * (BM_ + BN_) * BK_ * 2;                                                \
-        const unsigned nthreads = 256 * KG_ * GN_;                                                              \
-        const unsigned grid = (unsigned)(((M + BM_ - 1) / BM_) * ((N + BN_ - 1) / BN_ + extra));          \
-        if (fast && dbias) LAUNCH((conv_wgrad_k<BM_, BN_, BK_, ST_, KG_, GN_, true, true>), bytes, (const bf16_t*)x, (const bf16_t*)dy, dw, dbias, g, accumulate) \
-        else if (fast) LAUNCH((conv_wgrad_k<BM_, BN_, BK_, ST_, KG_, GN_, true, false>), bytes, (const bf16_t*)x, (const bf16_t*)dy, dw, (float*)nullptr, g, accumulate) \
-        else LAUNCH((conv_wgrad_k<BM_, BN_, BK_, ST_, KG_, GN_, false, false>), bytes, (const bf16_t*)x, (const bf16_t*)dy, dw, (float*)nullptr, g, accumulate) \
+        const long long steps = fast ? ((long long)(g.B - 1) * g.y_pitch + g.Tp + BK_ - 1) / BK_ : (long long)g.B * ((g.Tp + BK_ - 1) / BK_); \
+        const SplitRun sr = split_run(steps, splits);                                                     \
+        splits = sr.splits;                                                                               \
+        float* const out = splits > 1 ? (float*)scratch : dw;                                             \
+        float* const bout = splits > 1 ? out + splits * M * N : dbias;                                    \
+        const int acc = splits > 1 ? 0 : accumulate;                                                      \
+        const dim3 grid((unsigned)(((M + BM_ - 1) / BM_) * ((N + BN_ - 1) / BN_ + extra)), (unsigned)splits);   \
+        if (fast && dbias) W2L_LAUNCH((conv_wgrad_k<BM_, BN_, BK_, ST_, KG_, GN_, true, true>), bytes, 256 * KG_ * GN_, (const bf16_t*)x, (const bf16_t*)dy, out, bout, g, acc, sr.per) \
+        else if (fast) W2L_LAUNCH((conv_wgrad_k<BM_, BN_, BK_, ST_, KG_, GN_, true, false>), bytes, 256 * KG_ * GN_, (const bf16_t*)x, (const bf16_t*)dy, out, (float*)nullptr, g, acc, sr.per) \
+        else W2L_LAUNCH((conv_wgrad_k<BM_, BN_, BK_, ST_, KG_, GN_, false, false>), bytes, 256 * KG_ * GN_, (const bf16_t*)x, (const bf16_t*)dy, out, (float*)nullptr, g, acc, sr.per) \
     }
     W2L_TILE_DISPATCH(CALL)
 #undef CALL
-#undef LAUNCH
-    return rc ? rc : launch_status();
+#undef W2L_LAUNCH
+    if (!rc) rc = launch_status();
+    if (rc || splits == 1) return rc;
+    const float* const part = (const float*)scratch;
+    return finish_sums(part, splits, M * N, dw, dbias ? part + splits * M * N : nullptr, (int)M, dbias, accumulate, st);
 }
 
 }  // namespace w2l

@@ -59,7 +59,7 @@ struct Plan {
     std::vector<int> Tin, Tout, outch;
     std::vector<size_t> pre, post;  // workspace offsets of conv output (dense) and GLU output (haloed) per layer
     size_t dlogits = 0, crit_len = 0, gdy[3] = {0, 0, 0}, gdh[2] = {0, 0}, ctc = 0, conv = 0, conv0 = 0, dbias = 0, dgs = 0, part = 0, total = 0;
-    size_t ctc_bytes = 0, conv_bytes = 0, dgs_bytes = 0, part_bytes = 0;  // part: sums of split reductions on the caller's stream
+    size_t ctc_bytes = 0, conv_bytes = 0, conv0_bytes = 0, dgs_bytes = 0, part_bytes = 0;  // part: sums of split reductions on the caller's stream
     size_t xfold = 0;      // haloed copy of x with the first layer's stride folded into the channels (0 bytes if unused)
     bool fold0 = false;
     size_t cls = 0;        // operands of the last layer's data gradient prepared for the MFMA kernels (its dy is fp32)
@@ -69,6 +69,23 @@ struct Plan {
 
 size_t max_of(size_t a, size_t b) { return a > b ? a : b; }
 size_t haloed_bytes(int B, int frames, int ch, size_t es) { return ((size_t)B * (frames + 2 * HALO) + SLACK) * ch * es; }
+
+// Geometry of layer i's forward pass (its input is the caller's dense x, i = 0, or the haloed h_{i-1}) and of its
+// gradients (dy haloed too where the layer has a GLU).  p.Tin and p.Tout of the layer have to be known.
+ConvDesc layer_desc(const Plan& p, const w2l_layer* L, int B, int i)
+{
+    ConvDesc d = dense_desc(B, p.Tin[i], L[i].cin, L[i].cout, L[i].k, L[i].stride);
+    if (i > 0) { d.x_pitch = p.Tin[i] + 2 * HALO; d.x_halo = HALO; d.slack = SLACK; }
+    return d;
+}
+ConvDesc layer_bwd_desc(const Plan& p, const w2l_layer* L, int B, int i)
+{
+    ConvDesc d = layer_desc(p, L, B, i);
+    d.slack = 0;  // a dense dy: nothing may be read past its end
+    if (L[i].glu) { d.y_pitch = p.Tout[i] + 2 * HALO; d.y_halo = HALO; d.slack = SLACK; }
+    return d;
+}
+size_t planes_bytes(int parts, size_t values) { return parts > 1 ? parts * values * 4 : 0; }
 
 Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int criterion)
 {
@@ -111,11 +128,15 @@ Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int
         ConvDesc dd = dense_desc(B, t, l.cin, l.cout, l.k, l.stride);
         if (i > 0) { dd.x_pitch = t + 2 * HALO; dd.x_halo = HALO; dd.slack = SLACK; }
         if (l.glu) { dd.y_pitch = to + 2 * HALO; dd.y_halo = HALO; dd.slack = SLACK; }
-        p.conv_bytes = max_of(p.conv_bytes, conv_wgrad_scratch_bytes(dd));
-        if (conv_fwd_is_generic(dd, dtype))
-            p.part_bytes = max_of(p.part_bytes, l.glu ? (size_t)conv_fwd_generic_parts(dd) * B * to * l.cout * 4 : conv_fwd_generic_scratch(dd));
-        if (i > 0 && conv_dgrad_is_generic(dd, dtype, i == n - 1 ? W2L_F32 : dtype))
-            p.part_bytes = max_of(p.part_bytes, L[i - 1].glu ? (size_t)conv_dgrad_generic_parts(dd) * B * t * l.cin * 4 : conv_dgrad_generic_scratch(dd));
+        p.conv_bytes = max_of(p.conv_bytes, conv_wgrad_scratch_bytes(dd, dtype, i == n - 1 ? W2L_F32 : dtype));
+        // sums of split reductions: the geometries that the step's passes will have
+        const ConvDesc fd = layer_desc(p, L, B, i), bd = layer_bwd_desc(p, L, B, i);
+        p.part_bytes = max_of(p.part_bytes, l.glu ? planes_bytes(conv_fwd_parts(fd, dtype), (size_t)B * to * l.cout) : conv_fwd_scratch(fd, dtype));
+        if (i > 0) {
+            const int dydt = i == n - 1 ? W2L_F32 : dtype;
+            p.part_bytes = max_of(p.part_bytes, L[i - 1].glu ? planes_bytes(conv_dgrad_parts(bd, dtype, dydt), (size_t)B * t * l.cin)
+                                                             : conv_dgrad_scratch(bd, dtype, dydt));
+        }
         if (i > 0 && L[i - 1].glu) {
             // scratch of a split-reduction data gradient (tickets and the fp32 sums of both halves)
             ConvDesc sd = dense_desc(B, t, l.cin, l.cout, l.k, l.stride);
@@ -138,7 +159,9 @@ Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int
     p.ctc = off; off += round_up(p.ctc_bytes, 256);
     p.conv = off; off += round_up(p.conv_bytes, 256);
     // layer 0's weight gradient runs on the caller's stream next to the helper stream's launches: its own scratch
-    p.conv0 = off; off += round_up(conv_wgrad_scratch_bytes(dense_desc(B, T, L[0].cin, L[0].cout, L[0].k, L[0].stride)), 256);
+    p.conv0 = off;
+    p.conv0_bytes = conv_wgrad_scratch_bytes(dense_desc(B, T, L[0].cin, L[0].cout, L[0].k, L[0].stride), dtype, n == 1 ? W2L_F32 : dtype);
+    off += round_up(p.conv0_bytes, 256);
     int cmax = 0;
     for (int i = 0; i < n; ++i) cmax = L[i].cout > cmax ? L[i].cout : cmax;
     p.dbias = off; off += round_up((size_t)DBIAS_CHUNKS * cmax * 4, 256);
@@ -212,32 +235,25 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
     const int n = n_layers;
     int rc;
 
-    // geometry of layer i; its input is the caller's dense x (i = 0) or the haloed h_{i-1}
-    auto desc = [&](int i) {
-        const w2l_layer& l = layers[i];
-        ConvDesc d = dense_desc(B, p.Tin[i], l.cin, l.cout, l.k, l.stride);
-        if (i > 0) { d.x_pitch = p.Tin[i] + 2 * HALO; d.x_halo = HALO; d.slack = SLACK; }
-        return d;
-    };
-
     // ---- network forward: y_i = conv(h_{i-1}) + bias (dense), h_i = GLU(y_i) (haloed)
     const void* h = x;
     for (int i = 0; i < n; ++i) {
         const w2l_layer& l = layers[i];
         const int ydt = (i == n - 1) ? W2L_F32 : dtype;
-        const ConvDesc fd = desc(i);
-        if (l.glu && dtype == W2L_BF16 && ydt == W2L_BF16 && conv_fwd_glu_ok(fd)) {
-            rc = conv_fwd_glu(fd, h, weights[i], biases[i], ws + p.pre[i], ws + p.post[i], st);  // GLU in the epilogue
+        const ConvDesc fd = layer_desc(p, layers, B, i);
+        float* const part = reinterpret_cast<float*>(ws + p.part);
+        const int parts = l.glu ? conv_fwd_parts(fd, dtype) : 1;
+        if (parts > 1) {
+            rc = conv_fwd_partial(fd, h, weights[i], dtype, part, st);  // the GLU pass adds the parts up
+            if (rc) return rc;
+            rc = finish_glu_fwd(part, parts, biases[i], ws + p.pre[i], ws + p.post[i], B, p.Tout[i], l.cout, dtype,
+                                p.Tout[i] + 2 * HALO, HALO, SLACK_ZERO, st);
             if (rc) return rc;
             h = ws + p.post[i];
             continue;
         }
-        float* const part = reinterpret_cast<float*>(ws + p.part);
-        if (l.glu && conv_fwd_is_generic(fd, dtype) && conv_fwd_generic_parts(fd) > 1) {
-            rc = conv_fwd_generic_partial(fd, h, weights[i], dtype, part, st);  // the GLU pass adds the parts up
-            if (rc) return rc;
-            rc = finish_glu_fwd(part, conv_fwd_generic_parts(fd), biases[i], ws + p.pre[i], ws + p.post[i], B, p.Tout[i], l.cout, dtype,
-                                p.Tout[i] + 2 * HALO, HALO, SLACK_ZERO, st);
+        if (l.glu && dtype == W2L_BF16 && conv_fwd_glu_ok(fd)) {
+            rc = conv_fwd_glu(fd, h, weights[i], biases[i], ws + p.pre[i], ws + p.post[i], st);  // GLU in the epilogue
             if (rc) return rc;
             h = ws + p.post[i];
             continue;
@@ -300,7 +316,7 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
     bool dy_ready = false;  // dy of the current layer was already written by the layer above
     for (int i = n - 1; i >= 0; --i) {
         const w2l_layer& l = layers[i];
-        ConvDesc d = desc(i);
+        ConvDesc d = layer_bwd_desc(p, layers, B, i);
         const void* dy = dh;
         int dy_dt = dh_dt;
         if (l.glu) {
@@ -313,12 +329,8 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
             }
             dy = gdy;
             dy_dt = dtype;
-            d.y_pitch = p.Tout[i] + 2 * HALO;
-            d.y_halo = HALO;
-            d.slack = SLACK;
-        } else {
-            d.slack = 0;  // dy is dense here: nothing may be read past its end
-            if (side && i > 0 && cur >= 0) gdh_reader[cur] = i;
+        } else if (side && i > 0 && cur >= 0) {
+            gdh_reader[cur] = i;
         }
         dy_ready = false;
         // layer 0 has no data gradient: its weight gradient takes the main stream, next to the
@@ -348,7 +360,7 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
         // on the main stream, which has the shorter chain
         const bool fused_dbias = dbiases[i] && conv_wgrad_fuses_dbias(d, dtype, dy_dt);
         rc = conv_wgrad(d, xin, dy, dweights[i], (fused_dbias || !side) ? dbiases[i] : nullptr, dtype, dy_dt, 0,
-                        ws + (i == 0 ? p.conv0 : p.conv), wst);
+                        ws + (i == 0 ? p.conv0 : p.conv), i == 0 ? p.conv0_bytes : p.conv_bytes, wst);
         if (rc) return rc;
         if (on_side && !hip_ok(hipEventRecord(side->done[i], wst))) return W2L_ERR_LAUNCH;
         if (side && dbiases[i] && !fused_dbias) {
@@ -358,21 +370,22 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
             if (rc) return rc;
         }
         if (i > 0) {
-            if (layers[i - 1].glu && dtype == W2L_BF16 && dy_dt == W2L_BF16 && conv_dgrad_glu_ok(d)) {
+            const bool prepared = i == n - 1 && dy_dt == W2L_F32 && p.cls_prep.ok;
+            const int parts = layers[i - 1].glu && !prepared ? conv_dgrad_parts(d, dtype, dy_dt) : 1;
+            if (parts > 1) {
+                float* const part = reinterpret_cast<float*>(ws + p.part);
                 if (!wait_wgrad(i + 2)) return W2L_ERR_LAUNCH;  // last reader of the slot dy_{i-1} goes into
-                rc = conv_dgrad_glu(d, dy, weights[i], ws + p.pre[i - 1], ws + p.gdy[(i - 1) % 3], ws + p.dgs, p.dgs_bytes, st);
+                rc = conv_dgrad_partial(d, dy, weights[i], dtype, dy_dt, part, st);
+                if (rc) return rc;
+                rc = finish_glu_bwd(part, parts, ws + p.pre[i - 1], ws + p.gdy[(i - 1) % 3], B, p.Tout[i - 1],
+                                    layers[i - 1].cout, dtype, p.Tout[i - 1] + 2 * HALO, HALO, SLACK_ZERO, st);
                 if (rc) return rc;
                 dy_ready = true;
                 continue;
             }
-            const bool prepared = i == n - 1 && dy_dt == W2L_F32 && p.cls_prep.ok;
-            if (layers[i - 1].glu && !prepared && conv_dgrad_is_generic(d, dtype, dy_dt) && conv_dgrad_generic_parts(d) > 1) {
-                float* const part = reinterpret_cast<float*>(ws + p.part);
+            if (layers[i - 1].glu && dtype == W2L_BF16 && dy_dt == W2L_BF16 && conv_dgrad_glu_ok(d)) {
                 if (!wait_wgrad(i + 2)) return W2L_ERR_LAUNCH;
-                rc = conv_dgrad_generic_partial(d, dy, weights[i], dtype, dy_dt, part, st);
-                if (rc) return rc;
-                rc = finish_glu_bwd(part, conv_dgrad_generic_parts(d), ws + p.pre[i - 1], ws + p.gdy[(i - 1) % 3], B, p.Tout[i - 1],
-                                    layers[i - 1].cout, dtype, p.Tout[i - 1] + 2 * HALO, HALO, SLACK_ZERO, st);
+                rc = conv_dgrad_glu(d, dy, weights[i], ws + p.pre[i - 1], ws + p.gdy[(i - 1) % 3], ws + p.dgs, p.dgs_bytes, st);
                 if (rc) return rc;
                 dy_ready = true;
                 continue;
@@ -388,8 +401,7 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
             if (prepared)  // the criterion's fp32 gradient: cast, pad, MFMA
                 rc = conv_dgrad_prepared(p.cls_prep, dy, dy_dt, weights[i], gdhb[q], ws + p.cls, st);
             else
-                rc = conv_dgrad(dd, dy, weights[i], gdhb[q], dtype, dy_dt, st,
-                                conv_dgrad_is_generic(dd, dtype, dy_dt) ? ws + p.part : nullptr, p.part_bytes);
+                rc = conv_dgrad(dd, dy, weights[i], gdhb[q], dtype, dy_dt, st, ws + p.part, p.part_bytes);
             if (rc) return rc;
             dh = gdhb[q];
             cur = q;

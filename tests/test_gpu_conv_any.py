@@ -97,3 +97,56 @@ def test_train_step_haloed_layers_off_the_chunks(dtype):
               dict(k=3, stride=1, cin=70, cout=140, glu=1), dict(k=1, stride=1, cin=70, cout=40, glu=0)]
     cfg = W.small_model(52, 3, 120, 201, 40, layers, dtype == "bf16", 4, 20)
     check_train_step(run_train_step(P, cfg), oracle_train_step(cfg), dtype)
+
+
+SPLIT = [
+    # B, T, Cin, Cout, k, s
+    (1, 131, 256, 128, 11, 1),   # the smallest M of the bf16 kernels: forward and data gradient in many runs
+    (2, 300, 264, 136, 9, 1),    # panels that straddle taps, ragged tiles, a last run shorter than the others
+    (3, 701, 40, 72, 3, 1),      # one tile of weights, a long reduction: the weight gradient in runs
+    (2, 1400, 40, 128, 13, 2),   # the same through the folded stride
+    (2, 1401, 40, 128, 13, 2),   # ... and a stride that does not fold: utterance by utterance
+    (2, 640, 1024, 72, 1, 1),    # 1x1
+]
+
+
+@pytest.mark.parametrize("shape", SPLIT, ids=lambda s: "x".join(map(str, s)))
+def test_bf16_split_reductions(shape):
+    """bf16 passes with too few tiles for the chip: planes of fp32 sums and a finishing pass, against the oracle."""
+    import paper_1812_07625_amd as P
+    B, T, Cin, Cout, k, s = shape
+    rng = np.random.default_rng(sum(shape) + 1)
+    Tp = oracle.out_len(T, s)
+    grid = lambda a: W.round_to_bf16(a.astype(np.float32))
+    x, dy = grid(rng.standard_normal((B, T, Cin))), grid(rng.standard_normal((B, Tp, Cout)))
+    w = grid(rng.standard_normal((Cout, k, Cin)) / np.sqrt(k * Cin))
+    bias = rng.standard_normal(Cout).astype(np.float32)
+    xd, wd, bd, dyd = to_dev(x, "bf16"), to_dev(w, "bf16"), to_dev(bias), to_dev(dy, "bf16")
+    ws = lambda q: P.workspace(q(B, T, Cin, Cout, k, s, P.W2L_BF16))
+    y = P.w2l_conv1d_fwd(xd, wd, bd, empty((B, Tp, Cout), "bf16"), s, ws(P.w2l_conv1d_fwd_workspace_bytes))
+    _check(to_host(y), oracle.conv1d_fwd(x, w, bias, s), True, "y")
+    y = P.w2l_conv1d_fwd(xd, wd, bd, empty((B, Tp, Cout)), s, ws(P.w2l_conv1d_fwd_workspace_bytes))
+    _check(to_host(y), oracle.conv1d_fwd(x, w, bias, s), False, "fp32 y")
+    dx = P.w2l_conv1d_bwd_data(dyd, wd, empty((B, T, Cin), "bf16"), s, ws(P.w2l_conv1d_bwd_data_workspace_bytes))
+    _check(to_host(dx), oracle.conv1d_bwd_data(dy, w, T, s), True, "dx")
+    dw_o, db_o = oracle.conv1d_bwd_weight(x, dy, k, s)
+    wsw = ws(P.w2l_conv1d_bwd_weight_workspace_bytes)
+    dw, db = P.w2l_conv1d_bwd_weight(xd, dyd, empty((Cout, k, Cin)), empty((Cout,)), s, False, wsw)
+    _check(to_host(dw), dw_o, False, "dw")
+    _check(to_host(db), db_o, False, "db")
+    P.w2l_conv1d_bwd_weight(xd, dyd, dw, db, s, True, wsw)
+    _check(to_host(dw), 2 * dw_o, False, "dw accumulated")
+    _check(to_host(db), 2 * db_o, False, "db accumulated")
+
+
+def test_bf16_train_step_split_reductions():
+    """The same inside a step, where the GLU passes add the planes up: a strided first layer, bodies of two widths, a
+    1x1 layer, over few frames."""
+    import paper_1812_07625_amd as P
+    from test_gpu_parity import check_train_step, oracle_train_step
+    from workloads.device import run_train_step
+    layers = [dict(k=13, stride=2, cin=40, cout=512, glu=1), dict(k=7, stride=1, cin=256, cout=512, glu=1),
+              dict(k=5, stride=1, cin=256, cout=272, glu=1), dict(k=1, stride=1, cin=136, cout=512, glu=1),
+              dict(k=1, stride=1, cin=256, cout=29, glu=0)]
+    cfg = W.small_model(53, 3, 200, 301, 40, layers, True, 4, 20)
+    check_train_step(run_train_step(P, cfg), oracle_train_step(cfg), "bf16")
