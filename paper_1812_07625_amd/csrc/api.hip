@@ -99,8 +99,8 @@ size_t conv_wgrad_scratch_bytes(const ConvDesc& d, int dt, int dydt)
 
 bool conv_wgrad_fuses_dbias(const ConvDesc& d, int dt, int dydt)
 {
-    return wgrad_is_generic(d, dt, dydt) ||
-           (d.Cout > 32 && dt == W2L_BF16 && dydt == W2L_BF16 && conv_wgrad_mfma_takes_dbias(d));
+    return d.Cout <= 32 || wgrad_is_generic(d, dt, dydt) ||
+           ( dt == W2L_BF16 && dydt == W2L_BF16 && conv_wgrad_mfma_takes_dbias(d));
 }
 
 int conv_wgrad(const ConvDesc& d, const void* x, const void* dy, float* dw, float* dbias, int dt, int dydt,
@@ -111,13 +111,13 @@ int conv_wgrad(const ConvDesc& d, const void* x, const void* dy, float* dw, floa
     const size_t rest_bytes = scratch_bytes - wgrad_dbias_scratch(d);
     if (wgrad_is_generic(d, dt, dydt))
         return conv_wgrad_generic(d, x, dy, dw, dbias, dt, dydt, accumulate, st, rest, rest_bytes);
+    if (d.Cout <= 32) return conv_wgrad_skinny(d, x, dy, dw, dbias, dt, dydt, accumulate, reinterpret_cast<float*>(rest), st);
     if (dbias && conv_wgrad_fuses_dbias(d, dt, dydt)) return conv_wgrad_mfma(d, x, dy, dw, dbias, accumulate, st, rest, rest_bytes);
     if (dbias) {
         // halo frames hold zeros, so summing every frame of the allocation is the same sum
         const int rc = dbias_reduce(dy, dbias, (long long)d.B * d.y_pitch, d.Cout, dydt, accumulate, dbias_scratch, st);
         if (rc) return rc;
     }
-    if (d.Cout <= 32) return conv_wgrad_skinny(d, x, dy, dw, dt, dydt, accumulate, reinterpret_cast<float*>(rest), st);
     return conv_wgrad_mfma(d, x, dy, dw, nullptr, accumulate, st, rest, rest_bytes);
 }
 

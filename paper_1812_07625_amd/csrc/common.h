@@ -104,6 +104,7 @@ int conv_fwd(const ConvDesc& d, const void* x, const void* w, const float* bias,
 int conv_dgrad(const ConvDesc& d, const void* dy, const void* w, void* dx, int dt, int dydt, hipStream_t st,
                void* scratch = nullptr, size_t scratch_bytes = 0);
 size_t conv_dgrad_scratch_bytes(const ConvDesc& d);
+size_t conv_dgrad_pair_bytes(const ConvDesc& d);  // of conv_dgrad_glu (0: no use for any)
 // scratch: conv_wgrad_scratch_bytes() bytes of device memory
 size_t conv_wgrad_scratch_bytes(const ConvDesc& d, int dt, int dydt);
 // true where conv_wgrad() produces dbias inside the weight-gradient launch (no separate column-sum kernels)
@@ -140,9 +141,9 @@ int conv_dgrad_generic_parts(const ConvDesc& d);
 int conv_fwd_generic_partial(const ConvDesc& d, const void* x, const void* w, int dt, float* part, hipStream_t st);
 int conv_dgrad_generic_partial(const ConvDesc& d, const void* dy, const void* w, int dt, int dydt, float* part, hipStream_t st);
 // narrow outputs (Cout <= 32): row-chunked reduction, SKINNY_CHUNKS partials summed in a fixed order
-enum { SKINNY_CHUNKS = 64 };
+enum { SKINNY_CHUNKS = 64 };  // (dbias, nullable: one more column)
 size_t conv_wgrad_skinny_scratch(int Cin, int Cout, int k);
-int conv_wgrad_skinny(const ConvDesc& d, const void* x, const void* dy, float* dw, int dt, int dydt, int accumulate,
+int conv_wgrad_skinny(const ConvDesc& d, const void* x, const void* dy, float* dw, float* dbias, int dt, int dydt, int accumulate,
                       float* scratch, hipStream_t st);
 // column sums of dy[rows,Cout] -> dbias, two deterministic stages; scratch holds DBIAS_CHUNKS*Cout floats
 enum { DBIAS_CHUNKS = 64 };
@@ -167,6 +168,7 @@ bool conv_dgrad_mfma_ok(const ConvDesc& d);
 int conv_dgrad_mfma(const ConvDesc& d, const void* dy, const void* w, void* dx, void* scratch, size_t scratch_bytes,
                     hipStream_t st, bool tickets_zeroed = false);
 constexpr size_t DGRAD_TICKET_BYTES = 1024;
+int zero_dgrad_tickets(int* tickets, hipStream_t st);
 // forward pass fused with the layer's GLU: writes y (dense, pre-GLU, bf16) and h = GLU(y) into a
 // haloed tensor with the time layout of x (halo frames and the zeroed slack written as zeros)
 bool conv_fwd_glu_ok(const ConvDesc& d);
@@ -176,8 +178,9 @@ int conv_fwd_glu(const ConvDesc& d, const void* x, const void* w, const float* b
 // tensor with the same time layout as this layer's dy (halo frames are written as zeros).
 // yprev: dense [B*T, 2*Cin] pre-GLU activations of the layer below.
 bool conv_dgrad_glu_ok(const ConvDesc& d);
-// scratch (optional): conv_dgrad_scratch_bytes(d) bytes; given it, shapes dgrad_split_ok(d) accepts take
-// the split-reduction tiles and the GLU backward moves into their combining pass
+// scratch (optional): conv_dgrad_pair_bytes(d) bytes; given it, shapes dgrad_split_ok(d) accepts take
+// the split-reduction tiles and the GLU backward moves into their combining pass; the DGRAD_TICKET_BYTES at its head
+// have to be zero, and are again when the pass is done
 int conv_dgrad_glu(const ConvDesc& d, const void* dy, const void* w, const void* yprev, void* dyprev, void* scratch,
                    size_t scratch_bytes, hipStream_t st);
 bool dgrad_split_ok(const ConvDesc& d);

@@ -1050,7 +1050,7 @@ __global__ __launch_bounds__(256 * KG * GN) void conv_dgrad_k(const bf16_t* __re
 // part != nullptr (grid.y = 2): the reduction over channel blocks is split in two between the two
 // workgroups (blockIdx.y) of a tile -- twice the workgroups when one per tile leaves CUs idle.  Each
 // stores its fp32 sums to its own slot of `part` and then takes a ticket from the tile's counter
-// (zeroed before the launch); the one that draws the second ticket adds the other's sums to its own
+// (zero before the launch, and again after it); the one that draws the second ticket adds the other's sums to its own
 // and finishes the tile.  Nobody waits for anybody, and since a + b == b + a the result does not
 // depend on which of the two comes second.  The slots hold the accumulators in register order
 // ([wavefront][accumulator quad][lane], 16 bytes per lane: both workgroups map threads to elements
@@ -1123,6 +1123,7 @@ __global__ __launch_bounds__(256 * KG) void conv_dgrad_slab_k(const bf16_t* __re
         __syncthreads();
         const int ticket = *ticket_lds;
         if (ticket == 0) return;  // first of the pair: the other workgroup finishes the tile
+        if (threadIdx.x == 0) __hip_atomic_store(tickets + tile, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // as the next launch needs it
         if (kg == 0) core.template add_owned_sc1<0>(other);
         else core.template add_owned_sc1<1>(other);
     }
@@ -1176,19 +1177,23 @@ __global__ __launch_bounds__(256 * KG) void conv_dgrad_slab_k(const bf16_t* __re
         *reinterpret_cast<uint4*>(o) = oa;
         *reinterpret_cast<uint4*>(o + N) = og;
     }
+    // frames no tile covers: the leading halo (first row of tiles) and from the end of the last tile to the end of the
+    // zeroed slack (last row of tiles)
+    const long long t_end = (long long)g.y_halo + (long long)tiles_m * BM, z_end = (long long)g.B * g.y_pitch + LAYOUT_SLACK_ZERO;
+    const long long lead = (tm == 0) ? g.y_halo : 0, trail = (tm == tiles_m - 1 && t_end < z_end) ? z_end - t_end : 0;
+    for (long long c = threadIdx.x; c < (lead + trail) * CPRW; c += NTHR) {
+        const long long r = c / CPRW;
+        const int n = n0 + (int)(c - r * CPRW) * 8;
+        if (n >= N) continue;
+        bf16_t* o = dx + (size_t)(r < lead ? r : t_end + (r - lead)) * 2 * N + n;
+        *reinterpret_cast<uint4*>(o) = make_uint4(0, 0, 0, 0);
+        *reinterpret_cast<uint4*>(o + N) = make_uint4(0, 0, 0, 0);
+    }
 }
 
-// zero rows [r0, r1) and [r2, r3) of a [rows, C] bf16 tensor (C % 8 == 0), and n_tickets ints
-__global__ __launch_bounds__(256) void zero_rows_k(bf16_t* __restrict__ p, long long r0, long long r1, long long r2,
-                                                   long long r3, int C, int* __restrict__ tickets, int n_tickets)
+__global__ __launch_bounds__(256) void zero_tickets_k(int* __restrict__ tickets)
 {
-    const int cv = C / 8;
-    const long long na = (r1 - r0) * cv, nb = (r3 - r2) * cv;
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < na + nb; i += (long long)gridDim.x * blockDim.x) {
-        const long long e = i < na ? r0 * cv + i : r2 * cv + (i - na);
-        reinterpret_cast<uint4*>(p)[e] = make_uint4(0, 0, 0, 0);
-    }
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_tickets; i += gridDim.x * blockDim.x) tickets[i] = 0;
+    tickets[threadIdx.x] = 0;
 }
 
 // =============================== weight gradient ========================================
@@ -1594,9 +1599,9 @@ bool dgrad_split_ok(const ConvDesc& g)
     const long long t2 = ((F + 191) / 192) * ((N + 191) / 192);
     return t1 <= 170 && 2 * t2 <= 256 && 2 * t2 > t1;
 }
-// its scratch
-static size_t dgrad_pair_bytes(const ConvDesc& g)
+size_t conv_dgrad_pair_bytes(const ConvDesc& g)
 {
+    if (!dgrad_split_ok(g)) return 0;
     const long long F = (long long)(g.B - 1) * g.y_pitch + g.Tp;
     const size_t tiles = (size_t)((F + 191) / 192) * ((g.Cin + 191) / 192);
     return DGRAD_TICKET_BYTES + tiles * 2 * 192 * 192 * 4;
@@ -1640,7 +1645,7 @@ int conv_dgrad_mfma_partial(const ConvDesc& d, const void* dy, const void* w, fl
 size_t conv_dgrad_scratch_bytes(const ConvDesc& g)
 {
     const size_t a = conv_dgrad_mfma_ok(g) ? split_bytes(dgrad_split(g, FINISH_OWN), (long long)g.B * g.T, g.Cin) : 0;
-    const size_t b = dgrad_split_ok(g) ? dgrad_pair_bytes(g) : 0;
+    const size_t b = conv_dgrad_pair_bytes(g);
     return a > b ? a : b;
 }
 
@@ -1650,6 +1655,13 @@ static dim3 dgrad_split_grid(ConvDesc& g, long long tiles_m, long long tiles_n)
     g.xcd_m = xcd_split4(tiles_m, tiles_n, (double)(192 + g.k - 1) * g.Cout / 2, 192.0 * g.k * g.Cout / 2);
     const unsigned tiles = (unsigned)(tiles_m * tiles_n);
     return g.xcd_m > 0 ? dim3(2 * tiles) : dim3(tiles, 2);
+}
+
+int zero_dgrad_tickets(int* tickets, hipStream_t st)
+{
+    static_assert(DGRAD_TICKET_BYTES == 256 * 4, "one ticket per thread");
+    hipLaunchKernelGGL(zero_tickets_k, dim3(1), dim3(256), 0, st, tickets);
+    return launch_status();
 }
 
 int conv_dgrad_mfma(const ConvDesc& g0, const void* dy, const void* w, void* dx, void* scratch, size_t scratch_bytes,
@@ -1664,15 +1676,13 @@ int conv_dgrad_mfma(const ConvDesc& g0, const void* dy, const void* w, void* dx,
         rc = launch_dgrad<float>(g, pl.tc, pl.splits, dy, w, (float*)scratch, st);
         return rc ? rc : finish_rows((const float*)scratch, pl.splits, nullptr, dx, W2L_BF16, g.B, g.T, g.Cin, g.x_pitch, g.x_halo, st);
     }
-    if (scratch && dgrad_split_ok(g) && scratch_bytes >= dgrad_pair_bytes(g)) {
+    if (scratch && dgrad_split_ok(g) && scratch_bytes >= conv_dgrad_pair_bytes(g)) {
         constexpr int bytes = slab_lds_bytes(192, 192, 256, 2);
         const long long F = (long long)(g.B - 1) * g.y_pitch + g.Tp;
-        const int tiles = (int)(((F + 191) / 192) * ((N + 191) / 192));
         int* tickets = static_cast<int*>(scratch);
         float* part = reinterpret_cast<float*>(static_cast<unsigned char*>(scratch) + DGRAD_TICKET_BYTES);
         if (!tickets_zeroed) {
-            hipLaunchKernelGGL(zero_rows_k, dim3(1), dim3(256), 0, st, (bf16_t*)nullptr, 0LL, 0LL, 0LL, 0LL, 8, tickets, tiles);
-            rc = launch_status();
+            rc = zero_dgrad_tickets(tickets, st);
             if (rc) return rc;
         }
         const dim3 grid = dgrad_split_grid(g, (F + 191) / 192, (N + 191) / 192);
@@ -1702,21 +1712,13 @@ int conv_dgrad_glu(const ConvDesc& g0, const void* dy, const void* w, const void
     if (!conv_dgrad_glu_ok(g0)) return W2L_ERR_SHAPE;
     ConvDesc g = g0;
     const long long F = (long long)(g.B - 1) * g.y_pitch + g.Tp;
-    const long long z_end = (long long)g.B * g.y_pitch + LAYOUT_SLACK_ZERO;
-    if (scratch && dgrad_split_ok(g) && scratch_bytes >= dgrad_pair_bytes(g)) {
+    if (scratch && dgrad_split_ok(g) && scratch_bytes >= conv_dgrad_pair_bytes(g)) {
         // two workgroups per 192x192 tile; the one that finishes a tile applies the GLU backward in its epilogue
         constexpr int bytes = slab_lds_bytes(192, 192, 256, 2);
         const long long tiles_m = (F + 191) / 192;
-        const int tiles = (int)(tiles_m * ((g.Cin + 191) / 192));
         int* tickets = static_cast<int*>(scratch);
         float* part = reinterpret_cast<float*>(static_cast<unsigned char*>(scratch) + DGRAD_TICKET_BYTES);
-        // frames the tiles do not cover (leading halo; end of the last tile to the end of the zeroed slack), and the tickets
-        const long long t_end = g.y_halo + tiles_m * 192;
-        hipLaunchKernelGGL(zero_rows_k, dim3(64), dim3(256), 0, st, (bf16_t*)dyprev, 0LL, (long long)g.y_halo, t_end,
-                           t_end > z_end ? t_end : z_end, 2 * g.Cin, tickets, tiles);
-        int rc = launch_status();
-        if (rc) return rc;
-        rc = set_lds(conv_dgrad_slab_k<192, 192, 256, 2, true>, bytes);
+        int rc = set_lds(conv_dgrad_slab_k<192, 192, 256, 2, true>, bytes);
         if (rc) return rc;
         const dim3 grid = dgrad_split_grid(g, tiles_m, (g.Cin + 191) / 192);
         hipLaunchKernelGGL((conv_dgrad_slab_k<192, 192, 256, 2, true>), grid, dim3(512), bytes, st, (const bf16_t*)dy, (const bf16_t*)w, (bf16_t*)dyprev, (const bf16_t*)yprev, part, tickets, g);
@@ -1725,14 +1727,8 @@ int conv_dgrad_glu(const ConvDesc& g0, const void* dy, const void* w, const void
     constexpr int BM = 256, BN = 128;
     constexpr int bytes = slab_lds_bytes(BM, BN, 320, 2);
     const long long tiles_m = (F + BM - 1) / BM;
-    // frames the tiles do not cover: the leading halo, and from the end of the last tile to the end of the zeroed slack
-    const long long t_end = g.y_halo + tiles_m * BM;
-    hipLaunchKernelGGL(zero_rows_k, dim3(64), dim3(256), 0, st, (bf16_t*)dyprev, 0LL, (long long)g.y_halo, t_end,
-                       t_end > z_end ? t_end : z_end, 2 * g.Cin, (int*)nullptr, 0);
-    int rc = launch_status();
-    if (rc) return rc;
     const unsigned grid = (unsigned)(tiles_m * ((g.Cin + BN - 1) / BN));
-    rc = set_lds(conv_dgrad_slab_k<BM, BN, 320, 2, true>, bytes);
+    int rc = set_lds(conv_dgrad_slab_k<BM, BN, 320, 2, true>, bytes);
     if (!rc) hipLaunchKernelGGL((conv_dgrad_slab_k<BM, BN, 320, 2, true>), dim3(grid), dim3(512), bytes, st, (const bf16_t*)dy, (const bf16_t*)w, (bf16_t*)dyprev, (const bf16_t*)yprev, (float*)nullptr, (int*)nullptr, g);
     return rc ? rc : launch_status();
 }

@@ -137,15 +137,8 @@ Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int
             p.part_bytes = max_of(p.part_bytes, L[i - 1].glu ? planes_bytes(conv_dgrad_parts(bd, dtype, dydt), (size_t)B * t * l.cin)
                                                              : conv_dgrad_scratch(bd, dtype, dydt));
         }
-        if (i > 0 && L[i - 1].glu) {
-            // scratch of a split-reduction data gradient (tickets and the fp32 sums of both halves)
-            ConvDesc sd = dense_desc(B, t, l.cin, l.cout, l.k, l.stride);
-            sd.x_pitch = sd.y_pitch = to + 2 * HALO;
-            sd.x_halo = sd.y_halo = HALO;
-            sd.slack = SLACK;
-            const size_t sb = conv_dgrad_scratch_bytes(sd);
-            p.dgs_bytes = sb > p.dgs_bytes ? sb : p.dgs_bytes;
-        }
+        // a data gradient of two workgroups per tile: its tickets and the sums of both
+        if (i > 0 && L[i - 1].glu) p.dgs_bytes = max_of(p.dgs_bytes, conv_dgrad_pair_bytes(bd));
         t = to;
     }
     p.Tlast = t;
@@ -314,6 +307,7 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
     const void* dh = dz;
     int dh_dt = W2L_F32;
     bool dy_ready = false;  // dy of the current layer was already written by the layer above
+    bool tickets = false;   // of the split data gradients: zeroed
     for (int i = n - 1; i >= 0; --i) {
         const w2l_layer& l = layers[i];
         ConvDesc d = layer_bwd_desc(p, layers, B, i);
@@ -384,6 +378,11 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
                 continue;
             }
             if (layers[i - 1].glu && dtype == W2L_BF16 && dy_dt == W2L_BF16 && conv_dgrad_glu_ok(d)) {
+                if (!tickets && p.dgs_bytes) {
+                    rc = zero_dgrad_tickets(reinterpret_cast<int*>(ws + p.dgs), st);
+                    if (rc) return rc;
+                }
+                tickets = true;
                 if (!wait_wgrad(i + 2)) return W2L_ERR_LAUNCH;
                 rc = conv_dgrad_glu(d, dy, weights[i], ws + p.pre[i - 1], ws + p.gdy[(i - 1) % 3], ws + p.dgs, p.dgs_bytes, st);
                 if (rc) return rc;
