@@ -108,7 +108,7 @@ int conv_wgrad(const ConvDesc& d, const void* x, const void* dy, float* dw, floa
 {
     float* dbias_scratch = static_cast<float*>(scratch);
     unsigned char* rest = static_cast<unsigned char*>(scratch) + wgrad_dbias_scratch(d);
-    const size_t rest_bytes = scratch_bytes - wgrad_dbias_scratch(d);
+    const size_t rest_bytes = scratch_bytes > wgrad_dbias_scratch(d) ? scratch_bytes - wgrad_dbias_scratch(d) : 0;
     if (wgrad_is_generic(d, dt, dydt))
         return conv_wgrad_generic(d, x, dy, dw, dbias, dt, dydt, accumulate, st, rest, rest_bytes);
     if (d.Cout <= 32) return conv_wgrad_skinny(d, x, dy, dw, dbias, dt, dydt, accumulate, reinterpret_cast<float*>(rest), st);

@@ -190,6 +190,21 @@ bool conv_wgrad_mfma_takes_dbias(const ConvDesc& d);
 int conv_wgrad_mfma(const ConvDesc& d, const void* x, const void* dy, float* dw, float* dbias, int accumulate, hipStream_t st,
                     void* scratch = nullptr, size_t scratch_bytes = 0);
 
+// Both gradients of a layer with a layer with GLU below it, in one launch (dy, x and the dy of the layer below in the
+// haloed layout, bf16).
+struct ConvBwdPlan {
+    bool ok = false;
+    int dkind = 0, dparts = 1, dnx = 0, dper = 0;              // dparts > 1: planes of sums in dscratch, for finish_glu_bwd
+    int wtile = 0, wper = 0, wsplits = 1, wnx = 0, w_first = 0;
+    size_t wscratch = 0;
+    bool fused() const { return dkind < 2; }                   // dx is the dy of the layer below; otherwise (and without
+                                                               // planes) the dense gradient of its output
+};
+ConvBwdPlan conv_bwd_plan(const ConvDesc& d);
+// dscratch: the planes, or for the fused form conv_dgrad_pair_bytes(d) with zero tickets; wscratch: p.wscratch bytes
+int conv_bwd(const ConvBwdPlan& p, const ConvDesc& d, const void* dy, const void* w, const void* x, const void* yprev, void* dx, float* dw,
+             float* dbias, void* dscratch, void* wscratch, hipStream_t st);
+
 // w2l_ctc_fwd_bwd with in_len counted before a total stride len_div (ctc.hip): the criterion sees ceil(in_len / len_div)
 int ctc_fwd_bwd_strided(const float* input, int is_logits, const int* targets, const int* in_len, const int* tgt_len,
                         float* loss, float* grad, int B, int Tp, int C, int Lmax, int blank, float grad_scale,

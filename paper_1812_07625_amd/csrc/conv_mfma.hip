@@ -713,19 +713,19 @@ __device__ __forceinline__ void store_tile_bf16(const CoreT& core, unsigned char
 // xcd_m > 0 (chosen on the host, see xcd_split): the tile grid is cut into xcd_m x (8 / xcd_m)
 // rectangular blocks, one per XCD, so that an L2 streams only its block's share of either operand;
 // inside a block the column tiles run fastest.
-__device__ __forceinline__ void tile_of_block(int tiles_m, int tiles_n, int& tm, int& tn, bool m_fastest = false, int xcd_m = 0)
+__device__ __forceinline__ void tile_of_block(int bx, int tiles_m, int tiles_n, int& tm, int& tn, bool m_fastest = false, int xcd_m = 0)
 {
     if (xcd_m > 0) {
         const int xn = 8 / xcd_m, am = tiles_m / xcd_m, an = tiles_n / xn;
-        const int x = blockIdx.x % 8, q = blockIdx.x / 8;
+        const int x = bx % 8, q = bx / 8;
         tn = (x % xn) * an + q % an;
         tm = (x / xn) * am + q / an;
         return;
     }
     const int nb = tiles_m * tiles_n;
     const int per = (nb + 7) / 8;
-    int id = (blockIdx.x % 8) * per + blockIdx.x / 8;
-    if (nb % 8 != 0) id = blockIdx.x;  // keep it a bijection when the count does not split evenly
+    int id = (bx % 8) * per + bx / 8;
+    if (nb % 8 != 0) id = bx;  // keep it a bijection when the count does not split evenly
     if (tiles_n <= tiles_m && !m_fastest) { tm = id / tiles_n; tn = id % tiles_n; }
     else { tn = id / tiles_m; tm = id % tiles_m; }
 }
@@ -750,7 +750,7 @@ __global__ __launch_bounds__(256 * KG * GN) void conv_fwd_k(const bf16_t* __rest
     static_assert(KG == 1 || BM * BN * 4 <= STAGES * STAGE, "the group reduction reuses the panel ring");
     const int M = g.B * g.Tp, N = g.Cout, K = g.k * g.Cin;
     int tm, tn;
-    tile_of_block((M + BM - 1) / BM, (N + BN - 1) / BN, tm, tn);
+    tile_of_block(blockIdx.x, (M + BM - 1) / BM, (N + BN - 1) / BN, tm, tn);
     const int m0 = tm * BM, n0 = tn * BN;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int grp = wave >> 2, w4 = wave & 3, wm = w4 >> 1;
@@ -857,7 +857,7 @@ __global__ __launch_bounds__(256 * KG) void conv_fwd_slab_k(const bf16_t* __rest
     const int N = g.Cout, K = g.k * g.Cin, H = g.Cout / 2;
     const int tiles_m = (F + BM - 1) / BM;
     int tm, tn;
-    tile_of_block(tiles_m, (N + BN - 1) / BN, tm, tn, false, g.xcd_m);
+    tile_of_block(blockIdx.x, tiles_m, (N + BN - 1) / BN, tm, tn, false, g.xcd_m);
     const int f0 = g.x_halo + tm * BM, n0 = tn * BN;  // layout frame of tile row 0
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int kg = wave >> 2, w4 = wave & 3, wm = w4 >> 1, wn = w4 & 1;
@@ -957,17 +957,16 @@ __global__ __launch_bounds__(256 * KG) void conv_fwd_slab_k(const bf16_t* __rest
 // =============================== data gradient (stride 1) =============================
 // dx[b,t,ci] = sum_{j',co} dy[b, t-p+j', co] * w[co, k-1-j', ci]
 template <int BM, int BN, int BKT, int STAGES, int KG, int GN, bool FAST, typename TO>
-__global__ __launch_bounds__(256 * KG * GN) void conv_dgrad_k(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ w,
+__device__ __forceinline__ void dgrad_tile(unsigned char* lds, int bx, int by, const bf16_t* __restrict__ dy, const bf16_t* __restrict__ w,
                                                    TO* __restrict__ dx, ConvGeom g, int per, long long plane)
 {
     using PA = PanelK<BM, BKT, 4 * KG * GN>;
     using PB = PanelMN<BN, BKT, 4 * KG * GN>;
-    extern __shared__ __align__(1024) unsigned char lds[];
     constexpr int STAGE = PA::BYTES + PB::BYTES;
     static_assert(KG == 1 || BM * BN * 4 <= STAGES * STAGE, "the group reduction reuses the panel ring");
     const int M = g.B * g.T, N = g.Cin, K = g.k * g.Cout;
     int tm, tn;
-    tile_of_block((M + BM - 1) / BM, (N + BN - 1) / BN, tm, tn);
+    tile_of_block(bx, (M + BM - 1) / BM, (N + BN - 1) / BN, tm, tn);
     const int m0 = tm * BM, n0 = tn * BN;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int grp = wave >> 2, w4 = wave & 3, wm = w4 >> 1;
@@ -996,9 +995,9 @@ __global__ __launch_bounds__(256 * KG * GN) void conv_dgrad_k(const bf16_t* __re
     }
     Core<BM, BN, BKT, KG, GN, PA, PB> core;
     core.zero();
-    const int total = K / BKT, st0 = blockIdx.y * per;  // Cout is a multiple of BKT: a panel stays inside one tap
+    const int total = K / BKT, st0 = by * per;  // Cout is a multiple of BKT: a panel stays inside one tap
     const int nsteps = total - st0 < per ? total - st0 : per;  // this split's panels
-    dx += blockIdx.y * plane;
+    dx += by * plane;
     run_ring<STAGES, KG * GN, PA::NI + PB::NI, STAGE, PA::BYTES>(
         core, lds, nsteps,
         [&](int i, int st, unsigned dst) {
@@ -1041,6 +1040,14 @@ __global__ __launch_bounds__(256 * KG * GN) void conv_dgrad_k(const bf16_t* __re
         [&](int r) { return m0 + r < M ? out_row(m0 + r, g.T, g.x_pitch, g.x_halo) : -1LL; });
 }
 
+template <int BM, int BN, int BKT, int STAGES, int KG, int GN, bool FAST, typename TO>
+__global__ __launch_bounds__(256 * KG * GN) void conv_dgrad_k(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ w,
+                                                              TO* __restrict__ dx, ConvGeom g, int per, long long plane)
+{
+    extern __shared__ __align__(1024) unsigned char lds[];
+    dgrad_tile<BM, BN, BKT, STAGES, KG, GN, FAST, TO>(lds, blockIdx.x, blockIdx.y, dy, w, dx, g, per, plane);
+}
+
 // Data gradient with the dy window kept as an activation slab (dy has a zero halo, Cout % 64
 // == 0): same schedule as conv_fwd_slab_k; the weight panel of (channel block, tap j') is the
 // 64 x BN block w[co0 .. co0+63][k-1-j'][n0 .. n0+BN-1], read through the LDS transpose read.
@@ -1056,13 +1063,12 @@ __global__ __launch_bounds__(256 * KG * GN) void conv_dgrad_k(const bf16_t* __re
 // ([wavefront][accumulator quad][lane], 16 bytes per lane: both workgroups map threads to elements
 // alike), so every store and load instruction moves 1 KB of consecutive memory.
 template <int BM, int BN, int SROWS, int KG, bool GLUB>
-__global__ __launch_bounds__(256 * KG) void conv_dgrad_slab_k(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ w,
+__device__ __forceinline__ void dgrad_slab_tile(unsigned char* lds, int bx, int by, const bf16_t* __restrict__ dy, const bf16_t* __restrict__ w,
                                                               bf16_t* __restrict__ dx, const bf16_t* __restrict__ yprev,
                                                               float* __restrict__ part, int* __restrict__ tickets, ConvGeom g)
 {
     using PS = PanelK<SROWS, 64, 4 * KG>;
     using PB = PanelMN<BN, 64, 4 * KG>;
-    extern __shared__ __align__(1024) unsigned char lds[];
     constexpr int LDS_BYTES = slab_lds_bytes(BM, BN, SROWS, KG);
     const int F = (g.B - 1) * g.y_pitch + g.Tp;
     const int N = g.Cin;
@@ -1072,14 +1078,14 @@ __global__ __launch_bounds__(256 * KG) void conv_dgrad_slab_k(const bf16_t* __re
         // split reduction, 1-D grid of 2 * tiles workgroups: an XCD takes one half of the reduction (its parity)
         // of one of xcd_m x (4 / xcd_m) rectangular blocks of tiles, so its L2 streams only that block's rows of
         // dy and columns of w, and of those only its half of the channel blocks
-        const int x = blockIdx.x % 8, q = blockIdx.x / 8, blk = x >> 1;
+        const int x = bx % 8, q = bx / 8, blk = x >> 1;
         const int xn = 4 / g.xcd_m, am = tiles_m / g.xcd_m, an = tiles_n / xn;
         half = x & 1;
         tn = (blk % xn) * an + q % an;
         tm = (blk / xn) * am + q / an;
     } else {
-        tile_of_block(tiles_m, tiles_n, tm, tn, true);
-        half = blockIdx.y;
+        tile_of_block(bx, tiles_m, tiles_n, tm, tn, true);
+        half = by;
     }
     const int f0 = g.y_halo + tm * BM, n0 = tn * BN;  // dy layout frame of tile row 0
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1121,7 +1127,7 @@ __global__ __launch_bounds__(256 * KG) void conv_dgrad_slab_k(const bf16_t* __re
         int* ticket_lds = reinterpret_cast<int*>(lds);  // the panel ring is free by now
         if (threadIdx.x == 0) *ticket_lds = __hip_atomic_fetch_add(tickets + tile, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
-        const int ticket = *ticket_lds;
+        const int ticket = __builtin_amdgcn_readfirstlane(*ticket_lds);
         if (ticket == 0) return;  // first of the pair: the other workgroup finishes the tile
         if (threadIdx.x == 0) __hip_atomic_store(tickets + tile, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // as the next launch needs it
         if (kg == 0) core.template add_owned_sc1<0>(other);
@@ -1190,6 +1196,14 @@ __global__ __launch_bounds__(256 * KG) void conv_dgrad_slab_k(const bf16_t* __re
         *reinterpret_cast<uint4*>(o + N) = make_uint4(0, 0, 0, 0);
     }
 }
+template <int BM, int BN, int SROWS, int KG, bool GLUB>
+__global__ __launch_bounds__(256 * KG) void conv_dgrad_slab_k(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ w,
+                                                              bf16_t* __restrict__ dx, const bf16_t* __restrict__ yprev,
+                                                              float* __restrict__ part, int* __restrict__ tickets, ConvGeom g)
+{
+    extern __shared__ __align__(1024) unsigned char lds[];
+    dgrad_slab_tile<BM, BN, SROWS, KG, GLUB>(lds, blockIdx.x, blockIdx.y, dy, w, dx, yprev, part, tickets, g);
+}
 
 __global__ __launch_bounds__(256) void zero_tickets_k(int* __restrict__ tickets)
 {
@@ -1207,20 +1221,19 @@ __global__ __launch_bounds__(256) void zero_tickets_k(int* __restrict__ tickets)
 // row (1, 0, 0, ...) for every frame, so its first output column is sum_t dy[t, co] -- the bias
 // gradient -- computed by the same pipeline with the same loads per phase, in a fixed order.
 template <int BM, int BN, int BKT, int STAGES, int KG, int GN, bool FAST, bool BIAS>
-__global__ __launch_bounds__(256 * KG * GN) void conv_wgrad_k(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dy,
+__device__ __forceinline__ void wgrad_tile(unsigned char* lds, int bx, int by, int splits, const bf16_t* __restrict__ x, const bf16_t* __restrict__ dy,
                                                    float* __restrict__ dw, float* __restrict__ dbias, ConvGeom g, int accumulate,
                                                    int per)
 {
     static_assert(FAST || !BIAS, "the bias column rides on the dense walk through the frames");
     using PA = PanelMN<BM, BKT, 4 * KG * GN>;
     using PB = PanelMN<BN, BKT, 4 * KG * GN>;
-    extern __shared__ __align__(1024) unsigned char lds[];
     constexpr int STAGE = PA::BYTES + PB::BYTES;
     static_assert(KG == 1 || BM * BN * 4 <= STAGES * STAGE, "the group reduction reuses the panel ring");
     const int M = g.Cout, N = g.w_cols ? g.w_cols : g.k * g.Cin;
     const int tiles_n = (N + BN - 1) / BN;
     int tm, tn;
-    tile_of_block((M + BM - 1) / BM, tiles_n + (BIAS ? 1 : 0), tm, tn);
+    tile_of_block(bx, (M + BM - 1) / BM, tiles_n + (BIAS ? 1 : 0), tm, tn);
     const bool bias_tile = BIAS && tn == tiles_n;  // uniform over the workgroup
     const int m0 = tm * BM, n0 = tn * BN;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1241,10 +1254,10 @@ __global__ __launch_bounds__(256 * KG * GN) void conv_wgrad_k(const bf16_t* __re
     }
     const int spb = (g.Tp + BKT - 1) / BKT;  // CHECKED: panels per utterance
     const int frames = (g.B - 1) * g.y_pitch + g.Tp;  // FAST: first real frame of utterance 0 .. last real frame
-    const int total = FAST ? (frames + BKT - 1) / BKT : g.B * spb, st0 = blockIdx.y * per;
+    const int total = FAST ? (frames + BKT - 1) / BKT : g.B * spb, st0 = by * per;
     const int nsteps = total - st0 < per ? total - st0 : per;  // this split's panels
-    dw += (size_t)blockIdx.y * M * N;                          // (splits leave planes of sums)
-    if (BIAS) dbias += (size_t)blockIdx.y * M;
+    dw += (size_t)by * M * N;                          // (splits leave planes of sums)
+    if (BIAS) dbias += (size_t)by * M;
     if (FAST) {
         dy += (size_t)st0 * BKT * g.Cout;
         x += (size_t)st0 * BKT * g.Cin;
@@ -1296,7 +1309,7 @@ __global__ __launch_bounds__(256 * KG * GN) void conv_wgrad_k(const bf16_t* __re
         });
         return;
     }
-    if (gridDim.y > 1) {  // read again by the next launch
+    if (splits > 1) {  // read again by the next launch
         core.for_each(kg, wm, wn, lane, [&](int mm, int nn, float v, int) {
             const int m = m0 + mm, n = n0 + nn;
             if (m < M && n < N) dw[(size_t)m * N + n] = v;
@@ -1310,6 +1323,59 @@ __global__ __launch_bounds__(256 * KG * GN) void conv_wgrad_k(const bf16_t* __re
             __builtin_nontemporal_store(accumulate ? dw[i] + v : v, dw + i);  // 52 MB per layer that nothing reads before the step ends
         }
     });
+}
+template <int BM, int BN, int BKT, int STAGES, int KG, int GN, bool FAST, bool BIAS>
+__global__ __launch_bounds__(256 * KG * GN) void conv_wgrad_k(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dy,
+                                                              float* __restrict__ dw, float* __restrict__ dbias, ConvGeom g, int accumulate,
+                                                              int per)
+{
+    extern __shared__ __align__(1024) unsigned char lds[];
+    wgrad_tile<BM, BN, BKT, STAGES, KG, GN, FAST, BIAS>(lds, blockIdx.x, blockIdx.y, gridDim.y, x, dy, dw, dbias, g, accumulate, per);
+}
+
+// =============================== both gradients of a layer in one launch =================
+// The data and the weight gradient of a layer need the same dy and nothing of each other, and neither has the number
+// of workgroups that fills the chip: one launch takes both, the longer tiles first, and the dispatcher packs the rest
+// around them.  (On two streams they overlap as well, but the events between them cost about 10 us a layer on either
+// stream: 16 x 800 frames, k = 11, 256 -> 512, 96 us a layer so and 87 in one launch; 4 x 619 frames 57 and 35.)
+enum BwdData { BD_PAIR, BD_SLAB, BD_PLANES_128, BD_PLANES_256, BD_DH_128, BD_DH_256 };
+enum BwdTile { BT_128, BT_256x128, BT_192, BT_256 };
+struct BwdJobs {
+    const bf16_t *dy, *w, *x, *yprev;
+    void* dx;
+    float *dw, *dbias, *part;
+    int* tickets;
+    long long plane;                       // of the data gradient's sums
+    int dkind, nd, dnx, dper;              // data gradient: workgroups, of which dnx per run of panels
+    int wtile, nw, wnx, wper, wsplits;     // weight gradient
+    int w_first;
+    ConvGeom dg, wg;
+};
+__global__ __launch_bounds__(512) void conv_bwd_k(BwdJobs a)
+{
+    extern __shared__ __align__(1024) unsigned char lds[];
+    const int n0 = a.w_first ? a.nw : a.nd, n0p = (n0 + 7) & ~7;  // whole rounds over the XCDs: see tile_of_block
+    const bool first = (int)blockIdx.x < n0p;
+    const int id = first ? blockIdx.x : blockIdx.x - n0p;
+    if (first && id >= n0) return;
+    if (first == (a.w_first != 0)) {
+        const int by = __builtin_amdgcn_readfirstlane(id / a.wnx), bx = id - by * a.wnx;
+#define W2L_W(BM_, BN_, BK_, ST_, KG_, GN_) wgrad_tile<BM_, BN_, BK_, ST_, KG_, GN_, true, true>(lds, bx, by, a.wsplits, a.x, a.dy, a.dw, a.dbias, a.wg, 0, a.wper)
+        if (a.wtile == BT_256) W2L_W(256, 256, 32, 4, 1, 2);
+        else if (a.wtile == BT_192) W2L_W(192, 192, 64, 3, 2, 1);
+        else if (a.wtile == BT_256x128) W2L_W(256, 128, 64, 3, 2, 1);
+        else W2L_W(128, 128, 64, 3, 2, 1);
+#undef W2L_W
+        return;
+    }
+    const int by = __builtin_amdgcn_readfirstlane(id / a.dnx), bx = id - by * a.dnx;
+    bf16_t* const dxb = reinterpret_cast<bf16_t*>(a.dx);
+    if (a.dkind == BD_PAIR) dgrad_slab_tile<192, 192, 256, 2, true>(lds, bx, by, a.dy, a.w, dxb, a.yprev, a.part, a.tickets, a.dg);
+    else if (a.dkind == BD_SLAB) dgrad_slab_tile<256, 128, 320, 2, true>(lds, bx, by, a.dy, a.w, dxb, a.yprev, nullptr, nullptr, a.dg);
+    else if (a.dkind == BD_PLANES_128) dgrad_tile<128, 128, 64, 3, 2, 1, true, float>(lds, bx, by, a.dy, a.w, a.part, a.dg, a.dper, a.plane);
+    else if (a.dkind == BD_PLANES_256) dgrad_tile<256, 128, 64, 3, 2, 1, true, float>(lds, bx, by, a.dy, a.w, a.part, a.dg, a.dper, a.plane);
+    else if (a.dkind == BD_DH_128) dgrad_tile<128, 128, 64, 3, 2, 1, true, bf16_t>(lds, bx, by, a.dy, a.w, dxb, a.dg, a.dper, 0);
+    else dgrad_tile<256, 128, 64, 3, 2, 1, true, bf16_t>(lds, bx, by, a.dy, a.w, dxb, a.dg, a.dper, 0);
 }
 
 // Raise a kernel's dynamic-LDS limit: once per (device, kernel), remembered afterwards.
@@ -1787,11 +1853,145 @@ int conv_wgrad_mfma(const ConvDesc& g, const void* x, const void* dy, float* dw,
     }
     W2L_TILE_DISPATCH(CALL)
 #undef CALL
-#undef W2L_LAUNCH
     if (!rc) rc = launch_status();
     if (rc || splits == 1) return rc;
     const float* const part = (const float*)scratch;
     return finish_sums(part, splits, M * N, dw, dbias ? part + splits * M * N : nullptr, (int)M, dbias, accumulate, st);
 }
+
+// ---- both gradients in one launch ------------------------------------------------------
+// Time until the last of n1 jobs of t1 and then n2 of t2 is done, each taken by the CU that is free first.
+static double makespan(long long n1, double t1, long long n2, double t2)
+{
+    struct { double t; long long n; } q[64] = {{0, 256}};
+    int m = 1;
+    auto run = [&](long long n, double t) {
+        while (n > 0) {
+            int e = 0;
+            for (int i = 1; i < m; ++i) if (q[i].t < q[e].t) e = i;
+            const long long k = n < q[e].n ? n : q[e].n, rounds = m == 1 && n > q[e].n ? n / q[e].n : 1;
+            const double end = q[e].t + rounds * t;
+            if (k == q[e].n) q[e].t = end;
+            else if (m == 64) return;
+            else { q[e].n -= k; q[m++] = {end, k}; }
+            n -= k * rounds;
+        }
+    };
+    run(n1, t1);
+    run(n2, t2);
+    double last = 0;
+    for (int i = 0; i < m; ++i) last = q[i].t > last ? q[i].t : last;
+    return last;
+}
+
+ConvBwdPlan conv_bwd_plan(const ConvDesc& d)
+{
+    ConvBwdPlan p;
+    if (d.w_cols || !conv_wgrad_mfma_takes_dbias(d) || d.Cout <= 32 || !conv_dgrad_mfma_ok(d) || !halo_ok_y(d) || d.Cin % 8) return p;
+    const long long M = (long long)d.B * d.T, N = d.Cin, panels = (long long)d.k * d.Cout / 64, F = (long long)(d.B - 1) * d.y_pitch + d.Tp;
+    double td;
+    // the data gradient as it is taken alone
+    const SplitPlan sp = dgrad_split_glu(d);
+    if (sp.splits > 1) {
+        p.dkind = (sp.tc.bm == 128 && sp.tc.bn == 128) ? BD_PLANES_128 : BD_PLANES_256;
+        const int bm = p.dkind == BD_PLANES_128 ? 128 : 256;
+        p.dparts = sp.splits;
+        p.dnx = ((M + bm - 1) / bm) * ((N + 127) / 128);
+        const SplitRun sr = split_run(panels, sp.splits);
+        p.dper = sr.per;
+        p.dparts = sr.splits;
+        td = sr.per * tile_us(bm, 128) + ROUND_US;
+    } else if (conv_dgrad_glu_ok(d) && dgrad_split_ok(d)) {
+        p.dkind = BD_PAIR;
+        p.dnx = 2 * ((F + 191) / 192) * ((N + 191) / 192);
+        td = panels / 2 * tile_us(192, 192) + ROUND_US + 6;
+    } else if (conv_dgrad_glu_ok(d)) {
+        p.dkind = BD_SLAB;
+        p.dnx = ((F + 255) / 256) * ((N + 127) / 128);
+        td = panels * tile_us(256, 128) + ROUND_US;
+    } else {
+        const TileChoice tc = choose_tile(M, N);
+        p.dkind = (tc.bm == 128 && tc.bn == 128) ? BD_DH_128 : BD_DH_256;
+        const int bm = p.dkind == BD_DH_128 ? 128 : 256;
+        p.dnx = ((M + bm - 1) / bm) * ((N + 127) / 128);
+        p.dper = (int)panels;
+        td = panels * tile_us(bm, 128) + ROUND_US;
+    }
+    const long long nd = (long long)p.dnx * (p.dparts > 1 ? p.dparts : 1);
+    // the weight gradient's tile and runs: what gets both done soonest
+    const long long WM = d.Cout, WN = (long long)d.k * d.Cin, frames = (long long)(d.B - 1) * d.y_pitch + d.Tp;
+    const TileChoice cand[] = {{128, 128}, {256, 128}, {192, 192}, {256, 256}};
+    static const int runs[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16};
+    double best = -1, spread = 0;
+    for (int c = 0; c < 4; ++c) {
+        const int bk = c == BT_256 ? 32 : 64;
+        const long long steps = (frames + bk - 1) / bk, nx = ((WM + cand[c].bm - 1) / cand[c].bm) * ((WN + cand[c].bn - 1) / cand[c].bn + 1);
+        for (int s : runs) {
+            const SplitRun sr = split_run(steps, s);
+            if (s > 1 && (sr.per * bk < 128 || (size_t)s * WM * WN * 4 > MAX_PARTIALS)) break;
+            if (nx * sr.splits > 1 << 20) break;
+            const double tw = sr.per * (bk / 64.0) * tile_us(cand[c].bm, cand[c].bn) + ROUND_US;
+            const double span = tw > td ? makespan(nx * sr.splits, tw, nd, td) : makespan(nd, td, nx * sr.splits, tw);
+            const double t = span + (sr.splits > 1 ? 5.0 + 0.5 * PLANE_US * sr.splits * WM * WN : 0.0);
+            if (best < 0 || t < 0.98 * best) {
+                best = t;
+                spread = span - (nd * td + nx * sr.splits * tw) / 256;
+                p.wtile = c;
+                p.wper = sr.per;
+                p.wsplits = sr.splits;
+                p.wnx = (int)nx;
+                p.w_first = tw > td;
+            }
+            if (sr.splits == 1 && s > 1) break;
+        }
+    }
+    p.wscratch = p.wsplits > 1 ? round_up((size_t)p.wsplits * WM * (WN + 1) * 4, 256) : 0;
+    // CUs that wait for the last tiles are what the next layer's launch could use on two streams: beyond what those cost
+    // (8 x 750 frames, k = 11, 768 -> 1536: 256 + 204 workgroups of 130 us each, 262 us a layer on two streams, 273 in one)
+    p.ok = best >= 0 && spread <= 18;
+    return p;
+}
+
+int conv_bwd(const ConvBwdPlan& p, const ConvDesc& d, const void* dy, const void* w, const void* x, const void* yprev, void* dx, float* dw,
+             float* dbias, void* dscratch, void* wscratch, hipStream_t st)
+{
+    if (!p.ok || !dbias) return W2L_ERR_SHAPE;
+    const long long WN = (long long)d.k * d.Cin, plane = (long long)d.Cout * WN;
+    const bool split = p.wsplits > 1;
+    float* const part = static_cast<float*>(wscratch);
+    BwdJobs a;
+    a.dy = (const bf16_t*)dy; a.w = (const bf16_t*)w; a.x = (const bf16_t*)x; a.yprev = (const bf16_t*)yprev;
+    a.dx = dx;
+    a.dw = split ? part : dw;
+    a.dbias = split ? part + p.wsplits * plane : dbias;
+    a.part = static_cast<float*>(dscratch);
+    a.tickets = nullptr;
+    a.plane = (long long)d.B * d.T * d.Cin;
+    a.dkind = p.dkind; a.dnx = p.dnx; a.dper = p.dper;
+    a.nd = p.dnx * (p.dparts > 1 ? p.dparts : 1);
+    a.wtile = p.wtile; a.wnx = p.wnx; a.wper = p.wper; a.wsplits = p.wsplits;
+    a.nw = p.wnx * p.wsplits;
+    a.w_first = p.w_first;
+    a.dg = a.wg = d;
+    if (p.dkind == BD_PAIR) {
+        const long long F = (long long)(d.B - 1) * d.y_pitch + d.Tp;
+        a.tickets = static_cast<int*>(dscratch);
+        a.part = reinterpret_cast<float*>(static_cast<unsigned char*>(dscratch) + DGRAD_TICKET_BYTES);
+        const dim3 g = dgrad_split_grid(a.dg, (F + 191) / 192, (d.Cin + 191) / 192);
+        a.dnx = (int)g.x;
+    } else if (p.dkind == BD_DH_128 || p.dkind == BD_DH_256) {
+        a.dg.x_pitch = d.T;  // dh is dense
+        a.dg.x_halo = 0;
+    }
+    constexpr int bytes = slab_lds_bytes(192, 192, 256, 2) > slab_lds_bytes(256, 128, 320, 2) ? slab_lds_bytes(192, 192, 256, 2) : slab_lds_bytes(256, 128, 320, 2);
+    static_assert(bytes >= 4 * 512 * 32 * 2 && bytes >= 3 * 384 * 64 * 2, "every form fits");
+    int rc = W2L_OK;
+    const dim3 grid((unsigned)((((a.w_first ? a.nw : a.nd) + 7) & ~7) + (a.w_first ? a.nd : a.nw)));
+    W2L_LAUNCH(conv_bwd_k, bytes, 512, a)
+    if (!rc) rc = launch_status();
+    if (rc || !split) return rc;
+    return finish_sums(part, p.wsplits, plane, dw, part + p.wsplits * plane, d.Cout, dbias, 0, st);
+}
+#undef W2L_LAUNCH
 
 }  // namespace w2l

@@ -64,6 +64,7 @@ struct Plan {
     bool fold0 = false;
     size_t cls = 0;        // operands of the last layer's data gradient prepared for the MFMA kernels (its dy is fp32)
     DgradPrep cls_prep;
+    std::vector<ConvBwdPlan> bwd;  // per layer: both gradients in one launch, where that can be done
     int status = W2L_OK;
 };
 
@@ -86,6 +87,8 @@ ConvDesc layer_bwd_desc(const Plan& p, const w2l_layer* L, int B, int i)
     return d;
 }
 size_t planes_bytes(int parts, size_t values) { return parts > 1 ? parts * values * 4 : 0; }
+
+bool same_layer(const w2l_layer& a, const w2l_layer& b) { return a.k == b.k && a.stride == b.stride && a.cin == b.cin && a.cout == b.cout && a.glu == b.glu; }
 
 Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int criterion)
 {
@@ -128,7 +131,6 @@ Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int
         ConvDesc dd = dense_desc(B, t, l.cin, l.cout, l.k, l.stride);
         if (i > 0) { dd.x_pitch = t + 2 * HALO; dd.x_halo = HALO; dd.slack = SLACK; }
         if (l.glu) { dd.y_pitch = to + 2 * HALO; dd.y_halo = HALO; dd.slack = SLACK; }
-        p.conv_bytes = max_of(p.conv_bytes, conv_wgrad_scratch_bytes(dd, dtype, i == n - 1 ? W2L_F32 : dtype));
         // sums of split reductions: the geometries that the step's passes will have
         const ConvDesc fd = layer_desc(p, L, B, i), bd = layer_bwd_desc(p, L, B, i);
         p.part_bytes = max_of(p.part_bytes, l.glu ? planes_bytes(conv_fwd_parts(fd, dtype), (size_t)B * to * l.cout) : conv_fwd_scratch(fd, dtype));
@@ -137,6 +139,13 @@ Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int
             p.part_bytes = max_of(p.part_bytes, L[i - 1].glu ? planes_bytes(conv_dgrad_parts(bd, dtype, dydt), (size_t)B * t * l.cin)
                                                              : conv_dgrad_scratch(bd, dtype, dydt));
         }
+        const bool as_above = i > 1 && same_layer(l, L[i - 1]) && L[i - 2].glu && p.Tin[i] == p.Tin[i - 1];
+        p.bwd.push_back(as_above ? p.bwd.back()
+                        : i > 0 && i < n - 1 && l.glu && L[i - 1].glu && dtype == W2L_BF16 ? conv_bwd_plan(bd) : ConvBwdPlan{});
+        // scratch of the weight gradients: on the caller's stream, or on the helper stream beside it
+        if (p.bwd.back().ok) p.conv0_bytes = max_of(p.conv0_bytes, p.bwd.back().wscratch);
+        else if (i == 0) p.conv0_bytes = conv_wgrad_scratch_bytes(dense_desc(B, T, l.cin, l.cout, l.k, l.stride), dtype, n == 1 ? W2L_F32 : dtype);
+        if (!p.bwd.back().ok) p.conv_bytes = max_of(p.conv_bytes, conv_wgrad_scratch_bytes(bd, dtype, i == n - 1 ? W2L_F32 : dtype));
         // a data gradient of two workgroups per tile: its tickets and the sums of both
         if (i > 0 && L[i - 1].glu) p.dgs_bytes = max_of(p.dgs_bytes, conv_dgrad_pair_bytes(bd));
         t = to;
@@ -151,9 +160,9 @@ Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int
     if (p.ctc_bytes == 0) { p.status = W2L_ERR_SHAPE; return p; }  // more classes or labels than the criterion takes
     p.ctc = off; off += round_up(p.ctc_bytes, 256);
     p.conv = off; off += round_up(p.conv_bytes, 256);
-    // layer 0's weight gradient runs on the caller's stream next to the helper stream's launches: its own scratch
+    // weight gradients on the caller's stream (layer 0's, and those that share a launch with the data gradient) run next
+    // to the helper stream's launches: their own scratch
     p.conv0 = off;
-    p.conv0_bytes = conv_wgrad_scratch_bytes(dense_desc(B, T, L[0].cin, L[0].cout, L[0].k, L[0].stride), dtype, n == 1 ? W2L_F32 : dtype);
     off += round_up(p.conv0_bytes, 256);
     int cmax = 0;
     for (int i = 0; i < n; ++i) cmax = L[i].cout > cmax ? L[i].cout : cmax;
@@ -294,8 +303,10 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
     // writer of dy_i only has to wait for the weight gradient of layer i+3.
     SideStream* side = side_stream(n);
     auto hip_ok = [&](hipError_t e) { if (e != hipSuccess) { note_hip_error(e); return false; } return true; };
+    int on_helper = n;                  // layers n - 1 .. on_helper have a weight gradient on the helper stream, some of them
+    std::vector<char> helped(n, 0);     // (these)
     auto wait_wgrad = [&](int layer) {  // main stream waits until that layer's weight gradient has read its dy
-        if (!side || layer >= n) return true;
+        if (layer >= n || !helped[layer]) return true;
         return hip_ok(hipStreamWaitEvent(st, side->done[layer], 0));
     };
     // dh tensors that go to memory alternate between two buffers: a layer without GLU takes dh itself as its dy,
@@ -327,6 +338,36 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
             gdh_reader[cur] = i;
         }
         dy_ready = false;
+        const void* xin = (i == 0) ? x : (const void*)(ws + p.post[i - 1]);
+        const ConvBwdPlan& both = p.bwd[i];
+        if (both.ok && dbiases[i]) {
+            // both gradients in one launch: no other stream, nothing to wait for but the last reader of what it writes
+            if (both.fused() && !tickets && p.dgs_bytes) {
+                rc = zero_dgrad_tickets(reinterpret_cast<int*>(ws + p.dgs), st);
+                if (rc) return rc;
+            }
+            tickets = tickets || both.fused();
+            const bool planes = both.dparts > 1, below = both.fused() || planes;
+            const int q = (cur == 0) ? 1 : 0;
+            if (below ? !wait_wgrad(i + 2) : (gdh_reader[q] >= 0 && !wait_wgrad(gdh_reader[q]))) return W2L_ERR_LAUNCH;
+            if (!below) gdh_reader[q] = -1;
+            void* const dyb = ws + p.gdy[(i + 2) % 3];
+            rc = conv_bwd(both, d, dy, weights[i], xin, ws + p.pre[i - 1], below ? dyb : gdhb[q], dweights[i], dbiases[i],
+                          ws + (planes ? p.part : p.dgs), ws + p.conv0, st);
+            if (rc) return rc;
+            if (planes) {
+                rc = finish_glu_bwd(reinterpret_cast<float*>(ws + p.part), both.dparts, ws + p.pre[i - 1], dyb, B, p.Tout[i - 1],
+                                    layers[i - 1].cout, dtype, p.Tout[i - 1] + 2 * HALO, HALO, SLACK_ZERO, st);
+                if (rc) return rc;
+            }
+            dy_ready = below;
+            if (!below) {
+                dh = gdhb[q];
+                cur = q;
+                dh_dt = dtype;
+            }
+            continue;
+        }
         // layer 0 has no data gradient: its weight gradient takes the main stream, next to the
         // helper stream's last launch, instead of queueing behind it
         const bool on_side = side && i > 0;
@@ -335,7 +376,6 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
             if (!hip_ok(hipEventRecord(side->ready[i], st)) || !hip_ok(hipStreamWaitEvent(wst, side->ready[i], 0)))
                 return W2L_ERR_LAUNCH;
         }
-        const void* xin = (i == 0) ? x : (const void*)(ws + p.post[i - 1]);
         if (i == 0 && p.fold0) {
             // the strided first layer as a stride-1 layer over folded frames: x copied (2 MB) into the haloed time
             // layout of dy_0, then the same dense weight-gradient kernel as every other layer, bias gradient included
@@ -356,7 +396,11 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
         rc = conv_wgrad(d, xin, dy, dweights[i], (fused_dbias || !side) ? dbiases[i] : nullptr, dtype, dy_dt, 0,
                         ws + (i == 0 ? p.conv0 : p.conv), i == 0 ? p.conv0_bytes : p.conv_bytes, wst);
         if (rc) return rc;
-        if (on_side && !hip_ok(hipEventRecord(side->done[i], wst))) return W2L_ERR_LAUNCH;
+        if (on_side) {
+            if (!hip_ok(hipEventRecord(side->done[i], wst))) return W2L_ERR_LAUNCH;
+            helped[i] = 1;
+            on_helper = i;
+        }
         if (side && dbiases[i] && !fused_dbias) {
             // halo frames hold zeros, so summing every frame of the allocation is the same sum
             rc = dbias_reduce(dy, dbiases[i], (long long)d.B * d.y_pitch, d.Cout, dy_dt, 0,
@@ -408,7 +452,7 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
         }
     }
     // join: the side stream is in order, so its last event covers every weight gradient
-    if (side && n > 1 && !hip_ok(hipStreamWaitEvent(st, side->done[1], 0))) return W2L_ERR_LAUNCH;
+    if (on_helper < n && !hip_ok(hipStreamWaitEvent(st, side->done[on_helper], 0))) return W2L_ERR_LAUNCH;
     return W2L_OK;
 }
 
