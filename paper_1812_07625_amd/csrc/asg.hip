@@ -45,6 +45,7 @@ constexpr int AHEAD = 16;             // frames of scores held in registers ahea
 constexpr int CP = 64;                // pitch of an FCC lattice row; the class limit
 constexpr int GRAD_UNROLL = 4;        // target positions per lane whose loads asg_grad_em issues together
 constexpr int CHUNK = 32;             // frames per asg_trans_partial workgroup
+constexpr int FAL_AHEAD = 16;         // of them, frames whose loads a thread has in flight together
 
 struct AsgDims {
     int B, Tp, C, Lmax;
@@ -740,6 +741,8 @@ __global__ __launch_bounds__(MAXT) void asg_lattice(const float* __restrict__ em
 }
 
 // Node occupancies and the loss.  One wavefront per frame; a workgroup of 4 wavefronts takes `rows_per_wg` consecutive frames of one utterance.
+// The kernel is a chain of latencies (the target's sort, a frame's rows, its sums by class), so a wavefront requests its
+// first frame's rows beside the sort, and the occupancies lie in LDS in the order in which the classes add them.
 //   grad_em[t][c] = grad_scale * ( P_fcc(pi_t = c) - P_fal(pi_t = c) )
 __global__ __launch_bounds__(256) void asg_grad_em(const float* __restrict__ em, const int* __restrict__ targets,
                                                    const int* __restrict__ in_len, const int* __restrict__ tgt_len,
@@ -762,55 +765,69 @@ __global__ __launch_bounds__(256) void asg_grad_em(const float* __restrict__ em,
     }
     const int L = tgt_len[b];
     int* lab = reinterpret_cast<int*>(smem_raw);  // [Lmax]
-    int* order = lab + d.Lmax;                    // [Lmax] positions sorted by (class, position)
-    int* cstart = order + d.Lmax;                 // [C+1]
-    float* ebuf = reinterpret_cast<float*>(cstart + d.C + 1) + (size_t)wave * d.Sp;  // [4][Sp]
+    int* rank = lab + d.Lmax;                     // [Lmax] a position's place in the (class, position) order
+    int* cstart = rank + d.Lmax;                  // [C+1]
+    float* ebuf = reinterpret_cast<float*>(cstart + d.C + 1) + (size_t)wave * d.Sp;  // [4][Sp], in that order
     for (int i = tid; i < L; i += 256) {
         lab[i] = targets[(size_t)b * d.Lmax + i];
-        order[i] = w.order[(size_t)b * d.Lmax + i];
+        rank[w.order[(size_t)b * d.Lmax + i]] = i;
     }
     for (int c = tid; c <= d.C; c += 256) cstart[c] = w.cstart[(size_t)b * (d.C + 1) + c];
-    __syncthreads();
 
     const float log2e = (float)LOG2E;
     const size_t rowb = (size_t)b * (d.Tp + 1);
+    // a frame's rows: the first 64 * GRAD_UNROLL positions, the classes (lane = class) and the offsets
+    struct Row { float av[GRAD_UNROLL], bv[GRAD_UNROLL], fa, fb, er; double off_f, off_a; };
+    auto fetch = [&](int t, Row& r) {
+        const float* ar = w.fal[0] + (rowb + t) * d.Sp;
+        const float* br = w.fal[1] + (rowb + t) * d.Sp;
+#pragma unroll
+        for (int u = 0; u < GRAD_UNROLL; ++u) {
+            const int sidx = min(lane + 64 * u, L - 1);  // clamped lanes repeat a valid position and are dropped below
+            r.av[u] = ar[sidx];
+            r.bv[u] = br[L - 1 - sidx];  // backward rows are stored in reversed order
+        }
+        const int c = min(lane, d.C - 1);
+        r.fa = w.fcc[0][(rowb + t) * CP + c];
+        r.fb = w.fcc[1][(rowb + t) * CP + c];
+        r.er = em[((size_t)b * d.Tp + t) * d.C + c];
+        r.off_f = w.fccoff[0][rowb + t] + w.fccoff[1][rowb + t];
+        r.off_a = w.faloff[0][rowb + t] + w.faloff[1][rowb + t];
+    };
+    Row row;
+    if (t0 + wave < T) fetch(t0 + wave, row);
+    __syncthreads();  // lab, order and cstart are there
     for (int t = t0 + wave; t < t_end; t += 4) {
         float* grow = gb + (size_t)t * d.C;
         if (t >= T) {
             for (int c = lane; c < d.C; c += 64) grow[c] = 0.f;
             continue;
         }
-        const float* erow = em + ((size_t)b * d.Tp + t) * d.C;
+        if (t >= t0 + 4) fetch(t, row);
         // fully connected: lane = class
-        const float shiftF = (float)(w.fccoff[0][rowb + t] + w.fccoff[1][rowb + t] - fcc2);
+        const float shiftF = (float)(row.off_f - fcc2);
         float pf = 0.f;
-        if (lane < d.C) {
-            const float av = w.fcc[0][(rowb + t) * CP + lane], bv = w.fcc[1][(rowb + t) * CP + lane];
-            if (av > NEG_TEST && bv > NEG_TEST) pf = fast_exp2((av + bv) + (shiftF - erow[lane] * log2e));
-        }
+        if (lane < d.C && row.fa > NEG_TEST && row.fb > NEG_TEST) pf = fast_exp2((row.fa + row.fb) + (shiftF - row.er * log2e));
         const float zf = wave_sum_bcast(pf);
-        // forced alignment: lanes stride over the positions (backward rows are stored in reversed order);
-        // the loads of GRAD_UNROLL positions per lane are issued together
-        const float shiftA = (float)(w.faloff[0][rowb + t] + w.faloff[1][rowb + t] - fal2);
-        const float* ar = w.fal[0] + (rowb + t) * d.Sp;
-        const float* br = w.fal[1] + (rowb + t) * d.Sp;
+        // forced alignment: lanes stride over the positions; a position's score comes from the lane of its class
+        const float shiftA = (float)(row.off_a - fal2);
         float za = 0.f;
-        for (int s0 = lane; s0 < L; s0 += 64 * GRAD_UNROLL) {
-            float av[GRAD_UNROLL], bv[GRAD_UNROLL], sc[GRAD_UNROLL];
+        for (int s0 = 0; s0 < L; s0 += 64 * GRAD_UNROLL) {
+            float av[GRAD_UNROLL], bv[GRAD_UNROLL];
 #pragma unroll
             for (int u = 0; u < GRAD_UNROLL; ++u) {
-                const int sidx = min(s0 + 64 * u, L - 1);  // clamped lanes repeat a valid position and are dropped below
-                av[u] = ar[sidx];
-                bv[u] = br[L - 1 - sidx];
-                sc[u] = erow[lab[sidx]];
+                const int sidx = min(s0 + lane + 64 * u, L - 1);
+                av[u] = s0 == 0 ? row.av[u] : w.fal[0][(rowb + t) * d.Sp + sidx];
+                bv[u] = s0 == 0 ? row.bv[u] : w.fal[1][(rowb + t) * d.Sp + L - 1 - sidx];
             }
 #pragma unroll
             for (int u = 0; u < GRAD_UNROLL; ++u) {
-                const int sidx = s0 + 64 * u;
+                const int sidx = s0 + lane + 64 * u;
+                const float sc = __shfl(row.er, lab[min(sidx, L - 1)], 64);
                 float e = 0.f;
-                if (av[u] > NEG_TEST && bv[u] > NEG_TEST) e = fast_exp2((av[u] + bv[u]) + (shiftA - sc[u] * log2e));
+                if (av[u] > NEG_TEST && bv[u] > NEG_TEST) e = fast_exp2((av[u] + bv[u]) + (shiftA - sc * log2e));
                 if (sidx < L) {
-                    ebuf[sidx] = e;
+                    ebuf[rank[sidx]] = e;
                     za += e;
                 }
             }
@@ -824,7 +841,8 @@ __global__ __launch_bounds__(256) void asg_grad_em(const float* __restrict__ em,
         __builtin_amdgcn_wave_barrier();
         if (lane < d.C) {
             float g = 0.f;
-            for (int q = cstart[lane]; q < cstart[lane + 1]; ++q) g += ebuf[order[q]];
+#pragma unroll 4
+            for (int q = cstart[lane]; q < cstart[lane + 1]; ++q) g += ebuf[q];
             grow[lane] = grad_scale * (pf * izf - g * iza);
         }
         __builtin_amdgcn_wave_barrier();
@@ -840,7 +858,7 @@ __global__ __launch_bounds__(256) void asg_trans_partial(const float* __restrict
                                                          const int* __restrict__ in_len, const int* __restrict__ tgt_len,
                                                          AsgWs w, AsgDims d)
 {
-    __shared__ float sA[CHUNK + 1][CP];  // forward rows t0-1 .. t0+CHUNK-1
+    __shared__ __align__(16) float sA[CHUNK + 1][CP];  // forward rows t0-1 .. t0+CHUNK-1
     __shared__ float sB[CHUNK][CP];      // backward rows t0 .. t0+CHUNK-1
     __shared__ float wF[CHUNK], wA[CHUNK];
     const int ch = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
@@ -857,58 +875,95 @@ __global__ __launch_bounds__(256) void asg_trans_partial(const float* __restrict
     }
     const size_t rowb = (size_t)b * (d.Tp + 1);
     const double fcc2 = w.terms[2 * b], fal2 = w.terms[2 * b + 1];
-    for (int e = tid; e < (CHUNK + 1) * CP; e += 256) {
-        const int r = e / CP, c = e - r * CP, t = t0 - 1 + r;
-        sA[r][c] = (t >= 0 && t < T && c < d.C) ? w.fcc[0][(rowb + t) * CP + c] : NEG;
+    // everything the chunk reads of the lattices is requested at once: the FCC rows in 16-byte pieces on their way into
+    // LDS, the offsets, and the first FAL_AHEAD frames of a thread's first target position
+    constexpr int PIECES = ((CHUNK + 1) * CP / 4 + 255) / 256;
+    float4 fa[PIECES], fb[PIECES];
+#pragma unroll
+    for (int q = 0; q < PIECES; ++q) {
+        const int e = min(tid + 256 * q, (CHUNK + 1) * CP / 4 - 1), r = e / (CP / 4), c = e % (CP / 4) * 4;
+        fa[q] = *reinterpret_cast<const float4*>(w.fcc[0] + (rowb + min(max(t0 - 1 + r, 0), T - 1)) * CP + c);
+        fb[q] = *reinterpret_cast<const float4*>(w.fcc[1] + (rowb + min(t0 + r, T - 1)) * CP + c);
     }
-    for (int e = tid; e < CHUNK * CP; e += 256) {
-        const int r = e / CP, c = e - r * CP, t = t0 + r;
-        sB[r][c] = (t < T && c < d.C) ? w.fcc[1][(rowb + t) * CP + c] : NEG;
-    }
+    const int* lab = targets + (size_t)b * d.Lmax;
+    float x0[FAL_AHEAD], x1[FAL_AHEAD], y[FAL_AHEAD];
+    auto fetch = [&](int s, int t) {  // forward rows t-1 .., backward rows t .. (those are stored in reversed order)
+        const float* a0 = w.fal[0] + rowb * d.Sp + s;
+        const float* b0 = w.fal[1] + rowb * d.Sp + (L - 1 - s);
+        const int left = s >= 1 ? 1 : 0;
+#pragma unroll
+        for (int u = 0; u < FAL_AHEAD; ++u) {
+            const int tt = t + u < thi ? t + u : thi - 1;
+            x0[u] = a0[(size_t)(tt - 1) * d.Sp];
+            x1[u] = a0[(size_t)(tt - 1) * d.Sp - left];
+            y[u] = b0[(size_t)tt * d.Sp];
+        }
+    };
+    if (tid < L) fetch(tid, tlo);
     if (tid < CHUNK) {
         const int t = t0 + tid;
         float f = NEG, a = NEG;
         if (t >= tlo && t < thi) {
             const float izf = w.izf[(size_t)b * d.Tp + t], iza = w.iza[(size_t)b * d.Tp + t];
-            if (izf > 0.f) f = (float)(w.fccoff[0][rowb + t - 1] + w.fccoff[1][rowb + t] - fcc2) + fast_log2(izf);
-            if (iza > 0.f) a = (float)(w.faloff[0][rowb + t - 1] + w.faloff[1][rowb + t] - fal2) + fast_log2(iza);
+            const double of = w.fccoff[0][rowb + t - 1] + w.fccoff[1][rowb + t], oa = w.faloff[0][rowb + t - 1] + w.faloff[1][rowb + t];
+            if (izf > 0.f) f = (float)(of - fcc2) + fast_log2(izf);
+            if (iza > 0.f) a = (float)(oa - fal2) + fast_log2(iza);
         }
         wF[tid] = f;
         wA[tid] = a;
     }
+#pragma unroll
+    for (int q = 0; q < PIECES; ++q) {
+        const int e = tid + 256 * q, r = e / (CP / 4), c = e % (CP / 4) * 4, ta = t0 - 1 + r, tb = t0 + r;
+        const float* va = &fa[q].x;
+        const float* vb = &fb[q].x;
+        if (r <= CHUNK) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                sA[r][c + u] = (ta >= 0 && ta < T && c + u < d.C) ? va[u] : NEG;
+                if (r < CHUNK) sB[r][c + u] = (tb < T && c + u < d.C) ? vb[u] : NEG;
+            }
+        }
+    }
     __syncthreads();
     const float log2e = (float)LOG2E;
-    for (int p = tid; p < C2; p += 256) {
-        const int i = p / d.C, j = p - i * d.C;
-        const float g2 = trans[p] * log2e;
-        float acc = 0.f;
-        for (int r = tlo - t0; r < thi - t0; ++r) acc += fast_exp2((sA[r][j] + sB[r][i]) + (g2 + wF[r]));
-        pF[p] = acc;
+    // four source classes a thread: one 16-byte LDS read a frame for them (frames that do not count have wF = log zero)
+    const int quads = (d.C + 3) / 4;
+    for (int p = tid; p < d.C * quads; p += 256) {
+        const int i = p / quads, j = (p - i * quads) * 4;
+        float g2[4], acc[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            g2[u] = trans[i * d.C + min(j + u, d.C - 1)] * log2e;
+            acc[u] = 0.f;
+        }
+#pragma unroll 8
+        for (int r = 0; r < CHUNK; ++r) {
+            const float4 a4 = *reinterpret_cast<const float4*>(&sA[r][j]);
+            const float* av = &a4.x;
+            const float bv = sB[r][i], wv = wF[r];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) acc[u] += fast_exp2((av[u] + bv) + (g2[u] + wv));
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (j + u < d.C) pF[i * d.C + j + u] = acc[u];
     }
-    const int* lab = targets + (size_t)b * d.Lmax;
     for (int s = tid; s < d.Lmax; s += 256) {
         float stay = 0.f, adv = 0.f;
         if (s < L) {
             const int c = lab[s];
             const float gs = trans[(size_t)c * d.C + c] * log2e;
             const float ga = s >= 1 ? trans[(size_t)c * d.C + lab[s - 1]] * log2e : NEG;
-            const float* a0 = w.fal[0] + rowb * d.Sp + s;                // forward row t-1 is read at a0[(t-1) * Sp]
-            const float* b0 = w.fal[1] + rowb * d.Sp + (L - 1 - s);      // backward rows are stored in reversed order
-            for (int t = tlo; t < thi; t += 8) {   // loads of eight frames in flight together
-                float x0[8], x1[8], y[8];
+            for (int t = tlo; t < thi; t += FAL_AHEAD) {
+                if (s != tid || t != tlo) fetch(s, t);
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int tt = t + u < thi ? t + u : thi - 1;
-                    x0[u] = a0[(size_t)(tt - 1) * d.Sp];
-                    x1[u] = s >= 1 ? a0[(size_t)(tt - 1) * d.Sp - 1] : NEG;
-                    y[u] = b0[(size_t)tt * d.Sp];
-                }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    if (t + u >= thi) break;
-                    const float bv = y[u] + wA[t + u - t0];
-                    stay += fast_exp2((x0[u] + bv) + gs);
-                    adv += fast_exp2((x1[u] + bv) + ga);
+                for (int u = 0; u < FAL_AHEAD; ++u) {
+                    if (t + u < thi) {
+                        const float bv = y[u] + wA[t + u - t0];
+                        stay += fast_exp2((x0[u] + bv) + gs);
+                        adv += fast_exp2(((s >= 1 ? x1[u] : NEG) + bv) + ga);
+                    }
                 }
             }
         }
@@ -922,25 +977,26 @@ __global__ __launch_bounds__(256) void asg_trans_partial(const float* __restrict
 // addition does not depend on the order, so the result is reproducible -- and subtracted from
 // the FCC edge sums (added over the chunks in order).
 constexpr double FIXED_ONE = 4294967296.0;  // 2^32: occupancies up to 2^31 frames, resolved to 2.3e-10
-__global__ __launch_bounds__(256) void asg_trans_utt(const int* __restrict__ targets, const int* __restrict__ tgt_len,
+constexpr int UTT_THREADS = 1024;
+__global__ __launch_bounds__(UTT_THREADS) void asg_trans_utt(const int* __restrict__ targets, const int* __restrict__ tgt_len,
                                                      AsgWs w, AsgDims d)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int b = blockIdx.x, tid = threadIdx.x, C2 = d.C * d.C;
     float* tab = w.tabD + (size_t)b * C2;
     if (w.status[b] != 0) {
-        for (int p = tid; p < C2; p += 256) tab[p] = 0.f;
+        for (int p = tid; p < C2; p += UTT_THREADS) tab[p] = 0.f;
         return;
     }
     const int L = tgt_len[b];
     unsigned long long* fal = reinterpret_cast<unsigned long long*>(smem_raw);  // [C*C]
-    for (int p = tid; p < C2; p += 256) fal[p] = 0ull;
+    for (int p = tid; p < C2; p += UTT_THREADS) fal[p] = 0ull;
     __syncthreads();
     const int* lab = targets + (size_t)b * d.Lmax;
     const float* pA = w.partA + (size_t)b * d.nch * 2 * d.Lmax;
-    for (int s = tid; s < L; s += 256) {
+    for (int s = tid; s < L; s += UTT_THREADS) {
         float stay = 0.f, adv = 0.f;
-#pragma unroll 8
+#pragma unroll 16
         for (int ch = 0; ch < d.nch; ++ch) {
             stay += pA[(size_t)ch * 2 * d.Lmax + s];
             adv += pA[(size_t)ch * 2 * d.Lmax + d.Lmax + s];
@@ -952,9 +1008,9 @@ __global__ __launch_bounds__(256) void asg_trans_utt(const int* __restrict__ tar
     }
     __syncthreads();
     const float* pF = w.partF + (size_t)b * d.nch * C2;
-    for (int p = tid; p < C2; p += 256) {
+    for (int p = tid; p < C2; p += UTT_THREADS) {
         float f = 0.f;
-#pragma unroll 8
+#pragma unroll 16
         for (int ch = 0; ch < d.nch; ++ch) f += pF[(size_t)ch * C2 + p];
         tab[p] = f - (float)((double)(long long)fal[p] * (1.0 / FIXED_ONE));
     }
@@ -966,7 +1022,7 @@ __global__ __launch_bounds__(64) void asg_trans_reduce(float* __restrict__ grad_
     const int p = blockIdx.x * 64 + threadIdx.x, C2 = d.C * d.C;
     if (p >= C2) return;
     float acc = 0.f;
-#pragma unroll 8
+#pragma unroll 32
     for (int b = 0; b < d.B; ++b) acc += w.tabD[(size_t)b * C2 + p];
     grad_trans[p] = grad_scale * acc;
 }
@@ -1145,7 +1201,7 @@ extern "C" int w2l_asg_fwd_bwd(const float* emissions, const float* trans, const
     hipLaunchKernelGGL(asg_trans_partial, dim3(d.nch, B), dim3(256), 0, st, trans, targets, in_len, tgt_len, w, d);
     rc = launch_status();
     if (rc) return rc;
-    hipLaunchKernelGGL(asg_trans_utt, dim3(B), dim3(256), lds_tab, st, targets, tgt_len, w, d);
+    hipLaunchKernelGGL(asg_trans_utt, dim3(B), dim3(UTT_THREADS), lds_tab, st, targets, tgt_len, w, d);
     rc = launch_status();
     if (rc) return rc;
     hipLaunchKernelGGL(asg_trans_reduce, dim3((C * C + 63) / 64), dim3(64), 0, st, grad_trans, w, d, grad_scale);
