@@ -1545,11 +1545,11 @@ bool conv_fwd_mfma_ok(const ConvDesc& d)
     return d.Cin % 8 == 0 && common_ok(e) && d.Cout >= 16 && (long long)d.B * d.Tp >= 128;
 }
 
-// XCD cut of the 192x192 slab forward's tile grid: a row of tiles reads its 192 + k - 1 frames of x, a column
-// of tiles its 192 rows of w
-static int fwd_slab_xcd(const ConvDesc& g, long long tiles_m, long long tiles_n)
+// XCD cut of the slab forward's tile grid: a row of tiles reads its bm + k - 1 frames of x, a column of tiles its
+// bn rows of w
+static int fwd_slab_xcd(const ConvDesc& g, int bm, int bn, long long tiles_m, long long tiles_n)
 {
-    return xcd_split(tiles_m, tiles_n, (double)(192 + g.k - 1) * g.Cin, 192.0 * g.k * g.Cin);
+    return xcd_split(tiles_m, tiles_n, (double)(bm + g.k - 1) * g.Cin, (double)bn * g.k * g.Cin);
 }
 
 #define W2L_LAUNCH(KERN, BYTES, NTHR, ...)                                                \
@@ -1614,7 +1614,7 @@ int conv_fwd_mfma(const ConvDesc& g0, const void* x, const void* w, const float*
         constexpr int bytes = slab_lds_bytes(192, 192, 256, 2);
         const long long F = (long long)(g.B - 1) * g.x_pitch + g.T;
         const dim3 grid((unsigned)(((F + 191) / 192) * ((N + 191) / 192)));
-        g.xcd_m = fwd_slab_xcd(g, (F + 191) / 192, (N + 191) / 192);
+        g.xcd_m = fwd_slab_xcd(g, 192, 192, (F + 191) / 192, (N + 191) / 192);
         int rc = W2L_OK;
         if (ydt == W2L_BF16) W2L_LAUNCH((conv_fwd_slab_k<192, 192, 256, 2, bf16_t, false>), bytes, 512, (const bf16_t*)x, (const bf16_t*)w, bias, (bf16_t*)y, (bf16_t*)nullptr, g)
         else W2L_LAUNCH((conv_fwd_slab_k<192, 192, 256, 2, float, false>), bytes, 512, (const bf16_t*)x, (const bf16_t*)w, bias, (float*)y, (bf16_t*)nullptr, g)
@@ -1623,25 +1623,29 @@ int conv_fwd_mfma(const ConvDesc& g0, const void* x, const void* w, const float*
     return ydt == W2L_BF16 ? launch_fwd<bf16_t>(g, tc, 1, x, w, bias, (bf16_t*)y, st) : launch_fwd<float>(g, tc, 1, x, w, bias, (float*)y, st);
 }
 
-bool conv_fwd_glu_ok(const ConvDesc& d)
+// The slab kernel with the two GLU halves interleaved per tile; h in the time layout of x.  192x192 where those tiles
+// fill the chip best, else 256x128 where those do (16 x 800 frames, k = 11, 256 -> 512: 39 us where convolution and GLU pass took 39 + 5)
+static TileChoice fwd_glu_tile(const ConvDesc& d)
 {
-    // the 192x192 slab kernel with the two GLU halves interleaved per tile; h in the time layout of x
-    const long long M = (long long)d.B * d.Tp;
-    const TileChoice tc = choose_tile(M, d.Cout);
-    return conv_fwd_mfma_ok(d) && halo_ok_x(d) && tc.bm == 192 && tc.bn == 192 && d.Cout % 2 == 0 && (d.Cout / 2) % 96 == 0 &&
-           d.T == d.Tp && d.slack >= LAYOUT_SLACK_ZERO && slab_ok(d, 192, 256, d.Cin, d.T, d.x_pitch, d.x_halo);
+    const TileChoice none{0, 0}, tc = choose_tile((long long)d.B * d.Tp, d.Cout);
+    if (!conv_fwd_mfma_ok(d) || !halo_ok_x(d) || d.Cout % 2 || d.T != d.Tp || d.slack < LAYOUT_SLACK_ZERO) return none;
+    if (tc.bm == 192 && (d.Cout / 2) % 96 == 0 && slab_ok(d, 192, 256, d.Cin, d.T, d.x_pitch, d.x_halo)) return tc;
+    if (tc.bm * tc.bn == 256 * 128 && (d.Cout / 2) % 64 == 0 && slab_ok(d, 256, 320, d.Cin, d.T, d.x_pitch, d.x_halo)) return TileChoice{256, 128};
+    return none;
 }
+bool conv_fwd_glu_ok(const ConvDesc& d) { return fwd_glu_tile(d).bm > 0; }
 
 int conv_fwd_glu(const ConvDesc& g0, const void* x, const void* w, const float* bias, void* y, void* h, hipStream_t st)
 {
-    if (!conv_fwd_glu_ok(g0)) return W2L_ERR_SHAPE;
+    const TileChoice tc = fwd_glu_tile(g0);
+    if (!tc.bm) return W2L_ERR_SHAPE;
     ConvDesc g = g0;
-    constexpr int bytes = slab_lds_bytes(192, 192, 256, 2);
-    const long long F = (long long)(g.B - 1) * g.x_pitch + g.T;
-    const unsigned grid = (unsigned)(((F + 191) / 192) * (g.Cout / 192));
-    g.xcd_m = fwd_slab_xcd(g, (F + 191) / 192, g.Cout / 192);
-    int rc = set_lds(conv_fwd_slab_k<192, 192, 256, 2, bf16_t, true>, bytes);
-    if (!rc) hipLaunchKernelGGL((conv_fwd_slab_k<192, 192, 256, 2, bf16_t, true>), dim3(grid), dim3(512), bytes, st, (const bf16_t*)x, (const bf16_t*)w, bias, (bf16_t*)y, (bf16_t*)h, g);
+    const long long F = (long long)(g.B - 1) * g.x_pitch + g.T, tiles_m = (F + tc.bm - 1) / tc.bm, tiles_n = g.Cout / tc.bn;
+    const dim3 grid((unsigned)(tiles_m * tiles_n));
+    g.xcd_m = fwd_slab_xcd(g, tc.bm, tc.bn, tiles_m, tiles_n);
+    int rc = W2L_OK;
+    if (tc.bm == 192) W2L_LAUNCH((conv_fwd_slab_k<192, 192, 256, 2, bf16_t, true>), slab_lds_bytes(192, 192, 256, 2), 512, (const bf16_t*)x, (const bf16_t*)w, bias, (bf16_t*)y, (bf16_t*)h, g)
+    else W2L_LAUNCH((conv_fwd_slab_k<256, 128, 320, 2, bf16_t, true>), slab_lds_bytes(256, 128, 320, 2), 512, (const bf16_t*)x, (const bf16_t*)w, bias, (bf16_t*)y, (bf16_t*)h, g)
     return rc ? rc : launch_status();
 }
 
