@@ -691,79 +691,91 @@ int wgrad_t(const ConvDesc& d, const AnyPlan& pl, const void* x, const void* dy,
 }
 
 // ---- weight gradient for narrow outputs (Cout <= 32, e.g. the 29 grapheme classes) ---------
-// dw[co, n=(j,ci)] = sum_{r=(b,t')} dy[r,co] * x[b, s t' + j - p, ci].  A 64-wide GEMM tile would
-// leave all but one tile row empty and serialise the whole reduction in a handful of
-// workgroups; here the reduction is cut into SKINNY_CHUNKS row ranges (grid.y), every thread
-// owns one column n and keeps all Cout partial sums in registers, and a second pass adds the
-// chunks in a fixed order.
-constexpr int SKINNY_ROWS = 32;  // dy rows staged in LDS per pass
-
+// dw[co, n=(j,ci)] = sum_{r=(b,t')} dy[r,co] * x[b, s t' + j - p, ci].  A 64-wide tile would be half empty and there are
+// few of them: the reduction is cut into SKINNY_CHUNKS ranges of frames (grid.y), and a second pass adds the chunks in a
+// fixed order.
 // N1 columns: the N of the weights and, for the bias gradient, one more that meets ones instead of x.
-// 64 columns per workgroup; its four wavefronts take every fourth row of the chunk and add up through LDS at the end.
-// The kernel lives on memory latency: the next pass's rows of either operand are requested before this pass's products.
-// 16 x 800 frames, 512 -> 29: 31 us with the bias gradient in it (column sums of their own took 20 us more).
+// v_mfma_f32_32x32x2_f32 straight from memory: 32 classes by 2 x 32 columns a wavefront, two frames an instruction (one
+// in lanes 0..31, the next in lanes 32..63), SKINNY_AHEAD instructions' operands requested together; what bounds it is
+// the issue of their loads, one element a lane.  The four wavefronts of a workgroup interleave the chunk's frames and
+// add up through LDS.  16 x 800 frames, 512 -> 29: 18 us, where scalar FMAs over frames staged in LDS took 31 and the
+// bias gradient 20 more.
+constexpr int SKINNY_AHEAD = 16;
+
 template <typename TX, typename TDY>
 __global__ __launch_bounds__(256) void wgrad_skinny_stage1(const TX* __restrict__ x, const TDY* __restrict__ dy,
                                                            float* __restrict__ part, ConvDesc d, int N1)
 {
-    __shared__ float dyt[2][SKINNY_ROWS][32];
     __shared__ float red[3][32][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c = lane & 31, half = lane >> 5;
     const int N = d.k * d.Cin, R = d.B * d.Tp;
-    const int n = blockIdx.x * 64 + lane;
     const int per = (R + gridDim.y - 1) / gridDim.y;
-    const int r_begin = per * blockIdx.y, r_end = (r_begin + per < R) ? r_begin + per : R;
-    const int j = (n < N) ? n / d.Cin : 0, ci = (n < N) ? n - j * d.Cin : 0;
-    constexpr int DV = SKINNY_ROWS * 32 / 256, XV = SKINNY_ROWS / 4;
-    float dv[DV], xv[XV];
-    // (rows past the chunk and frames outside the utterance read the chunk's last row or the first frame and count 0)
-    auto fetch = [&](int r0) {
+    const int r_begin = per * blockIdx.y < R ? per * blockIdx.y : R, r_end = (r_begin + per < R) ? r_begin + per : R;
+    int j[2], ci[2];
+    bool real[2];
 #pragma unroll
-        for (int q = 0; q < DV; ++q) {
-            const int e = threadIdx.x + 256 * q, rr = e >> 5, c = e & 31, rq = r0 + rr, r = min(rq, r_end - 1);
-            const int b = r / d.Tp, tp = r - b * d.Tp;
-            const bool ok = rq < r_end && c < d.Cout;
-            const float v = Elem<TDY>::load(dy, ((size_t)b * d.y_pitch + d.y_halo + tp) * d.Cout + (c < d.Cout ? c : 0));
-            dv[q] = ok ? v : 0.f;
+    for (int q = 0; q < 2; ++q) {
+        const int n = blockIdx.x * 64 + 32 * q + c;
+        real[q] = n < N;  // (columns past the end meet ones: the first of them is the bias gradient)
+        j[q] = real[q] ? n / d.Cin : 0;
+        ci[q] = real[q] ? n - j[q] * d.Cin : 0;
+    }
+    f32x16 acc[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[q][e] = 0.f;
+    // this lane's frame, and where its dy row and (tap 0, channel 0) of its window lie: from frame to frame by addition
+    int r = r_begin + 2 * wave + half, tp = r % d.Tp, t0 = d.s * tp - d.p;
+    const long long b0 = r / d.Tp, xstep = 8LL * d.s * d.Cin, ystep = 8LL * d.Cout;
+    const long long xwrap = ((long long)d.x_pitch - (long long)d.s * d.Tp) * d.Cin, ywrap = (long long)(d.y_pitch - d.Tp) * d.Cout;
+    const TDY* py = dy + (b0 * d.y_pitch + d.y_halo + tp) * d.Cout + (c < d.Cout ? c : 0);
+    const TX* px = x + (b0 * d.x_pitch + d.x_halo + t0) * d.Cin;
+    const int xo[2] = {j[0] * d.Cin + ci[0], j[1] * d.Cin + ci[1]};
+    const int steps = r_end > r_begin ? (r_end - r_begin + 7) / 8 : 0;  // of eight frames, two a wavefront
+    for (int st = 0; st < steps; st += SKINNY_AHEAD) {
+        float dv[SKINNY_AHEAD], xv[SKINNY_AHEAD][2];
+#pragma unroll
+        for (int u = 0; u < SKINNY_AHEAD; ++u) {
+            const bool ok = r < r_end;  // (frames past the chunk read element 0 and count 0)
+            const float v = Elem<TDY>::load(ok ? py : dy, 0);
+            dv[u] = ok && c < d.Cout ? v : 0.f;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const bool in = ok && (unsigned)(t0 + j[q]) < (unsigned)d.T;
+                const float xe = Elem<TX>::load(in ? px + xo[q] : x, 0);
+                xv[u][q] = real[q] ? (in ? xe : 0.f) : 1.f;
+            }
+            r += 8;
+            tp += 8;
+            t0 += 8 * d.s;
+            px += xstep;
+            py += ystep;
+            while (tp >= d.Tp) { tp -= d.Tp; t0 -= d.s * d.Tp; px += xwrap; py += ywrap; }
         }
 #pragma unroll
-        for (int u = 0; u < XV; ++u) {
-            const int rq = r0 + wave + 4 * u, r = min(rq, r_end - 1);
-            const int b = r / d.Tp, tp = r - b * d.Tp;
-            const int t = d.s * tp + j - d.p;
-            const bool ok = t >= 0 && t < d.T && rq < r_end;
-            const float v = Elem<TX>::load(x, ((size_t)b * d.x_pitch + d.x_halo + (ok ? t : 0)) * d.Cin + ci);
-            xv[u] = n < N ? (ok ? v : 0.f) : 1.f;  // (dy is 0 where rq is past the chunk)
-        }
-    };
-    float acc[32];
+        for (int u = 0; u < SKINNY_AHEAD; ++u)
 #pragma unroll
-    for (int c = 0; c < 32; ++c) acc[c] = 0.f;
-    if (r_begin < r_end) fetch(r_begin);
-    int slot = 0;
-    for (int r0 = r_begin; r0 < r_end; r0 += SKINNY_ROWS, slot ^= 1) {
-        float xc[XV];
-#pragma unroll
-        for (int u = 0; u < XV; ++u) xc[u] = xv[u];
-#pragma unroll
-        for (int q = 0; q < DV; ++q) dyt[slot][0][threadIdx.x + 256 * q] = dv[q];
-        __syncthreads();  // (the other slot is written after the next barrier's worth of reads of this one)
-        if (r0 + SKINNY_ROWS < r_end) fetch(r0 + SKINNY_ROWS);
-#pragma unroll
-        for (int u = 0; u < XV; ++u)
-#pragma unroll
-            for (int c = 0; c < 32; ++c) acc[c] = fmaf(dyt[slot][wave + 4 * u][c], xc[u], acc[c]);
+            for (int q = 0; q < 2; ++q) acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(dv[u], xv[u][q], acc[q], 0, 0, 0);
     }
     if (wave > 0) {
 #pragma unroll
-        for (int c = 0; c < 32; ++c) red[wave - 1][c][lane] = acc[c];
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) red[wave - 1][8 * (e >> 2) + 4 * half + (e & 3)][32 * q + c] = acc[q][e];
     }
     __syncthreads();
-    if (wave == 0 && n < N1) {
+    if (wave == 0) {
 #pragma unroll
-        for (int c = 0; c < 32; ++c)
-            if (c < d.Cout)
-                part[((size_t)blockIdx.y * d.Cout + c) * N1 + n] = ((acc[c] + red[0][c][lane]) + red[1][c][lane]) + red[2][c][lane];
+        for (int q = 0; q < 2; ++q) {
+            const int n = blockIdx.x * 64 + 32 * q + c;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int m = 8 * (e >> 2) + 4 * half + (e & 3);
+                if (m < d.Cout && n < N1)
+                    part[((size_t)blockIdx.y * d.Cout + m) * N1 + n] = ((acc[q][e] + red[0][m][32 * q + c]) + red[1][m][32 * q + c]) + red[2][m][32 * q + c];
+            }
+        }
     }
 }
 __global__ __launch_bounds__(256) void wgrad_skinny_stage2(const float* __restrict__ part, float* __restrict__ dw, float* __restrict__ dbias,

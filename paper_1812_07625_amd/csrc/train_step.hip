@@ -88,6 +88,9 @@ ConvDesc layer_bwd_desc(const Plan& p, const w2l_layer* L, int B, int i)
 }
 size_t planes_bytes(int parts, size_t values) { return parts > 1 ? parts * values * 4 : 0; }
 
+// Layer 0 has no data gradient to run beside, and the weight gradient of narrow outputs is shorter than the events that
+// a second stream takes: these stay on the caller's stream.
+bool main_wgrad(const w2l_layer& l, int i) { return i == 0 || l.cout <= 32; }
 bool same_layer(const w2l_layer& a, const w2l_layer& b) { return a.k == b.k && a.stride == b.stride && a.cin == b.cin && a.cout == b.cout && a.glu == b.glu; }
 
 Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int criterion)
@@ -144,8 +147,8 @@ Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int
                         : i > 0 && i < n - 1 && l.glu && L[i - 1].glu && dtype == W2L_BF16 ? conv_bwd_plan(bd) : ConvBwdPlan{});
         // scratch of the weight gradients: on the caller's stream, or on the helper stream beside it
         if (p.bwd.back().ok) p.conv0_bytes = max_of(p.conv0_bytes, p.bwd.back().wscratch);
-        else if (i == 0) p.conv0_bytes = conv_wgrad_scratch_bytes(dense_desc(B, T, l.cin, l.cout, l.k, l.stride), dtype, n == 1 ? W2L_F32 : dtype);
-        if (!p.bwd.back().ok) p.conv_bytes = max_of(p.conv_bytes, conv_wgrad_scratch_bytes(bd, dtype, i == n - 1 ? W2L_F32 : dtype));
+        else if (main_wgrad(l, i)) p.conv0_bytes = max_of(p.conv0_bytes, conv_wgrad_scratch_bytes(i ? bd : dense_desc(B, T, l.cin, l.cout, l.k, l.stride), dtype, i == n - 1 ? W2L_F32 : dtype));
+        else p.conv_bytes = max_of(p.conv_bytes, conv_wgrad_scratch_bytes(bd, dtype, i == n - 1 ? W2L_F32 : dtype));
         // a data gradient of two workgroups per tile: its tickets and the sums of both
         if (i > 0 && L[i - 1].glu) p.dgs_bytes = max_of(p.dgs_bytes, conv_dgrad_pair_bytes(bd));
         t = to;
@@ -370,7 +373,7 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
         }
         // layer 0 has no data gradient: its weight gradient takes the main stream, next to the
         // helper stream's last launch, instead of queueing behind it
-        const bool on_side = side && i > 0;
+        const bool on_main = main_wgrad(l, i), on_side = side && !on_main;
         hipStream_t wst = on_side ? side->stream : st;
         if (on_side) {
             if (!hip_ok(hipEventRecord(side->ready[i], st)) || !hip_ok(hipStreamWaitEvent(wst, side->ready[i], 0)))
@@ -394,7 +397,7 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
         // on the main stream, which has the shorter chain
         const bool fused_dbias = dbiases[i] && conv_wgrad_fuses_dbias(d, dtype, dy_dt);
         rc = conv_wgrad(d, xin, dy, dweights[i], (fused_dbias || !side) ? dbiases[i] : nullptr, dtype, dy_dt, 0,
-                        ws + (i == 0 ? p.conv0 : p.conv), i == 0 ? p.conv0_bytes : p.conv_bytes, wst);
+                        ws + (on_main ? p.conv0 : p.conv), on_main ? p.conv0_bytes : p.conv_bytes, wst);
         if (rc) return rc;
         if (on_side) {
             if (!hip_ok(hipEventRecord(side->done[i], wst))) return W2L_ERR_LAUNCH;
