@@ -15,6 +15,7 @@
 // on exact binary fractions; the mel points in double) -- there is no table in memory.  A lane
 // then owns mel bands (lane, lane + 64, ...) and adds its weighted bins in ascending order, so the
 // result does not depend on scheduling.
+#include <cmath>
 #include "common.h"
 
 namespace w2l {
@@ -25,6 +26,7 @@ struct LogmelDims {
     int B, Nmax, Tmax, F, sr, win, hop, nfft;
     int fpw;  // frames per workgroup (a multiple of 4)
     float fmin, fmax, floor;
+    double mlo, mhi;  // the mel scale's ends
 };
 
 template <typename T> __device__ __forceinline__ void store_as(T* p, float v) { Elem<T>::store(p, 0, v); }
@@ -85,58 +87,82 @@ __global__ __launch_bounds__(256) void logmel_k(const float* __restrict__ wav, c
         }
         return;
     }
-    // ---- per workgroup: twiddles, window, mel points, band weights
+    // a frame's samples, two a lane and register: the first frame's on their way during the set-up, every next frame's
+    // during the frame before
+    const float* wb = wav + (size_t)b * d.Nmax;
+    constexpr int MOST = 8;  // nfft <= 1024
+    float2 pre[MOST];
+    auto fetch = [&](int t) {
+        const float* seg = wb + (size_t)t * d.hop;
+#pragma unroll
+        for (int q = 0; q < MOST; ++q) {
+            const int e = 2 * (lane + 64 * q);
+            pre[q] = make_float2(e < d.win ? seg[e] : 0.f, e + 1 < d.win ? seg[e + 1] : 0.f);
+        }
+    };
+    if (t0 + wave < T) fetch(t0 + wave);
+    // ---- per workgroup: twiddles, window, mel points, band weights.  It lasts about as long as two frames' passes, all
+    // of it latency, so every part is spread over the threads: the points (a double-precision power each) start from the
+    // last thread, the table entries from the first.  (8 x 1500 frames: 23.5 -> 22.3 us with this and the early fetch.)
+    for (int i = 255 - tid; i < d.F + 2; i += 256) {
+        const double m = d.mlo + (d.mhi - d.mlo) * (double)i / (double)(d.F + 1);
+        pts[i] = (float)(700.0 * (pow(10.0, m / 2595.0) - 1.0));
+    }
     for (int k = tid; k <= 3 * N / 4; k += 256) {
         float s, c;
         sincospif(2.f * (float)k / (float)N, &s, &c);  // the argument is an exact binary fraction
         tw[k] = make_float2(c, -s);
     }
     for (int i = tid; i < d.win; i += 256) window[i] = 0.54f - 0.46f * cospif(2.f * (float)i / (float)(d.win - 1));
-    for (int i = tid; i < d.F + 2; i += 256) {
-        const double mlo = 2595.0 * log10(1.0 + (double)d.fmin / 700.0), mhi = 2595.0 * log10(1.0 + (double)d.fmax / 700.0);
-        const double m = mlo + (mhi - mlo) * (double)i / (double)(d.F + 1);
-        pts[i] = (float)(700.0 * (pow(10.0, m / 2595.0) - 1.0));
-    }
     __syncthreads();
     const float bin_hz = (float)d.sr / (float)N;
-    for (int f = tid; f < d.F; f += 256) {  // bins of a band: a superset of those with a positive weight
-        int k0 = (int)(pts[f] / bin_hz), k1 = (int)(pts[f + 2] / bin_hz) + 1;
+    // bins of a band: a superset of those with a positive weight; thread f takes band f (F <= 255) and the start of its
+    // weights is the sum of the counts before it
+    int cnt_f = 0;
+    if (tid < d.F) {
+        int k0 = (int)(pts[tid] / bin_hz), k1 = (int)(pts[tid + 2] / bin_hz) + 1;
         k0 = k0 < 0 ? 0 : k0;
         k1 = k1 > M ? M : k1;
-        bk0[f] = k0;
-        boff[f + 1] = k1 - k0 + 1;  // the count, for now
+        bk0[tid] = k0;
+        cnt_f = k1 - k0 + 1;
     }
+    int sum = cnt_f;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(sum, o, 64);
+        if (lane >= o) sum += v;
+    }
+    __shared__ int wave_sum[4];
+    if (lane == 63) wave_sum[wave] = sum;
     __syncthreads();
-    int my_off[1];
-    my_off[0] = 0;
-    if (tid <= d.F)                  // start of band tid's weights = sum of the counts before it (F <= 256: one band per thread)
-        for (int g = 0; g < tid; ++g) my_off[0] += boff[g + 1];
+    for (int q = 0; q < wave; ++q) sum += wave_sum[q];
+    if (tid < d.F) boff[tid + 1] = sum;
+    if (tid == 0) boff[0] = 0;
     __syncthreads();
-    if (tid <= d.F) boff[tid] = my_off[0];
-    __syncthreads();
-    for (int f = tid; f < d.F; f += 256) {
+    const int share = 256 / d.F;  // threads per band
+    for (int f = tid / share, i0 = tid % share; f < d.F; f += 256) {
         const float lo = pts[f], ce = pts[f + 1], hi = pts[f + 2];
         const float ru = 1.f / (ce - lo), rd = 1.f / (hi - ce);
         const int k0 = bk0[f], cnt = boff[f + 1] - boff[f];
-        for (int i = 0; i < cnt; ++i) {
+        for (int i = i0; i < cnt; i += share) {
             const float fr = (float)(k0 + i) * bin_hz;
             bw[boff[f] + i] = fmaxf(0.f, fminf((fr - lo) * ru, (hi - fr) * rd));
         }
     }
     __syncthreads();
 
-    const float* wb = wav + (size_t)b * d.Nmax;
     for (int t = t0 + wave; t < t0 + d.fpw && t < d.Tmax; t += 4) {
         TO* out = fb + (size_t)t * d.F;
         if (t >= T) {
             for (int f = lane; f < d.F; f += 64) store_as(out + f, 0.f);
             continue;
         }
-        const float* seg = wb + (size_t)t * d.hop;
-        for (int i = lane; i < M; i += 64) {
-            const int e = 2 * i;
-            x[i] = make_float2(e < d.win ? seg[e] * window[e] : 0.f, e + 1 < d.win ? seg[e + 1] * window[e + 1] : 0.f);
+#pragma unroll
+        for (int q = 0; q < MOST; ++q) {
+            const int i = lane + 64 * q, e = 2 * i;
+            if (i < M) x[i] = make_float2(e < d.win ? pre[q].x * window[e] : 0.f, e + 1 < d.win ? pre[q].y * window[e + 1] : 0.f);
         }
+        if (t + 4 < t0 + d.fpw && t + 4 < T) fetch(t + 4);
         __builtin_amdgcn_wave_barrier();
         // Stockham radix-4, decimation in frequency, on M points: at a pass the sequence length is
         // len = M / s; butterfly (p, q), p < len/4, q < s, takes src[q + s (p + r len/4)], r = 0..3,
@@ -185,6 +211,7 @@ __global__ __launch_bounds__(256) void logmel_k(const float* __restrict__ wav, c
         for (int f = lane; f < d.F; f += 64) {
             const int k0 = bk0[f], o0 = boff[f], cnt = boff[f + 1] - o0;
             float acc = 0.f;
+#pragma unroll 8
             for (int i = 0; i < cnt; ++i) acc = fmaf(bw[o0 + i], power[k0 + i], acc);
             store_as(out + f, logf(fmaxf(acc, d.floor)));
         }
@@ -218,7 +245,8 @@ extern "C" int w2l_logmel_fwd(const float* wav, const int* wav_len, void* feat, 
     long long fpw = ((long long)B * Tmax + 999) / 1000;
     fpw = fpw < 4 ? 4 : (fpw > 256 ? 256 : fpw);
     fpw = (fpw + 3) / 4 * 4;
-    LogmelDims d{B, Nmax, Tmax, n_mels, sample_rate, win, hop, nfft, (int)fpw, fmin, fmax, floor};
+    LogmelDims d{B, Nmax, Tmax, n_mels, sample_rate, win, hop, nfft, (int)fpw, fmin, fmax, floor,
+                 2595.0 * std::log10(1.0 + (double)fmin / 700.0), 2595.0 * std::log10(1.0 + (double)fmax / 700.0)};
     const size_t lds = (size_t)logmel_lds(nfft, win, n_mels).total;
     hipStream_t st = (hipStream_t)stream;
     const dim3 grid((Tmax + (int)fpw - 1) / (int)fpw, B), block(256);
