@@ -193,7 +193,7 @@ int conv_wgrad_mfma(const ConvDesc& d, const void* x, const void* dy, float* dw,
 // Both gradients of a layer with a layer with GLU below it, in one launch (dy, x and the dy of the layer below in the
 // haloed layout, bf16).
 struct ConvBwdPlan {
-    bool ok = false;
+    bool ok = false, crowded = false;                          // crowded: it could be done, and two streams fill the chip better
     int dkind = 0, dparts = 1, dnx = 0, dper = 0;              // dparts > 1: planes of sums in dscratch, for finish_glu_bwd
     int wtile = 0, wper = 0, wsplits = 1, wnx = 0, w_first = 0;
     size_t wscratch = 0;

@@ -1953,6 +1953,7 @@ ConvBwdPlan conv_bwd_plan(const ConvDesc& d)
     // CUs that wait for the last tiles are what the next layer's launch could use on two streams: beyond what those cost
     // (8 x 750 frames, k = 11, 768 -> 1536: 256 + 204 workgroups of 130 us each, 262 us a layer on two streams, 273 in one)
     p.ok = best >= 0 && spread <= 18;
+    p.crowded = best >= 0 && !p.ok;
     return p;
 }
 

@@ -65,6 +65,7 @@ struct Plan {
     size_t cls = 0;        // operands of the last layer's data gradient prepared for the MFMA kernels (its dy is fp32)
     DgradPrep cls_prep;
     std::vector<ConvBwdPlan> bwd;  // per layer: both gradients in one launch, where that can be done
+    bool crowded = false;
     int status = W2L_OK;
 };
 
@@ -89,8 +90,8 @@ ConvDesc layer_bwd_desc(const Plan& p, const w2l_layer* L, int B, int i)
 size_t planes_bytes(int parts, size_t values) { return parts > 1 ? parts * values * 4 : 0; }
 
 // Layer 0 has no data gradient to run beside, and the weight gradient of narrow outputs is shorter than the events that
-// a second stream takes: these stay on the caller's stream.
-bool main_wgrad(const w2l_layer& l, int i) { return i == 0 || l.cout <= 32; }
+// a second stream takes: these stay on the caller's stream (unless the second stream is there anyway).
+bool main_wgrad(const Plan& p, const w2l_layer& l, int i) { return i == 0 || (l.cout <= 32 && !p.crowded); }
 bool same_layer(const w2l_layer& a, const w2l_layer& b) { return a.k == b.k && a.stride == b.stride && a.cin == b.cin && a.cout == b.cout && a.glu == b.glu; }
 
 Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int criterion)
@@ -145,13 +146,20 @@ Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int
         const bool as_above = i > 1 && same_layer(l, L[i - 1]) && L[i - 2].glu && p.Tin[i] == p.Tin[i - 1];
         p.bwd.push_back(as_above ? p.bwd.back()
                         : i > 0 && i < n - 1 && l.glu && L[i - 1].glu && dtype == W2L_BF16 ? conv_bwd_plan(bd) : ConvBwdPlan{});
-        // scratch of the weight gradients: on the caller's stream, or on the helper stream beside it
-        if (p.bwd.back().ok) p.conv0_bytes = max_of(p.conv0_bytes, p.bwd.back().wscratch);
-        else if (main_wgrad(l, i)) p.conv0_bytes = max_of(p.conv0_bytes, conv_wgrad_scratch_bytes(i ? bd : dense_desc(B, T, l.cin, l.cout, l.k, l.stride), dtype, i == n - 1 ? W2L_F32 : dtype));
-        else p.conv_bytes = max_of(p.conv_bytes, conv_wgrad_scratch_bytes(bd, dtype, i == n - 1 ? W2L_F32 : dtype));
+        p.crowded = p.crowded || p.bwd.back().crowded;
         // a data gradient of two workgroups per tile: its tickets and the sums of both
         if (i > 0 && L[i - 1].glu) p.dgs_bytes = max_of(p.dgs_bytes, conv_dgrad_pair_bytes(bd));
         t = to;
+    }
+    // A network with layers whose gradients fill the chip from two streams keeps those streams for all of them, and cuts no
+    // bf16 weight gradient: their workgroups take turns with the other stream's as it is (105M step, 8 x 1500 frames: 3467 us, mixed 3.49 ms on the same scale).
+    if (p.crowded) p.bwd.assign(n, ConvBwdPlan{});
+    // scratch of the weight gradients: on the caller's stream, or on the helper stream beside it
+    for (int i = 0; i < n; ++i) {
+        const w2l_layer& l = L[i];
+        const ConvDesc d = i ? layer_bwd_desc(p, L, B, i) : dense_desc(B, T, l.cin, l.cout, l.k, l.stride);
+        size_t& bytes = p.bwd[i].ok || main_wgrad(p, l, i) ? p.conv0_bytes : p.conv_bytes;
+        bytes = max_of(bytes, p.bwd[i].ok ? p.bwd[i].wscratch : conv_wgrad_scratch_bytes(d, dtype, i == n - 1 ? W2L_F32 : dtype));
     }
     p.Tlast = t;
     p.C = L[n - 1].cout;
@@ -373,7 +381,7 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
         }
         // layer 0 has no data gradient: its weight gradient takes the main stream, next to the
         // helper stream's last launch, instead of queueing behind it
-        const bool on_main = main_wgrad(l, i), on_side = side && !on_main;
+        const bool on_main = main_wgrad(p, l, i), on_side = side && !on_main;
         hipStream_t wst = on_side ? side->stream : st;
         if (on_side) {
             if (!hip_ok(hipEventRecord(side->ready[i], st)) || !hip_ok(hipStreamWaitEvent(wst, side->ready[i], 0)))
@@ -397,7 +405,7 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
         // on the main stream, which has the shorter chain
         const bool fused_dbias = dbiases[i] && conv_wgrad_fuses_dbias(d, dtype, dy_dt);
         rc = conv_wgrad(d, xin, dy, dweights[i], (fused_dbias || !side) ? dbiases[i] : nullptr, dtype, dy_dt, 0,
-                        ws + (on_main ? p.conv0 : p.conv), on_main ? p.conv0_bytes : p.conv_bytes, wst);
+                        ws + (on_main ? p.conv0 : p.conv), p.crowded && dy_dt == W2L_BF16 ? 0 : on_main ? p.conv0_bytes : p.conv_bytes, wst);
         if (rc) return rc;
         if (on_side) {
             if (!hip_ok(hipEventRecord(side->done[i], wst))) return W2L_ERR_LAUNCH;
