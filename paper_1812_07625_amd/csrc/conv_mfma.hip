@@ -1482,7 +1482,7 @@ bool slab_ok(const ConvDesc& d, int bm, int srows, int C, int frames, int pitch,
 // A problem whose tiles do not fill the 256 CUs (each holds one workgroup of these kernels) lasts as long as one tile's
 // reduction whatever the idle CUs could do, so the reduction is cut into runs of panels: a workgroup per tile and run,
 // a plane of fp32 sums per run, and the pass that reads the result next adds the planes up in order (finish_*).
-// Times in us, on which the choice of tile and cut rests, measured on 8 x 128 .. 16 x 1600 frames, 64 .. 2048 channels:
+// Times in us, on which the choice of tile and cut rests, from kernel traces of 1000 .. 12800 frames, 64 .. 2048 channels:
 //   64 steps of the reduction on one CU 0.55 (128 x 128), 0.80 (256 x 128), 0.88 (192 x 192), 1.50 (256 x 256);
 //   a workgroup's first panels and its way out 4; the sums' way to memory and back 4 TB/s;
 //   a finishing pass of its own with its launch 6, where a GLU pass does it about as long as that takes anyway.

@@ -152,7 +152,7 @@ Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int
         t = to;
     }
     // A network with layers whose gradients fill the chip from two streams keeps those streams for all of them, and cuts no
-    // bf16 weight gradient: their workgroups take turns with the other stream's as it is (105M step, 8 x 1500 frames: 3467 us, mixed 3.49 ms on the same scale).
+    // bf16 weight gradient: their workgroups take turns with the other stream's as it is (105M step, 8 x 1500 frames, mixed with shared launches and cut: 1.3 % slower).
     if (p.crowded) p.bwd.assign(n, ConvBwdPlan{});
     // scratch of the weight gradients: on the caller's stream, or on the helper stream beside it
     for (int i = 0; i < n; ++i) {
