@@ -106,6 +106,15 @@ int w2l_conv1d_bwd_weight(const void *x, const void *dy, float *dw, float *dbias
                           int dtype, int dy_dtype, int accumulate,
                           void *workspace, size_t ws_bytes, void *stream);
 
+/* Host-only query: which kernel a convolution pass (0: fwd, 1: bwd_data, 2: bwd_weight) of these sizes launches, with
+ * all tensors of `dtype`, with the queried workspace or (fwd, bwd_data) without one.  form: 0 the bf16 matrix kernels;
+ * of the kernels for any shape and type, 1: operands on their way through registers, 2: fp32 operands copied into LDS
+ * in 16-byte chunks, each checked against the window's edges, 3: the same unchecked, from operands with a zero halo;
+ * 4: the weight gradient of narrow outputs (Cout <= 32).  splits: runs of the reduction that workgroups of their own
+ * sum up (forms 1 to 4; 0 for form 0).  For tests and tuning; launches nothing.  Errors as the pass itself. */
+int w2l_conv1d_launch_config(int pass, int B, int T, int Cin, int Cout, int k, int stride, int dtype,
+                             int with_workspace, int *form, int *splits);
+
 /* ---- gated linear unit (the gated convnet of Sec. 4.1) -----------------------------
  * y: [rows,Cout], Cout even.  Value half a = y[:, :Cout/2], gate half g = y[:, Cout/2:].
  *   fwd:  h = a * sigmoid(g)                          h: [rows,Cout/2]

@@ -136,6 +136,9 @@ bool stage_f32(int k, int s, int dt) { return dt == W2L_F32 && k > 1 && (k - 1) 
 bool stage_fwd_f32(int Cin, int k, int s, int dt) { return stage_f32(k, s, dt) && k * Cin % 32 == 0 && Cin % 4 == 0; }
 bool stage_dgrad_f32(int Cin, int Cout, int k, int s, int dt) { return stage_f32(k, s, dt) && Cout % 32 == 0 && Cin % 4 == 0; }
 bool stage_wgrad_f32(int Cin, int Cout, int k, int s, int dt) { return stage_f32(k, s, dt) && Cin % 4 == 0 && Cout % 4 == 0 && Cout > 32; }
+// the geometry that staged operands have
+void staged_x(ConvDesc& d) { d.x_pitch = d.T + 2 * ABI_HALO; d.x_halo = ABI_HALO; d.slack = ABI_SLACK; }
+void staged_y(ConvDesc& d) { d.y_pitch = d.Tp + 2 * ABI_HALO; d.y_halo = ABI_HALO; d.slack = ABI_SLACK; }
 // a strided layer whose stride folds into the channels (fold_stride) is staged as the stride-1 layer it folds to
 bool stage_wgrad_folded(int B, int T, int Cin, int Cout, int k, int s, int dt, ConvDesc& f)
 {
@@ -171,9 +174,7 @@ extern "C" int w2l_conv1d_fwd(const void* x, const void* w, const float* bias, v
         const int C = f32 ? 2 * Cin : Cin;
         rc = pad_layout_bf16(x, workspace, B, T, C, T + 2 * ABI_HALO, ABI_HALO, ABI_SLACK_ZERO, st);
         if (rc) return rc;
-        d.x_pitch = T + 2 * ABI_HALO;
-        d.x_halo = ABI_HALO;
-        d.slack = ABI_SLACK;
+        staged_x(d);
         const size_t copy = haloed_bytes(B, T, C);
         return conv_fwd(d, workspace, w, bias, y, dtype, y_dtype, st, static_cast<unsigned char*>(workspace) + copy, need - copy);
     }
@@ -263,9 +264,7 @@ extern "C" int w2l_conv1d_bwd_data(const void* dy, const void* w, void* dx, int 
             if (!stage_dgrad_f32(Cin, Cout, k, stride, dtype)) return conv_dgrad(d, dy, w, dx, dtype, dy_dtype, st, workspace, need);
             rc = pad_layout_bf16(dy, workspace, B, T, 2 * Cout, T + 2 * ABI_HALO, ABI_HALO, ABI_SLACK_ZERO, st);
             if (rc) return rc;
-            d.y_pitch = T + 2 * ABI_HALO;
-            d.y_halo = ABI_HALO;
-            d.slack = ABI_SLACK;
+            staged_y(d);
             const size_t copy = haloed_bytes(B, T, 2 * Cout);
             return conv_dgrad(d, workspace, w, dx, dtype, dy_dtype, st, static_cast<unsigned char*>(workspace) + copy, need - copy);
         }
@@ -308,9 +307,8 @@ extern "C" int w2l_conv1d_bwd_weight(const void* x, const void* dy, float* dw, f
         unsigned char* dyp = xp + haloed_bytes(B, f.T, f.Cin);
         rc = pad_layout2_bf16(x, xp, f.Cin, dy, dyp, Cout, B, f.T, f.T + 2 * ABI_HALO, ABI_HALO, ABI_SLACK_ZERO, st);
         if (rc) return rc;
-        f.x_pitch = f.y_pitch = f.T + 2 * ABI_HALO;
-        f.x_halo = f.y_halo = ABI_HALO;
-        f.slack = ABI_SLACK;
+        staged_x(f);
+        staged_y(f);
         return conv_wgrad(f, xp, dyp, dw, dbias, dtype, dy_dtype, accumulate, workspace, scratch, st);
     }
     const bool f32 = stage_wgrad_f32(Cin, Cout, k, stride, dtype);
@@ -320,13 +318,41 @@ extern "C" int w2l_conv1d_bwd_weight(const void* x, const void* dy, float* dw, f
         unsigned char* dyp = xp + haloed_bytes(B, T, e * Cin);
         rc = pad_layout2_bf16(x, xp, e * Cin, dy, dyp, e * Cout, B, T, T + 2 * ABI_HALO, ABI_HALO, ABI_SLACK_ZERO, st);
         if (rc) return rc;
-        d.x_pitch = d.y_pitch = T + 2 * ABI_HALO;
-        d.x_halo = d.y_halo = ABI_HALO;
-        d.slack = ABI_SLACK;
+        staged_x(d);
+        staged_y(d);
         x = xp;
         dy = dyp;
     }
     return conv_wgrad(d, x, dy, dw, dbias, dtype, dy_dtype, accumulate, workspace, scratch, st);
+}
+
+extern "C" int w2l_conv1d_launch_config(int pass, int B, int T, int Cin, int Cout, int k, int stride, int dtype, int with_workspace, int* form,
+                                        int* splits)
+{
+    if (!form || !splits) return W2L_ERR_NULL;
+    const int rc = check_conv_shape(B, T, Cin, Cout, k, stride);
+    if (rc) return rc;
+    if (!valid_dtype(dtype)) return W2L_ERR_DTYPE;
+    ConvDesc d = dense_desc(B, T, Cin, Cout, k, stride);
+    *form = CONV_BF16;
+    *splits = 0;
+    if (pass == 0) {
+        if (!conv_fwd_is_generic(d, dtype)) return W2L_OK;
+        const size_t scratch = with_workspace ? conv_fwd_scratch(d, dtype) : 0;
+        if (with_workspace && stage_fwd_f32(Cin, k, stride, dtype)) staged_x(d);
+        return conv_fwd_generic_form(d, dtype, scratch, form, splits);
+    }
+    if (pass == 1) {
+        if ((with_workspace && dgrad_prep(B, T, Cin, Cout, k, stride, dtype).ok) || !conv_dgrad_is_generic(d, dtype, dtype)) return W2L_OK;
+        const size_t scratch = with_workspace ? conv_dgrad_scratch(d, dtype, dtype) : 0;
+        if (with_workspace && stage_dgrad_f32(Cin, Cout, k, stride, dtype)) staged_y(d);
+        return conv_dgrad_generic_form(d, dtype, scratch, form, splits);
+    }
+    if (pass != 2) return W2L_ERR_SHAPE;
+    if (Cout <= 32) { *form = CONV_NARROW; *splits = SKINNY_CHUNKS; return W2L_OK; }
+    if (!wgrad_is_generic(d, dtype, dtype)) return W2L_OK;
+    if (stage_wgrad_f32(Cin, Cout, k, stride, dtype)) { staged_x(d); staged_y(d); }
+    return conv_wgrad_generic_form(d, dtype, form, splits);
 }
 
 // ---- measurement aid: what the matrix pipe sustains with nothing else going on -----------

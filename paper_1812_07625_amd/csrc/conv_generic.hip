@@ -28,12 +28,25 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x4a __attribute__((ext_vector_type(4)));
 
+constexpr int TILE = 64, PANEL = 32;  // a workgroup's outputs in either direction; steps of the reduction per panel
+
 // ---- operands ------------------------------------------------------------------------
 // A line is a run of memory: element c of line i is base[off + c], real where lo <= c < hi and zero elsewhere.
 // K_LINES: the lines are the rows (columns) of the output and c runs along the reduction; otherwise the lines are
 // the steps of the reduction and c runs along the output.
 struct Line { long long off; int lo, hi; };
 __device__ __forceinline__ Line no_line() { return Line{0, 0, 0}; }
+
+// What an unpredicated panel (DmaPanel, FAST) needs of an operand's lines beyond whole chunks: a lane keeps its offset
+// from the first line of its tile or panel in 32 bits of bytes, so they have to lie within 2 GB of each other.
+inline bool near_lines(long long elements) { return elements < (1LL << 29) - TILE; }
+// Frames between the first and the last of a tile's rows at most; row r: frame step * (r % count) of utterance r / count
+inline long long row_reach(int count, int step, int pitch)
+{
+    const long long cross = (TILE - 2LL + count) / count, gap = pitch - (long long)count * step;  // utterance ends met, and what each adds
+    const long long a = (TILE - 1LL) * step + cross * (gap > 0 ? gap : 0), b = cross * pitch + (count - 1LL) * step;
+    return a < b ? a : b;
+}
 
 template <typename T>
 struct XWindow {  // fwd A: m = (b,t') -> x[b, s t' - p ..], r = (j,ci)
@@ -42,7 +55,7 @@ struct XWindow {  // fwd A: m = (b,t') -> x[b, s t' - p ..], r = (j,ci)
     const T* base; int M, T_, Tp, Cin, k, s, p, pitch, halo;
     // every line starts and ends on a 16-byte chunk of fp32
     bool chunks() const { return aligned16(base) && Cin % 4 == 0; }
-    bool fast() const { return chunks() && k * Cin % 32 == 0 && (p == 0 || halo >= p); }
+    bool fast() const { return chunks() && k * Cin % 32 == 0 && (p == 0 || halo >= p) && near_lines(row_reach(Tp, s, pitch) * Cin); }
     __device__ __forceinline__ long long fast_line(int m) const { return line(m < M ? m : M - 1).off; }
     __device__ __forceinline__ Line line(int m) const
     {
@@ -57,7 +70,7 @@ struct WRows {  // fwd B: n = co -> w[co], r = (j,ci)
     typedef T type;
     const T* base; int N, KC;
     bool chunks() const { return aligned16(base) && KC % 4 == 0; }
-    bool fast() const { return chunks() && KC % 32 == 0; }
+    bool fast() const { return chunks() && KC % 32 == 0 && near_lines((TILE - 1LL) * KC); }
     __device__ __forceinline__ long long fast_line(int n) const { return (long long)(n < N ? n : N - 1) * KC; }
     __device__ __forceinline__ Line line(int n) const { return n < N ? Line{(long long)n * KC, 0, KC} : no_line(); }
 };
@@ -79,7 +92,7 @@ struct DyWindow {  // dgrad A: m = (b, frame of the phase) -> its dy frames, r =
     typedef T type;
     const T* base; int B, Tp, Cout, s, p, pitch, halo; Phase q;
     bool chunks() const { return aligned16(base) && Cout % 4 == 0; }
-    bool fast() const { return chunks() && s == 1 && Cout % 32 == 0 && (p == 0 || halo >= p); }
+    bool fast() const { return chunks() && s == 1 && Cout % 32 == 0 && (p == 0 || halo >= p) && near_lines(row_reach(q.count, 1, pitch) * Cout); }
     __device__ __forceinline__ long long fast_line(int m) const { return line(m < B * q.count ? m : B * q.count - 1).off; }
     __device__ __forceinline__ Line line(int m) const
     {
@@ -96,7 +109,8 @@ struct WCols {  // dgrad B: r = (q,co) -> w[co, tap], n = ci
     const T* base; int Cin, Cout, k, s; Phase q;
     // every line starts and ends on a 16-byte chunk of fp32
     bool chunks() const { return aligned16(base) && Cin % 4 == 0; }
-    bool fast() const { return chunks() && s == 1 && Cout % 32 == 0; }  // the 32 lines of a panel lie in one tap
+    // (the 32 lines of a panel lie in one tap)
+    bool fast() const { return chunks() && s == 1 && Cout % 32 == 0 && near_lines((PANEL - 1LL) * k * Cin); }
     __device__ __forceinline__ long long fast_base(int r) const { return line(r).off; }
     __device__ __forceinline__ int fast_pitch() const { return k * Cin; }
     __device__ __forceinline__ int width() const { return Cin; }
@@ -112,7 +126,9 @@ struct DyT {  // wgrad A: r = (b,t') -> dy[b,t'], m = co
     typedef T type;
     const T* base; int Tp, Cout, pitch, halo;
     bool chunks() const { return aligned16(base) && Cout % 4 == 0; }
-    // (the walk of wgrad_t through the frames of a haloed layout)
+    // (the walk of wgrad_t through the frames of a haloed layout; a grid holds fewer than 2^22 rows of dw, so these lines
+    // are near)
+    bool fast() const { return chunks(); }
     __device__ __forceinline__ long long fast_base(int r) const { return (long long)(halo + r) * Cout; }
     __device__ __forceinline__ int fast_pitch() const { return Cout; }
     __device__ __forceinline__ int width() const { return Cout; }
@@ -129,6 +145,7 @@ struct XShift {  // wgrad B: r = (b,t') -> x[b, s t' - p ..], n = (j,ci)
     const T* base; int T_, Tp, Cin, k, s, p, pitch, halo;
     // every line starts and ends on a 16-byte chunk of fp32
     bool chunks() const { return aligned16(base) && Cin % 4 == 0; }
+    bool fast() const { return chunks() && near_lines((PANEL - 1LL) * Cin); }
     __device__ __forceinline__ long long fast_base(int r) const { return (long long)(halo - p + r) * Cin; }
     __device__ __forceinline__ int fast_pitch() const { return Cin; }
     __device__ __forceinline__ int width() const { return k * Cin; }
@@ -190,8 +207,6 @@ __device__ __forceinline__ void load4(const T* base, const Line& l, int c, float
         for (int e = 0; e < 4; ++e) v[e] = (c + e >= l.lo && c + e < l.hi) ? Elem<T>::load(q, e) : 0.f;
     }
 }
-
-constexpr int TILE = 64, PANEL = 32;  // a workgroup's outputs in either direction; steps of the reduction per panel
 
 // One operand's share of a panel: W rows of the output by BK steps of the reduction.
 template <class OP, int W, int BK>
@@ -625,15 +640,21 @@ AnyPlan any_plan(long long M, long long N, long long R, size_t budget, double fi
 
 template <class OA, class OB, class EP>
 int launch_any(const AnyPlan& pl, OA oa, OB ob, EP ep, long long M, long long N, long long R, hipStream_t st, float* colsum = nullptr,
-               int colsum_acc = 0, bool fast = false)
+               int colsum_acc = 0, bool fast = false, int* form = nullptr)
 {
     const long long gy = (M + TILE - 1) / TILE, gx = (N + TILE - 1) / TILE;
     if (M > 2147483647LL || R > 2147483647LL - 4096 || gy > 65535 || gx > 2147483647LL) return W2L_ERR_SHAPE;
     if (M <= 0) return W2L_OK;
+    constexpr bool f32 = std::is_same<typename OA::type, float>::value && std::is_same<typename OB::type, float>::value;
+    const bool chunks = f32 && oa.chunks() && ob.chunks();
+    if (form) {  // asked which kernel it is (w2l_conv1d_launch_config)
+        *form = !chunks ? CONV_REGISTERS : fast ? CONV_PLAIN : CONV_CHUNKS;
+        return W2L_OK;
+    }
     const dim3 g((unsigned)gx, (unsigned)gy, (unsigned)pl.splits);
 #define W2L_ANY(KERN) hipLaunchKernelGGL(KERN, g, dim3(256), 0, st, oa, ob, ep, (int)M, (int)N, (int)R, pl.per, pl.splits, colsum, colsum_acc)
-    if constexpr (std::is_same<typename OA::type, float>::value && std::is_same<typename OB::type, float>::value) {
-        if (oa.chunks() && ob.chunks()) {
+    if constexpr (f32) {
+        if (chunks) {
             if (fast) W2L_ANY((gemm_f32_k<OA, OB, EP, true>));
             else W2L_ANY((gemm_f32_k<OA, OB, EP, false>));
             return launch_status();
@@ -652,30 +673,31 @@ bool wgrad_walks(const ConvDesc& d)
 
 template <typename TI, typename TO>
 int fwd_t(const ConvDesc& d, const AnyPlan& pl, const void* x, const void* w, const float* bias, TO* y, int pitch, int halo,
-          long long plane, hipStream_t st)
+          long long plane, hipStream_t st, int* form = nullptr)
 {
     const long long M = (long long)d.B * d.Tp;
     XWindow<TI> a{(const TI*)x, (int)M, d.T, d.Tp, d.Cin, d.k, d.s, d.p, d.x_pitch, d.x_halo};
     WRows<TI> b{(const TI*)w, d.Cout, d.k * d.Cin};
     StoreRows<TO> ep{y, bias, d.Cout, d.Tp, 0, 1, pitch, halo, plane};
-    return launch_any(pl, a, b, ep, M, d.Cout, (long long)d.k * d.Cin, st, nullptr, 0, a.fast() && b.fast());
+    return launch_any(pl, a, b, ep, M, d.Cout, (long long)d.k * d.Cin, st, nullptr, 0, a.fast() && b.fast(), form);
 }
 template <typename TW, typename TDY, typename TO>
-int dgrad_t(const ConvDesc& d, const AnyPlan& pl, const void* dy, const void* w, TO* dx, int pitch, int halo, long long plane, hipStream_t st)
+int dgrad_t(const ConvDesc& d, const AnyPlan& pl, const void* dy, const void* w, TO* dx, int pitch, int halo, long long plane, hipStream_t st,
+            int* form = nullptr)
 {
     for (int ph = 0; ph < d.s; ++ph) {
         const Phase q = phase_of(ph, d.T, d.k, d.s, d.p);
         DyWindow<TDY> a{(const TDY*)dy, d.B, d.Tp, d.Cout, d.s, d.p, d.y_pitch, d.y_halo, q};
         WCols<TW> b{(const TW*)w, d.Cin, d.Cout, d.k, d.s, q};
         StoreRows<TO> ep{dx, nullptr, d.Cin, q.count, q.first, d.s, pitch, halo, plane};
-        const int rc = launch_any(pl, a, b, ep, (long long)d.B * q.count, d.Cin, (long long)q.taps * d.Cout, st, nullptr, 0, a.fast() && b.fast());
-        if (rc) return rc;
+        const int rc = launch_any(pl, a, b, ep, (long long)d.B * q.count, d.Cin, (long long)q.taps * d.Cout, st, nullptr, 0, a.fast() && b.fast(), form);
+        if (rc || form) return rc;
     }
     return W2L_OK;
 }
 template <typename TX, typename TDY>
 int wgrad_t(const ConvDesc& d, const AnyPlan& pl, const void* x, const void* dy, float* dw, float* dbias, int accumulate, long long plane,
-            hipStream_t st)
+            hipStream_t st, int* form = nullptr)
 {
     DyT<TDY> a{(const TDY*)dy, d.Tp, d.Cout, d.y_pitch, d.y_halo};
     XShift<TX> b{(const TX*)x, d.T, d.Tp, d.Cin, d.k, d.s, d.p, d.x_pitch, d.x_halo};
@@ -684,10 +706,10 @@ int wgrad_t(const ConvDesc& d, const AnyPlan& pl, const void* x, const void* dy,
     // frames, and in the slack that the last panel reads into
     const long long walk = (long long)(d.B - 1) * d.y_pitch + d.Tp;
     // (only the kernel that launch_any takes for fp32 operands in whole chunks walks; the others count real frames)
-    const bool fast = std::is_same<TX, float>::value && std::is_same<TDY, float>::value && a.chunks() && b.chunks() && wgrad_walks(d) &&
+    const bool fast = std::is_same<TX, float>::value && std::is_same<TDY, float>::value && a.fast() && b.fast() && wgrad_walks(d) &&
                       walk <= (long long)pl.per * pl.splits;
     const long long R = fast ? walk : (long long)d.B * d.Tp;
-    return launch_any(pl, a, b, ep, d.Cout, (long long)d.k * d.Cin, R, st, dbias, accumulate, fast);
+    return launch_any(pl, a, b, ep, d.Cout, (long long)d.k * d.Cin, R, st, dbias, accumulate, fast, form);
 }
 
 // ---- weight gradient for narrow outputs (Cout <= 32, e.g. the 29 grapheme classes) ---------
@@ -974,6 +996,31 @@ int conv_wgrad_generic(const ConvDesc& d, const void* x, const void* dy, float* 
     if (rc || !split) return rc;
     return finish_sums(part, pl.splits, plane, dw, bout, d.Cout, dbias, accumulate, st);
 }
+// Which kernel the calls below would take and into how many runs the reduction goes (operands aligned; nothing is launched)
+int conv_fwd_generic_form(const ConvDesc& d, int dt, size_t scratch_bytes, int* form, int* splits)
+{
+    const AnyPlan pl = fwd_plan(d, scratch_bytes < MAX_PARTIALS ? scratch_bytes : MAX_PARTIALS, FINISH_OWN);
+    *splits = pl.splits;
+    float* const y = nullptr;
+    if (dt == W2L_F32) return fwd_t<float, float>(d, pl, nullptr, nullptr, nullptr, y, d.y_pitch, d.y_halo, 0, nullptr, form);
+    return fwd_t<bf16_t, float>(d, pl, nullptr, nullptr, nullptr, y, d.y_pitch, d.y_halo, 0, nullptr, form);
+}
+int conv_dgrad_generic_form(const ConvDesc& d, int dt, size_t scratch_bytes, int* form, int* splits)
+{
+    const AnyPlan pl = dgrad_plan(d, scratch_bytes < MAX_PARTIALS ? scratch_bytes : MAX_PARTIALS, FINISH_OWN);
+    *splits = pl.splits;
+    float* const dx = nullptr;
+    if (dt == W2L_F32) return dgrad_t<float, float, float>(d, pl, nullptr, nullptr, dx, d.x_pitch, d.x_halo, 0, nullptr, form);
+    return dgrad_t<bf16_t, bf16_t, float>(d, pl, nullptr, nullptr, dx, d.x_pitch, d.x_halo, 0, nullptr, form);
+}
+int conv_wgrad_generic_form(const ConvDesc& d, int dt, int* form, int* splits)
+{
+    const AnyPlan pl = wgrad_plan(d, MAX_PARTIALS);
+    *splits = pl.splits;
+    if (dt == W2L_F32) return wgrad_t<float, float>(d, pl, nullptr, nullptr, nullptr, nullptr, 0, 0, nullptr, form);
+    return wgrad_t<bf16_t, bf16_t>(d, pl, nullptr, nullptr, nullptr, nullptr, 0, 0, nullptr, form);
+}
+
 size_t conv_wgrad_skinny_scratch(int Cin, int Cout, int k)
 {
     return Cout <= 32 ? round_up((size_t)SKINNY_CHUNKS * Cout * ((size_t)k * Cin + 1) * 4, 256) : 0;
