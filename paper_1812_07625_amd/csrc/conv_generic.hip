@@ -393,6 +393,9 @@ __global__ __launch_bounds__(256, 4) void gemm_any_k(OA oa, OB ob, EP ep, int M,
 // FAST: tensors in the haloed time layout (the train step's, and what the entry points stage).  Every window is then
 // plain memory: a lane's offset from the first line of its panel never changes and the loads cost no vector
 // instruction at all, which counts, because fp32 matrix instructions run on the vector units (the two do not overlap).
+// (The weight gradient then walks through the frames between two utterances as well: dy is zero there, and the x that
+// it would meet is taken for zero too -- in the panels that hold such frames -- or an infinite x near an utterance's
+// end would turn up as a NaN in taps that never see it.)
 __device__ __align__(16) const float g_zero_chunk[4] = {0.f, 0.f, 0.f, 0.f};
 typedef __attribute__((address_space(3))) unsigned char lds_byte;
 
@@ -533,6 +536,9 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
         if (i < PA::NI) pa.issue(oa, i, m0, r0, r_end, dst);
         else pb.issue(ob, i - PA::NI, n0, r0, r_end, dst + PA::FLOATS * 4);
     };
+    constexpr bool WALK = FAST && !PA::KL;  // the weight gradient
+    int walk0 = 0;                          // WALK: the panel's first frame, counted from its utterance's first one
+    if constexpr (WALK) walk0 = r_begin % oa.pitch;
     float fa[2][NA][4], fb[2][NB][4];
     if (steps > 0) {
 #pragma unroll
@@ -546,6 +552,8 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
     for (int st = 0; st < steps; ++st) {
         const float* cur = lds + (st & 1) * STAGE;
         const float* nxt = lds + ((st + 1) & 1) * STAGE;
+        bool between = false;  // some of the panel's frames lie behind an utterance
+        if constexpr (WALK) between = walk0 + BK > oa.Tp || r_begin + (st + 1) * BK > r_end;
 #pragma unroll
         for (int g = 0; g < GROUPS; ++g) {
             const int u = g & 1;
@@ -558,6 +566,19 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
             PA::template frags<NA>(src, wm, (g + 1) % GROUPS * 8, lane, fa[1 - u]);
             PB::template frags<NB>(src + PA::FLOATS, wn, (g + 1) % GROUPS * 8, lane, fb[1 - u]);
             __builtin_amdgcn_sched_barrier(0);
+            if constexpr (WALK) {
+                if (between) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int l = g * 8 + 4 * (lane >> 5) + q;
+                        int t = walk0 + l;
+                        while (t >= oa.pitch) t -= oa.pitch;
+                        const bool real = t < oa.Tp && r_begin + st * BK + l < r_end;
+#pragma unroll
+                        for (int j = 0; j < NB; ++j) fb[u][j][q] = real ? fb[u][j][q] : 0.f;
+                    }
+                }
+            }
 #pragma unroll
             for (int q = 0; q < 4; ++q)
 #pragma unroll
@@ -575,6 +596,10 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
 #pragma unroll
                 for (int i = 0; i < NA; ++i) asum[i] += (fa[u][i][0] + fa[u][i][1]) + (fa[u][i][2] + fa[u][i][3]);
             }
+        }
+        if constexpr (WALK) {
+            walk0 += BK;
+            while (walk0 >= oa.pitch) walk0 -= oa.pitch;
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing may land in LDS once it is used otherwise

@@ -73,6 +73,36 @@ def test_conv_any_edges(shape, dtype):
     _check(to_host(dw), dw_o, False, "dw without db")
 
 
+@pytest.mark.parametrize("shape", [(3, 50, 32, 64, 5, 1), (2, 75, 64, 64, 11, 1), (5, 3, 32, 64, 3, 1), (1, 401, 32, 64, 13, 1)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_fp32_weight_gradient_infinite_x(shape):
+    """An infinity in the first or last frame of an utterance reaches the taps whose sum contains that frame and no
+    others, although the kernel walks through the zero frames between utterances; a NaN likewise."""
+    import paper_1812_07625_amd as P
+    B, T, Cin, Cout, k, s = shape
+    assert P.w2l_conv1d_launch_config(2, B, T, Cin, Cout, k, s, P.W2L_F32)[0] == 3   # the kernel that walks
+    rng = np.random.default_rng(sum(shape) + 2)
+    x, dy = rng.standard_normal((B, T, Cin)).astype(np.float32), rng.standard_normal((B, T, Cout)).astype(np.float32)
+    x[0, T - 1, 3], x[B - 1, 0, 5], x[B - 1, T - 1, 7], x[0, 0, 9] = np.inf, -np.inf, np.nan, np.inf
+    p = (k - 1) // 2
+    dw_o = np.zeros((Cout, k, Cin))
+    with np.errstate(invalid="ignore"):
+        for j in range(k):               # frames t' whose window holds frame t' + j - p: nothing else is multiplied
+            lo, hi = max(0, p - j), min(T, T + p - j)
+            for c in range(Cin):
+                dw_o[:, j, c] = sum((dy[b, lo:hi].astype(np.float64) * x[b, lo + j - p:hi + j - p, c, None]).sum(0) for b in range(B))
+    ws = P.workspace(P.w2l_conv1d_bwd_weight_workspace_bytes(B, T, Cin, Cout, k, s, P.W2L_F32))
+    dw, db = P.w2l_conv1d_bwd_weight(to_dev(x), to_dev(dy), empty((Cout, k, Cin)), empty((Cout,)), s, False, ws)
+    got = to_host(dw)
+    assert np.isfinite(dw_o).any() and not np.isfinite(dw_o).all()
+    np.testing.assert_array_equal(np.isfinite(got), np.isfinite(dw_o))
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(dw_o))
+    np.testing.assert_array_equal(np.sign(got[np.isinf(got)]), np.sign(dw_o[np.isinf(dw_o)]))
+    fin = np.isfinite(dw_o)
+    _check(got[fin], dw_o[fin], False, "dw")
+    _check(to_host(db), dy.astype(np.float64).sum((0, 1)), False, "db")
+
+
 def test_fp32_train_step_split_and_ragged():
     """An fp32 network whose layers take every form of the kernels inside a step: a strided first layer over dense
     features, split reductions finished by the GLU passes, channel counts off the chunks."""
