@@ -644,17 +644,18 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
 // 2.18 ms, data gradient 2.69 against 2.38, weight gradient 3.06 against 2.45), four small workgroups on a CU
 // covering each other's barriers better than two large ones.
 struct AnyPlan { int splits, per; };
-AnyPlan any_plan(long long M, long long N, long long R, size_t budget, double finish_cycles)
+// values: of a plane; launches: one after the other, each of the M x N x R problem (the phases of a stride)
+AnyPlan any_plan(long long M, long long N, long long R, size_t budget, double finish_cycles, long long values, int launches = 1)
 {
     const long long tiles = ((M + TILE - 1) / TILE) * ((N + TILE - 1) / TILE), panels = (R + PANEL - 1) / PANEL;
     AnyPlan best{1, 0};
     double best_t = -1;
     for (int s = 1; s <= 16; ++s) {
         const long long per = (panels + s - 1) / s;
-        if (s > 1 && (per * (s - 1) >= panels || per < 2 || (size_t)s * M * N * 4 > budget)) continue;
+        if (s > 1 && (per * (s - 1) >= panels || per < 2 || (size_t)s * values * 4 > budget)) continue;
         const long long load = (tiles * s + 255) / 256;
-        double t = load * per * 1024.0 / (load > 2 ? 0.76 : load > 1 ? 0.72 : 0.67) + 12000;
-        if (s > 1) t += 8.0 * s * M * N / 2500 + finish_cycles;
+        double t = launches * (load * per * 1024.0 / (load > 2 ? 0.76 : load > 1 ? 0.72 : 0.67) + 12000);
+        if (s > 1) t += 8.0 * s * values / 2500 + finish_cycles;
         if (best_t < 0 || t < best_t) {
             best_t = t;
             best = AnyPlan{s, (int)(per * PANEL)};
@@ -919,16 +920,22 @@ __global__ void colsum_stage2(const float* part, float* dbias, int chunks, int C
 namespace {
 // a finishing launch of its own costs about 5 us; inside the train step it is the layer's GLU, launched in any case
 constexpr double FINISH_OWN = 12000, FINISH_FREE = 2000;
-AnyPlan fwd_plan(const ConvDesc& d, size_t budget, double fin) { return any_plan((long long)d.B * d.Tp, d.Cout, (long long)d.k * d.Cin, budget, fin); }
+AnyPlan fwd_plan(const ConvDesc& d, size_t budget, double fin)
+{
+    const long long M = (long long)d.B * d.Tp;
+    return any_plan(M, d.Cout, (long long)d.k * d.Cin, budget, fin, M * d.Cout);
+}
 AnyPlan dgrad_plan(const ConvDesc& d, size_t budget, double fin)
 {
-    // of a stride's phases, the one with the most taps (they are launched one after the other)
-    return any_plan((long long)d.B * ((d.T + d.s - 1) / d.s), d.Cin, (long long)((d.k + d.s - 1) / d.s) * d.Cout, budget, fin);
+    // of a stride's phases, the one with the most taps (they are launched one after the other); a plane takes all of them
+    return any_plan((long long)d.B * ((d.T + d.s - 1) / d.s), d.Cin, (long long)((d.k + d.s - 1) / d.s) * d.Cout, budget, fin,
+                    (long long)d.B * d.T * d.Cin, d.s);
 }
 AnyPlan wgrad_plan(const ConvDesc& d, size_t budget)
 {
     // the reduction as long as the walk through the haloed layout makes it
-    return any_plan(d.Cout, (long long)d.k * d.Cin, (long long)d.B * (d.Tp + 2 * LAYOUT_HALO), budget, FINISH_OWN);
+    return any_plan(d.Cout, (long long)d.k * d.Cin, (long long)d.B * (d.Tp + 2 * LAYOUT_HALO), budget, FINISH_OWN,
+                    (long long)d.Cout * d.k * d.Cin);
 }
 size_t part_bytes(int splits, long long rows, long long cols) { return splits > 1 ? round_up((size_t)splits * rows * cols * 4, 256) : 0; }
 }  // namespace

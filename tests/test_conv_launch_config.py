@@ -30,3 +30,22 @@ def test_lines_too_far_apart_for_32_bit_offsets(pass_, shape):
     # the same layer with its channels a hundredth as wide is near enough
     small = (B, T, max(64, Cin // 100 // 64 * 64), max(64, Cout // 100 // 64 * 64), k, s)
     assert P.w2l_conv1d_launch_config(pass_, *small, F32)[0] == PLAIN
+
+
+STRIDED = [(B, T, cin, cout, k, s) for B, T in ((1, 200), (4, 400), (4, 1600), (16, 1600)) for cin, cout in ((64, 64), (256, 512), (1024, 1024))
+           for k in (3, 11) for s in (1, 2, 4, 8)]
+
+
+@pytest.mark.parametrize("dtype", [P.W2L_F32, P.W2L_BF16])
+def test_planes_of_a_data_gradient_stay_within_their_bound(dtype):
+    """Every split of the reduction leaves a plane of the whole dx, whatever the stride: 96 MB in all at most."""
+    split = 0
+    for B, T, cin, cout, k, s in STRIDED:
+        cin += dtype == P.W2L_BF16                          # (a channel count that the bf16 kernels do not take)
+        shape = (B, T, cin, cout, k, s, dtype)
+        form, splits = P.w2l_conv1d_launch_config(BWD_DATA, *shape)
+        assert form != 0 and (splits == 1 or splits * B * T * cin * 4 <= 96 << 20), (shape, splits)
+        copy = (B * (T + 16) + 320) * cout * 4 if form == PLAIN else 0
+        assert P.w2l_conv1d_bwd_data_workspace_bytes(*shape) <= copy + (96 << 20) + 512, shape
+        split += s > 1 and splits > 1
+    assert split >= 4
