@@ -50,7 +50,7 @@ inline long long row_reach(int count, int step, int pitch)
 
 template <typename T>
 struct XWindow {  // fwd A: m = (b,t') -> x[b, s t' - p ..], r = (j,ci)
-    static constexpr bool K_LINES = true;
+    static constexpr bool K_LINES = true, PHASED = false;
     typedef T type;
     const T* base; int M, T_, Tp, Cin, k, s, p, pitch, halo;
     // every line starts and ends on a 16-byte chunk of fp32
@@ -76,6 +76,8 @@ struct WRows {  // fwd B: n = co -> w[co], r = (j,ci)
 };
 // The frames t of the data gradient with the same (t + p) mod s = ph meet the same taps j = ph, ph + s, .. (taps of
 // them) and read taps consecutive frames of dy, the last tap first: each such phase is a stride-1 problem of its own.
+// One launch takes all of them, a phase per index of grid.z (phase f: the frames f, f + s, ..; phases without taps store
+// zeros), however wide the stride.
 struct Phase { int ph, taps, first, count; };  // first frame of the phase, frames per utterance
 __host__ __device__ inline Phase phase_of(int ph, int T, int k, int s, int p)
 {
@@ -88,9 +90,10 @@ __host__ __device__ inline Phase phase_of(int ph, int T, int k, int s, int p)
 }
 template <typename T>
 struct DyWindow {  // dgrad A: m = (b, frame of the phase) -> its dy frames, r = (q,co), q-th frame <-> tap ph + s (taps-1-q)
-    static constexpr bool K_LINES = true;
+    static constexpr bool K_LINES = true, PHASED = true;
     typedef T type;
-    const T* base; int B, Tp, Cout, s, p, pitch, halo; Phase q;
+    const T* base; int B, T_, Tp, Cout, k, s, p, pitch, halo, f0; Phase q;  // f0: phase of grid.z = 0
+    static __host__ __device__ Phase phase(int f, int T_, int k, int s, int p) { return phase_of((int)(((long long)f + p) % s), T_, k, s, p); }
     bool chunks() const { return aligned16(base) && Cout % 4 == 0; }
     bool fast() const { return chunks() && s == 1 && Cout % 32 == 0 && (p == 0 || halo >= p) && near_lines(row_reach(q.count, 1, pitch) * Cout); }
     __device__ __forceinline__ long long fast_line(int m) const { return line(m < B * q.count ? m : B * q.count - 1).off; }
@@ -122,7 +125,7 @@ struct WCols {  // dgrad B: r = (q,co) -> w[co, tap], n = ci
 };
 template <typename T>
 struct DyT {  // wgrad A: r = (b,t') -> dy[b,t'], m = co
-    static constexpr bool K_LINES = false;
+    static constexpr bool K_LINES = false, PHASED = false;
     typedef T type;
     const T* base; int Tp, Cout, pitch, halo;
     bool chunks() const { return aligned16(base) && Cout % 4 == 0; }
@@ -179,6 +182,23 @@ struct StoreAcc {
         *q = accumulate ? *q + v : v;
     }
 };
+
+// the phase of a strided data gradient that the workgroup belongs to: its operands, rows and reduction
+template <class OA, class OB, class EP>
+__device__ __forceinline__ void take_phase(OA& oa, OB& ob, EP& ep, int z, int& M, int& R)
+{
+    if constexpr (OA::PHASED) {
+        if (oa.s > 1) {
+            const Phase q = OA::phase(oa.f0 + z, oa.T_, oa.k, oa.s, oa.p);
+            oa.q = q;
+            ob.q = q;
+            ep.first = q.first;
+            ep.count = q.count;
+            M = oa.B * q.count;
+            R = q.taps * oa.Cout;
+        }
+    }
+}
 
 // four consecutive elements from c on
 template <typename T>
@@ -282,7 +302,7 @@ struct AnyPanel {
     template <int NB> static __device__ __forceinline__ int at(int i, int c) { return KL ? 32 * i + c : NB * c + i; }
 };
 
-// TILE x TILE outputs per workgroup of four wavefronts (2 x 2).  grid.z = splits.  colsum (A by reduction lines, i.e. the weight gradient): the sums of A over the reduction -- the bias
+// TILE x TILE outputs per workgroup of four wavefronts (2 x 2).  grid.z = phases * splits.  colsum (A by reduction lines, i.e. the weight gradient): the sums of A over the reduction -- the bias
 // gradient -- from the values that pass through the first column of workgroups anyway.
 template <class OA, class OB, class EP>
 __global__ __launch_bounds__(256, 4) void gemm_any_k(OA oa, OB ob, EP ep, int M, int N, int R, int per, int splits, float* colsum, int colsum_acc)
@@ -294,6 +314,8 @@ __global__ __launch_bounds__(256, 4) void gemm_any_k(OA oa, OB ob, EP ep, int M,
     __shared__ __align__(16) float lds[2 * STAGE];
     const int split = blockIdx.z % splits;
     const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
+    take_phase(oa, ob, ep, blockIdx.z / splits, M, R);
+    if (OA::PHASED && m0 >= M) return;  // (phases differ by a frame per utterance)
     const int r_begin = split * per, r_end = R < r_begin + per ? R : r_begin + per;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wm = (wave >> 1) * (BM / 2), wn = (wave & 1) * (BN / 2);
     const bool sum_a = !PA::KL && colsum && blockIdx.x == 0;
@@ -510,6 +532,8 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
     __shared__ __align__(1024) float lds[2 * STAGE];
     const int split = blockIdx.z % splits;
     const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
+    take_phase(oa, ob, ep, blockIdx.z / splits, M, R);
+    if (OA::PHASED && m0 >= M) return;  // (phases differ by a frame per utterance)
     const int r_begin = split * per, r_end = R < r_begin + per ? R : r_begin + per;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wm = (wave >> 1) * (BM / 2), wn = (wave & 1) * (BN / 2);
     const bool sum_a = !PA::KL && colsum && blockIdx.x == 0;
@@ -644,17 +668,17 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
 // 2.18 ms, data gradient 2.69 against 2.38, weight gradient 3.06 against 2.45), four small workgroups on a CU
 // covering each other's barriers better than two large ones.
 struct AnyPlan { int splits, per; };
-// values: of a plane; launches: one after the other, each of the M x N x R problem (the phases of a stride)
-AnyPlan any_plan(long long M, long long N, long long R, size_t budget, double finish_cycles, long long values, int launches = 1)
+// values: of a plane; problems: that share a launch, each M x N x R (the phases of a stride)
+AnyPlan any_plan(long long M, long long N, long long R, size_t budget, double finish_cycles, long long values, int problems = 1)
 {
-    const long long tiles = ((M + TILE - 1) / TILE) * ((N + TILE - 1) / TILE), panels = (R + PANEL - 1) / PANEL;
+    const long long tiles = problems * ((M + TILE - 1) / TILE) * ((N + TILE - 1) / TILE), panels = (R + PANEL - 1) / PANEL;
     AnyPlan best{1, 0};
     double best_t = -1;
     for (int s = 1; s <= 16; ++s) {
         const long long per = (panels + s - 1) / s;
         if (s > 1 && (per * (s - 1) >= panels || per < 2 || (size_t)s * values * 4 > budget)) continue;
         const long long load = (tiles * s + 255) / 256;
-        double t = launches * (load * per * 1024.0 / (load > 2 ? 0.76 : load > 1 ? 0.72 : 0.67) + 12000);
+        double t = load * per * 1024.0 / (load > 2 ? 0.76 : load > 1 ? 0.72 : 0.67) + 12000;
         if (s > 1) t += 8.0 * s * values / 2500 + finish_cycles;
         if (best_t < 0 || t < best_t) {
             best_t = t;
@@ -666,7 +690,7 @@ AnyPlan any_plan(long long M, long long N, long long R, size_t budget, double fi
 
 template <class OA, class OB, class EP>
 int launch_any(const AnyPlan& pl, OA oa, OB ob, EP ep, long long M, long long N, long long R, hipStream_t st, float* colsum = nullptr,
-               int colsum_acc = 0, bool fast = false, int* form = nullptr)
+               int colsum_acc = 0, bool fast = false, int* form = nullptr, int phases = 1)
 {
     const long long gy = (M + TILE - 1) / TILE, gx = (N + TILE - 1) / TILE;
     if (M > 2147483647LL || R > 2147483647LL - 4096 || gy > 65535 || gx > 2147483647LL) return W2L_ERR_SHAPE;
@@ -677,7 +701,7 @@ int launch_any(const AnyPlan& pl, OA oa, OB ob, EP ep, long long M, long long N,
         *form = !chunks ? CONV_REGISTERS : fast ? CONV_PLAIN : CONV_CHUNKS;
         return W2L_OK;
     }
-    const dim3 g((unsigned)gx, (unsigned)gy, (unsigned)pl.splits);
+    const dim3 g((unsigned)gx, (unsigned)gy, (unsigned)(phases * pl.splits));
 #define W2L_ANY(KERN) hipLaunchKernelGGL(KERN, g, dim3(256), 0, st, oa, ob, ep, (int)M, (int)N, (int)R, pl.per, pl.splits, colsum, colsum_acc)
     if constexpr (f32) {
         if (chunks) {
@@ -711,12 +735,14 @@ template <typename TW, typename TDY, typename TO>
 int dgrad_t(const ConvDesc& d, const AnyPlan& pl, const void* dy, const void* w, TO* dx, int pitch, int halo, long long plane, hipStream_t st,
             int* form = nullptr)
 {
-    for (int ph = 0; ph < d.s; ++ph) {
-        const Phase q = phase_of(ph, d.T, d.k, d.s, d.p);
-        DyWindow<TDY> a{(const TDY*)dy, d.B, d.Tp, d.Cout, d.s, d.p, d.y_pitch, d.y_halo, q};
+    const int phases = d.s < d.T ? d.s : d.T, most = 65535 / pl.splits;  // (that have frames; that a grid takes)
+    for (int f = 0; f < phases; f += most) {
+        const Phase q = DyWindow<TDY>::phase(f, d.T, d.k, d.s, d.p);  // of the launch, the one with the most frames
+        DyWindow<TDY> a{(const TDY*)dy, d.B, d.T, d.Tp, d.Cout, d.k, d.s, d.p, d.y_pitch, d.y_halo, f, q};
         WCols<TW> b{(const TW*)w, d.Cin, d.Cout, d.k, d.s, q};
         StoreRows<TO> ep{dx, nullptr, d.Cin, q.count, q.first, d.s, pitch, halo, plane};
-        const int rc = launch_any(pl, a, b, ep, (long long)d.B * q.count, d.Cin, (long long)q.taps * d.Cout, st, nullptr, 0, a.fast() && b.fast(), form);
+        const int rc = launch_any(pl, a, b, ep, (long long)d.B * q.count, d.Cin, (long long)q.taps * d.Cout, st, nullptr, 0, a.fast() && b.fast(),
+                                  form, phases - f < most ? phases - f : most);
         if (rc || form) return rc;
     }
     return W2L_OK;
@@ -927,9 +953,10 @@ AnyPlan fwd_plan(const ConvDesc& d, size_t budget, double fin)
 }
 AnyPlan dgrad_plan(const ConvDesc& d, size_t budget, double fin)
 {
-    // of a stride's phases, the one with the most taps (they are launched one after the other); a plane takes all of them
+    // of a stride's phases, the one with the most taps, as often as there are any with taps; a plane takes all of them
+    const int phases = d.s < d.k ? d.s : d.k;
     return any_plan((long long)d.B * ((d.T + d.s - 1) / d.s), d.Cin, (long long)((d.k + d.s - 1) / d.s) * d.Cout, budget, fin,
-                    (long long)d.B * d.T * d.Cin, d.s);
+                    (long long)d.B * d.T * d.Cin, phases < d.T ? phases : d.T);
 }
 AnyPlan wgrad_plan(const ConvDesc& d, size_t budget)
 {

@@ -27,6 +27,8 @@ SHAPES = [
     (2, 131, 40, 64, 13, 2),     # strides: phases with unequal taps and frames
     (3, 70, 24, 48, 3, 4),       # a stride wider than the window: phases without taps
     (1, 7, 5, 40, 5, 3),
+    (2, 300, 32, 40, 5, 37),     # few phases with taps, tiles of few frames
+    (3, 5, 32, 40, 3, 9),        # a stride longer than the utterance
 ]
 
 
@@ -101,6 +103,26 @@ def test_fp32_weight_gradient_infinite_x(shape):
     fin = np.isfinite(dw_o)
     _check(got[fin], dw_o[fin], False, "dw")
     _check(to_host(db), dy.astype(np.float64).sum((0, 1)), False, "db")
+
+
+@pytest.mark.parametrize("use_ws", [False, True])
+def test_strided_data_gradient_is_one_launch(use_ws):
+    """... whatever the stride, and a finishing one if it is split: the nodes of a captured graph."""
+    import ctypes
+    import torch
+    import paper_1812_07625_amd as P
+    hip = ctypes.CDLL([l.split()[-1] for l in open("/proc/self/maps") if "libamdhip64.so" in l][0])
+    for B, T, Cin, Cout, k, s in [(2, 512, 64, 64, 3, 128), (1, 64, 40, 64, 13, 8), (4, 400, 128, 256, 7, 4)]:
+        dy, w, dx = empty((B, -(-T // s), Cout)), empty((Cout, k, Cin)), empty((B, T, Cin))
+        ws = P.workspace(P.w2l_conv1d_bwd_data_workspace_bytes(B, T, Cin, Cout, k, s, P.W2L_F32)) if use_ws else None
+        P.w2l_conv1d_bwd_data(dy, w, dx, s, ws)
+        g = torch.cuda.CUDAGraph(keep_graph=True)
+        with torch.cuda.graph(g):
+            P.w2l_conv1d_bwd_data(dy, w, dx, s, ws)
+        n = ctypes.c_size_t()
+        assert hip.hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+        splits = P.w2l_conv1d_launch_config(1, B, T, Cin, Cout, k, s, P.W2L_F32, use_ws)[1]
+        assert n.value == (2 if splits > 1 else 1), (T, s, n.value)
 
 
 def test_fp32_train_step_split_and_ragged():
