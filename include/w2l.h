@@ -45,7 +45,7 @@ typedef enum {
     W2L_ERR_SHAPE = -2,     /* non-positive size, even k, odd Cout with GLU, size over a limit */
     W2L_ERR_DTYPE = -3,     /* unknown or unsupported dtype combination */
     W2L_ERR_ALIGN = -4,     /* a pointer is not 16-byte aligned */
-    W2L_ERR_WORKSPACE = -5, /* workspace NULL or smaller than *_workspace_bytes() */
+    W2L_ERR_WORKSPACE = -5, /* workspace NULL, misaligned or too small */
     W2L_ERR_TARGET = -6,    /* (host validation helper) bad label or length */
     W2L_ERR_LAUNCH = -7     /* HIP reported an error; see w2l_last_hip_error() */
 } w2l_status;
@@ -70,10 +70,14 @@ int w2l_last_hip_error(void);
  * bias: [Cout] fp32 or NULL;  y: [B,T',Cout] (y_dtype; W2L_F32 is allowed with bf16
  * operands, e.g. for logits).
  * Workspace is optional for fwd and bwd_data: with NULL the kernels predicate every load
- * against the utterance edges; given the queried number of bytes they first copy the
- * window-read operand into a layout with a zero halo around every utterance (one extra
- * bandwidth-bound pass) and then run the faster unpredicated kernel.  A non-NULL workspace
- * smaller than the query is W2L_ERR_WORKSPACE. */
+ * against the utterance edges and one workgroup sums up a tile's whole reduction; given the
+ * queried number of bytes they first copy the window-read operand into a layout with a zero
+ * halo around every utterance (one extra bandwidth-bound pass), run the faster unpredicated
+ * kernel, and where a problem's tiles would leave compute units idle cut the reduction into runs
+ * whose fp32 sums (96 MB at most) a last pass adds up in a fixed order.  So results with and without workspace may
+ * differ in the rounding of the fp32 sums; either is bit-reproducible.  A smaller workspace is
+ * taken as one that has no room for such sums and for fp32 copies, down to the haloed copies of
+ * bf16 layers; a non-NULL workspace smaller than those is W2L_ERR_WORKSPACE. */
 size_t w2l_conv1d_fwd_workspace_bytes(int B, int T, int Cin, int Cout, int k, int stride, int dtype);
 int w2l_conv1d_fwd(const void *x, const void *w, const float *bias, void *y,
                    int B, int T, int Cin, int Cout, int k, int stride,
@@ -87,7 +91,7 @@ int w2l_conv1d_fwd(const void *x, const void *w, const float *bias, void *y,
  * a stride s > 1 with p % s == 0 and T % s == 0: dy is staged as bf16 (an fp32 dy is rounded to
  * bf16 there) with its channels padded to a multiple of 64, the weights are copied padded and with
  * the stride folded into the channels.  Without workspace, fp32 dy, odd channel counts and strided
- * layers take a shape-agnostic fp32 kernel. */
+ * layers take the kernels for any shape (fp32 matrix instruction). */
 size_t w2l_conv1d_bwd_data_workspace_bytes(int B, int T, int Cin, int Cout, int k, int stride, int dtype);
 int w2l_conv1d_bwd_data(const void *dy, const void *w, void *dx,
                         int B, int T, int Cin, int Cout, int k, int stride,
@@ -99,7 +103,9 @@ int w2l_conv1d_bwd_data(const void *dy, const void *w, void *dx,
  * x: [B,T,Cin] (dtype);  dy: [B,T',Cout] (dy_dtype);  dw: [Cout,k,Cin] fp32;
  * dbias: [Cout] fp32 or NULL.  accumulate = 0 overwrites dw/dbias, 1 adds to them.
  * Reductions run in a fixed order: results are bit-reproducible run to run.
- * The workspace is required here (reduction scratch, plus the haloed operand copies). */
+ * The workspace is required here (reduction scratch, plus the haloed operand copies); a smaller one
+ * than the query's is taken, as for fwd, down to the bf16 copies and the bias sums (256 bytes a channel;
+ * for Cout <= 32 the queried size). */
 size_t w2l_conv1d_bwd_weight_workspace_bytes(int B, int T, int Cin, int Cout, int k, int stride, int dtype);
 int w2l_conv1d_bwd_weight(const void *x, const void *dy, float *dw, float *dbias,
                           int B, int T, int Cin, int Cout, int k, int stride,

@@ -88,7 +88,7 @@ size_t conv_dgrad_scratch(const ConvDesc& d, int dt, int dydt)
 }
 
 // scratch of a weight gradient: column sums, then what the kernel of the shape needs
-static size_t wgrad_dbias_scratch(const ConvDesc& d) { return round_up((size_t)DBIAS_CHUNKS * d.Cout * 4, 256); }
+static size_t wgrad_dbias_scratch(const ConvDesc& d) { return d.Cout <= 32 ? 0 : round_up((size_t)DBIAS_CHUNKS * d.Cout * 4, 256); }
 size_t conv_wgrad_scratch_bytes(const ConvDesc& d, int dt, int dydt)
 {
     const size_t rest = d.Cout <= 32                  ? conv_wgrad_skinny_scratch(d.Cin, d.Cout, d.k)
@@ -165,20 +165,23 @@ extern "C" int w2l_conv1d_fwd(const void* x, const void* w, const float* bias, v
     if (!valid_dtype(dtype) || !valid_dtype(y_dtype) || (dtype == W2L_F32 && y_dtype != W2L_F32))
         return W2L_ERR_DTYPE;
     if (!aligned16(x) || !aligned16(w) || !aligned16(y) || (bias && !aligned16(bias))) return W2L_ERR_ALIGN;
-    const size_t need = w2l_conv1d_fwd_workspace_bytes(B, T, Cin, Cout, k, stride, dtype);
-    if (workspace && !ws_ok(workspace, ws_bytes, need)) return W2L_ERR_WORKSPACE;
+    // given a workspace, a bf16 layer takes its haloed copy; a split reduction and an fp32 layer's copy where there is
+    // room for all of it
+    const bool bf16 = stage_fwd(Cin, Cout, k, stride, dtype), f32 = stage_fwd_f32(Cin, k, stride, dtype);
+    const size_t need = w2l_conv1d_fwd_workspace_bytes(B, T, Cin, Cout, k, stride, dtype), least = bf16 ? haloed_bytes(B, T, Cin) : 0;
+    const bool all = workspace && ws_ok(workspace, ws_bytes, need);
+    if (workspace && !all && !ws_ok(workspace, ws_bytes, least)) return W2L_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     ConvDesc d = dense_desc(B, T, Cin, Cout, k, stride);
-    const bool f32 = stage_fwd_f32(Cin, k, stride, dtype);
-    if (workspace && (f32 || stage_fwd(Cin, Cout, k, stride, dtype))) {
+    if (workspace && (bf16 || (all && f32))) {
         const int C = f32 ? 2 * Cin : Cin;
         rc = pad_layout_bf16(x, workspace, B, T, C, T + 2 * ABI_HALO, ABI_HALO, ABI_SLACK_ZERO, st);
         if (rc) return rc;
         staged_x(d);
         const size_t copy = haloed_bytes(B, T, C);
-        return conv_fwd(d, workspace, w, bias, y, dtype, y_dtype, st, static_cast<unsigned char*>(workspace) + copy, need - copy);
+        return conv_fwd(d, workspace, w, bias, y, dtype, y_dtype, st, static_cast<unsigned char*>(workspace) + copy, all ? need - copy : 0);
     }
-    return conv_fwd(d, x, w, bias, y, dtype, y_dtype, st, workspace, workspace ? need : 0);
+    return conv_fwd(d, x, w, bias, y, dtype, y_dtype, st, all ? workspace : nullptr, all ? need : 0);
 }
 
 namespace w2l {
@@ -203,16 +206,18 @@ DgradPrep dgrad_prep(int B, int T, int Cin, int Cout, int k, int s, int dt)
     p.dy_bytes = haloed_bytes(B, f.Tp, Cp);
     p.w_bytes = p.copy_w ? round_up((size_t)Cp * f.k * f.Cin * 2, 256) : 0;
     p.split_bytes = round_up(conv_dgrad_scratch_bytes(f), 256);
+    p.pair_bytes = round_up(conv_dgrad_pair_bytes(f), 256);
     return p;
 }
 
-int conv_dgrad_prepared(const DgradPrep& prep, const void* dy, int dydt, const void* w, void* dx, void* ws, hipStream_t st)
+int conv_dgrad_prepared(const DgradPrep& prep, const void* dy, int dydt, const void* w, void* dx, void* ws, size_t ws_bytes, hipStream_t st)
 {
     if (!prep.ok) return W2L_ERR_SHAPE;
     const ConvDesc& f = prep.d;
     unsigned char* base = static_cast<unsigned char*>(ws);
+    const size_t split_bytes = ws_bytes >= prep.total() ? prep.split_bytes : prep.pair_bytes;
     // the staging launch also zeroes the split reduction's tickets (the head of its scratch)
-    int* const tickets = prep.split_bytes ? reinterpret_cast<int*>(base + prep.dy_bytes + prep.w_bytes) : nullptr;
+    int* const tickets = split_bytes ? reinterpret_cast<int*>(base + prep.dy_bytes + prep.w_bytes) : nullptr;
     int rc = prep_dgrad_dy(dy, dydt, base, f.B, f.Tp, prep.Cout, f.Cout, f.y_pitch, f.y_halo, ABI_SLACK_ZERO, st, tickets,
                            tickets ? (int)(DGRAD_TICKET_BYTES / 4) : 0);
     if (rc) return rc;
@@ -222,7 +227,7 @@ int conv_dgrad_prepared(const DgradPrep& prep, const void* dy, int dydt, const v
         if (rc) return rc;
         wp = base + prep.dy_bytes;
     }
-    return conv_dgrad_mfma(f, base, wp, dx, tickets, prep.split_bytes, st, tickets != nullptr);
+    return conv_dgrad_mfma(f, base, wp, dx, tickets, split_bytes, st, tickets != nullptr);
 }
 }  // namespace w2l
 
@@ -248,28 +253,33 @@ extern "C" int w2l_conv1d_bwd_data(const void* dy, const void* w, void* dx, int 
     if (!valid_dtype(dtype) || !valid_dtype(dy_dtype) || (dtype == W2L_F32 && dy_dtype != W2L_F32))
         return W2L_ERR_DTYPE;
     if (!aligned16(dy) || !aligned16(w) || !aligned16(dx)) return W2L_ERR_ALIGN;
+    const DgradPrep p = dgrad_prep(B, T, Cin, Cout, k, stride, dtype);
     const size_t need = w2l_conv1d_bwd_data_workspace_bytes(B, T, Cin, Cout, k, stride, dtype);
-    if (workspace && !ws_ok(workspace, ws_bytes, need)) return W2L_ERR_WORKSPACE;
+    const bool all = workspace && ws_ok(workspace, ws_bytes, need);
+    if (workspace && !all && !ws_ok(workspace, ws_bytes, p.ok ? p.least() : 0)) return W2L_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
-    if (workspace && need) {
-        // dy staged as bf16 into the haloed layout (channels padded to whole blocks of 64), weights copied padded /
-        // with the stride folded where the layer needs it: every bf16 shape the MFMA kernels can be brought to.
-        // (A 1x1 layer with bf16 dy and whole channel blocks needs none of it: the kernels read its dense dy as it is.)
-        const DgradPrep p = dgrad_prep(B, T, Cin, Cout, k, stride, dtype);
-        const bool plain_1x1 = k == 1 && stride == 1 && dy_dtype == W2L_BF16 && !p.copy_w;
-        if (p.ok && !plain_1x1) return conv_dgrad_prepared(p, dy, dy_dtype, w, dx, workspace, st);
-        if (plain_1x1 && p.ok) return conv_dgrad(dense_desc(B, T, Cin, Cout, k, stride), dy, w, dx, dtype, dy_dtype, st, workspace, need);
-        if (!p.ok) {
-            ConvDesc d = dense_desc(B, T, Cin, Cout, k, stride);
-            if (!stage_dgrad_f32(Cin, Cout, k, stride, dtype)) return conv_dgrad(d, dy, w, dx, dtype, dy_dtype, st, workspace, need);
-            rc = pad_layout_bf16(dy, workspace, B, T, 2 * Cout, T + 2 * ABI_HALO, ABI_HALO, ABI_SLACK_ZERO, st);
-            if (rc) return rc;
-            staged_y(d);
-            const size_t copy = haloed_bytes(B, T, 2 * Cout);
-            return conv_dgrad(d, workspace, w, dx, dtype, dy_dtype, st, static_cast<unsigned char*>(workspace) + copy, need - copy);
-        }
+    ConvDesc d = dense_desc(B, T, Cin, Cout, k, stride);
+    // dy staged as bf16 into the haloed layout (channels padded to whole blocks of 64), weights copied padded /
+    // with the stride folded where the layer needs it: every bf16 shape the MFMA kernels can be brought to.
+    // (A 1x1 layer with bf16 dy and whole channel blocks needs none of it: the kernels read its dense dy as it is.)
+    const bool plain_1x1 = k == 1 && stride == 1 && dy_dtype == W2L_BF16 && !p.copy_w;
+    if (workspace && p.ok && !plain_1x1) return conv_dgrad_prepared(p, dy, dy_dtype, w, dx, workspace, all ? need : p.least(), st);
+    if (all && !p.ok && stage_dgrad_f32(Cin, Cout, k, stride, dtype)) {
+        rc = pad_layout_bf16(dy, workspace, B, T, 2 * Cout, T + 2 * ABI_HALO, ABI_HALO, ABI_SLACK_ZERO, st);
+        if (rc) return rc;
+        staged_y(d);
+        const size_t copy = haloed_bytes(B, T, 2 * Cout);
+        return conv_dgrad(d, workspace, w, dx, dtype, dy_dtype, st, static_cast<unsigned char*>(workspace) + copy, need - copy);
     }
-    return conv_dgrad(dense_desc(B, T, Cin, Cout, k, stride), dy, w, dx, dtype, dy_dtype, st);
+    return conv_dgrad(d, dy, w, dx, dtype, dy_dtype, st, all ? workspace : nullptr, all ? need : 0);
+}
+
+// haloed copies of a bf16 weight gradient's operands
+static size_t wgrad_copies(int B, int T, int Cin, int Cout, int k, int stride, int dtype)
+{
+    ConvDesc f;
+    if (stage_wgrad(Cin, Cout, k, stride, dtype)) return haloed_bytes(B, T, Cin) + haloed_bytes(B, T, Cout);
+    return stage_wgrad_folded(B, T, Cin, Cout, k, stride, dtype, f) ? haloed_bytes(B, f.T, f.Cin) + haloed_bytes(B, f.T, Cout) : 0;
 }
 
 extern "C" size_t w2l_conv1d_bwd_weight_workspace_bytes(int B, int T, int Cin, int Cout, int k, int stride,
@@ -277,12 +287,8 @@ extern "C" size_t w2l_conv1d_bwd_weight_workspace_bytes(int B, int T, int Cin, i
 {
     if (check_conv_shape(B, T, Cin, Cout, k, stride)) return 0;
     if (!valid_dtype(dtype)) return 0;
-    size_t n = conv_wgrad_scratch_bytes(dense_desc(B, T, Cin, Cout, k, stride), dtype, dtype);
-    ConvDesc f;
-    if (stage_wgrad(Cin, Cout, k, stride, dtype)) n += haloed_bytes(B, T, Cin) + haloed_bytes(B, T, Cout);
-    else if (stage_wgrad_f32(Cin, Cout, k, stride, dtype)) n += haloed_bytes(B, T, 2 * Cin) + haloed_bytes(B, T, 2 * Cout);
-    else if (stage_wgrad_folded(B, T, Cin, Cout, k, stride, dtype, f)) n += haloed_bytes(B, f.T, f.Cin) + haloed_bytes(B, f.T, Cout);
-    return n;
+    return conv_wgrad_scratch_bytes(dense_desc(B, T, Cin, Cout, k, stride), dtype, dtype) + wgrad_copies(B, T, Cin, Cout, k, stride, dtype) +
+           (stage_wgrad_f32(Cin, Cout, k, stride, dtype) ? haloed_bytes(B, T, 2 * Cin) + haloed_bytes(B, T, 2 * Cout) : 0);
 }
 
 extern "C" int w2l_conv1d_bwd_weight(const void* x, const void* dy, float* dw, float* dbias, int B, int T,
@@ -295,12 +301,15 @@ extern "C" int w2l_conv1d_bwd_weight(const void* x, const void* dy, float* dw, f
     if (!valid_dtype(dtype) || !valid_dtype(dy_dtype) || (dtype == W2L_F32 && dy_dtype != W2L_F32))
         return W2L_ERR_DTYPE;
     if (!aligned16(x) || !aligned16(dy) || !aligned16(dw) || (dbias && !aligned16(dbias))) return W2L_ERR_ALIGN;
-    if (!ws_ok(workspace, ws_bytes, w2l_conv1d_bwd_weight_workspace_bytes(B, T, Cin, Cout, k, stride, dtype)))
-        return W2L_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     ConvDesc d = dense_desc(B, T, Cin, Cout, k, stride);
+    // room for the bf16 copies and the bias sums has to be there; a split reduction and fp32 copies where there is room
+    // for all of it (an fp32 dy of bf16 operands splits as far as the scratch of a bf16 one takes it)
+    const size_t split = conv_wgrad_scratch_bytes(d, dtype, dtype), least = Cout <= 32 ? split : wgrad_dbias_scratch(d);
+    const bool all = ws_ok(workspace, ws_bytes, w2l_conv1d_bwd_weight_workspace_bytes(B, T, Cin, Cout, k, stride, dtype));
+    const size_t scratch = all ? split : least;
+    if (!all && !ws_ok(workspace, ws_bytes, least + wgrad_copies(B, T, Cin, Cout, k, stride, dtype))) return W2L_ERR_WORKSPACE;
     unsigned char* ws = static_cast<unsigned char*>(workspace);
-    const size_t scratch = conv_wgrad_scratch_bytes(d, dtype, dtype);  // (an fp32 dy of bf16 operands splits as far as this takes it)
     ConvDesc f;
     if (dy_dtype == W2L_BF16 && stage_wgrad_folded(B, T, Cin, Cout, k, stride, dtype, f)) {
         unsigned char* xp = ws + scratch;
@@ -311,7 +320,7 @@ extern "C" int w2l_conv1d_bwd_weight(const void* x, const void* dy, float* dw, f
         staged_y(f);
         return conv_wgrad(f, xp, dyp, dw, dbias, dtype, dy_dtype, accumulate, workspace, scratch, st);
     }
-    const bool f32 = stage_wgrad_f32(Cin, Cout, k, stride, dtype);
+    const bool f32 = all && stage_wgrad_f32(Cin, Cout, k, stride, dtype);
     if (f32 || (dy_dtype == W2L_BF16 && stage_wgrad(Cin, Cout, k, stride, dtype))) {
         const int e = f32 ? 2 : 1;
         unsigned char* xp = ws + scratch;

@@ -250,17 +250,20 @@ int prep_dgrad_dy(const void* src, int src_dtype, void* dst, int B, int Tp, int 
 int prep_dgrad_w(const void* w, void* dst, int Cout, int k, int Cin, int Cp, int kf, int s, hipStream_t st);
 // A data gradient brought into the form the MFMA kernels take (api.hip).  ok: the shape can be prepared; d: the
 // geometry of the prepared problem (stride 1, Cout a multiple of 64, dy haloed); copy_w: the weights need the
-// padded / folded copy.  Workspace: dy_bytes, then w_bytes, then split_bytes (conv_dgrad_scratch_bytes(d)).
+// padded / folded copy.  Workspace: dy_bytes, then w_bytes, then split_bytes (conv_dgrad_scratch_bytes(d)) or, where
+// planes of sums have no room, pair_bytes (conv_dgrad_pair_bytes(d)).
 struct DgradPrep {
     bool ok = false, copy_w = false;
     ConvDesc d;
     int Cout = 0, k = 0, Cin = 0, s = 1;  // the layer as the caller describes it
-    size_t dy_bytes = 0, w_bytes = 0, split_bytes = 0;
+    size_t dy_bytes = 0, w_bytes = 0, split_bytes = 0, pair_bytes = 0;
     size_t total() const { return dy_bytes + w_bytes + split_bytes; }
+    size_t least() const { return dy_bytes + w_bytes + pair_bytes; }
 };
 DgradPrep dgrad_prep(int B, int T, int Cin, int Cout, int k, int s, int dt);
-// dy: dense [B, Tp, Cout] of dtype dydt; dx: dense [B, T, Cin] bf16; ws: prep.total() bytes, 256-byte aligned
-int conv_dgrad_prepared(const DgradPrep& prep, const void* dy, int dydt, const void* w, void* dx, void* ws, hipStream_t st);
+// dy: dense [B, Tp, Cout] of dtype dydt; dx: dense [B, T, Cin] bf16; ws: prep.total() or prep.least() bytes, 256-byte
+// aligned
+int conv_dgrad_prepared(const DgradPrep& prep, const void* dy, int dydt, const void* w, void* dx, void* ws, size_t ws_bytes, hipStream_t st);
 // the same for two tensors that share B, Tp and the layout, in one launch
 int pad_layout2_bf16(const void* src0, void* dst0, int C0, const void* src1, void* dst1, int C1, int B, int Tp, int pitch,
                      int halo, int slack, hipStream_t st);

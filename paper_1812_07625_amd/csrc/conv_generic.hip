@@ -960,8 +960,10 @@ AnyPlan dgrad_plan(const ConvDesc& d, size_t budget, double fin)
 }
 AnyPlan wgrad_plan(const ConvDesc& d, size_t budget)
 {
-    // the reduction as long as the walk through the haloed layout makes it
-    return any_plan(d.Cout, (long long)d.k * d.Cin, (long long)d.B * (d.Tp + 2 * LAYOUT_HALO), budget, FINISH_OWN,
+    // the reduction as long as the walk through the haloed layout makes it (where that is no more frames than an entry
+    // point takes: a run's end has to stay below 2^31)
+    const long long walk = (long long)d.B * (d.Tp + 2 * LAYOUT_HALO);
+    return any_plan(d.Cout, (long long)d.k * d.Cin, walk <= 1LL << 30 ? walk : (long long)d.B * d.Tp, budget, FINISH_OWN,
                     (long long)d.Cout * d.k * d.Cin);
 }
 size_t part_bytes(int splits, long long rows, long long cols) { return splits > 1 ? round_up((size_t)splits * rows * cols * 4, 256) : 0; }

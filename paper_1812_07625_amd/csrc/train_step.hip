@@ -453,7 +453,7 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
                 gdh_reader[q] = -1;
             }
             if (prepared)  // the criterion's fp32 gradient: cast, pad, MFMA
-                rc = conv_dgrad_prepared(p.cls_prep, dy, dy_dt, weights[i], gdhb[q], ws + p.cls, st);
+                rc = conv_dgrad_prepared(p.cls_prep, dy, dy_dt, weights[i], gdhb[q], ws + p.cls, p.cls_prep.total(), st);
             else
                 rc = conv_dgrad(dd, dy, weights[i], gdhb[q], dtype, dy_dt, st, ws + p.part, p.part_bytes);
             if (rc) return rc;

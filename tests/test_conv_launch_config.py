@@ -49,3 +49,10 @@ def test_planes_of_a_data_gradient_stay_within_their_bound(dtype):
         assert P.w2l_conv1d_bwd_data_workspace_bytes(*shape) <= copy + (96 << 20) + 512, shape
         split += s > 1 and splits > 1
     assert split >= 4
+
+
+def test_many_short_utterances_do_not_walk():
+    """The walk through the frames of a haloed layout counts 17 for every utterance of one frame: beyond 2^30 of them the
+    weight gradient counts real frames."""
+    assert P.w2l_conv1d_launch_config(BWD_WEIGHT, 1 << 27, 1, 4, 36, 3, 1, F32)[0] == CHUNKS
+    assert P.w2l_conv1d_launch_config(BWD_WEIGHT, 1 << 20, 1, 4, 36, 3, 1, F32)[0] == PLAIN

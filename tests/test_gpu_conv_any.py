@@ -191,6 +191,64 @@ def test_bf16_split_reductions(shape):
     _check(to_host(db), 2 * db_o, False, "db accumulated")
 
 
+@pytest.mark.parametrize("case", [
+    # dtype, B, T, Cin, Cout, k, s
+    ("f32", 2, 131, 256, 128, 5, 1), ("f32", 2, 131, 40, 64, 5, 2), ("f32", 2, 90, 64, 29, 3, 1),
+    ("bf16", 1, 131, 256, 128, 11, 1), ("bf16", 2, 300, 264, 136, 9, 1), ("bf16", 2, 640, 256, 512, 1, 1), ("bf16", 3, 701, 40, 72, 3, 1),
+    ("bf16", 2, 1400, 40, 128, 13, 2), ("bf16", 2, 90, 64, 29, 3, 1),
+], ids=lambda c: "x".join(map(str, c)))
+def test_smaller_workspaces(case):
+    """A workspace too small for a split reduction or for an fp32 layer's haloed copies is taken as one without them: bf16
+    layers need their haloed copies and weight gradients the room of the bias sums; less is refused, and so is a
+    misaligned workspace that is used."""
+    import paper_1812_07625_amd as P
+    dtype, B, T, Cin, Cout, k, s = case
+    bf16 = dtype == "bf16"
+    rng = np.random.default_rng(sum(case[1:]) + 3)
+    Tp, code = oracle.out_len(T, s), P.W2L_BF16 if bf16 else P.W2L_F32
+    grid = lambda a: W.round_to_bf16(a.astype(np.float32)) if bf16 else a.astype(np.float32)
+    x, dy = grid(rng.standard_normal((B, T, Cin))), grid(rng.standard_normal((B, Tp, Cout)))
+    w = grid(rng.standard_normal((Cout, k, Cin)) / np.sqrt(k * Cin))
+    xd, wd, dyd = to_dev(x, dtype), to_dev(w, dtype), to_dev(dy, dtype)
+    up = lambda n: (n + 255) // 256 * 256
+    haloed = lambda t, c: up((B * (t + 16) + 320) * c * 2)
+    exactly = lambda n: P.workspace(n)[:n] if n else P.workspace(64)[16:64]      # (nothing needed: any pointer does)
+
+    def refused(call, n):
+        for ws in (P.workspace(n)[:n - 1], P.workspace(n + 256)[16:16 + n]):
+            with pytest.raises(P.W2LError) as e:
+                call(ws)
+            assert e.value.status == -5
+
+    fwd = lambda ws: P.w2l_conv1d_fwd(xd, wd, None, empty((B, Tp, Cout), dtype), s, ws)
+    n = haloed(T, Cin) if bf16 and k > 1 and Cin % 64 == 0 and Cout >= 16 else 0
+    assert n <= P.w2l_conv1d_fwd_workspace_bytes(B, T, Cin, Cout, k, s, code)
+    _check(to_host(fwd(exactly(n))), oracle.conv1d_fwd(x, w, None, s), bf16, "y")
+    if n:
+        refused(fwd, n)
+
+    dgrad = lambda ws: P.w2l_conv1d_bwd_data(dyd, wd, empty((B, T, Cin), dtype), s, ws)
+    n, folds = 0, s == 1 or ((k - 1) // 2 % s == 0 and T % s == 0)
+    if bf16 and folds and s * Cin >= 64 and s * Cin % 8 == 0:
+        Cp, kf = -(-Cout // 64) * 64, k if s == 1 else 2 * ((k - 1) // 2 // s) + 1
+        n = haloed(T // s, Cp) + (up(Cp * kf * s * Cin * 2) if s > 1 or Cp != Cout else 0)   # (none of these takes pairs of workgroups)
+    assert n <= P.w2l_conv1d_bwd_data_workspace_bytes(B, T, Cin, Cout, k, s, code)
+    _check(to_host(dgrad(exactly(n))), oracle.conv1d_bwd_data(dy, w, T, s), bf16, "dx")
+    if n:
+        refused(dgrad, n)
+
+    wgrad = lambda ws: P.w2l_conv1d_bwd_weight(xd, dyd, empty((Cout, k, Cin)), empty((Cout,)), s, False, ws)
+    n = 256 * Cout * ((k * Cin + 1) if Cout <= 32 else 1)
+    if bf16 and folds and Cout >= 64 and s * Cin % 8 == 0 and Cout % 8 == 0:
+        n += haloed(T // s, s * Cin) + haloed(T // s, Cout)
+    assert n <= P.w2l_conv1d_bwd_weight_workspace_bytes(B, T, Cin, Cout, k, s, code)
+    dw, db = wgrad(exactly(n))
+    dw_o, db_o = oracle.conv1d_bwd_weight(x, dy, k, s)
+    _check(to_host(dw), dw_o, False, "dw")
+    _check(to_host(db), db_o, False, "db")
+    refused(wgrad, n)
+
+
 def test_bf16_train_step_split_reductions():
     """The same inside a step, where the GLU passes add the planes up: a strided first layer, bodies of two widths, a
     1x1 layer, over few frames."""
