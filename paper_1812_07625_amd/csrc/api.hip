@@ -89,9 +89,10 @@ size_t conv_dgrad_scratch(const ConvDesc& d, int dt, int dydt)
 
 // scratch of a weight gradient: column sums, then what the kernel of the shape needs
 static size_t wgrad_dbias_scratch(const ConvDesc& d) { return d.Cout <= 32 ? 0 : round_up((size_t)DBIAS_CHUNKS * d.Cout * 4, 256); }
-size_t conv_wgrad_scratch_bytes(const ConvDesc& d, int dt, int dydt)
+size_t conv_wgrad_scratch_bytes(const ConvDesc& d, int dt, int dydt, bool split)
 {
-    const size_t rest = d.Cout <= 32                  ? conv_wgrad_skinny_scratch(d.Cin, d.Cout, d.k)
+    const size_t rest = d.Cout <= 32                    ? conv_wgrad_skinny_scratch(d.Cin, d.Cout, d.k)
+                        : !split                        ? 0
                         : wgrad_is_generic(d, dt, dydt) ? conv_wgrad_generic_scratch(d)
                                                         : conv_wgrad_mfma_scratch(d);
     return wgrad_dbias_scratch(d) + rest;
@@ -104,11 +105,11 @@ bool conv_wgrad_fuses_dbias(const ConvDesc& d, int dt, int dydt)
 }
 
 int conv_wgrad(const ConvDesc& d, const void* x, const void* dy, float* dw, float* dbias, int dt, int dydt,
-               int accumulate, void* scratch, size_t scratch_bytes, hipStream_t st)
+               int accumulate, void* scratch, size_t scratch_bytes, hipStream_t st, bool split)
 {
     float* dbias_scratch = static_cast<float*>(scratch);
     unsigned char* rest = static_cast<unsigned char*>(scratch) + wgrad_dbias_scratch(d);
-    const size_t rest_bytes = scratch_bytes > wgrad_dbias_scratch(d) ? scratch_bytes - wgrad_dbias_scratch(d) : 0;
+    const size_t rest_bytes = split && scratch_bytes > wgrad_dbias_scratch(d) ? scratch_bytes - wgrad_dbias_scratch(d) : 0;
     if (wgrad_is_generic(d, dt, dydt))
         return conv_wgrad_generic(d, x, dy, dw, dbias, dt, dydt, accumulate, st, rest, rest_bytes);
     if (d.Cout <= 32) return conv_wgrad_skinny(d, x, dy, dw, dbias, dt, dydt, accumulate, reinterpret_cast<float*>(rest), st);

@@ -105,12 +105,12 @@ int conv_dgrad(const ConvDesc& d, const void* dy, const void* w, void* dx, int d
                void* scratch = nullptr, size_t scratch_bytes = 0);
 size_t conv_dgrad_scratch_bytes(const ConvDesc& d);
 size_t conv_dgrad_pair_bytes(const ConvDesc& d);  // of conv_dgrad_glu (0: no use for any)
-// scratch: conv_wgrad_scratch_bytes() bytes of device memory
-size_t conv_wgrad_scratch_bytes(const ConvDesc& d, int dt, int dydt);
+// scratch: conv_wgrad_scratch_bytes() bytes of device memory; split = false: the reduction stays whole
+size_t conv_wgrad_scratch_bytes(const ConvDesc& d, int dt, int dydt, bool split = true);
 // true where conv_wgrad() produces dbias inside the weight-gradient launch (no separate column-sum kernels)
 bool conv_wgrad_fuses_dbias(const ConvDesc& d, int dt, int dydt);
 int conv_wgrad(const ConvDesc& d, const void* x, const void* dy, float* dw, float* dbias, int dt, int dydt,
-               int accumulate, void* scratch, size_t scratch_bytes, hipStream_t st);
+               int accumulate, void* scratch, size_t scratch_bytes, hipStream_t st, bool split = true);
 
 constexpr size_t MAX_PARTIALS = 96u << 20;  // bytes of partial sums that a split reduction may leave (they stay in the memory-side cache)
 // Planes of fp32 sums that the pass leaves in front of the GLU pass that adds them up (1: the pass is not split), the

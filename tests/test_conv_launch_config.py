@@ -56,3 +56,11 @@ def test_many_short_utterances_do_not_walk():
     weight gradient counts real frames."""
     assert P.w2l_conv1d_launch_config(BWD_WEIGHT, 1 << 27, 1, 4, 36, 3, 1, F32)[0] == CHUNKS
     assert P.w2l_conv1d_launch_config(BWD_WEIGHT, 1 << 20, 1, 4, 36, 3, 1, F32)[0] == PLAIN
+
+
+def test_networks_on_two_streams_reserve_no_planes():
+    """The 105M-parameter network keeps its bf16 weight gradients whole (their workgroups and the data gradients' share the
+    chip from two streams): its workspace holds no planes for them (24 MB on either stream; 467 MB without)."""
+    import workloads as W
+    n = P.w2l_train_step_workspace_bytes(W.layers_105m(), 8, 1500, 93, P.W2L_BF16)
+    assert 460e6 < n < 490e6, n
