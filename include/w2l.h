@@ -325,6 +325,14 @@ int w2l_train_step_asg(const w2l_layer *layers, int n_layers,
                        const float *trans, float *dtrans, float *loss, float *logits,
                        int B, int T, int Lmax, int dtype, float grad_scale,
                        void *workspace, size_t ws_bytes, void *stream);
+/* Host-only query: how both train steps compute the gradients of one layer.  data_form 0: weight and data gradient are
+ * launches of their own (then the others are 0 too); otherwise one launch takes both (if the layer's bias gradient is
+ * wanted), the data gradient as 1: 192x192 tiles by two workgroups each, GLU backward of the layer below in their
+ * epilogue; 2: 256x128 tiles with that epilogue; 3 / 4: data_runs planes of sums in 128x128 / 256x128 tiles; 5 / 6: the
+ * gradient of the layer below's output in 128x128 / 256x128 tiles.  weight_tile: 0: 128x128, 1: 256x128, 2: 192x192,
+ * 3: 256x256, its reduction in weight_runs runs.  For tests and tuning; launches nothing. */
+int w2l_train_step_launch_config(const w2l_layer *layers, int n_layers, int B, int T, int dtype, int layer,
+                                 int *data_form, int *data_runs, int *weight_tile, int *weight_runs);
 
 /* ---- measurement aid (not part of the training path) -----------------------------------
  * Launches `blocks` workgroups of 4 wavefronts, each wavefront issuing 8*iters independent

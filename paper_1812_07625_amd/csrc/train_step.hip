@@ -229,6 +229,21 @@ extern "C" size_t w2l_train_step_asg_workspace_bytes(const w2l_layer* layers, in
     return p.status == W2L_OK ? p.total : 0;
 }
 
+extern "C" int w2l_train_step_launch_config(const w2l_layer* layers, int n_layers, int B, int T, int dtype, int layer, int* data_form, int* data_runs,
+                                            int* weight_tile, int* weight_runs)
+{
+    if (!layers || !data_form || !data_runs || !weight_tile || !weight_runs) return W2L_ERR_NULL;
+    const Plan p = make_plan(layers, n_layers, B, T, 1, dtype, CRIT_CTC);
+    if (p.status) return p.status;
+    if (layer < 0 || layer >= n_layers) return W2L_ERR_SHAPE;
+    const ConvBwdPlan& b = p.bwd[layer];
+    *data_form = b.ok ? 1 + b.dkind : 0;
+    *data_runs = b.ok ? b.dparts : 0;
+    *weight_tile = b.ok ? b.wtile : 0;
+    *weight_runs = b.ok ? b.wsplits : 0;
+    return W2L_OK;
+}
+
 // network forward, criterion (CTC on the log-softmax of the output, or ASG on the output itself), backward
 static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers, const void* const* weights,
                            const float* const* biases, float* const* dweights, float* const* dbiases, const void* x,

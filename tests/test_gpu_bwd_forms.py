@@ -1,0 +1,63 @@
+"""Train steps whose middle layer takes each form of the shared gradient launch (six data-gradient forms, four weight
+tiles), and one whose layers keep launches of their own, against the fp64 oracle; bounds of a whole bf16 step as in
+test_gpu_parity.py.  Frame counts are mostly no multiple of any tile and targets short, so that the oracle stays cheap."""
+import pytest
+
+import workloads as W
+from test_gpu_parity import check_train_step, oracle_train_step
+from variant_cases import BWD_CASES, bwd_network, bwd_variant
+from workloads.device import run_train_step
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def P():
+    import paper_1812_07625_amd as P
+    return P
+
+
+@pytest.mark.parametrize("case", BWD_CASES, ids=lambda c: "x".join(map(str, c)))
+def test_shared_gradient_launch(P, case):
+    B, T, k, cin, cout = case
+    i = BWD_CASES.index(case)
+    assert bwd_variant(P, *case) == (1 + i // 4, i % 4)
+    cfg = W.small_model(60 + i, B, max(20, T - T // 4), T, 16, bwd_network(k, cin, cout), True, 2, 8)
+    check_train_step(run_train_step(P, cfg), oracle_train_step(cfg), "bf16")
+
+
+def test_gradients_in_launches_of_their_own(P):
+    """The second body layer's tiles would leave CUs waiting in a shared launch, so every layer keeps two streams: the
+    first body layer's data gradient by two workgroups a tile and the third one's with the GLU backward in its epilogue."""
+    widths = [(3, 320, 256), (7, 128, 128), (5, 64, 128)]
+    layers = [dict(k=3, stride=1, cin=16, cout=640, glu=1)] + [dict(k=k, stride=1, cin=a, cout=b, glu=1) for k, a, b in widths]
+    layers += [dict(k=1, stride=1, cin=64, cout=29, glu=0)]
+    B, T = 16, 98
+    assert [bwd_variant(P, B, T, *w)[0] for w in widths] == [1, 0, 2]      # each by itself
+    assert all(P.w2l_train_step_launch_config(layers, B, T, P.W2L_BF16, i)[0] == 0 for i in range(5))
+    cfg = W.small_model(90, B, 70, T, 16, layers, True, 2, 8)
+    check_train_step(run_train_step(P, cfg), oracle_train_step(cfg), "bf16")
+
+
+def test_bias_gradients_not_wanted(P):
+    """A layer whose bias gradient is not wanted (NULL) keeps launches of its own between layers that share theirs; the
+    other gradients are the oracle's, and what is not wanted stays as it was."""
+    import numpy as np
+    layers = [dict(k=5, stride=2, cin=40, cout=256, glu=1)] + [dict(k=5, stride=1, cin=128, cout=256, glu=1)] * 4
+    layers += [dict(k=1, stride=1, cin=128, cout=29, glu=0)]
+    assert all(P.w2l_train_step_launch_config(layers, 4, 301, P.W2L_BF16, i)[0] > 0 for i in range(1, 5))
+
+    class Without:  # the binding, with some bias gradients left out
+        def __init__(self, skip): self.skip = skip
+        def __getattr__(self, name): return getattr(P, name)
+        def w2l_train_step(self, layers, w, b, dw, db, *rest):
+            return P.w2l_train_step(layers, w, b, dw, [None if i in self.skip else t for i, t in enumerate(db)], *rest)
+
+    cfg = W.small_model(91, 4, 220, 301, 40, layers, True, 4, 20)
+    ref = oracle_train_step(cfg)
+    for skip in ((2,), (1, 3), (0, 4, 5), tuple(range(6))):
+        got = run_train_step(Without(skip), cfg)
+        for i in skip:
+            assert np.isnan(got["db"][i]).all()
+            got["db"][i] = ref["db"][i]
+        check_train_step(got, ref, "bf16")

@@ -375,14 +375,15 @@ def test_train_step_10m_model_reduced_batch(P):
 
 def test_train_step_wide_layer_fused_epilogues(P):
     """A model whose second layer has the benchmark's output shape (B*T' = 6000 frames, 1536
-    channels) but a short reduction, so that the fp64 oracle stays affordable: the train step then
-    takes the kernels the 105M model takes -- forward convolution with the GLU in its epilogue
-    (layer 1), data gradient with its reduction split over two workgroups per tile and the GLU
-    backward of the layer below in the combining pass (layer 2 writes dy of layer 1), data gradient
-    with the GLU backward in its own epilogue (layer 1 writes dy of layer 0), activation slabs,
-    256x256 weight-gradient tiles -- and every gradient is compared with the oracle."""
+    channels) but a short reduction, so that the fp64 oracle stays affordable: forward convolution
+    with the GLU in its epilogue (layer 1), data gradient with its reduction split over two
+    workgroups per tile and the GLU backward of the layer below in the combining pass (layer 2
+    writes dy of layer 1, beside its own weight gradient), data gradient as planes of sums that the
+    GLU backward adds up (layer 1 writes dy of layer 0) -- and every gradient is compared with the
+    oracle.  (The 105M model's layers take launches of their own: test_gpu_bwd_forms.py.)"""
     layers = [dict(k=3, stride=1, cin=16, cout=128, glu=1), dict(k=3, stride=1, cin=64, cout=1536, glu=1),
               dict(k=5, stride=1, cin=768, cout=256, glu=1), dict(k=1, stride=1, cin=128, cout=29, glu=0)]
+    assert [P.w2l_train_step_launch_config(layers, 8, 750, P.W2L_BF16, i)[0] for i in range(4)] == [0, 3, 1, 0]
     cfg = W.small_model(33, 8, 700, 750, 16, layers, True, 20, 60)
     check_train_step(run_train_step(P, cfg), oracle_train_step(cfg), "bf16")
 
@@ -403,8 +404,8 @@ def test_train_step_layers_without_glu(P, bf16):
 
 
 def test_train_step_two_narrow_layers(P):
-    """Both weight gradients take the narrow-output kernel and its scratch: layer 1's on the helper
-    stream, layer 0's on the caller's stream at the same time -- each in its own scratch."""
+    """Both weight gradients take the narrow-output kernel, one after the other on the caller's stream
+    in the same scratch."""
     layers = [dict(k=3, stride=1, cin=40, cout=32, glu=1), dict(k=1, stride=1, cin=16, cout=29, glu=0)]
     cfg = W.small_model(42, 6, 300, 400, 40, layers, True, 5, 40)
     ref = oracle_train_step(cfg)

@@ -1,8 +1,11 @@
-"""Host-only: every lattice-kernel variant the criterion entry points can dispatch to is the
-variant of at least one GPU parity case (tests/variant_cases.py).  The set of reachable variants
-is found by asking the library's launch-configuration query for every size it accepts."""
+"""Host-only: every lattice-kernel variant the criterion entry points can dispatch to, and every form of the train
+step's shared gradient launch, is the variant of at least one GPU parity case (tests/variant_cases.py).  The set of
+reachable variants is found by asking the library's launch-configuration query for every size it accepts (gradients:
+for layers all over the range)."""
+import random
+
 import paper_1812_07625_amd as P
-from variant_cases import ASG_CASES, CTC_CASES, asg_variant, ctc_variant
+from variant_cases import ASG_CASES, BWD_CASES, CTC_CASES, asg_variant, bwd_variant, ctc_variant
 
 
 def _reachable(query, classes, lmax_max):
@@ -32,6 +35,19 @@ def test_asg_cases_cover_every_reachable_variant():
     assert not missing, "variants (positions, class lanes, max threads, block, row values) with no parity case: %r" % missing
 
 
+def test_gradient_cases_cover_every_reachable_form():
+    rng, reach = random.Random(4), {}
+    for _ in range(60000):
+        unit = rng.choice((64, 64, 16, 8))
+        case = (rng.choice((1, 2, 3, 4, 6, 8, 12, 16)), int(2 ** rng.uniform(5, 10.7)), rng.choice((1, 1, 3, 5, 7, 9, 11, 13)),
+                max(64, int(2 ** rng.uniform(6, 10.7) / unit) * unit), int(2 ** rng.uniform(6, 11.2) / 64) * 64)
+        reach.setdefault(bwd_variant(P, *case), case)
+    assert set(reach) == {(0, 0)} | {(d, t) for d in range(1, 7) for t in range(4)}, sorted(reach)
+    covered = {bwd_variant(P, *c) for c in BWD_CASES}
+    missing = {v: eg for v, eg in reach.items() if v not in covered and v != (0, 0)}
+    assert not missing, "forms (data gradient, weight tile) of the shared launch with no parity case; e.g. (B, T, k, cin, cout): %r" % missing
+
+
 def test_launch_config_rejects_what_the_entry_points_reject():
     import pytest
     for bad in ((0, 10), (5000, 10), (29, 0), (29, 3001)):
@@ -40,3 +56,7 @@ def test_launch_config_rejects_what_the_entry_points_reject():
     for bad in ((0, 10), (65, 10), (28, 0), (28, 3001)):
         with pytest.raises(P.W2LError):
             P.w2l_asg_launch_config(*bad)
+    net = [dict(k=3, stride=1, cin=16, cout=64, glu=1), dict(k=1, stride=1, cin=32, cout=29, glu=0)]
+    for B, T, dtype, layer in ((0, 10, 1, 0), (2, 10, 7, 0), (2, 10, 1, 2), (2, 10, 1, -1)):
+        with pytest.raises(P.W2LError):
+            P.w2l_train_step_launch_config(net, B, T, dtype, layer)
