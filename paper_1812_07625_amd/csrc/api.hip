@@ -87,8 +87,9 @@ size_t conv_dgrad_scratch(const ConvDesc& d, int dt, int dydt)
     return conv_dgrad_is_generic(d, dt, dydt) ? conv_dgrad_generic_scratch(d) : conv_dgrad_scratch_bytes(d);
 }
 
-// scratch of a weight gradient: column sums, then what the kernel of the shape needs
-static size_t wgrad_dbias_scratch(const ConvDesc& d) { return d.Cout <= 32 ? 0 : round_up((size_t)DBIAS_CHUNKS * d.Cout * 4, 256); }
+// scratch of a weight gradient: column sums (in the 256 bytes a channel that a workspace has to have at least: the sums
+// take 64), then what the kernel of the shape needs
+static size_t wgrad_dbias_scratch(const ConvDesc& d) { return d.Cout <= 32 ? 0 : (size_t)256 * d.Cout; }
 size_t conv_wgrad_scratch_bytes(const ConvDesc& d, int dt, int dydt, bool split)
 {
     const size_t rest = d.Cout <= 32                    ? conv_wgrad_skinny_scratch(d.Cin, d.Cout, d.k)
@@ -101,7 +102,7 @@ size_t conv_wgrad_scratch_bytes(const ConvDesc& d, int dt, int dydt, bool split)
 bool conv_wgrad_fuses_dbias(const ConvDesc& d, int dt, int dydt)
 {
     return d.Cout <= 32 || wgrad_is_generic(d, dt, dydt) ||
-           ( dt == W2L_BF16 && dydt == W2L_BF16 && conv_wgrad_mfma_takes_dbias(d));
+           (dt == W2L_BF16 && dydt == W2L_BF16 && conv_wgrad_mfma_takes_dbias(d));
 }
 
 int conv_wgrad(const ConvDesc& d, const void* x, const void* dy, float* dw, float* dbias, int dt, int dydt,
@@ -116,7 +117,7 @@ int conv_wgrad(const ConvDesc& d, const void* x, const void* dy, float* dw, floa
     if (dbias && conv_wgrad_fuses_dbias(d, dt, dydt)) return conv_wgrad_mfma(d, x, dy, dw, dbias, accumulate, st, rest, rest_bytes);
     if (dbias) {
         // halo frames hold zeros, so summing every frame of the allocation is the same sum
-        const int rc = dbias_reduce(dy, dbias, (long long)d.B * d.y_pitch, d.Cout, dydt, accumulate, dbias_scratch, st);
+        const int rc = dbias_reduce(dy, dbias, (long long)d.B * d.y_pitch, d.Cout, accumulate, dbias_scratch, st);
         if (rc) return rc;
     }
     return conv_wgrad_mfma(d, x, dy, dw, nullptr, accumulate, st, rest, rest_bytes);

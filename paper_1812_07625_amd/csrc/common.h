@@ -150,10 +150,9 @@ enum { SKINNY_CHUNKS = 64 };  // (dbias, nullable: one more column)
 size_t conv_wgrad_skinny_scratch(int Cin, int Cout, int k);
 int conv_wgrad_skinny(const ConvDesc& d, const void* x, const void* dy, float* dw, float* dbias, int dt, int dydt, int accumulate,
                       float* scratch, hipStream_t st);
-// column sums of dy[rows,Cout] -> dbias, two deterministic stages; scratch holds DBIAS_CHUNKS*Cout floats
-enum { DBIAS_CHUNKS = 64 };
-int dbias_reduce(const void* dy, float* dbias, long long rows, int Cout, int dydt, int accumulate,
-                 float* scratch, hipStream_t st);
+// column sums of bf16 dy[rows, Cout] (Cout % 8 == 0) -> dbias, two deterministic stages; scratch: DBIAS_CHUNKS * Cout floats
+enum { DBIAS_CHUNKS = 16 };
+int dbias_reduce(const void* dy, float* dbias, long long rows, int Cout, int accumulate, float* scratch, hipStream_t st);
 
 // MFMA (bf16 operands, fp32 accumulate) paths; *_ok() says whether a shape is taken
 bool conv_fwd_mfma_ok(const ConvDesc& d);

@@ -274,43 +274,33 @@ struct AnyPanel {
             *reinterpret_cast<f32x4a*>(lds + l_of(i) * PITCH + c_of()) = u;
         }
     }
-    // Operand registers of NB blocks of 32 rows from row w on, for the four instructions of reduction steps
-    // r .. r + 7: instruction q takes step r + q from lanes 0..31 and step r + 4 + q from lanes 32..63, so that a
-    // lane's four values are consecutive in a [W][BK] image.  In a [BK][W] image the NB values of a line are taken
-    // from consecutive rows instead: block i, lane c is row NB * c + i there and 32 * i + c here (at()).
-    template <int NB>
-    static __device__ __forceinline__ void frags(const float* lds, int w, int r, int lane, float (&f)[NB][4])
+    // Operand registers of the 32 rows from row w on, for the four instructions of reduction steps r .. r + 7:
+    // instruction q takes step r + q from lanes 0..31 and step r + 4 + q from lanes 32..63, so that a lane's four values
+    // are consecutive in a [W][BK] image.
+    static __device__ __forceinline__ void frags(const float* lds, int w, int r, int lane, float (&f)[4])
     {
         const int c = lane & 31, h = lane >> 5;
         if constexpr (KL) {
+            const f32x4a u = *reinterpret_cast<const f32x4a*>(lds + (w + c) * PITCH + r + 4 * h);
 #pragma unroll
-            for (int i = 0; i < NB; ++i) {
-                const f32x4a u = *reinterpret_cast<const f32x4a*>(lds + (w + 32 * i + c) * PITCH + r + 4 * h);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) f[i][q] = u[q];
-            }
+            for (int q = 0; q < 4; ++q) f[q] = u[q];
         } else {
-            typedef float vec __attribute__((ext_vector_type(NB)));
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const vec u = *reinterpret_cast<const vec*>(lds + (r + 4 * h + q) * PITCH + w + NB * c);
-#pragma unroll
-                for (int i = 0; i < NB; ++i) f[i][q] = u[i];
-            }
+            for (int q = 0; q < 4; ++q) f[q] = lds[(r + 4 * h + q) * PITCH + w + c];
         }
     }
-    template <int NB> static __device__ __forceinline__ int at(int i, int c) { return KL ? 32 * i + c : NB * c + i; }
 };
 
-// TILE x TILE outputs per workgroup of four wavefronts (2 x 2).  grid.z = phases * splits.  colsum (A by reduction lines, i.e. the weight gradient): the sums of A over the reduction -- the bias
-// gradient -- from the values that pass through the first column of workgroups anyway.
+// TILE x TILE outputs per workgroup of four wavefronts (2 x 2), 32 x 32 each.  grid.z = phases * splits.  colsum (A by
+// reduction lines, i.e. the weight gradient): the sums of A over the reduction -- the bias gradient -- from the values
+// that pass through the first column of workgroups anyway.
 template <class OA, class OB, class EP>
 __global__ __launch_bounds__(256, 4) void gemm_any_k(OA oa, OB ob, EP ep, int M, int N, int R, int per, int splits, float* colsum, int colsum_acc)
 {
     constexpr int BM = TILE, BN = TILE, BK = PANEL;
     using PA = AnyPanel<OA, BM, BK>;
     using PB = AnyPanel<OB, BN, BK>;
-    constexpr int STAGE = PA::FLOATS + PB::FLOATS, NA = BM / 64, NB = BN / 64;
+    constexpr int STAGE = PA::FLOATS + PB::FLOATS;
     __shared__ __align__(16) float lds[2 * STAGE];
     const int split = blockIdx.z % splits;
     const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
@@ -323,13 +313,9 @@ __global__ __launch_bounds__(256, 4) void gemm_any_k(OA oa, OB ob, EP ep, int M,
     PB pb;
     pa.init(oa, m0, r_end);
     pb.init(ob, n0, r_end);
-    f32x16 acc[NA][NB];
+    f32x16 acc;
 #pragma unroll
-    for (int i = 0; i < NA; ++i)
-#pragma unroll
-        for (int j = 0; j < NB; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
     float asum[4] = {0.f, 0.f, 0.f, 0.f};
     auto fetch = [&](int r0) {
         pa.load(oa, m0, r0, r_end);
@@ -357,39 +343,22 @@ __global__ __launch_bounds__(256, 4) void gemm_any_k(OA oa, OB ob, EP ep, int M,
         const float* lb = la + PA::FLOATS;
 #pragma unroll
         for (int r = 0; r < BK; r += 8) {
-            float fa[NA][4], fb[NB][4];
-            PA::template frags<NA>(la, wm, r, lane, fa);
-            PB::template frags<NB>(lb, wn, r, lane, fb);
+            float fa[4], fb[4];
+            PA::frags(la, wm, r, lane, fa);
+            PB::frags(lb, wn, r, lane, fb);
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int i = 0; i < NA; ++i)
-#pragma unroll
-                    for (int j = 0; j < NB; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][q], fb[j][q], acc[i][j], 0, 0, 0);
+            for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[q], fb[q], acc, 0, 0, 0);
         }
         if (st + 1 < steps) put(lds + ((st + 1) & 1) * STAGE);
         __syncthreads();
     }
-    float addn[NB];
+    const int n = n0 + wn + (lane & 31);
+    const float addn = n < N ? ep.add(n) : 0.f;
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-        const int n = n0 + wn + PB::template at<NB>(j, lane & 31);
-        addn[j] = n < N ? ep.add(n) : 0.f;
+    for (int e = 0; e < 16; ++e) {
+        const int m = m0 + wm + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+        if (m < M && n < N) ep.store(ep.row(m) + n, acc[e] + addn, split);
     }
-#pragma unroll
-    for (int i = 0; i < NA; ++i)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int m = m0 + wm + PA::template at<NA>(i, 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3));
-            if (m >= M) continue;
-            const long long row = ep.row(m);
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                const int n = n0 + wn + PB::template at<NB>(j, lane & 31);
-                if (n < N) ep.store(row + n, acc[i][j][e] + addn[j], split);
-            }
-        }
     if (sum_a) {  // thread (line, column chunk) partial sums, added over the lines in order
         float* red = lds;  // every wavefront is past its last read of the panels
 #pragma unroll
@@ -489,29 +458,19 @@ struct DmaPanel {
         dma16(c >= l.lo && c < l.hi ? (const void*)(op.base + l.off + c) : (const void*)g_zero_chunk, dst);
     }
     // as AnyPanel::frags
-    template <int NB>
-    static __device__ __forceinline__ void frags(const float* lds, int w, int r, int lane, float (&f)[NB][4])
+    static __device__ __forceinline__ void frags(const float* lds, int w, int r, int lane, float (&f)[4])
     {
         const int c = lane & 31, h = lane >> 5;
         if constexpr (KL) {
+            const int row = w + c;
+            const f32x4a u = *reinterpret_cast<const f32x4a*>(lds + row * BK + (((r >> 2) + h) ^ swz(row)) * 4);
 #pragma unroll
-            for (int i = 0; i < NB; ++i) {
-                const int row = w + 32 * i + c;
-                const f32x4a u = *reinterpret_cast<const f32x4a*>(lds + row * BK + (((r >> 2) + h) ^ swz(row)) * 4);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) f[i][q] = u[q];
-            }
+            for (int q = 0; q < 4; ++q) f[q] = u[q];
         } else {
-            typedef float vec __attribute__((ext_vector_type(NB)));
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const vec u = *reinterpret_cast<const vec*>(lds + (r + 4 * h + q) * W + w + NB * c);
-#pragma unroll
-                for (int i = 0; i < NB; ++i) f[i][q] = u[i];
-            }
+            for (int q = 0; q < 4; ++q) f[q] = lds[(r + 4 * h + q) * W + w + c];
         }
     }
-    template <int NB> static __device__ __forceinline__ int at(int i, int c) { return KL ? 32 * i + c : NB * c + i; }
 };
 
 // Same tiles, splits and results as gemm_any_k.  The next panel is requested under the first matrix instructions of a
@@ -526,9 +485,9 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
     constexpr int BM = TILE, BN = TILE, BK = PANEL;
     using PA = DmaPanel<OA, BM, FAST>;
     using PB = DmaPanel<OB, BN, FAST>;
-    constexpr int STAGE = PA::FLOATS + PB::FLOATS, NA = BM / 64, NB = BN / 64, NL = PA::NI + PB::NI;
-    constexpr int GROUPS = BK / 8, MPG = 4 * NA * NB;        // groups of eight steps, matrix instructions per group
-    static_assert(NL <= (GROUPS - 1) * MPG, "a load after every instruction: all of them before the hand-over");
+    constexpr int STAGE = PA::FLOATS + PB::FLOATS, NL = PA::NI + PB::NI;
+    constexpr int GROUPS = BK / 8;                           // of eight steps, four matrix instructions
+    static_assert(NL <= (GROUPS - 1) * 4, "a load after every instruction: all of them before the hand-over");
     __shared__ __align__(1024) float lds[2 * STAGE];
     const int split = blockIdx.z % splits;
     const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
@@ -542,16 +501,10 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
     PB pb;
     pa.init(oa, m0, r_end);
     pb.init(ob, n0, r_end);
-    f32x16 acc[NA][NB];
+    f32x16 acc;
 #pragma unroll
-    for (int i = 0; i < NA; ++i)
-#pragma unroll
-        for (int j = 0; j < NB; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-    float asum[NA];
-#pragma unroll
-    for (int i = 0; i < NA; ++i) asum[i] = 0.f;
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    float asum = 0.f;
     const int steps = r_end > r_begin ? (r_end - r_begin + BK - 1) / BK : 0;
     // (past the last panel the loads fetch zeros, or that panel again: the number in flight never changes)
     auto issue = [&](int i, int st) {
@@ -563,15 +516,15 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
     constexpr bool WALK = FAST && !PA::KL;  // the weight gradient
     int walk0 = 0;                          // WALK: the panel's first frame, counted from its utterance's first one
     if constexpr (WALK) walk0 = r_begin % oa.pitch;
-    float fa[2][NA][4], fb[2][NB][4];
+    float fa[2][4], fb[2][4];
     if (steps > 0) {
 #pragma unroll
         for (int i = 0; i < NL; ++i) issue(i, 0);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        PA::template frags<NA>(lds, wm, 0, lane, fa[0]);
-        PB::template frags<NB>(lds + PA::FLOATS, wn, 0, lane, fb[0]);
+        PA::frags(lds, wm, 0, lane, fa[0]);
+        PB::frags(lds + PA::FLOATS, wn, 0, lane, fb[0]);
     }
     for (int st = 0; st < steps; ++st) {
         const float* cur = lds + (st & 1) * STAGE;
@@ -587,8 +540,8 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
             }
-            PA::template frags<NA>(src, wm, (g + 1) % GROUPS * 8, lane, fa[1 - u]);
-            PB::template frags<NB>(src + PA::FLOATS, wn, (g + 1) % GROUPS * 8, lane, fb[1 - u]);
+            PA::frags(src, wm, (g + 1) % GROUPS * 8, lane, fa[1 - u]);
+            PB::frags(src + PA::FLOATS, wn, (g + 1) % GROUPS * 8, lane, fb[1 - u]);
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (WALK) {
                 if (between) {
@@ -597,28 +550,20 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
                         const int l = g * 8 + 4 * (lane >> 5) + q;
                         int t = walk0 + l;
                         while (t >= oa.pitch) t -= oa.pitch;
-                        const bool real = t < oa.Tp && r_begin + st * BK + l < r_end;
-#pragma unroll
-                        for (int j = 0; j < NB; ++j) fb[u][j][q] = real ? fb[u][j][q] : 0.f;
+                        fb[u][q] = t < oa.Tp && r_begin + st * BK + l < r_end ? fb[u][q] : 0.f;
                     }
                 }
             }
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int i = 0; i < NA; ++i)
-#pragma unroll
-                    for (int j = 0; j < NB; ++j) {
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[u][i][q], fb[u][j][q], acc[i][j], 0, 0, 0);
-                        __builtin_amdgcn_sched_barrier(0);
-                        const int t = (g * 4 + q) * NA * NB + i * NB + j;
-                        if (t < NL) issue(t, st + 1);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
+            for (int q = 0; q < 4; ++q) {
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[u][q], fb[u][q], acc, 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (g * 4 + q < NL) issue(g * 4 + q, st + 1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
             if (sum_a) {
                 asm volatile("");  // a branch: without it every workgroup would add, and select
-#pragma unroll
-                for (int i = 0; i < NA; ++i) asum[i] += (fa[u][i][0] + fa[u][i][1]) + (fa[u][i][2] + fa[u][i][3]);
+                asum += (fa[u][0] + fa[u][1]) + (fa[u][2] + fa[u][3]);
             }
         }
         if constexpr (WALK) {
@@ -627,34 +572,19 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing may land in LDS once it is used otherwise
-    float addn[NB];
+    const int n = n0 + wn + (lane & 31);
+    const float addn = n < N ? ep.add(n) : 0.f;
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-        const int n = n0 + wn + PB::template at<NB>(j, lane & 31);
-        addn[j] = n < N ? ep.add(n) : 0.f;
+    for (int e = 0; e < 16; ++e) {
+        const int m = m0 + wm + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+        if (m < M && n < N) ep.store(ep.row(m) + n, acc[e] + addn, split);
     }
-#pragma unroll
-    for (int i = 0; i < NA; ++i)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int m = m0 + wm + PA::template at<NA>(i, 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3));
-            if (m >= M) continue;
-            const long long row = ep.row(m);
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                const int n = n0 + wn + PB::template at<NB>(j, lane & 31);
-                if (n < N) ep.store(row + n, acc[i][j][e] + addn[j], split);
-            }
-        }
     if (sum_a && (wave & 1) == 0) {  // the two wavefronts of a row of the tile hold the same values: one writes
-#pragma unroll
-        for (int i = 0; i < NA; ++i) {
-            const float v = asum[i] + __shfl_xor(asum[i], 32, 64);  // lanes 0..31 and 32..63 took different steps
-            const int m = m0 + wm + PA::template at<NA>(i, lane & 31);
-            if (lane < 32 && m < M) {
-                float* q = colsum + (long long)split * M + m;
-                *q = colsum_acc ? *q + v : v;
-            }
+        const float v = asum + __shfl_xor(asum, 32, 64);  // lanes 0..31 and 32..63 took different steps
+        const int m = m0 + wm + (lane & 31);
+        if (lane < 32 && m < M) {
+            float* q = colsum + (long long)split * M + m;
+            *q = colsum_acc ? *q + v : v;
         }
     }
 }
@@ -868,28 +798,9 @@ __global__ __launch_bounds__(256) void wgrad_skinny_stage2(const float* __restri
 }
 
 // ---- dbias: deterministic two-stage column sum -------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void colsum_stage1(const T* dy, float* part, long long rows, int Cout)
-{
-    // block: 64 columns x 4 row lanes; grid.y = row chunks
-    const int c = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int rl = threadIdx.x >> 6;
-    const long long per = (rows + gridDim.y - 1) / gridDim.y;
-    const long long r0 = per * blockIdx.y, r1 = (r0 + per < rows) ? r0 + per : rows;
-    float acc = 0.f;
-    if (c < Cout)
-        for (long long r = r0 + rl; r < r1; r += 4) acc += Elem<T>::load(dy, (size_t)r * Cout + c);
-    __shared__ float sm[4][64];
-    sm[rl][threadIdx.x & 63] = acc;
-    __syncthreads();
-    if (rl == 0 && c < Cout)
-        part[(size_t)blockIdx.y * Cout + c] = (sm[0][threadIdx.x] + sm[1][threadIdx.x]) +
-                                              (sm[2][threadIdx.x] + sm[3][threadIdx.x]);
-}
 // bf16, Cout % 8 == 0.  A workgroup owns 32 columns (4 lanes x 16-byte loads) of one of
-// DBIAS_VCHUNKS row ranges, 64 row lanes each; the 64 partial sums per column are added in a
+// DBIAS_CHUNKS row ranges, 64 row lanes each; the 64 partial sums per column are added in a
 // fixed tree through LDS; colsum_stage2 then adds the chunks in order.
-constexpr int DBIAS_VCHUNKS = 16;
 __global__ __launch_bounds__(256) void colsum_bf16_stage1(const bf16_t* __restrict__ dy, float* __restrict__ part,
                                                           long long rows, int Cout)
 {
@@ -1106,29 +1017,12 @@ int conv_wgrad_skinny(const ConvDesc& d, const void* x, const void* dy, float* d
                        (int)total, accumulate);
     return launch_status();
 }
-int dbias_reduce(const void* dy, float* dbias, long long rows, int Cout, int dydt, int accumulate,
-                 float* scratch, hipStream_t st)
+int dbias_reduce(const void* dy, float* dbias, long long rows, int Cout, int accumulate, float* scratch, hipStream_t st)
 {
-    if (dydt == W2L_BF16 && Cout % 8 == 0) {
-        hipLaunchKernelGGL(colsum_bf16_stage1, dim3((Cout + 31) / 32, DBIAS_VCHUNKS), dim3(256), 0, st,
-                           (const bf16_t*)dy, scratch, rows, Cout);
-        int rc = launch_status();
-        if (rc) return rc;
-        hipLaunchKernelGGL(colsum_stage2, dim3((Cout + 255) / 256), dim3(256), 0, st, scratch, dbias,
-                           (int)DBIAS_VCHUNKS, Cout, accumulate);
-        return launch_status();
-    }
-    const dim3 g1((Cout + 63) / 64, DBIAS_CHUNKS);
-    if (dydt == W2L_F32)
-        hipLaunchKernelGGL(colsum_stage1<float>, g1, dim3(256), 0, st, (const float*)dy, scratch, rows, Cout);
-    else if (dydt == W2L_BF16)
-        hipLaunchKernelGGL(colsum_stage1<bf16_t>, g1, dim3(256), 0, st, (const bf16_t*)dy, scratch, rows, Cout);
-    else
-        return W2L_ERR_DTYPE;
-    int rc = launch_status();
+    hipLaunchKernelGGL(colsum_bf16_stage1, dim3((Cout + 31) / 32, DBIAS_CHUNKS), dim3(256), 0, st, (const bf16_t*)dy, scratch, rows, Cout);
+    const int rc = launch_status();
     if (rc) return rc;
-    hipLaunchKernelGGL(colsum_stage2, dim3((Cout + 255) / 256), dim3(256), 0, st, scratch, dbias,
-                       (int)DBIAS_CHUNKS, Cout, accumulate);
+    hipLaunchKernelGGL(colsum_stage2, dim3((Cout + 255) / 256), dim3(256), 0, st, scratch, dbias, (int)DBIAS_CHUNKS, Cout, accumulate);
     return launch_status();
 }
 

@@ -432,7 +432,7 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
         }
         if (side && dbiases[i] && !fused_dbias) {
             // halo frames hold zeros, so summing every frame of the allocation is the same sum
-            rc = dbias_reduce(dy, dbiases[i], (long long)d.B * d.y_pitch, d.Cout, dy_dt, 0,
+            rc = dbias_reduce(dy, dbiases[i], (long long)d.B * d.y_pitch, d.Cout, 0,
                               reinterpret_cast<float*>(ws + p.dbias), st);
             if (rc) return rc;
         }
