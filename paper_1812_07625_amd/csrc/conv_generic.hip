@@ -530,7 +530,11 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
         const float* cur = lds + (st & 1) * STAGE;
         const float* nxt = lds + ((st + 1) & 1) * STAGE;
         bool between = false;  // some of the panel's frames lie behind an utterance
-        if constexpr (WALK) between = walk0 + BK > oa.Tp || r_begin + (st + 1) * BK > r_end;
+        int left = 0;          // frames up to the end of the run
+        if constexpr (WALK) {
+            left = r_end - r_begin - st * BK;
+            between = walk0 + BK > oa.Tp || left < BK;
+        }
 #pragma unroll
         for (int g = 0; g < GROUPS; ++g) {
             const int u = g & 1;
@@ -548,9 +552,10 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         const int l = g * 8 + 4 * (lane >> 5) + q;
-                        int t = walk0 + l;
-                        while (t >= oa.pitch) t -= oa.pitch;
-                        fb[u][q] = t < oa.Tp && r_begin + st * BK + l < r_end ? fb[u][q] : 0.f;
+                        unsigned t = walk0 + l;
+                        t = min(t, t - oa.pitch);  // a panel may reach into the utterance after the next one, no further:
+                        t = min(t, t - oa.pitch);  // wgrad_walks
+                        fb[u][q] = t < (unsigned)oa.Tp && l < left ? fb[u][q] : 0.f;
                     }
                 }
             }
@@ -568,7 +573,8 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
         }
         if constexpr (WALK) {
             walk0 += BK;
-            while (walk0 >= oa.pitch) walk0 -= oa.pitch;
+            walk0 = min((unsigned)walk0, (unsigned)(walk0 - oa.pitch));
+            walk0 = min((unsigned)walk0, (unsigned)(walk0 - oa.pitch));
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing may land in LDS once it is used otherwise
@@ -647,7 +653,7 @@ int launch_any(const AnyPlan& pl, OA oa, OB ob, EP ep, long long M, long long N,
 
 bool wgrad_walks(const ConvDesc& d)
 {
-    return d.s == 1 && d.x_pitch == d.y_pitch && d.x_halo == d.y_halo && d.x_halo >= d.p && d.slack >= 64 &&
+    return d.s == 1 && d.x_pitch == d.y_pitch && d.x_halo == d.y_halo && d.x_halo >= d.p && d.slack >= 64 && d.x_pitch >= PANEL / 2 &&
            (d.B == 1 || d.x_halo > 0 || d.p == 0);
 }
 

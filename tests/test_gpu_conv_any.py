@@ -75,7 +75,8 @@ def test_conv_any_edges(shape, dtype):
     _check(to_host(dw), dw_o, False, "dw without db")
 
 
-@pytest.mark.parametrize("shape", [(3, 50, 32, 64, 5, 1), (2, 75, 64, 64, 11, 1), (5, 3, 32, 64, 3, 1), (1, 401, 32, 64, 13, 1)],
+@pytest.mark.parametrize("shape", [(3, 50, 32, 64, 5, 1), (2, 75, 64, 64, 11, 1), (5, 3, 32, 64, 3, 1), (40, 1, 32, 64, 3, 1),
+                                   (1, 401, 32, 64, 13, 1)],
                          ids=lambda s: "x".join(map(str, s)))
 def test_fp32_weight_gradient_infinite_x(shape):
     """An infinity in the first or last frame of an utterance reaches the taps whose sum contains that frame and no
