@@ -17,7 +17,7 @@
 // a fixed order -- inside the train step that pass is the layer's GLU, which would be launched anyway.
 // Measured inside the train step of the 10M-parameter network in fp32 (4 x 400 frames, k = 11, 256 -> 512, 4.6 GFLOP
 // a pass; 30 us at the pipe's rate), before (64 x 64 tiles of scalar FMAs, one workgroup per tile) and now: forward
-// 476 -> 46 us, data gradient 1190 -> 58, weight gradient 325 -> 70 (the last two side by side), step 11.4 -> 1.02 ms.
+// 476 -> 47 us, data gradient 1190 -> 64, weight gradient 325 -> 66 (the last two side by side), step 11.4 -> 1.00 ms.
 #include <type_traits>
 #include "common.h"
 

@@ -1,10 +1,11 @@
-// One training step of the conv-GLU network with the CTC criterion, sequenced on one
+// One training step of the conv-GLU network with the CTC or ASG criterion, ordered by the caller's
 // stream with no host synchronisation (paper Sec. 2.3: network forward, criterion,
 // backward; the optimiser update is a separate stage of the paper's loop, Sec. 2.4).
 //
 //   forward   for each layer: conv1d(+bias) -> [GLU]      (pre-GLU and post-GLU kept)
-//   criterion log-softmax + CTC on the fp32 logits; yields d loss / d logits directly
-//   backward  for each layer, last to first: [GLU bwd] -> wgrad(+dbias) -> dgrad
+//   criterion log-softmax + CTC, or ASG, on the fp32 logits; yields d loss / d logits directly
+//   backward  for each layer, last to first: [GLU bwd] -> wgrad(+dbias) and dgrad, in one launch where their tiles
+//             pack, else dgrad on the caller's stream and most wgrads on a helper stream that it waits for
 //             (dgrad is skipped for layer 0: the features need no gradient)
 #include <mutex>
 #include <vector>
@@ -21,7 +22,8 @@ constexpr int HALO = LAYOUT_HALO;
 constexpr int SLACK = LAYOUT_SLACK;            // allocated after the last utterance
 constexpr int SLACK_ZERO = LAYOUT_SLACK_ZERO;  // of which kept zero
 
-// A helper stream (default priority) on which the weight gradients run: wgrad of layer i needs
+// A helper stream (default priority) for the weight gradients that neither share a launch with their layer's data
+// gradient (conv_bwd) nor are shorter than its events (main_wgrad): wgrad of layer i needs
 // only dy_i and h_{i-1}, nothing downstream needs it before the step ends, and neither wgrad
 // nor dgrad fills all 256 CUs with its tile grid alone -- side by side they do.  Created once
 // per device on first use; no device memory is allocated.
@@ -325,11 +327,15 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
 
     // ---- backward.  dh = gradient wrt layer i's output (dense); dy = gradient wrt its conv
     // output: the haloed result of the GLU backward, or dh itself for a layer without GLU.
-    // Main stream: the dgrad chain.  Where the shapes allow, the data gradient of layer i applies
-    // the GLU backward of layer i-1 in its epilogue and writes dy_{i-1} directly; otherwise dh
-    // goes to memory and a GLU-backward kernel follows.  Side stream: wgrad (+dbias) of every
-    // layer, each started as soon as its dy exists.  dy buffers rotate over three slots, so the
-    // writer of dy_i only has to wait for the weight gradient of layer i+3.
+    // Caller's stream: the dgrad chain.  Where the shapes allow, the data gradient of layer i applies
+    // the GLU backward of layer i-1 in its epilogue or in the pass that adds its planes, and writes dy_{i-1} directly;
+    // otherwise dh goes to memory and a GLU-backward kernel follows.  A layer's weight gradient (+dbias) is one of
+    //   part of that launch     (p.bwd[i].ok and the bias gradient wanted): no event,
+    //   on the caller's stream  (main_wgrad): no event,
+    //   on the helper stream    (the others): started by ready[i] as soon as its dy exists, done[i] recorded behind it
+    //                           and helped[i] set.
+    // dy buffers rotate over three slots, so the writer of dy_i only has to wait for the weight gradient of layer i+3,
+    // if that one is on the helper stream.
     SideStream* side = side_stream(n);
     auto hip_ok = [&](hipError_t e) { if (e != hipSuccess) { note_hip_error(e); return false; } return true; };
     int on_helper = n;                  // layers n - 1 .. on_helper have a weight gradient on the helper stream, some of them
@@ -397,8 +403,7 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
             }
             continue;
         }
-        // layer 0 has no data gradient: its weight gradient takes the main stream, next to the
-        // helper stream's last launch, instead of queueing behind it
+        // (layer 0's takes the caller's stream next to the helper stream's last launch instead of queueing behind it)
         const bool on_main = main_wgrad(p, l, i), on_side = side && !on_main;
         hipStream_t wst = on_side ? side->stream : st;
         if (on_side) {
@@ -418,9 +423,9 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
             d = f;
             xin = ws + p.xfold;
         }
-        // weight gradient on the side stream.  Where the MFMA kernel takes it, the bias gradient is one more
-        // column of tiles of the same launch; otherwise it is a (small, bandwidth-bound) column sum that stays
-        // on the main stream, which has the shorter chain
+        // The bias gradient comes out of the same launch, except of bf16 layers whose reduction does not walk through
+        // haloed frames: there it is a (small, bandwidth-bound) column sum that stays on the caller's stream, which has
+        // the shorter chain
         const bool fused_dbias = dbiases[i] && conv_wgrad_fuses_dbias(d, dtype, dy_dt);
         rc = conv_wgrad(d, xin, dy, dweights[i], (fused_dbias || !side) ? dbiases[i] : nullptr, dtype, dy_dt, 0,
                         ws + (on_main ? p.conv0 : p.conv), on_main ? p.conv0_bytes : p.conv_bytes, wst, cut_wgrad(p, dy_dt));
