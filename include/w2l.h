@@ -293,8 +293,9 @@ int w2l_logmel_fwd(const float *wav, const int *wav_len, void *feat, int *feat_l
  * tgt_len, loss, logits are device pointers.  With W2L_BF16, activations and
  * gradients between layers are stored as bf16, the last layer's output (logits), the
  * log-softmax and CTC are fp32.
- * Concurrency: the step runs the weight gradients on one helper stream (default priority,
- * created on first use, one per device, never destroyed) tied to `stream` by events, and is
+ * Concurrency: weight gradients that neither share a launch with their layer's data gradient nor are
+ * too short for it run on one helper stream (default priority, created on first use, one per device,
+ * never destroyed) tied to `stream` by events; the step is
  * complete in `stream` order when the call's work on `stream` is.  Host threads may call
  * concurrently for different devices; two steps in flight on the SAME device at the same time
  * (two streams or two host threads) share that helper stream and its events and are not

@@ -61,3 +61,43 @@ def test_bias_gradients_not_wanted(P):
             assert np.isnan(got["db"][i]).all()
             got["db"][i] = ref["db"][i]
         check_train_step(got, ref, "bf16")
+
+
+@pytest.mark.parametrize("net, dtype", [("shared", "bf16"), ("two streams", "bf16"), ("shared", "f32")])
+def test_captured_step_replays_the_eager_one(P, net, dtype):
+    """A train step recorded into a HIP graph leaves the eager step's bits at every replay, with eager work of the same
+    kernels on other data, and synchronisations, in between."""
+    import torch
+    from workloads.device import empty, to_dev
+    widths = [(5, 128, 256)] * 3 if net == "shared" else [(3, 320, 256), (7, 128, 128), (5, 64, 128)]
+    layers = [dict(k=5, stride=1, cin=40, cout=2 * widths[0][1], glu=1)] + [dict(k=k, stride=1, cin=a, cout=b, glu=1) for k, a, b in widths]
+    layers += [dict(k=1, stride=1, cin=widths[-1][2] // 2, cout=29, glu=0)]
+
+    def state(seed):
+        cfg = W.small_model(seed, 16, 70, 98, 40, layers, dtype == "bf16", 2, 8)
+        code = P.W2L_BF16 if dtype == "bf16" else P.W2L_F32
+        s = dict(w=[to_dev(a, dtype) for a in cfg["weights"]], b=[to_dev(a) for a in cfg["biases"]], dw=[empty(a.shape) for a in cfg["weights"]],
+                 db=[empty(a.shape) for a in cfg["biases"]], loss=empty((16,)), logits=empty((16, 98, 29)))
+        args = [to_dev(cfg["x"], dtype), to_dev(cfg["in_len"]), to_dev(cfg["targets"]), to_dev(cfg["tgt_len"])]
+        s["ws"] = P.workspace(P.w2l_train_step_workspace_bytes(layers, 16, 98, cfg["targets"].shape[1], code))
+        s["run"] = lambda: P.w2l_train_step(layers, s["w"], s["b"], s["dw"], s["db"], *args, s["loss"], s["logits"], cfg["blank"], 1.0, s["ws"])
+        s["out"] = [s["loss"], s["logits"]] + s["dw"] + s["db"]
+        return s
+
+    a, other = state(95), state(96)
+    other["run"]()
+    a["run"]()
+    torch.cuda.synchronize()
+    ref = [t.clone() for t in a["out"]]
+    assert all(torch.isfinite(t).all() for t in ref)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        a["run"]()
+    for _ in range(4):
+        for t in a["out"]:
+            t.fill_(float("nan"))
+        a["ws"].fill_(255)
+        other["run"]()
+        g.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(t, r) for t, r in zip(a["out"], ref))
