@@ -69,6 +69,24 @@ def test_logmel_matches_oracle(P, kw):
     check(feat, flen, cfg["wav"], cfg["wav_len"], n_mels, **kw)
 
 
+@pytest.mark.parametrize("kw", [
+    dict(B=3, n=3000, n_mels=255, win=512, hop=100),            # whole window, most bands
+    dict(B=2, n=2500, n_mels=16, win=383, hop=111),             # odd window below the unchecked rows; one sixteen of bands
+    dict(B=2, n=900, n_mels=17, win=2, hop=7),                  # smallest window
+    dict(B=5, n=405, n_mels=64, win=400, hop=1),                # fewer frames than a group of four, and two groups
+    dict(B=1, n=40001, n_mels=33, win=65, hop=2, fmin=100.0, fmax=3000.0),  # more groups than wavefronts on the chip
+    dict(B=2, n=3000, n_mels=2, win=400, hop=160),              # bands too wide for the kernel's tables: the one for any size
+])
+def test_logmel_512_edges(P, kw):
+    """The transform of 512 points in registers at the edges of its rows, groups of frames and sixteens of bands."""
+    kw = dict(kw)
+    B, n, n_mels = kw.pop("B"), kw.pop("n"), kw.pop("n_mels")
+    cfg = W.waveforms(seed=17, B=B, n_lo=max(kw["win"], n - 3 * kw["hop"]), n_hi=n)
+    Tmax = oracle.logmel_num_frames(n, kw["win"], kw["hop"]) + 1
+    feat, flen = run_logmel(P, cfg["wav"], cfg["wav_len"], Tmax, n_mels, nfft=512, **kw)
+    check(feat, flen, cfg["wav"], cfg["wav_len"], n_mels, nfft=512, **kw)
+
+
 def test_logmel_benchmark_shape_and_bf16(P):
     """The shape bench.py times (B=8, up to 240240 samples -> 1500 frames of 80 bands): every
     element against the oracle; then the bf16 output the train step would read."""
