@@ -33,6 +33,8 @@ struct CtcDims {
     int len_div;  // in_len[] counts frames before the network's total stride: the criterion sees ceil(in_len / len_div)
     int Sp;    // lattice row pitch in states = 2*Lmax+4 (the last pair is a spare); a state is 8 bytes
     int rows;  // lattice rows per utterance = Tp + 2*LAT_PAD: frame t is row LAT_PAD + t
+    int waves; // wavefronts that run the recursion (more of a workgroup: stagers)
+    int trows; // rows of the score table: the classes, or (fewer) the blank and the positions of the target
 };
 
 __device__ __forceinline__ int crit_len(int n, int div) { return (n < 0 || div <= 1) ? n : (n + div - 1) / div; }
@@ -102,14 +104,17 @@ __device__ __forceinline__ double pair_log2(float v, int e) { return v > 0.f ? (
 // rows that every utterance's lattice has at either end (alpha runs off the far end, beta off
 // the near one) or in rows t >= T_b that nobody reads.
 // Stored per frame and state: the pair (v, biased e), the integer as the bits of the second float.
-// NQ > 0 (the class rows of a block of frames fit NQ values per thread): the scores do not come
-// through per-lane loads at all.  The workgroup keeps the rows lp[t, 0..C-1] of the current
-// block of BLK frames in LDS, already split into (mantissa, exponent), class-major
-// (the frames of one class are adjacent, so a step's read is the lane's fixed address plus a
-// constant), in two buffers: the rows of the next block are loaded (coalesced) before the
-// block's steps start and written to the other buffer after them, so the recursion itself issues
+// NQ > 0 (the score rows of a block of frames fit NQ values per stager): the scores do not come
+// through per-lane loads at all.  The workgroup keeps them for the current block of BLK frames in LDS -- a row per class, or
+// per position of the target where those are fewer -- already split into (mantissa, exponent), a row's frames
+// adjacent (a step's read is the lane's fixed address plus a constant), in two buffers: the values of the next block
+// are loaded before the block's steps start and written to the other buffer, so the recursion itself issues
 // no vector loads and never waits on the memory counter that its own lattice stores keep busy.
-// NQ == 0 (large alphabets): the scores lp[t, blank] and lp[t, label] are gathered per lane
+// STAGERS wavefronts of their own do this where the recursion has no more than four: splitting a value is about as much
+// work as a step, and on the recursion's wavefronts it was serial with the steps (the launch for 32 x 750 frames, 29 classes,
+// 2 values a thread: 55 -> 47 us; for 4 x 187 frames, 200 classes, where scores were gathered: 26 -> 15).  Targets of more
+// wavefronts stage on these.
+// NQ == 0 (large alphabets and targets): the scores lp[t, blank] and lp[t, label] are gathered per lane
 // BLK frames early into a register ring.
 // BLK = 16, or 12 where that brings the target onto four wavefronts (64 + 3 (64 - BLK) owned lanes):
 // the step is bound by instruction issue -- one wavefront alone on its SIMD issues the ~25
@@ -184,9 +189,10 @@ __global__ __launch_bounds__(1024) void ctc_lattice(const float* __restrict__ lp
     }
     // pair i (in this direction's order) = states q = 2i (blank), 2i+1 (label i, absent for i = L)
     // this lane's group of PPT pairs: wavefront 0 has nobody on its left and owns all 64 of its lanes' groups
+    const bool stager = NT > 64 * d.waves ? wave >= d.waves : true;  // brings scores into LDS
     const int gi = wave == 0 ? lane : 64 + (wave - 1) * OWN_LANES + lane - HALO_LANES;
     const bool owner = wave == 0 || lane >= HALO_LANES;  // not a mirror of the wavefront on the left
-    int cls[PPT];        // class of the label state
+    int cls[PPT], trow[PPT];  // class of the label state, its row in the score table
     bool skip[PPT];      // label state may be entered from the label of the pair to the left
     unsigned slot[PPT];  // byte offset of the pair in a lattice row (the spare pair for lanes that own no real pair)
     float vb[PPT], vl[PPT];
@@ -197,6 +203,7 @@ __global__ __launch_bounds__(1024) void ctc_lattice(const float* __restrict__ lp
         const bool real = gi >= 0 && i <= L, has_l = gi >= 0 && i < L;
         const int li = dir ? L - 1 - i : i;          // label index in the target
         cls[j] = has_l ? lab[li] : d.blank;
+        trow[j] = d.trows == d.C ? cls[j] : has_l ? 1 + li : 0;
         skip[j] = has_l && i >= 1 && lab[dir ? li + 1 : li - 1] != cls[j];
         slot[j] = 16u * (unsigned)((real && owner) ? i : d.Lmax + 1);
         // the state "before frame 0": all mass in front of pair 0, so that frame 0 comes out of the recursion itself
@@ -210,7 +217,7 @@ __global__ __launch_bounds__(1024) void ctc_lattice(const float* __restrict__ lp
     float2* lat = (dir ? beta : alpha) + ((size_t)b * d.rows + LAT_PAD) * d.Sp;  // row of frame 0
     auto frame = [&](int step) { return dir ? T - 1 - step : step; };
 
-    const int nwaves = NT >> 6;
+    const int nwaves = d.waves;
     const int tblocks = (T + BLK - 1) / BLK;
     // running pointers instead of per-step index arithmetic: the lattice row written next
     // (and, without the table, the score row fetched next, clamped at the last frame)
@@ -289,24 +296,26 @@ __global__ __launch_bounds__(1024) void ctc_lattice(const float* __restrict__ lp
     };
 
     if constexpr (TABLE) {
-        // element e of a block's rows: step k = e / C of the block, class c = e % C.  In memory the
-        // rows of a block are adjacent (in reversed order for beta), so an element's address is the
-        // block's base plus a per-thread constant; steps past the last frame are clamped to a
-        // valid address (whatever they read only feeds the spare rows).
-        const int nel = BLK * d.C, per_buf = d.C * TABLE_PITCH, last = T * d.C - 1;
-        int goff[NQ], loff[NQ];
-        float raw0[NQ], raw1[NQ];  // rows in flight: loaded two blocks before the block that uses them
+        // element e of a block: step k = e / rows of the block, table row r = e % rows.  Its address is the block's base plus a
+        // per-thread constant; steps past the last frame are clamped to it (whatever they read only feeds the spare rows).
+        const bool shared = NT == 64 * d.waves;  // the recursion's wavefronts are the stagers
+        const int nst = NT > 64 * d.waves ? NT - 64 * d.waves : NT, sid = tid - (NT - nst);
+        const int nel = BLK * d.trows, per_buf = d.trows * TABLE_PITCH;
+        int koff[NQ], goff[NQ], loff[NQ];
+        float raw0[NQ], raw1[NQ];  // values in flight: loaded two blocks before the block that uses them
+        if (stager) {
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const int e = min(tid + q * NT, nel - 1);
-            const int k = e / d.C, c = e - k * d.C;
-            goff[q] = dir ? c - k * d.C : e;
-            loff[q] = (tid + q * NT < nel) ? c * TABLE_PITCH + k : -1;
+            for (int q = 0; q < NQ; ++q) {
+                const int e = min(sid + q * nst, nel - 1);
+                const int k = e / d.trows, r = e - k * d.trows;
+                koff[q] = k;
+                goff[q] = d.trows == d.C ? r : r >= 1 && r <= L ? lab[r - 1] : d.blank;
+                loff[q] = (sid + q * nst < nel) ? r * TABLE_PITCH + k : -1;
+            }
         }
         auto load_rows = [&](int tb, float (&raw)[NQ]) {
-            const int base = dir ? (T - 1 - tb * BLK) * d.C : tb * BLK * d.C;
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) raw[q] = lpb[min(max(base + goff[q], 0), last)];
+            for (int q = 0; q < NQ; ++q) raw[q] = lpb[frame(min(tb * BLK + koff[q], T - 1)) * d.C + goff[q]];
         };
         auto write_rows = [&](int buf, const float (&raw)[NQ]) {
 #pragma unroll
@@ -317,15 +326,15 @@ __global__ __launch_bounds__(1024) void ctc_lattice(const float* __restrict__ lp
                 if (loff[q] >= 0) tbl[buf * per_buf + loff[q]] = make_float2(pm, __uint_as_float(pq));
             }
         };
-        const float2* tb_blank = tbl + d.blank * TABLE_PITCH;
+        const float2* tb_blank = tbl + (d.trows == d.C ? d.blank : 0) * TABLE_PITCH;
         const float2* tb_label[PPT];
 #pragma unroll
-        for (int j = 0; j < PPT; ++j) tb_label[j] = tbl + cls[j] * TABLE_PITCH;
+        for (int j = 0; j < PPT; ++j) tb_label[j] = tbl + trow[j] * TABLE_PITCH;
         // block tb: its scores are in table buffer tb & 1; the rows of block tb + 2 are requested into
         // `load`, the rows of block tb + 1 (requested a block ago) are in `next` and go into the other buffer
         auto block = [&](int tb, float (&next)[NQ], float (&load)[NQ]) {
             const int cur = (tb & 1) * per_buf;
-            load_rows(tb + 2, load);
+            if (shared) load_rows(tb + 2, load);
             {
                 float2 nb = tb_blank[cur], nl[PPT];  // scores of the block's first frame
 #pragma unroll
@@ -349,14 +358,32 @@ __global__ __launch_bounds__(1024) void ctc_lattice(const float* __restrict__ lp
             }
             // the rows in flight are not touched before the steps are done (tied to a value the last step
             // produced): their wait must not move ahead of the steps
+            if (shared) {
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) asm volatile("" : "+v"(next[q]), "+v"(vb[0]));
-            boundary(tb, true, [&] { write_rows((tb + 1) & 1, next); });
+                for (int q = 0; q < NQ; ++q) asm volatile("" : "+v"(next[q]), "+v"(vb[0]));
+            }
+            boundary(tb, true, [&] { if (shared) write_rows((tb + 1) & 1, next); });
         };
-        load_rows(0, raw0);
-        write_rows(0, raw0);
-        load_rows(1, raw1);
+        if (stager) {
+            load_rows(0, raw0);
+            load_rows(1, raw1);
+            write_rows(0, raw0);
+        }
         __syncthreads();
+        if (wave >= nwaves) {
+            for (int tb = 0; tb < tblocks; tb += 2) {
+                load_rows(tb + 2, raw0);
+                write_rows((tb + 1) & 1, raw1);
+                __syncthreads();
+                if (tb + 1 < tblocks) {
+                    load_rows(tb + 3, raw1);
+                    write_rows(tb & 1, raw0);
+                    __syncthreads();
+                }
+            }
+            return;
+        }
+        __builtin_amdgcn_s_setprio(3);  // the stagers take what the recursion leaves of a SIMD
         for (int tb = 0; tb < tblocks; tb += 2) {
             block(tb, raw1, raw0);
             if (tb + 1 < tblocks) block(tb + 1, raw0, raw1);
@@ -534,8 +561,9 @@ size_t grad_lds_bytes(int Lmax, int C)
 // every further one.  The step is bound by instruction issue, so a wavefront wants a SIMD of its own: the
 // smallest PPT that fits four wavefronts, with blocks of 16 frames if that fits (208 lanes) and of 12 (220
 // lanes) otherwise; targets beyond 220 * 4 pairs take four pairs per lane on as many wavefronts as they need.
-// NQ > 0 (score table in LDS): a block's class rows must fit 8 elements per thread and, in two buffers, 64 KB.
-struct CtcLaunch { int ppt, blk, nt, nq; size_t lds; };
+// NQ > 0 (score table in LDS): a block's score rows must fit 8 elements per stager and, in two buffers, 64 KB.
+constexpr int STAGERS = 4;
+struct CtcLaunch { int ppt, blk, waves, nt, nq, trows; size_t lds; };
 CtcLaunch ctc_launch_config(int C, int Lmax)
 {
     const int pairs = Lmax + 1;
@@ -545,11 +573,13 @@ CtcLaunch ctc_launch_config(int C, int Lmax)
         if (pairs <= (64 + 3 * 52) * p) { ppt = p; blk = 12; break; }
     }
     const int own = 64 - blk, groups = (pairs + ppt - 1) / ppt;
-    const int nt = 64 * (groups <= 64 ? 1 : 1 + (groups - 64 + own - 1) / own);
-    const long long nel = (long long)blk * C;
-    const size_t table_bytes = (size_t)2 * C * (blk + 1) * 8;
-    const int nq = (nel <= 8LL * nt && table_bytes <= 64 * 1024) ? (nel <= 2LL * nt ? 2 : (nel <= 4LL * nt ? 4 : 8)) : 0;
-    return CtcLaunch{ppt, blk, nt, nq, nq ? table_bytes : 0};
+    const int waves = groups <= 64 ? 1 : 1 + (groups - 64 + own - 1) / own;
+    const int trows = pairs < C ? pairs : C, nst = 64 * (waves <= 4 ? STAGERS : waves);
+    const long long nel = (long long)blk * trows;
+    const size_t table_bytes = (size_t)2 * trows * (blk + 1) * 8;
+    const int nq = (nel <= 8LL * nst && table_bytes <= 64 * 1024) ? (nel <= 2LL * nst ? 2 : (nel <= 4LL * nst ? 4 : 8)) : 0;
+    const int nt = 64 * waves + (nq && waves <= 4 ? nst : 0);
+    return CtcLaunch{ppt, blk, waves, nt, nq, trows, nq ? table_bytes : 0};
 }
 
 struct WsLayout { size_t lp, logp, order, cstart, alpha, beta, total; };
@@ -640,7 +670,7 @@ int ctc_run(const float* input, int is_logits, const int* targets, const int* in
     float2* beta = reinterpret_cast<float2*>(ws + w.beta);
     int* sort_order = reinterpret_cast<int*>(ws + w.order);
     int* sort_start = reinterpret_cast<int*>(ws + w.cstart);
-    CtcDims d{B, Tp, C, Lmax, blank, len_div, 2 * Lmax + 4, Tp + 2 * LAT_PAD};
+    CtcDims d{B, Tp, C, Lmax, blank, len_div, 2 * Lmax + 4, Tp + 2 * LAT_PAD, 0, 0};
 
     const size_t lds2 = grad_lds_bytes(Lmax, C);
     if (lds2 > 160 * 1024) return W2L_ERR_SHAPE;
@@ -651,6 +681,8 @@ int ctc_run(const float* input, int is_logits, const int* targets, const int* in
     const CtcLaunch cfg = ctc_launch_config(C, Lmax);
     if (cfg.nt > 1024) return W2L_ERR_SHAPE;
     const int ppt = cfg.ppt, blk = cfg.blk, nt = cfg.nt, nq = cfg.nq;
+    d.waves = cfg.waves;
+    d.trows = cfg.trows;
     const dim3 g1(3, B), b1(nt);  // alpha, beta, and the sort of the target for the gradient kernel
     const size_t lds1 = cfg.lds;
 #define W2L_CTC_LAUNCH(P_, Q_, B_)                                                                                    \

@@ -272,6 +272,18 @@ def test_ctc_large_alphabet_gathers_scores_per_lane(P):
     _check_ctc(loss, grad, loss_o, dz_o)
 
 
+@pytest.mark.parametrize("Cc,Lmax", [(12, 11), (13, 11), (14, 11), (300, 127), (400, 207), (90, 63), (90, 64)])
+def test_ctc_score_rows_per_class_or_position(P, Cc, Lmax):
+    """The score table has a row per class, or per position of the target where those are fewer: at the change from one to the
+    other, and at the largest tables (128 rows) and first gathered sizes."""
+    T = 2 * Lmax + 21
+    cfg = W.config2(seed=300 + Cc, B=2, T=T, Cc=Cc, in_lo=T - 5, in_hi=T, l_lo=Lmax, l_hi=Lmax)
+    cfg["tgt_len"][1] = Lmax // 2
+    loss, grad = _run_ctc(P, cfg["logits"], 1, cfg["targets"], cfg["in_len"], cfg["tgt_len"], 0, 1.0)
+    loss_o, _, dz_o = oracle.ctc_from_logits(cfg["logits"].astype(np.float64), cfg["targets"], cfg["in_len"], cfg["tgt_len"])
+    _check_ctc(loss, grad, loss_o, dz_o)
+
+
 def test_ctc_peaked_and_impossible_scores(P):
     # log-probabilities far outside the range of a linear fp32 recursion (about -1300 per frame), and -inf entries
     rng = np.random.default_rng(22)
