@@ -68,10 +68,10 @@ int conv_dgrad(const ConvDesc& d, const void* dy, const void* w, void* dx, int d
     return conv_dgrad_generic(d, dy, w, dx, dt, dydt, st, scratch, scratch_bytes);
 }
 
-int conv_fwd_parts(const ConvDesc& d, int dt) { return conv_fwd_is_generic(d, dt) ? conv_fwd_generic_parts(d) : conv_fwd_mfma_parts(d); }
+int conv_fwd_parts(const ConvDesc& d, int dt) { return conv_fwd_is_generic(d, dt) ? conv_fwd_generic_parts(d, dt) : conv_fwd_mfma_parts(d); }
 int conv_dgrad_parts(const ConvDesc& d, int dt, int dydt)
 {
-    return conv_dgrad_is_generic(d, dt, dydt) ? conv_dgrad_generic_parts(d) : conv_dgrad_mfma_parts(d);
+    return conv_dgrad_is_generic(d, dt, dydt) ? conv_dgrad_generic_parts(d, dt) : conv_dgrad_mfma_parts(d);
 }
 int conv_fwd_partial(const ConvDesc& d, const void* x, const void* w, int dt, float* part, hipStream_t st)
 {
@@ -81,10 +81,10 @@ int conv_dgrad_partial(const ConvDesc& d, const void* dy, const void* w, int dt,
 {
     return conv_dgrad_is_generic(d, dt, dydt) ? conv_dgrad_generic_partial(d, dy, w, dt, dydt, part, st) : conv_dgrad_mfma_partial(d, dy, w, part, st);
 }
-size_t conv_fwd_scratch(const ConvDesc& d, int dt) { return conv_fwd_is_generic(d, dt) ? conv_fwd_generic_scratch(d) : conv_fwd_mfma_scratch(d); }
+size_t conv_fwd_scratch(const ConvDesc& d, int dt) { return conv_fwd_is_generic(d, dt) ? conv_fwd_generic_scratch(d, dt) : conv_fwd_mfma_scratch(d); }
 size_t conv_dgrad_scratch(const ConvDesc& d, int dt, int dydt)
 {
-    return conv_dgrad_is_generic(d, dt, dydt) ? conv_dgrad_generic_scratch(d) : conv_dgrad_scratch_bytes(d);
+    return conv_dgrad_is_generic(d, dt, dydt) ? conv_dgrad_generic_scratch(d, dt) : conv_dgrad_scratch_bytes(d);
 }
 
 // scratch of a weight gradient: column sums (in the 256 bytes a channel that a workspace has to have at least: the sums
@@ -94,7 +94,7 @@ size_t conv_wgrad_scratch_bytes(const ConvDesc& d, int dt, int dydt, bool split)
 {
     const size_t rest = d.Cout <= 32                    ? conv_wgrad_skinny_scratch(d.Cin, d.Cout, d.k)
                         : !split                        ? 0
-                        : wgrad_is_generic(d, dt, dydt) ? conv_wgrad_generic_scratch(d)
+                        : wgrad_is_generic(d, dt, dydt) ? conv_wgrad_generic_scratch(d, dt)
                                                         : conv_wgrad_mfma_scratch(d);
     return wgrad_dbias_scratch(d) + rest;
 }

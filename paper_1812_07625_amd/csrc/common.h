@@ -125,9 +125,9 @@ size_t conv_dgrad_scratch(const ConvDesc& d, int dt, int dydt);
 
 // kernels for any shape and type (conv_generic.hip).  scratch (optional): *_scratch() bytes; given them, a problem
 // with too few tiles for the chip splits its reduction and adds the fp32 sums in a finishing launch
-size_t conv_fwd_generic_scratch(const ConvDesc& d);
-size_t conv_dgrad_generic_scratch(const ConvDesc& d);
-size_t conv_wgrad_generic_scratch(const ConvDesc& d);
+size_t conv_fwd_generic_scratch(const ConvDesc& d, int dt);
+size_t conv_dgrad_generic_scratch(const ConvDesc& d, int dt);
+size_t conv_wgrad_generic_scratch(const ConvDesc& d, int dt);
 // forms of w2l_conv1d_launch_config
 enum { CONV_BF16 = 0, CONV_REGISTERS = 1, CONV_CHUNKS = 2, CONV_PLAIN = 3, CONV_NARROW = 4 };
 int conv_fwd_generic_form(const ConvDesc& d, int dt, size_t scratch_bytes, int* form, int* splits);
@@ -141,8 +141,8 @@ int conv_wgrad_generic(const ConvDesc& d, const void* x, const void* dy, float* 
                        hipStream_t st, void* scratch = nullptr, size_t scratch_bytes = 0);
 // The same, leaving the *_parts() planes of fp32 sums ([parts][B * frames][channels], dense) to the finish_* pass that
 // the caller fuses with its next elementwise step.
-int conv_fwd_generic_parts(const ConvDesc& d);
-int conv_dgrad_generic_parts(const ConvDesc& d);
+int conv_fwd_generic_parts(const ConvDesc& d, int dt);
+int conv_dgrad_generic_parts(const ConvDesc& d, int dt);
 int conv_fwd_generic_partial(const ConvDesc& d, const void* x, const void* w, int dt, float* part, hipStream_t st);
 int conv_dgrad_generic_partial(const ConvDesc& d, const void* dy, const void* w, int dt, int dydt, float* part, hipStream_t st);
 // narrow outputs (Cout <= 32): row-chunked reduction, SKINNY_CHUNKS partials summed in a fixed order

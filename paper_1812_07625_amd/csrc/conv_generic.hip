@@ -1,6 +1,8 @@
 // Temporal-convolution kernels for any shape and type, on the fp32 matrix instruction
 // (v_mfma_f32_32x32x2_f32: fp32 operands, fp32 accumulation).
 //
+// (fp32 tensors in the train step's layout: their exact split into bf16 values, gemm_split_k.)
+//
 // These take every problem that the bf16 kernels do not: fp32 tensors, channel counts that are not multiples of 8,
 // strides that do not fold, calls without workspace.  bf16 operands are widened on their way into LDS, so their
 // products stay exact.  Each of the three passes is the GEMM C[m,n] = sum_r A(m,r) * B(r,n) over the convolution's
@@ -17,7 +19,8 @@
 // a fixed order -- inside the train step that pass is the layer's GLU, which would be launched anyway.
 // Measured inside the train step of the 10M-parameter network in fp32 (4 x 400 frames, k = 11, 256 -> 512, 4.6 GFLOP
 // a pass; 30 us at the pipe's rate), before (64 x 64 tiles of scalar FMAs, one workgroup per tile) and now: forward
-// 476 -> 47 us, data gradient 1190 -> 64, weight gradient 325 -> 66 (the last two side by side), step 11.4 -> 1.00 ms.
+// 476 -> 47 us, data gradient 1190 -> 64, weight gradient 325 -> 66 (the last two side by side), step 11.4 -> 1.00 ms,
+// and 0.86 ms with gemm_split_k.
 #include <type_traits>
 #include "common.h"
 
@@ -41,10 +44,10 @@ __device__ __forceinline__ Line no_line() { return Line{0, 0, 0}; }
 // from the first line of its tile or panel in 32 bits of bytes, so they have to lie within 2 GB of each other.
 inline bool near_lines(long long elements) { return elements < (1LL << 29) - TILE; }
 // Frames between the first and the last of a tile's rows at most; row r: frame step * (r % count) of utterance r / count
-inline long long row_reach(int count, int step, int pitch)
+inline long long row_reach(int count, int step, int pitch, int rows = TILE)
 {
-    const long long cross = (TILE - 2LL + count) / count, gap = pitch - (long long)count * step;  // utterance ends met, and what each adds
-    const long long a = (TILE - 1LL) * step + cross * (gap > 0 ? gap : 0), b = cross * pitch + (count - 1LL) * step;
+    const long long cross = (rows - 2LL + count) / count, gap = pitch - (long long)count * step;  // utterance ends met, and what each adds
+    const long long a = (rows - 1LL) * step + cross * (gap > 0 ? gap : 0), b = cross * pitch + (count - 1LL) * step;
     return a < b ? a : b;
 }
 
@@ -56,6 +59,7 @@ struct XWindow {  // fwd A: m = (b,t') -> x[b, s t' - p ..], r = (j,ci)
     // every line starts and ends on a 16-byte chunk of fp32
     bool chunks() const { return aligned16(base) && Cin % 4 == 0; }
     bool fast() const { return chunks() && k * Cin % 32 == 0 && (p == 0 || halo >= p) && near_lines(row_reach(Tp, s, pitch) * Cin); }
+    bool tall() const { return near_lines(row_reach(Tp, s, pitch, 2 * TILE) * Cin + 2 * TILE); }  // as near over 128 rows
     __device__ __forceinline__ long long fast_line(int m) const { return line(m < M ? m : M - 1).off; }
     __device__ __forceinline__ Line line(int m) const
     {
@@ -96,6 +100,7 @@ struct DyWindow {  // dgrad A: m = (b, frame of the phase) -> its dy frames, r =
     static __host__ __device__ Phase phase(int f, int T_, int k, int s, int p) { return phase_of((int)(((long long)f + p) % s), T_, k, s, p); }
     bool chunks() const { return aligned16(base) && Cout % 4 == 0; }
     bool fast() const { return chunks() && s == 1 && Cout % 32 == 0 && (p == 0 || halo >= p) && near_lines(row_reach(q.count, 1, pitch) * Cout); }
+    bool tall() const { return near_lines(row_reach(q.count, 1, pitch, 2 * TILE) * Cout + 2 * TILE); }
     __device__ __forceinline__ long long fast_line(int m) const { return line(m < B * q.count ? m : B * q.count - 1).off; }
     __device__ __forceinline__ Line line(int m) const
     {
@@ -132,6 +137,7 @@ struct DyT {  // wgrad A: r = (b,t') -> dy[b,t'], m = co
     // (the walk of wgrad_t through the frames of a haloed layout; a grid holds fewer than 2^22 rows of dw, so these lines
     // are near)
     bool fast() const { return chunks(); }
+    bool tall() const { return true; }
     __device__ __forceinline__ long long fast_base(int r) const { return (long long)(halo + r) * Cout; }
     __device__ __forceinline__ int fast_pitch() const { return Cout; }
     __device__ __forceinline__ int width() const { return Cout; }
@@ -383,7 +389,7 @@ __global__ __launch_bounds__(256, 4) void gemm_any_k(OA oa, OB ob, EP ep, int M,
 // so a dozen other instructions pass in the shadow of one): a wavefront alone on its SIMD keeps the pipe busy.
 // FAST: tensors in the haloed time layout (the train step's, and what the entry points stage).  Every window is then
 // plain memory: a lane's offset from the first line of its panel never changes and the loads cost no vector
-// instruction at all, which counts, because fp32 matrix instructions run on the vector units (the two do not overlap).
+// instruction at all: gemm_split_k's panels.
 // (The weight gradient then walks through the frames between two utterances as well: dy is zero there, and the x that
 // it would meet is taken for zero too -- in the panels that hold such frames -- or an infinite x near an utterance's
 // end would turn up as a NaN in taps that never see it.)
@@ -478,13 +484,13 @@ struct DmaPanel {
 // barrier makes it everybody's, so that its first operands are read under those last instructions.  (Three slots are
 // no faster for 64 x 64 tiles -- 2.33 against 2.18 ms for the forward pass of 16 x 1600 frames, k = 11, 512 -> 1024 --
 // because their 48 KB leave room for three workgroups on a CU instead of four.)
-template <class OA, class OB, class EP, bool FAST>
+template <class OA, class OB, class EP>
 __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M, int N, int R, int per, int splits,
                                                                    float* colsum, int colsum_acc)
 {
     constexpr int BM = TILE, BN = TILE, BK = PANEL;
-    using PA = DmaPanel<OA, BM, FAST>;
-    using PB = DmaPanel<OB, BN, FAST>;
+    using PA = DmaPanel<OA, BM, false>;
+    using PB = DmaPanel<OB, BN, false>;
     constexpr int STAGE = PA::FLOATS + PB::FLOATS, NL = PA::NI + PB::NI;
     constexpr int GROUPS = BK / 8;                           // of eight steps, four matrix instructions
     static_assert(NL <= (GROUPS - 1) * 4, "a load after every instruction: all of them before the hand-over");
@@ -506,16 +512,13 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
     for (int e = 0; e < 16; ++e) acc[e] = 0.f;
     float asum = 0.f;
     const int steps = r_end > r_begin ? (r_end - r_begin + BK - 1) / BK : 0;
-    // (past the last panel the loads fetch zeros, or that panel again: the number in flight never changes)
+    // (past the last panel the loads fetch zeros: the number in flight never changes)
     auto issue = [&](int i, int st) {
         const unsigned dst = lds0 + (st & 1) * (STAGE * 4);
-        const int r0 = r_begin + (FAST && st >= steps ? steps - 1 : st) * BK;
+        const int r0 = r_begin + st * BK;
         if (i < PA::NI) pa.issue(oa, i, m0, r0, r_end, dst);
         else pb.issue(ob, i - PA::NI, n0, r0, r_end, dst + PA::FLOATS * 4);
     };
-    constexpr bool WALK = FAST && !PA::KL;  // the weight gradient
-    int walk0 = 0;                          // WALK: the panel's first frame, counted from its utterance's first one
-    if constexpr (WALK) walk0 = r_begin % oa.pitch;
     float fa[2][4], fb[2][4];
     if (steps > 0) {
 #pragma unroll
@@ -529,12 +532,6 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
     for (int st = 0; st < steps; ++st) {
         const float* cur = lds + (st & 1) * STAGE;
         const float* nxt = lds + ((st + 1) & 1) * STAGE;
-        bool between = false;  // some of the panel's frames lie behind an utterance
-        int left = 0;          // frames up to the end of the run
-        if constexpr (WALK) {
-            left = r_end - r_begin - st * BK;
-            between = walk0 + BK > oa.Tp || left < BK;
-        }
 #pragma unroll
         for (int g = 0; g < GROUPS; ++g) {
             const int u = g & 1;
@@ -547,18 +544,6 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
             PA::frags(src, wm, (g + 1) % GROUPS * 8, lane, fa[1 - u]);
             PB::frags(src + PA::FLOATS, wn, (g + 1) % GROUPS * 8, lane, fb[1 - u]);
             __builtin_amdgcn_sched_barrier(0);
-            if constexpr (WALK) {
-                if (between) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int l = g * 8 + 4 * (lane >> 5) + q;
-                        unsigned t = walk0 + l;
-                        t = min(t, t - oa.pitch);  // a panel may reach into the utterance after the next one, no further:
-                        t = min(t, t - oa.pitch);  // wgrad_walks
-                        fb[u][q] = t < (unsigned)oa.Tp && l < left ? fb[u][q] : 0.f;
-                    }
-                }
-            }
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[u][q], fb[u][q], acc, 0, 0, 0);
@@ -570,11 +555,6 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
                 asm volatile("");  // a branch: without it every workgroup would add, and select
                 asum += (fa[u][0] + fa[u][1]) + (fa[u][2] + fa[u][3]);
             }
-        }
-        if constexpr (WALK) {
-            walk0 += BK;
-            walk0 = min((unsigned)walk0, (unsigned)(walk0 - oa.pitch));
-            walk0 = min((unsigned)walk0, (unsigned)(walk0 - oa.pitch));
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing may land in LDS once it is used otherwise
@@ -595,6 +575,239 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
     }
 }
 
+// ---- fp32 products on the bf16 matrix instruction -------------------------------------
+// A float is the sum of three bf16 values, exactly: its rounding h, the rounding m of the rest x - h, and l = x - h - m, at
+// most eight significant bits (below 2^-109 what lies under the smallest bf16, 2^-133, is lost).  Of the nine products of
+// two such sums six are taken; the others, m l', l m' and l l', stay below 2^-25 of the product, and a sum over 16 products
+// is rounded six times with v_mfma_f32_32x32x16_bf16, eight times with the fp32 instruction.  Those roundings all go down,
+// towards minus infinity, 5e-8 of the result's rms in its mean, which adds up where many outputs are summed (a bias
+// gradient over the frames came out at twice its distance from 64 bits): so one wavefront of a pair adds up the products
+// and the other one their negatives, and the difference of the two sums has the mean error of the fp32 instruction (1e-9).
+// Distance from 64 bits against that instruction, 12 layers and 8 steps of random sizes: 0.47 to 1.0 and 0.60 to 0.96 of it.
+//
+// Six of these instructions take 192 cycles where the fp32 ones take 512 for the same 16 steps; what bounds the kernel is the
+// vector instructions of the splits, 5.5 an element, beside them.  So every wavefront takes 64 rows (two operand blocks of A to
+// one or two of B) and half of a panel's steps: its neighbour's sums meet its own through LDS at the end.  128 rows: fewer
+// splits and LDS reads per product, where there are enough tiles (any_plan); 128 x 128 was no faster (16 x 800 frames, k = 11,
+// 256 -> 512: the three passes 779 against 776 us).
+// An operand that is not finite, or that rounds to infinity, makes a NaN of the split; so does a sum that overflows.
+// Where the sums are not finite in the end, the workgroup starts over with the fp32 instruction.
+// Panels and outputs as gemm_f32_k, over FAST lines only.  Measured, layers of 256 -> 512, k = 11, forward and backward, this
+// kernel against gemm_f32_k over the same lines: 4 x 400 frames 162 -> 147 us, 16 x 800 981 -> 798; 512 -> 1024, k = 3, 8 x 501
+// frames 357 -> 314; the 10M-parameter network's step 999 -> 861.
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+struct Split8 { bf16x8 h, m, l; };
+// of sign * v, flip: the sign bits of two bf16 values, set where sign is -1
+__device__ __forceinline__ Split8 split8(const float (&v)[8], float sign = 1.f, unsigned flip = 0)
+{
+    u32x4 h, m, l;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        float a = v[2 * q], b = v[2 * q + 1];
+        auto round2 = [&] { return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){a, b}, bf16x2)); };
+        h[q] = round2() ^ flip;
+        a = __builtin_fmaf(a, sign, -__uint_as_float(h[q] << 16));
+        b = __builtin_fmaf(b, sign, -__uint_as_float(h[q] & 0xffff0000u));
+        m[q] = round2();
+        a -= __uint_as_float(m[q] << 16);
+        b -= __uint_as_float(m[q] & 0xffff0000u);
+        l[q] = round2();
+    }
+    return Split8{__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
+}
+
+template <class OA, class OB, class EP, int BM>
+__global__ __launch_bounds__(256, BM == TILE ? 4 : OA::K_LINES ? 3 : 2) void gemm_split_k(OA oa, OB ob, EP ep, int M, int N, int R, int per,
+                                                                                          int splits, float* colsum, int colsum_acc)
+{
+    constexpr int BN = TILE, BK = PANEL, NB = BM / 64;  // operand blocks of B a wavefront takes, to two of A
+    using PA = DmaPanel<OA, BM, true>;
+    using PB = DmaPanel<OB, BN, true>;
+    constexpr int STAGE = PA::FLOATS + PB::FLOATS;
+    __shared__ __align__(1024) float lds[2 * STAGE];
+    __shared__ float colsums[2 * BM];
+    const int split = blockIdx.z % splits;
+    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
+    take_phase(oa, ob, ep, blockIdx.z / splits, M, R);
+    if (OA::PHASED && m0 >= M) return;  // (phases differ by a frame per utterance)
+    const int r_begin = split * per, r_end = R < r_begin + per ? R : r_begin + per;
+    // wavefront: 64 rows from wm and 32 NB columns from wn of the tile, steps kh .. kh + 15 of every panel
+    const int lane = threadIdx.x & 63, half = lane >> 5, wave = threadIdx.x >> 6;
+    const int wm = BM == 128 ? (wave & 1) * 64 : 0, wn = BM == 128 ? 0 : (wave & 1) * 32, kh = __builtin_amdgcn_readfirstlane((wave >> 1) * 16);
+    const bool sum_a = !PA::KL && colsum && blockIdx.x == 0;
+    const unsigned lds0 = (unsigned)(size_t)(lds_byte*)lds;
+    PA pa;
+    PB pb;
+    pa.init(oa, m0, r_end);
+    pb.init(ob, n0, r_end);
+    f32x16 acc[2][NB];
+    float asum[2];
+    const int steps = r_end > r_begin ? (r_end - r_begin + BK - 1) / BK : 0;
+    auto request = [&](int st) {  // (past the last panel: that panel again)
+        const unsigned dst = lds0 + (st & 1) * (STAGE * 4);
+        const int r0 = r_begin + (st >= steps ? steps - 1 : st) * BK;
+#pragma unroll
+        for (int i = 0; i < PA::NI; ++i) pa.issue(oa, i, m0, r0, r_end, dst);
+#pragma unroll
+        for (int i = 0; i < PB::NI; ++i) pb.issue(ob, i, n0, r0, r_end, dst + PA::FLOATS * 4);
+    };
+    auto arrived = [] {  // my share of the panel in flight, then everybody's
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    constexpr bool WALK = !PA::KL;  // the weight gradient
+    const float sign = kh ? -1.f : 1.f;  // of this wavefront's sums, in bf16
+    const unsigned flip = kh ? 0x80008000u : 0u;
+    auto run = [&](auto exact) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            asum[i] = 0.f;
+#pragma unroll
+            for (int n = 0; n < NB; ++n)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[i][n][e] = 0.f;
+        }
+        int walk0 = 0;  // WALK: the panel's first frame, counted from its utterance's first one
+        if constexpr (WALK) walk0 = r_begin % oa.pitch;
+        if (steps > 0) {
+            request(0);
+            arrived();
+        }
+        for (int st = 0; st < steps; ++st) {
+            const float* cur = lds + (st & 1) * STAGE;
+            request(st + 1);  // into the slot that every wavefront had read before the last barrier
+            float fa[2][8], fb[NB][8];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                float f[4];
+#pragma unroll
+                for (int n = 0; n < NB; ++n) {
+                    PB::frags(cur + PA::FLOATS, wn + 32 * n, kh + 8 * u, lane, f);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) fb[n][4 * u + q] = f[q];
+                }
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    PA::frags(cur, wm + 32 * i, kh + 8 * u, lane, f);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) fa[i][4 * u + q] = f[q];
+                }
+            }
+            if constexpr (WALK) {
+                const int left = r_end - r_begin - st * BK;       // frames up to the end of the run
+                if (walk0 + BK > oa.Tp || left < BK) {            // some of the panel's frames lie behind an utterance
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const int l = kh + 8 * (e >> 2) + 4 * half + (e & 3);
+                        unsigned t = walk0 + l;
+                        t = min(t, t - oa.pitch);  // a panel may reach into the utterance after the next one, no further:
+                        t = min(t, t - oa.pitch);  // wgrad_walks
+#pragma unroll
+                        for (int n = 0; n < NB; ++n) fb[n][e] = t < (unsigned)oa.Tp && l < left ? fb[n][e] : 0.f;
+                    }
+                }
+                walk0 += BK;
+                walk0 = min((unsigned)walk0, (unsigned)(walk0 - oa.pitch));
+                walk0 = min((unsigned)walk0, (unsigned)(walk0 - oa.pitch));
+            }
+            if constexpr (decltype(exact)::value) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int n = 0; n < NB; ++n) acc[i][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][e], fb[n][e], acc[i][n], 0, 0, 0);
+            } else {
+                Split8 b[NB];
+#pragma unroll
+                for (int n = 0; n < NB; ++n) b[n] = split8(fb[n], sign, flip);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const Split8 a = split8(fa[i]);
+                    auto add = [&](const bf16x8& x, bf16x8 Split8::*y) {
+#pragma unroll
+                        for (int n = 0; n < NB; ++n) acc[i][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, b[n].*y, acc[i][n], 0, 0, 0);
+                    };
+                    add(a.l, &Split8::h);
+                    add(a.h, &Split8::l);
+                    add(a.m, &Split8::m);
+                    add(a.m, &Split8::h);
+                    add(a.h, &Split8::m);
+                    add(a.h, &Split8::h);
+                }
+            }
+            if (sum_a) {
+                asm volatile("");  // a branch: without it every workgroup would add, and select
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const float(&f)[8] = fa[i];
+                    asum[i] += ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7]));
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);  // the wait stays behind the matrix instructions
+            arrived();
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing may land in LDS once it is used otherwise
+        __syncthreads();
+    };
+    run(std::false_type{});
+    bool finite = true;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) finite = finite && fabsf(acc[i][n][e]) <= 3.402823466e38f;
+    if (__syncthreads_or(!finite)) {
+        run(std::true_type{});
+    } else if (kh) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int n = 0; n < NB; ++n)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[i][n][e] = -acc[i][n][e];
+    }
+    // the two wavefronts of a part of the tile: each finishes one of its two blocks of rows, with the other's sums of it
+    constexpr int EXCH = NB * 1024;
+    float* const mine = lds + wave * EXCH;
+    const int keep = wave >> 1;
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) mine[(n * 16 + e) * 64 + lane] = keep ? acc[0][n][e] : acc[1][n][e];
+    if (sum_a) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) asum[i] += __shfl_xor(asum[i], 32, 64);  // lanes 0..31 and 32..63 took different steps
+        if ((BM == 128 || (wave & 1) == 0) && lane < 32) {  // (64 rows: the two wavefronts of a half of the steps have the same sums)
+            colsums[keep * BM + wm + lane] = asum[0];
+            colsums[keep * BM + wm + 32 + lane] = asum[1];
+        }
+    }
+    __syncthreads();
+    const float* const other = lds + (wave ^ 2) * EXCH;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        const int n = n0 + wn + 32 * nb + (lane & 31);
+        const float addn = n < N ? ep.add(n) : 0.f;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int m = m0 + wm + 32 * keep + 8 * (e >> 2) + 4 * half + (e & 3);
+            const float own = keep ? acc[1][nb][e] : acc[0][nb][e], far = other[(nb * 16 + e) * 64 + lane];
+            if (m < M && n < N) ep.store(ep.row(m) + n, (own + far) + addn, split);
+        }
+    }
+    if (sum_a && threadIdx.x < BM && m0 + (int)threadIdx.x < M) {
+        float* const q = colsum + (long long)split * M + m0 + threadIdx.x;
+        const float v = colsums[threadIdx.x] + colsums[BM + threadIdx.x];
+        *q = colsum_acc ? *q + v : v;
+    }
+}
+
 // How many workgroups share the reduction of an M x N x R problem's tiles.  The candidates' times are added up from
 // cycles: panels at 16 instructions of 64 cycles, one after the other for the workgroups that share a CU (at 0.67 of
 // the rate if there is one, 0.76 from three on: measured, 4 x 400 frames, k = 11, 256 -> 512, forward: 200 workgroups
@@ -603,22 +816,29 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
 // 128 x 128 was slower on the largest problems as well (16 x 1600 frames, k = 11, 512 -> 1024: forward 2.30 against
 // 2.18 ms, data gradient 2.69 against 2.38, weight gradient 3.06 against 2.45), four small workgroups on a CU
 // covering each other's barriers better than two large ones.
-struct AnyPlan { int splits, per; };
+// fp32 operands in haloed tensors take gemm_split_k, whose tiles have 64 or 128 rows: 800 and 1470 cycles a panel for the
+// matrix instructions and the splits, at rates fitted to the layers named there with either tile.
+struct AnyPlan { int splits, per, rows; };  // rows: of a tile
+struct TileCost { int rows; double cycles, fill[3]; };  // of a panel; the rate with one, two, or more workgroups on a CU
+constexpr TileCost FP32_TILE{64, 1024, {0.67, 0.72, 0.76}}, SPLIT_TILES[2] = {{64, 800, {0.62, 0.70, 0.76}}, {128, 1470, {0.50, 0.62, 0.78}}};
 // values: of a plane; problems: that share a launch, each M x N x R (the phases of a stride)
-AnyPlan any_plan(long long M, long long N, long long R, size_t budget, double finish_cycles, long long values, int problems = 1)
+AnyPlan any_plan(long long M, long long N, long long R, size_t budget, double finish_cycles, long long values, int problems, bool f32)
 {
-    const long long tiles = problems * ((M + TILE - 1) / TILE) * ((N + TILE - 1) / TILE), panels = (R + PANEL - 1) / PANEL;
-    AnyPlan best{1, 0};
+    AnyPlan best{1, 0, TILE};
     double best_t = -1;
-    for (int s = 1; s <= 16; ++s) {
-        const long long per = (panels + s - 1) / s;
-        if (s > 1 && (per * (s - 1) >= panels || per < 2 || (size_t)s * values * 4 > budget)) continue;
-        const long long load = (tiles * s + 255) / 256;
-        double t = load * per * 1024.0 / (load > 2 ? 0.76 : load > 1 ? 0.72 : 0.67) + 12000;
-        if (s > 1) t += 8.0 * s * values / 2500 + finish_cycles;
-        if (best_t < 0 || t < best_t) {
-            best_t = t;
-            best = AnyPlan{s, (int)(per * PANEL)};
+    for (int v = 0; v < (f32 ? 2 : 1); ++v) {
+        const TileCost& c = f32 ? SPLIT_TILES[v] : FP32_TILE;
+        const long long tiles = problems * ((M + c.rows - 1) / c.rows) * ((N + TILE - 1) / TILE), panels = (R + PANEL - 1) / PANEL;
+        for (int s = 1; s <= 16; ++s) {
+            const long long per = (panels + s - 1) / s;
+            if (s > 1 && (per * (s - 1) >= panels || per < 2 || (size_t)s * values * 4 > budget)) continue;
+            const long long load = (tiles * s + 255) / 256;
+            double t = load * per * c.cycles / c.fill[load > 2 ? 2 : load > 1 ? 1 : 0] + 12000;
+            if (s > 1) t += 8.0 * s * values / 2500 + finish_cycles;
+            if (best_t < 0 || t < best_t) {
+                best_t = t;
+                best = AnyPlan{s, (int)(per * PANEL), c.rows};
+            }
         }
     }
     return best;
@@ -628,10 +848,12 @@ template <class OA, class OB, class EP>
 int launch_any(const AnyPlan& pl, OA oa, OB ob, EP ep, long long M, long long N, long long R, hipStream_t st, float* colsum = nullptr,
                int colsum_acc = 0, bool fast = false, int* form = nullptr, int phases = 1)
 {
-    const long long gy = (M + TILE - 1) / TILE, gx = (N + TILE - 1) / TILE;
+    constexpr bool f32 = std::is_same<typename OA::type, float>::value && std::is_same<typename OB::type, float>::value;
+    const bool tall = f32 && fast && pl.rows > TILE && oa.tall();
+    const int rows = tall ? 2 * TILE : TILE;
+    const long long gy = (M + rows - 1) / rows, gx = (N + TILE - 1) / TILE;
     if (M > 2147483647LL || R > 2147483647LL - 4096 || gy > 65535 || gx > 2147483647LL) return W2L_ERR_SHAPE;
     if (M <= 0) return W2L_OK;
-    constexpr bool f32 = std::is_same<typename OA::type, float>::value && std::is_same<typename OB::type, float>::value;
     const bool chunks = f32 && oa.chunks() && ob.chunks();
     if (form) {  // asked which kernel it is (w2l_conv1d_launch_config)
         *form = !chunks ? CONV_REGISTERS : fast ? CONV_PLAIN : CONV_CHUNKS;
@@ -641,8 +863,9 @@ int launch_any(const AnyPlan& pl, OA oa, OB ob, EP ep, long long M, long long N,
 #define W2L_ANY(KERN) hipLaunchKernelGGL(KERN, g, dim3(256), 0, st, oa, ob, ep, (int)M, (int)N, (int)R, pl.per, pl.splits, colsum, colsum_acc)
     if constexpr (f32) {
         if (chunks) {
-            if (fast) W2L_ANY((gemm_f32_k<OA, OB, EP, true>));
-            else W2L_ANY((gemm_f32_k<OA, OB, EP, false>));
+            if (tall) W2L_ANY((gemm_split_k<OA, OB, EP, 2 * TILE>));
+            else if (fast) W2L_ANY((gemm_split_k<OA, OB, EP, TILE>));
+            else W2L_ANY((gemm_f32_k<OA, OB, EP>));
             return launch_status();
         }
     }
@@ -863,54 +1086,58 @@ __global__ void colsum_stage2(const float* part, float* dbias, int chunks, int C
 namespace {
 // a finishing launch of its own costs about 5 us; inside the train step it is the layer's GLU, launched in any case
 constexpr double FINISH_OWN = 12000, FINISH_FREE = 2000;
-AnyPlan fwd_plan(const ConvDesc& d, size_t budget, double fin)
+AnyPlan fwd_plan(const ConvDesc& d, size_t budget, double fin, bool f32)
 {
     const long long M = (long long)d.B * d.Tp;
-    return any_plan(M, d.Cout, (long long)d.k * d.Cin, budget, fin, M * d.Cout);
+    return any_plan(M, d.Cout, (long long)d.k * d.Cin, budget, fin, M * d.Cout, 1, f32);
 }
-AnyPlan dgrad_plan(const ConvDesc& d, size_t budget, double fin)
+AnyPlan dgrad_plan(const ConvDesc& d, size_t budget, double fin, bool f32)
 {
     // of a stride's phases, the one with the most taps, as often as there are any with taps; a plane takes all of them
     const int phases = d.s < d.k ? d.s : d.k;
     return any_plan((long long)d.B * ((d.T + d.s - 1) / d.s), d.Cin, (long long)((d.k + d.s - 1) / d.s) * d.Cout, budget, fin,
-                    (long long)d.B * d.T * d.Cin, phases < d.T ? phases : d.T);
+                    (long long)d.B * d.T * d.Cin, phases < d.T ? phases : d.T, f32);
 }
-AnyPlan wgrad_plan(const ConvDesc& d, size_t budget)
+AnyPlan wgrad_plan(const ConvDesc& d, size_t budget, bool f32)
 {
     // the reduction as long as the walk through the haloed layout makes it (where that is no more frames than an entry
     // point takes: a run's end has to stay below 2^31)
     const long long walk = (long long)d.B * (d.Tp + 2 * LAYOUT_HALO);
     return any_plan(d.Cout, (long long)d.k * d.Cin, walk <= 1LL << 30 ? walk : (long long)d.B * d.Tp, budget, FINISH_OWN,
-                    (long long)d.Cout * d.k * d.Cin);
+                    (long long)d.Cout * d.k * d.Cin, 1, f32);
 }
+// Passes whose operands gemm_split_k takes, given the haloed layout (the fast() of their operands)
+bool fwd_splits(const ConvDesc& d, int dt) { return dt == W2L_F32 && d.Cin % 4 == 0 && d.k * (long long)d.Cin % 32 == 0; }
+bool dgrad_splits(const ConvDesc& d, int dt) { return dt == W2L_F32 && d.s == 1 && d.Cin % 4 == 0 && d.Cout % 32 == 0; }
+bool wgrad_splits(const ConvDesc& d, int dt) { return dt == W2L_F32 && d.s == 1 && d.Cin % 4 == 0 && d.Cout % 4 == 0; }
 size_t part_bytes(int splits, long long rows, long long cols) { return splits > 1 ? round_up((size_t)splits * rows * cols * 4, 256) : 0; }
 }  // namespace
 
-size_t conv_fwd_generic_scratch(const ConvDesc& d)
+size_t conv_fwd_generic_scratch(const ConvDesc& d, int dt)
 {
-    return part_bytes(fwd_plan(d, MAX_PARTIALS, FINISH_OWN).splits, (long long)d.B * d.Tp, d.Cout);
+    return part_bytes(fwd_plan(d, MAX_PARTIALS, FINISH_OWN, fwd_splits(d, dt)).splits, (long long)d.B * d.Tp, d.Cout);
 }
-size_t conv_dgrad_generic_scratch(const ConvDesc& d)
+size_t conv_dgrad_generic_scratch(const ConvDesc& d, int dt)
 {
-    return part_bytes(dgrad_plan(d, MAX_PARTIALS, FINISH_OWN).splits, (long long)d.B * d.T, d.Cin);
+    return part_bytes(dgrad_plan(d, MAX_PARTIALS, FINISH_OWN, dgrad_splits(d, dt)).splits, (long long)d.B * d.T, d.Cin);
 }
-size_t conv_wgrad_generic_scratch(const ConvDesc& d)
+size_t conv_wgrad_generic_scratch(const ConvDesc& d, int dt)
 {
-    return part_bytes(wgrad_plan(d, MAX_PARTIALS).splits, d.Cout, (long long)d.k * d.Cin + 1);
+    return part_bytes(wgrad_plan(d, MAX_PARTIALS, wgrad_splits(d, dt)).splits, d.Cout, (long long)d.k * d.Cin + 1);
 }
-int conv_fwd_generic_parts(const ConvDesc& d) { return fwd_plan(d, MAX_PARTIALS, FINISH_FREE).splits; }
-int conv_dgrad_generic_parts(const ConvDesc& d) { return dgrad_plan(d, MAX_PARTIALS, FINISH_FREE).splits; }
+int conv_fwd_generic_parts(const ConvDesc& d, int dt) { return fwd_plan(d, MAX_PARTIALS, FINISH_FREE, fwd_splits(d, dt)).splits; }
+int conv_dgrad_generic_parts(const ConvDesc& d, int dt) { return dgrad_plan(d, MAX_PARTIALS, FINISH_FREE, dgrad_splits(d, dt)).splits; }
 
 int conv_fwd_generic_partial(const ConvDesc& d, const void* x, const void* w, int dt, float* part, hipStream_t st)
 {
-    const AnyPlan pl = fwd_plan(d, MAX_PARTIALS, FINISH_FREE);
+    const AnyPlan pl = fwd_plan(d, MAX_PARTIALS, FINISH_FREE, fwd_splits(d, dt));
     const long long plane = (long long)d.B * d.Tp * d.Cout;
     if (dt == W2L_F32) return fwd_t<float, float>(d, pl, x, w, nullptr, part, d.Tp, 0, plane, st);
     return fwd_t<bf16_t, float>(d, pl, x, w, nullptr, part, d.Tp, 0, plane, st);
 }
 int conv_dgrad_generic_partial(const ConvDesc& d, const void* dy, const void* w, int dt, int dydt, float* part, hipStream_t st)
 {
-    const AnyPlan pl = dgrad_plan(d, MAX_PARTIALS, FINISH_FREE);
+    const AnyPlan pl = dgrad_plan(d, MAX_PARTIALS, FINISH_FREE, dgrad_splits(d, dt));
     const long long plane = (long long)d.B * d.T * d.Cin;
     if (dt == W2L_F32) return dgrad_t<float, float, float>(d, pl, dy, w, part, d.T, 0, plane, st);
     if (dydt == W2L_BF16) return dgrad_t<bf16_t, bf16_t, float>(d, pl, dy, w, part, d.T, 0, plane, st);
@@ -921,7 +1148,7 @@ int conv_fwd_generic(const ConvDesc& d, const void* x, const void* w, const floa
                      hipStream_t st, void* scratch, size_t scratch_bytes)
 {
     if (dt == W2L_F32 && ydt != W2L_F32) return W2L_ERR_DTYPE;
-    const AnyPlan pl = fwd_plan(d, scratch ? (scratch_bytes < MAX_PARTIALS ? scratch_bytes : MAX_PARTIALS) : 0, FINISH_OWN);
+    const AnyPlan pl = fwd_plan(d, scratch ? (scratch_bytes < MAX_PARTIALS ? scratch_bytes : MAX_PARTIALS) : 0, FINISH_OWN, fwd_splits(d, dt));
     if (pl.splits > 1) {
         float* part = static_cast<float*>(scratch);
         const long long rows = (long long)d.B * d.Tp, plane = rows * d.Cout;
@@ -937,7 +1164,7 @@ int conv_dgrad_generic(const ConvDesc& d, const void* dy, const void* w, void* d
                        size_t scratch_bytes)
 {
     if (dt == W2L_F32 && dydt != W2L_F32) return W2L_ERR_DTYPE;
-    const AnyPlan pl = dgrad_plan(d, scratch ? (scratch_bytes < MAX_PARTIALS ? scratch_bytes : MAX_PARTIALS) : 0, FINISH_OWN);
+    const AnyPlan pl = dgrad_plan(d, scratch ? (scratch_bytes < MAX_PARTIALS ? scratch_bytes : MAX_PARTIALS) : 0, FINISH_OWN, dgrad_splits(d, dt));
     if (pl.splits > 1) {
         float* part = static_cast<float*>(scratch);
         const long long plane = (long long)d.B * d.T * d.Cin;
@@ -957,10 +1184,10 @@ int conv_wgrad_generic(const ConvDesc& d, const void* x, const void* dy, float* 
     if (dt == W2L_F32 && dydt != W2L_F32) return W2L_ERR_DTYPE;
     // (the bias sums of the splits lie behind the weight sums: one more column)
     const long long n = (long long)d.k * d.Cin, plane = d.Cout * n;
-    AnyPlan pl = wgrad_plan(d, MAX_PARTIALS);
+    AnyPlan pl = wgrad_plan(d, MAX_PARTIALS, wgrad_splits(d, dt));
     if (!scratch || scratch_bytes < part_bytes(pl.splits, d.Cout, n + 1)) {
         const size_t bias = (size_t)17 * d.Cout * 4;  // (room for the bias sums of 16 splits, rounded up)
-        pl = wgrad_plan(d, scratch && scratch_bytes > bias ? scratch_bytes - bias : 0);
+        pl = wgrad_plan(d, scratch && scratch_bytes > bias ? scratch_bytes - bias : 0, wgrad_splits(d, dt));
     }
     float* part = static_cast<float*>(scratch);
     const bool split = pl.splits > 1;
@@ -977,7 +1204,7 @@ int conv_wgrad_generic(const ConvDesc& d, const void* x, const void* dy, float* 
 // Which kernel the calls below would take and into how many runs the reduction goes (operands aligned; nothing is launched)
 int conv_fwd_generic_form(const ConvDesc& d, int dt, size_t scratch_bytes, int* form, int* splits)
 {
-    const AnyPlan pl = fwd_plan(d, scratch_bytes < MAX_PARTIALS ? scratch_bytes : MAX_PARTIALS, FINISH_OWN);
+    const AnyPlan pl = fwd_plan(d, scratch_bytes < MAX_PARTIALS ? scratch_bytes : MAX_PARTIALS, FINISH_OWN, fwd_splits(d, dt));
     *splits = pl.splits;
     float* const y = nullptr;
     if (dt == W2L_F32) return fwd_t<float, float>(d, pl, nullptr, nullptr, nullptr, y, d.y_pitch, d.y_halo, 0, nullptr, form);
@@ -985,7 +1212,7 @@ int conv_fwd_generic_form(const ConvDesc& d, int dt, size_t scratch_bytes, int* 
 }
 int conv_dgrad_generic_form(const ConvDesc& d, int dt, size_t scratch_bytes, int* form, int* splits)
 {
-    const AnyPlan pl = dgrad_plan(d, scratch_bytes < MAX_PARTIALS ? scratch_bytes : MAX_PARTIALS, FINISH_OWN);
+    const AnyPlan pl = dgrad_plan(d, scratch_bytes < MAX_PARTIALS ? scratch_bytes : MAX_PARTIALS, FINISH_OWN, dgrad_splits(d, dt));
     *splits = pl.splits;
     float* const dx = nullptr;
     if (dt == W2L_F32) return dgrad_t<float, float, float>(d, pl, nullptr, nullptr, dx, d.x_pitch, d.x_halo, 0, nullptr, form);
@@ -993,7 +1220,7 @@ int conv_dgrad_generic_form(const ConvDesc& d, int dt, size_t scratch_bytes, int
 }
 int conv_wgrad_generic_form(const ConvDesc& d, int dt, int* form, int* splits)
 {
-    const AnyPlan pl = wgrad_plan(d, MAX_PARTIALS);
+    const AnyPlan pl = wgrad_plan(d, MAX_PARTIALS, wgrad_splits(d, dt));
     *splits = pl.splits;
     if (dt == W2L_F32) return wgrad_t<float, float>(d, pl, nullptr, nullptr, nullptr, nullptr, 0, 0, nullptr, form);
     return wgrad_t<bf16_t, bf16_t>(d, pl, nullptr, nullptr, nullptr, nullptr, 0, 0, nullptr, form);

@@ -261,3 +261,57 @@ def test_bf16_train_step_split_reductions():
               dict(k=1, stride=1, cin=256, cout=29, glu=0)]
     cfg = W.small_model(53, 3, 200, 301, 40, layers, True, 4, 20)
     check_train_step(run_train_step(P, cfg), oracle_train_step(cfg), "bf16")
+
+
+@pytest.mark.parametrize("shape", [
+    # B, T, Cin, Cout, k: fp32, haloed; the passes with tiles of 128 rows, by any_plan's rule
+    (2, 1321, 32, 3104, 1),      # forward, one panel, rows 82 over
+    (3, 701, 512, 1088, 1),      # data gradient in runs
+    (2, 450, 1024, 96, 9),       # weight gradient in runs, rows 96 of 128, utterance ends inside a panel
+    (1, 130, 1100, 1600, 3),     # weight gradient unsplit, half a tile of rows over
+], ids=lambda s: "x".join(map(str, s)))
+def test_fp32_products_from_bf16_terms(shape):
+    """The three passes against the oracle, and the mean of their errors: the bf16 instruction rounds sums towards minus
+    infinity, 2e-8 to 9e-8 of the rms at these lengths, which the pairs of opposite sums have to cancel.  (Errors of
+    at most 1e-6 of the rms over 86000 outputs or more leave their mean below 1e-6 / sqrt(86000) = 3.4e-9.)"""
+    import paper_1812_07625_amd as P
+    B, T, Cin, Cout, k = shape
+    rng = np.random.default_rng(sum(shape))
+    x, dy = rng.standard_normal((B, T, Cin)).astype(np.float32), rng.standard_normal((B, T, Cout)).astype(np.float32)
+    w = (rng.standard_normal((Cout, k, Cin)) / np.sqrt(k * Cin)).astype(np.float32)
+    bias = rng.standard_normal(Cout).astype(np.float32)
+    ws = lambda q: P.workspace(q(B, T, Cin, Cout, k, 1, P.W2L_F32))
+    xd, wd, dyd = to_dev(x), to_dev(w), to_dev(dy)
+    y = P.w2l_conv1d_fwd(xd, wd, to_dev(bias), empty((B, T, Cout)), 1, ws(P.w2l_conv1d_fwd_workspace_bytes))
+    dx = P.w2l_conv1d_bwd_data(dyd, wd, empty((B, T, Cin)), 1, ws(P.w2l_conv1d_bwd_data_workspace_bytes))
+    dw, db = P.w2l_conv1d_bwd_weight(xd, dyd, empty((Cout, k, Cin)), empty((Cout,)), 1, False,
+                                     ws(P.w2l_conv1d_bwd_weight_workspace_bytes))
+    dw_o, db_o = oracle.conv1d_bwd_weight(x, dy, k, 1)
+    for got, ref, what in ((y, oracle.conv1d_fwd(x, w, bias, 1), "y"), (dx, oracle.conv1d_bwd_data(dy, w, T, 1), "dx"), (dw, dw_o, "dw")):
+        got = to_host(got)
+        _check(got, ref, False, what)
+        assert abs((got - ref).mean()) <= 1e-8 * np.sqrt((ref ** 2).mean()), what
+    _check(to_host(db), db_o, False, "db")
+
+
+@pytest.mark.parametrize("shape", [(2, 70, 32, 64, 3), (2, 1321, 32, 3104, 1)], ids=lambda s: "x".join(map(str, s)))
+def test_fp32_beyond_the_bf16_terms(shape):
+    """Values that have no bf16 terms (an infinity, a NaN, a float above the largest bf16): as the fp32 sum, with
+    |error| <= K 2^-24 sum |x||w| where that is finite."""
+    import paper_1812_07625_amd as P
+    B, T, Cin, Cout, k = shape
+    rng = np.random.default_rng(sum(shape))
+    x = rng.standard_normal((B, T, Cin)).astype(np.float32)
+    w = rng.uniform(0.1, 0.9, (Cout, k, Cin)).astype(np.float32)
+    x[0, 5, 3], x[0, 20, 4], x[1, 7, 5], x[1, 69, 6] = 3.4e38, -3.4e38, np.inf, np.nan
+    bias = np.zeros(Cout, np.float32)
+    ws = P.workspace(P.w2l_conv1d_fwd_workspace_bytes(B, T, Cin, Cout, k, 1, P.W2L_F32))
+    got = to_host(P.w2l_conv1d_fwd(to_dev(x), to_dev(w), to_dev(bias), empty((B, T, Cout)), 1, ws))
+    with np.errstate(invalid="ignore"):
+        ref = oracle.conv1d_fwd(x, w, bias, 1)
+        bound = k * Cin * 2.0 ** -24 * oracle.conv1d_fwd(np.abs(x), w, bias, 1)
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(ref))
+    np.testing.assert_array_equal(np.isposinf(got), np.isposinf(ref))
+    fin = np.isfinite(ref)
+    assert (~fin).sum() >= 2 * Cout and (np.abs(ref[fin]) > 1e37).sum() >= 2 * Cout
+    assert (np.abs(got[fin] - ref[fin]) <= bound[fin]).all()
