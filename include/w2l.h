@@ -197,8 +197,8 @@ int w2l_ctc_fwd_bwd_noalloc(const float *input, int is_logits, const int *target
                             int B, int Tp, int C, int Lmax, int blank, float grad_scale, void *stream);
 /* Host-only query: which variant of the alpha/beta kernel w2l_ctc_fwd_bwd launches for C classes
  * and targets of up to Lmax labels -- (blank, label) pairs per lane (1, 2 or 4), score-table values
- * a thread stages per block of frames (2, 4, 8; 0 = scores gathered per lane, large alphabets),
- * frames per block (16 or 12) and threads per workgroup.  For tests and tuning; launches nothing.
+ * a staging thread brings in per block of frames (2, 4, 8; 0 = scores gathered per lane, large tables),
+ * frames per block (16 or 12) and threads per workgroup, staging wavefronts included.  For tests and tuning; launches nothing.
  * W2L_ERR_SHAPE for sizes w2l_ctc_fwd_bwd refuses. */
 int w2l_ctc_launch_config(int C, int Lmax, int *pairs_per_lane, int *table_values_per_thread,
                           int *frames_per_block, int *threads);
