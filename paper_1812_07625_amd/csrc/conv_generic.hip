@@ -389,7 +389,7 @@ __global__ __launch_bounds__(256, 4) void gemm_any_k(OA oa, OB ob, EP ep, int M,
 // so a dozen other instructions pass in the shadow of one): a wavefront alone on its SIMD keeps the pipe busy.
 // FAST: tensors in the haloed time layout (the train step's, and what the entry points stage).  Every window is then
 // plain memory: a lane's offset from the first line of its panel never changes and the loads cost no vector
-// instruction at all: gemm_split_k's panels.
+// instruction at all, which counts, because fp32 matrix instructions run on the vector units (the two do not overlap).
 // (The weight gradient then walks through the frames between two utterances as well: dy is zero there, and the x that
 // it would meet is taken for zero too -- in the panels that hold such frames -- or an infinite x near an utterance's
 // end would turn up as a NaN in taps that never see it.)
@@ -484,13 +484,13 @@ struct DmaPanel {
 // barrier makes it everybody's, so that its first operands are read under those last instructions.  (Three slots are
 // no faster for 64 x 64 tiles -- 2.33 against 2.18 ms for the forward pass of 16 x 1600 frames, k = 11, 512 -> 1024 --
 // because their 48 KB leave room for three workgroups on a CU instead of four.)
-template <class OA, class OB, class EP>
+template <class OA, class OB, class EP, bool FAST>
 __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M, int N, int R, int per, int splits,
                                                                    float* colsum, int colsum_acc)
 {
     constexpr int BM = TILE, BN = TILE, BK = PANEL;
-    using PA = DmaPanel<OA, BM, false>;
-    using PB = DmaPanel<OB, BN, false>;
+    using PA = DmaPanel<OA, BM, FAST>;
+    using PB = DmaPanel<OB, BN, FAST>;
     constexpr int STAGE = PA::FLOATS + PB::FLOATS, NL = PA::NI + PB::NI;
     constexpr int GROUPS = BK / 8;                           // of eight steps, four matrix instructions
     static_assert(NL <= (GROUPS - 1) * 4, "a load after every instruction: all of them before the hand-over");
@@ -512,13 +512,16 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
     for (int e = 0; e < 16; ++e) acc[e] = 0.f;
     float asum = 0.f;
     const int steps = r_end > r_begin ? (r_end - r_begin + BK - 1) / BK : 0;
-    // (past the last panel the loads fetch zeros: the number in flight never changes)
+    // (past the last panel the loads fetch zeros, or that panel again: the number in flight never changes)
     auto issue = [&](int i, int st) {
         const unsigned dst = lds0 + (st & 1) * (STAGE * 4);
-        const int r0 = r_begin + st * BK;
+        const int r0 = r_begin + (FAST && st >= steps ? steps - 1 : st) * BK;
         if (i < PA::NI) pa.issue(oa, i, m0, r0, r_end, dst);
         else pb.issue(ob, i - PA::NI, n0, r0, r_end, dst + PA::FLOATS * 4);
     };
+    constexpr bool WALK = FAST && !PA::KL;  // the weight gradient
+    int walk0 = 0;                          // WALK: the panel's first frame, counted from its utterance's first one
+    if constexpr (WALK) walk0 = r_begin % oa.pitch;
     float fa[2][4], fb[2][4];
     if (steps > 0) {
 #pragma unroll
@@ -532,6 +535,12 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
     for (int st = 0; st < steps; ++st) {
         const float* cur = lds + (st & 1) * STAGE;
         const float* nxt = lds + ((st + 1) & 1) * STAGE;
+        bool between = false;  // some of the panel's frames lie behind an utterance
+        int left = 0;          // frames up to the end of the run
+        if constexpr (WALK) {
+            left = r_end - r_begin - st * BK;
+            between = walk0 + BK > oa.Tp || left < BK;
+        }
 #pragma unroll
         for (int g = 0; g < GROUPS; ++g) {
             const int u = g & 1;
@@ -544,6 +553,18 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
             PA::frags(src, wm, (g + 1) % GROUPS * 8, lane, fa[1 - u]);
             PB::frags(src + PA::FLOATS, wn, (g + 1) % GROUPS * 8, lane, fb[1 - u]);
             __builtin_amdgcn_sched_barrier(0);
+            if constexpr (WALK) {
+                if (between) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int l = g * 8 + 4 * (lane >> 5) + q;
+                        unsigned t = walk0 + l;
+                        t = min(t, t - oa.pitch);  // a panel may reach into the utterance after the next one, no further:
+                        t = min(t, t - oa.pitch);  // wgrad_walks
+                        fb[u][q] = t < (unsigned)oa.Tp && l < left ? fb[u][q] : 0.f;
+                    }
+                }
+            }
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[u][q], fb[u][q], acc, 0, 0, 0);
@@ -555,6 +576,11 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
                 asm volatile("");  // a branch: without it every workgroup would add, and select
                 asum += (fa[u][0] + fa[u][1]) + (fa[u][2] + fa[u][3]);
             }
+        }
+        if constexpr (WALK) {
+            walk0 += BK;
+            walk0 = min((unsigned)walk0, (unsigned)(walk0 - oa.pitch));
+            walk0 = min((unsigned)walk0, (unsigned)(walk0 - oa.pitch));
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing may land in LDS once it is used otherwise
@@ -592,7 +618,7 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
 // 256 -> 512: the three passes 779 against 776 us).
 // An operand that is not finite, or that rounds to infinity, makes a NaN of the split; so does a sum that overflows.
 // Where the sums are not finite in the end, the workgroup starts over with the fp32 instruction.
-// Panels and outputs as gemm_f32_k, over FAST lines only.  Measured, layers of 256 -> 512, k = 11, forward and backward, this
+// Panels and outputs as gemm_f32_k's over FAST lines.  Measured, layers of 256 -> 512, k = 11, forward and backward, this
 // kernel against gemm_f32_k over the same lines: 4 x 400 frames 162 -> 147 us, 16 x 800 981 -> 798; 512 -> 1024, k = 3, 8 x 501
 // frames 357 -> 314; the 10M-parameter network's step 999 -> 861.
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
@@ -816,28 +842,30 @@ __global__ __launch_bounds__(256, BM == TILE ? 4 : OA::K_LINES ? 3 : 2) void gem
 // 128 x 128 was slower on the largest problems as well (16 x 1600 frames, k = 11, 512 -> 1024: forward 2.30 against
 // 2.18 ms, data gradient 2.69 against 2.38, weight gradient 3.06 against 2.45), four small workgroups on a CU
 // covering each other's barriers better than two large ones.
-// fp32 operands in haloed tensors take gemm_split_k, whose tiles have 64 or 128 rows: 800 and 1470 cycles a panel for the
-// matrix instructions and the splits, at rates fitted to the layers named there with either tile.
-struct AnyPlan { int splits, per, rows; };  // rows: of a tile
-struct TileCost { int rows; double cycles, fill[3]; };  // of a panel; the rate with one, two, or more workgroups on a CU
-constexpr TileCost FP32_TILE{64, 1024, {0.67, 0.72, 0.76}}, SPLIT_TILES[2] = {{64, 800, {0.62, 0.70, 0.76}}, {128, 1470, {0.50, 0.62, 0.78}}};
+// fp32 operands in haloed tensors choose between gemm_f32_k and gemm_split_k's tiles of 64 or 128 rows: 800 and 1470 cycles a
+// panel for the matrix instructions and the splits, at rates fitted to the layers named there with either tile, and 2400 more
+// for the exchange of sums and the longer code.  So runs of up to about ten panels that leave CUs idle keep the fp32
+// instruction (2 x 100 frames, 64 -> 128, k = 5, forward / data gradient: 6.1 / 6.2 us against 7.1 / 7.4).
+struct AnyPlan { int splits, per, rows; bool terms; };  // rows: of a tile; terms: gemm_split_k
+struct TileCost { int rows; double cycles, fill[3], fixed; };  // of a panel; the rate with one, two, or more workgroups on a CU
+constexpr TileCost TILES[3] = {{64, 1024, {0.67, 0.72, 0.76}, 12000}, {64, 800, {0.62, 0.70, 0.76}, 14400}, {128, 1470, {0.50, 0.62, 0.78}, 14400}};
 // values: of a plane; problems: that share a launch, each M x N x R (the phases of a stride)
 AnyPlan any_plan(long long M, long long N, long long R, size_t budget, double finish_cycles, long long values, int problems, bool f32)
 {
-    AnyPlan best{1, 0, TILE};
+    AnyPlan best{1, 0, TILE, false};
     double best_t = -1;
-    for (int v = 0; v < (f32 ? 2 : 1); ++v) {
-        const TileCost& c = f32 ? SPLIT_TILES[v] : FP32_TILE;
+    for (int v = 0; v < (f32 ? 3 : 1); ++v) {
+        const TileCost& c = TILES[v];
         const long long tiles = problems * ((M + c.rows - 1) / c.rows) * ((N + TILE - 1) / TILE), panels = (R + PANEL - 1) / PANEL;
         for (int s = 1; s <= 16; ++s) {
             const long long per = (panels + s - 1) / s;
             if (s > 1 && (per * (s - 1) >= panels || per < 2 || (size_t)s * values * 4 > budget)) continue;
             const long long load = (tiles * s + 255) / 256;
-            double t = load * per * c.cycles / c.fill[load > 2 ? 2 : load > 1 ? 1 : 0] + 12000;
+            double t = load * per * c.cycles / c.fill[load > 2 ? 2 : load > 1 ? 1 : 0] + c.fixed;
             if (s > 1) t += 8.0 * s * values / 2500 + finish_cycles;
             if (best_t < 0 || t < best_t) {
                 best_t = t;
-                best = AnyPlan{s, (int)(per * PANEL), c.rows};
+                best = AnyPlan{s, (int)(per * PANEL), c.rows, v > 0};
             }
         }
     }
@@ -864,8 +892,9 @@ int launch_any(const AnyPlan& pl, OA oa, OB ob, EP ep, long long M, long long N,
     if constexpr (f32) {
         if (chunks) {
             if (tall) W2L_ANY((gemm_split_k<OA, OB, EP, 2 * TILE>));
-            else if (fast) W2L_ANY((gemm_split_k<OA, OB, EP, TILE>));
-            else W2L_ANY((gemm_f32_k<OA, OB, EP>));
+            else if (fast && pl.terms) W2L_ANY((gemm_split_k<OA, OB, EP, TILE>));
+            else if (fast) W2L_ANY((gemm_f32_k<OA, OB, EP, true>));
+            else W2L_ANY((gemm_f32_k<OA, OB, EP, false>));
             return launch_status();
         }
     }

@@ -294,7 +294,7 @@ def test_fp32_products_from_bf16_terms(shape):
     _check(to_host(db), db_o, False, "db")
 
 
-@pytest.mark.parametrize("shape", [(2, 70, 32, 64, 3), (2, 1321, 32, 3104, 1)], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("shape", [(2, 70, 32, 64, 3), (4, 400, 256, 512, 3), (2, 1321, 32, 3104, 1)], ids=lambda s: "x".join(map(str, s)))
 def test_fp32_beyond_the_bf16_terms(shape):
     """Values that have no bf16 terms (an infinity, a NaN, a float above the largest bf16): as the fp32 sum, with
     |error| <= K 2^-24 sum |x||w| where that is finite."""
