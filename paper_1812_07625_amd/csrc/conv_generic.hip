@@ -603,7 +603,7 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
 
 // ---- fp32 products on the bf16 matrix instruction -------------------------------------
 // A float is the sum of three bf16 values, exactly: its rounding h, the rounding m of the rest x - h, and l = x - h - m, at
-// most eight significant bits (below 2^-109 what lies under the smallest bf16, 2^-133, is lost).  Of the nine products of
+// most eight significant bits (of a float below 2^-109, to within 2^-134: bf16 values are multiples of 2^-133).  Of the nine products of
 // two such sums six are taken; the others, m l', l m' and l l', stay below 2^-25 of the product, and a sum over 16 products
 // is rounded six times with v_mfma_f32_32x32x16_bf16, eight times with the fp32 instruction.  Those roundings all go down,
 // towards minus infinity, 5e-8 of the result's rms in its mean, which adds up where many outputs are summed (a bias
@@ -616,8 +616,15 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
 // one or two of B) and half of a panel's steps: its neighbour's sums meet its own through LDS at the end.  128 rows: fewer
 // splits and LDS reads per product, where there are enough tiles (any_plan); 128 x 128 was no faster (16 x 800 frames, k = 11,
 // 256 -> 512: the three passes 779 against 776 us).
-// An operand that is not finite, or that rounds to infinity, makes a NaN of the split; so does a sum that overflows.
-// Where the sums are not finite in the end, the workgroup starts over with the fp32 instruction.
+// The workgroup starts over with the fp32 instruction where the terms do not carry its operands:
+//  - An operand that is not finite, or that rounds to infinity, makes a NaN of the split; so does a sum that overflows: sums that
+//    are not finite in the end.
+//  - Operands below 2^-109 lose up to 2^-134 each, a sum of K products K 2^-133 M at most, M the largest operand of the tile:
+//    a sum below 2^24 times that, but not zero.  (The loss stays below 2^-24 of any other.)
+//  - Some row or column whose operands are all below 2^-108, but not all zero.  (So where a sum is zero the loss stays below
+//    K 2^-26 of the largest operand of its row times that of its column.)
+// The look at the magnitudes, one instruction for two operands in one of the wavefronts that split them, costs 3 % (the
+// 10M-parameter network's step 889 -> 914 us); a test of every third term for bits below the smallest bf16 cost 5 %.
 // Panels and outputs as gemm_f32_k's over FAST lines.  Measured, layers of 256 -> 512, k = 11, forward and backward, this
 // kernel against gemm_f32_k over the same lines: 4 x 400 frames 162 -> 147 us, 16 x 800 981 -> 798; 512 -> 1024, k = 3, 8 x 501
 // frames 357 -> 314; the 10M-parameter network's step 999 -> 861.
@@ -626,13 +633,14 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 struct Split8 { bf16x8 h, m, l; };
-// of sign * v, flip: the sign bits of two bf16 values, set where sign is -1
-__device__ __forceinline__ Split8 split8(const float (&v)[8], float sign = 1.f, unsigned flip = 0)
+// of sign * v, flip: the sign bits of two bf16 values, set where sign is -1; most (or null): the largest magnitude so far
+__device__ __forceinline__ Split8 split8(const float (&v)[8], float* most, float sign = 1.f, unsigned flip = 0)
 {
     u32x4 h, m, l;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         float a = v[2 * q], b = v[2 * q + 1];
+        if (most) *most = fmaxf(fmaxf(*most, fabsf(a)), fabsf(b));
         auto round2 = [&] { return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){a, b}, bf16x2)); };
         h[q] = round2() ^ flip;
         a = __builtin_fmaf(a, sign, -__uint_as_float(h[q] << 16));
@@ -645,6 +653,18 @@ __device__ __forceinline__ Split8 split8(const float (&v)[8], float sign = 1.f, 
     return Split8{__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
 }
 
+// the largest of a wavefront's magnitudes (their bits are in the same order)
+__device__ __forceinline__ unsigned wave_most(float v)
+{
+    unsigned u = __float_as_uint(v);
+    u = max(u, (unsigned)__builtin_amdgcn_update_dpp(0, (int)u, 0xb1 /* quad_perm 1 0 3 2 */, 0xf, 0xf, true));
+    u = max(u, (unsigned)__builtin_amdgcn_update_dpp(0, (int)u, 0x4e /* quad_perm 2 3 0 1 */, 0xf, 0xf, true));
+    u = max(u, (unsigned)__builtin_amdgcn_update_dpp(0, (int)u, 0x141 /* row_half_mirror */, 0xf, 0xf, true));
+    u = max(u, (unsigned)__builtin_amdgcn_update_dpp(0, (int)u, 0x140 /* row_mirror */, 0xf, 0xf, true));
+    auto row = [&](int l) { return (unsigned)__builtin_amdgcn_readlane((int)u, l); };
+    return max(max(row(0), row(16)), max(row(32), row(48)));
+}
+
 template <class OA, class OB, class EP, int BM>
 __global__ __launch_bounds__(256, BM == TILE ? 4 : OA::K_LINES ? 3 : 2) void gemm_split_k(OA oa, OB ob, EP ep, int M, int N, int R, int per,
                                                                                           int splits, float* colsum, int colsum_acc)
@@ -655,14 +675,17 @@ __global__ __launch_bounds__(256, BM == TILE ? 4 : OA::K_LINES ? 3 : 2) void gem
     constexpr int STAGE = PA::FLOATS + PB::FLOATS;
     __shared__ __align__(1024) float lds[2 * STAGE];
     __shared__ float colsums[2 * BM];
+    __shared__ unsigned largest[4];
     const int split = blockIdx.z % splits;
     const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
     take_phase(oa, ob, ep, blockIdx.z / splits, M, R);
     if (OA::PHASED && m0 >= M) return;  // (phases differ by a frame per utterance)
     const int r_begin = split * per, r_end = R < r_begin + per ? R : r_begin + per;
-    // wavefront: 64 rows from wm and 32 NB columns from wn of the tile, steps kh .. kh + 15 of every panel
+    // wavefront: 64 rows from wm and 32 NB columns from wn of the tile, steps kh .. kh + 15 of every panel.  Two wavefronts take the
+    // same rows (128 rows: the same columns), each begins with another 32 of them (xa, xb) and looks at the magnitudes of these
     const int lane = threadIdx.x & 63, half = lane >> 5, wave = threadIdx.x >> 6;
-    const int wm = BM == 128 ? (wave & 1) * 64 : 0, wn = BM == 128 ? 0 : (wave & 1) * 32, kh = __builtin_amdgcn_readfirstlane((wave >> 1) * 16);
+    const int wm = BM == 128 ? (wave & 1) * 64 : 0, wn = BM == 128 ? 0 : (wave & 1) * 32;
+    const int xa = BM == 128 ? 0 : (wave & 1) * 32, xb = BM == 128 ? (wave & 1) * 32 : 0, kh = __builtin_amdgcn_readfirstlane((wave >> 1) * 16);
     const bool sum_a = !PA::KL && colsum && blockIdx.x == 0;
     const unsigned lds0 = (unsigned)(size_t)(lds_byte*)lds;
     PA pa;
@@ -670,7 +693,7 @@ __global__ __launch_bounds__(256, BM == TILE ? 4 : OA::K_LINES ? 3 : 2) void gem
     pa.init(oa, m0, r_end);
     pb.init(ob, n0, r_end);
     f32x16 acc[2][NB];
-    float asum[2];
+    float asum[2], most[3] = {0.f, 0.f, 0.f};  // most: of a row or column of A's blocks and B's first
     const int steps = r_end > r_begin ? (r_end - r_begin + BK - 1) / BK : 0;
     auto request = [&](int st) {  // (past the last panel: that panel again)
         const unsigned dst = lds0 + (st & 1) * (STAGE * 4);
@@ -712,13 +735,13 @@ __global__ __launch_bounds__(256, BM == TILE ? 4 : OA::K_LINES ? 3 : 2) void gem
                 float f[4];
 #pragma unroll
                 for (int n = 0; n < NB; ++n) {
-                    PB::frags(cur + PA::FLOATS, wn + 32 * n, kh + 8 * u, lane, f);
+                    PB::frags(cur + PA::FLOATS, wn + (32 * n ^ xb), kh + 8 * u, lane, f);
 #pragma unroll
                     for (int q = 0; q < 4; ++q) fb[n][4 * u + q] = f[q];
                 }
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
-                    PA::frags(cur, wm + 32 * i, kh + 8 * u, lane, f);
+                    PA::frags(cur, wm + (32 * i ^ xa), kh + 8 * u, lane, f);
 #pragma unroll
                     for (int q = 0; q < 4; ++q) fa[i][4 * u + q] = f[q];
                 }
@@ -750,10 +773,10 @@ __global__ __launch_bounds__(256, BM == TILE ? 4 : OA::K_LINES ? 3 : 2) void gem
             } else {
                 Split8 b[NB];
 #pragma unroll
-                for (int n = 0; n < NB; ++n) b[n] = split8(fb[n], sign, flip);
+                for (int n = 0; n < NB; ++n) b[n] = split8(fb[n], n ? nullptr : &most[2], sign, flip);
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
-                    const Split8 a = split8(fa[i]);
+                    const Split8 a = split8(fa[i], BM == 128 || i == 0 ? &most[i] : nullptr);
                     auto add = [&](const bf16x8& x, bf16x8 Split8::*y) {
 #pragma unroll
                         for (int n = 0; n < NB; ++n) acc[i][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, b[n].*y, acc[i][n], 0, 0, 0);
@@ -777,18 +800,28 @@ __global__ __launch_bounds__(256, BM == TILE ? 4 : OA::K_LINES ? 3 : 2) void gem
             __builtin_amdgcn_sched_barrier(0);  // the wait stays behind the matrix instructions
             arrived();
         }
+        if constexpr (!decltype(exact)::value) {
+            const unsigned u = wave_most(fmaxf(fmaxf(most[0], most[1]), most[2]));
+            if (lane == 0) largest[wave] = u;
+        }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing may land in LDS once it is used otherwise
         __syncthreads();
     };
     run(std::false_type{});
-    bool finite = true;
+    bool redo = false;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) redo |= most[i] > 0.f && most[i] < 0x1p-108f;
+    const float least = __uint_as_float(max(max(largest[0], largest[1]), max(largest[2], largest[3]))) * 0x1p-109f * (float)(16 * steps);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int n = 0; n < NB; ++n)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) finite = finite && fabsf(acc[i][n][e]) <= 3.402823466e38f;
-    if (__syncthreads_or(!finite)) {
+            for (int e = 0; e < 16; ++e) {
+                const float v = fabsf(acc[i][n][e]);
+                redo |= !(v <= 3.402823466e38f) | (v != 0.f & v < least);
+            }
+    if (__syncthreads_or(redo)) {
         run(std::true_type{});
     } else if (kh) {
 #pragma unroll
@@ -810,19 +843,19 @@ __global__ __launch_bounds__(256, BM == TILE ? 4 : OA::K_LINES ? 3 : 2) void gem
 #pragma unroll
         for (int i = 0; i < 2; ++i) asum[i] += __shfl_xor(asum[i], 32, 64);  // lanes 0..31 and 32..63 took different steps
         if ((BM == 128 || (wave & 1) == 0) && lane < 32) {  // (64 rows: the two wavefronts of a half of the steps have the same sums)
-            colsums[keep * BM + wm + lane] = asum[0];
-            colsums[keep * BM + wm + 32 + lane] = asum[1];
+            colsums[keep * BM + wm + xa + lane] = asum[0];
+            colsums[keep * BM + wm + (32 ^ xa) + lane] = asum[1];
         }
     }
     __syncthreads();
     const float* const other = lds + (wave ^ 2) * EXCH;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-        const int n = n0 + wn + 32 * nb + (lane & 31);
+        const int n = n0 + wn + (32 * nb ^ xb) + (lane & 31);
         const float addn = n < N ? ep.add(n) : 0.f;
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-            const int m = m0 + wm + 32 * keep + 8 * (e >> 2) + 4 * half + (e & 3);
+            const int m = m0 + wm + (32 * keep ^ xa) + 8 * (e >> 2) + 4 * half + (e & 3);
             const float own = keep ? acc[1][nb][e] : acc[0][nb][e], far = other[(nb * 16 + e) * 64 + lane];
             if (m < M && n < N) ep.store(ep.row(m) + n, (own + far) + addn, split);
         }

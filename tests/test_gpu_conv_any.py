@@ -315,3 +315,49 @@ def test_fp32_beyond_the_bf16_terms(shape):
     fin = np.isfinite(ref)
     assert (~fin).sum() >= 2 * Cout and (np.abs(ref[fin]) > 1e37).sum() >= 2 * Cout
     assert (np.abs(got[fin] - ref[fin]) <= bound[fin]).all()
+
+
+@pytest.mark.parametrize("shape", [(4, 400, 256, 512, 3), (2, 1321, 32, 3104, 1), (1, 130, 1100, 1600, 3)], ids=lambda s: "x".join(map(str, s)))
+def test_fp32_operands_below_the_bf16_terms(shape):
+    """Operands whose low bits lie under the smallest bf16 (2^-133: floats below 2^-109) against operands of size 1: as
+    accurate as any other.  All of them so small; one row in four; and next to larger operands that meet zeros."""
+    import paper_1812_07625_amd as P
+    B, T, Cin, Cout, k = shape
+    rng = np.random.default_rng(sum(shape) + 5)
+    x, dy = rng.standard_normal((B, T, Cin)).astype(np.float32), rng.standard_normal((B, T, Cout)).astype(np.float32)
+    w = (rng.standard_normal((Cout, k, Cin)) / np.sqrt(k * Cin)).astype(np.float32)
+    x[:, :, 7], dy[:, :, 9], w[:, :, 7], w[9] = 0, 0, 0, 0     # a channel that the products do not see
+    ws = lambda q: P.workspace(q(B, T, Cin, Cout, k, 1, P.W2L_F32))
+    fwd = lambda x: to_host(P.w2l_conv1d_fwd(to_dev(x), to_dev(w), None, empty((B, T, Cout)), 1, ws(P.w2l_conv1d_fwd_workspace_bytes)))
+    dgrad = lambda dy: to_host(P.w2l_conv1d_bwd_data(to_dev(dy), to_dev(w), empty((B, T, Cin)), 1, ws(P.w2l_conv1d_bwd_data_workspace_bytes)))
+
+    def wgrad(x, dy):
+        dw, db = P.w2l_conv1d_bwd_weight(to_dev(x), to_dev(dy), empty((Cout, k, Cin)), empty((Cout,)), 1, False,
+                                         ws(P.w2l_conv1d_bwd_weight_workspace_bytes))
+        return to_host(dw), to_host(db)
+
+    y_o, dx_o = oracle.conv1d_fwd(x, w, None, 1), oracle.conv1d_bwd_data(dy, w, T, 1)
+    dw_o, db_o = oracle.conv1d_bwd_weight(x, dy, k, 1)
+    for e in (-112, -118, -123):
+        s = np.float32(2.0 ** e)
+        up = lambda a: a.astype(np.float64) * 2.0 ** -e
+        _check(up(fwd(x * s)), y_o, False, "y")
+        _check(up(dgrad(dy * s)), dx_o, False, "dx")
+        dw, db = wgrad(x, dy * s)
+        _check(up(dw), dw_o, False, "dw")
+        _check(up(db), db_o, False, "db")
+        _check(up(wgrad(x * s, dy)[0]), dw_o, False, "dw of small x")
+        # rows: frames of the forward pass and the data gradient, channels of the weight gradient
+        rows = np.where(np.arange(T) % 4 == 1, s, np.float32(1))[None, :, None]
+        small = rows[0, :, 0] < 1
+        if k == 1:
+            _check(up(fwd(x * rows)[:, small]), y_o[:, small], False, "small rows of y")
+            _check(up(dgrad(dy * rows)[:, small]), dx_o[:, small], False, "small rows of dx")
+        rows = np.where(np.arange(Cout) % 4 == 1, s, np.float32(1))
+        small = rows < 1
+        _check(up(wgrad(x, dy * rows)[0][small]), dw_o[small], False, "small rows of dw")
+        # larger operands in the same row, whose products are zeros
+        big_x, big_dy = x * s, dy * s
+        big_x[:, :, 7], big_dy[:, :, 9] = 1, 1
+        _check(up(fwd(big_x)), y_o, False, "y beside ones")
+        _check(up(dgrad(big_dy)), dx_o, False, "dx beside ones")
