@@ -151,9 +151,10 @@ bool stage_wgrad_folded(int B, int T, int Cin, int Cout, int k, int s, int dt, C
 extern "C" size_t w2l_conv1d_fwd_workspace_bytes(int B, int T, int Cin, int Cout, int k, int stride, int dtype)
 {
     if (check_conv_shape(B, T, Cin, Cout, k, stride)) return 0;
-    const ConvDesc d = dense_desc(B, T, Cin, Cout, k, stride);
+    ConvDesc d = dense_desc(B, T, Cin, Cout, k, stride);
     if (!valid_dtype(dtype)) return 0;
     const bool f32 = stage_fwd_f32(Cin, k, stride, dtype);
+    if (f32) staged_x(d);  // (the layout decides on the kernel, and that on the runs of its reduction)
     return (f32 || stage_fwd(Cin, Cout, k, stride, dtype) ? haloed_bytes(B, T, f32 ? 2 * Cin : Cin) : 0) + conv_fwd_scratch(d, dtype);
 }
 
@@ -240,7 +241,8 @@ extern "C" size_t w2l_conv1d_bwd_data_workspace_bytes(int B, int T, int Cin, int
     if (p.ok) return p.total();
     if (!valid_dtype(dtype)) return 0;
     const size_t copy = stage_dgrad_f32(Cin, Cout, k, stride, dtype) ? haloed_bytes(B, T, 2 * Cout) : 0;
-    const ConvDesc d = dense_desc(B, T, Cin, Cout, k, stride);
+    ConvDesc d = dense_desc(B, T, Cin, Cout, k, stride);
+    if (copy) staged_y(d);
     const size_t a = conv_dgrad_scratch(d, dtype, dtype), b = conv_dgrad_scratch(d, dtype, W2L_F32);
     return copy + (a > b ? a : b);
 }
@@ -284,12 +286,20 @@ static size_t wgrad_copies(int B, int T, int Cin, int Cout, int k, int stride, i
     return stage_wgrad_folded(B, T, Cin, Cout, k, stride, dtype, f) ? haloed_bytes(B, f.T, f.Cin) + haloed_bytes(B, f.T, Cout) : 0;
 }
 
+// scratch of the kernels: fp32 layers in the layout of their copies
+static size_t wgrad_split_scratch(int B, int T, int Cin, int Cout, int k, int stride, int dtype)
+{
+    ConvDesc d = dense_desc(B, T, Cin, Cout, k, stride);
+    if (stage_wgrad_f32(Cin, Cout, k, stride, dtype)) { staged_x(d); staged_y(d); }
+    return conv_wgrad_scratch_bytes(d, dtype, dtype);
+}
+
 extern "C" size_t w2l_conv1d_bwd_weight_workspace_bytes(int B, int T, int Cin, int Cout, int k, int stride,
                                                         int dtype)
 {
     if (check_conv_shape(B, T, Cin, Cout, k, stride)) return 0;
     if (!valid_dtype(dtype)) return 0;
-    return conv_wgrad_scratch_bytes(dense_desc(B, T, Cin, Cout, k, stride), dtype, dtype) + wgrad_copies(B, T, Cin, Cout, k, stride, dtype) +
+    return wgrad_split_scratch(B, T, Cin, Cout, k, stride, dtype) + wgrad_copies(B, T, Cin, Cout, k, stride, dtype) +
            (stage_wgrad_f32(Cin, Cout, k, stride, dtype) ? haloed_bytes(B, T, 2 * Cin) + haloed_bytes(B, T, 2 * Cout) : 0);
 }
 
@@ -307,7 +317,7 @@ extern "C" int w2l_conv1d_bwd_weight(const void* x, const void* dy, float* dw, f
     ConvDesc d = dense_desc(B, T, Cin, Cout, k, stride);
     // room for the bf16 copies and the bias sums has to be there; a split reduction and fp32 copies where there is room
     // for all of it (an fp32 dy of bf16 operands splits as far as the scratch of a bf16 one takes it)
-    const size_t split = conv_wgrad_scratch_bytes(d, dtype, dtype), least = Cout <= 32 ? split : wgrad_dbias_scratch(d);
+    const size_t split = wgrad_split_scratch(B, T, Cin, Cout, k, stride, dtype), least = Cout <= 32 ? split : wgrad_dbias_scratch(d);
     const bool all = ws_ok(workspace, ws_bytes, w2l_conv1d_bwd_weight_workspace_bytes(B, T, Cin, Cout, k, stride, dtype));
     const size_t scratch = all ? split : least;
     if (!all && !ws_ok(workspace, ws_bytes, least + wgrad_copies(B, T, Cin, Cout, k, stride, dtype))) return W2L_ERR_WORKSPACE;
@@ -349,14 +359,14 @@ extern "C" int w2l_conv1d_launch_config(int pass, int B, int T, int Cin, int Cou
     *splits = 0;
     if (pass == 0) {
         if (!conv_fwd_is_generic(d, dtype)) return W2L_OK;
-        const size_t scratch = with_workspace ? conv_fwd_scratch(d, dtype) : 0;
         if (with_workspace && stage_fwd_f32(Cin, k, stride, dtype)) staged_x(d);
+        const size_t scratch = with_workspace ? conv_fwd_scratch(d, dtype) : 0;
         return conv_fwd_generic_form(d, dtype, scratch, form, splits);
     }
     if (pass == 1) {
         if ((with_workspace && dgrad_prep(B, T, Cin, Cout, k, stride, dtype).ok) || !conv_dgrad_is_generic(d, dtype, dtype)) return W2L_OK;
-        const size_t scratch = with_workspace ? conv_dgrad_scratch(d, dtype, dtype) : 0;
         if (with_workspace && stage_dgrad_f32(Cin, Cout, k, stride, dtype)) staged_y(d);
+        const size_t scratch = with_workspace ? conv_dgrad_scratch(d, dtype, dtype) : 0;
         return conv_dgrad_generic_form(d, dtype, scratch, form, splits);
     }
     if (pass != 2) return W2L_ERR_SHAPE;

@@ -936,6 +936,14 @@ int launch_any(const AnyPlan& pl, OA oa, OB ob, EP ep, long long M, long long N,
     return launch_status();
 }
 
+// the operands of the three passes
+template <typename T> XWindow<T> fwd_a(const ConvDesc& d, const void* x) { return {(const T*)x, (int)((long long)d.B * d.Tp), d.T, d.Tp, d.Cin, d.k, d.s, d.p, d.x_pitch, d.x_halo}; }
+template <typename T> WRows<T> fwd_b(const ConvDesc& d, const void* w) { return {(const T*)w, d.Cout, d.k * d.Cin}; }
+template <typename T> DyWindow<T> dgrad_a(const ConvDesc& d, const void* dy, int f, Phase q) { return {(const T*)dy, d.B, d.T, d.Tp, d.Cout, d.k, d.s, d.p, d.y_pitch, d.y_halo, f, q}; }
+template <typename T> WCols<T> dgrad_b(const ConvDesc& d, const void* w, Phase q) { return {(const T*)w, d.Cin, d.Cout, d.k, d.s, q}; }
+template <typename T> DyT<T> wgrad_a(const ConvDesc& d, const void* dy) { return {(const T*)dy, d.Tp, d.Cout, d.y_pitch, d.y_halo}; }
+template <typename T> XShift<T> wgrad_b(const ConvDesc& d, const void* x) { return {(const T*)x, d.T, d.Tp, d.Cin, d.k, d.s, d.p, d.x_pitch, d.x_halo}; }
+
 bool wgrad_walks(const ConvDesc& d)
 {
     return d.s == 1 && d.x_pitch == d.y_pitch && d.x_halo == d.y_halo && d.x_halo >= d.p && d.slack >= 64 && d.x_pitch >= PANEL / 2 &&
@@ -947,8 +955,8 @@ int fwd_t(const ConvDesc& d, const AnyPlan& pl, const void* x, const void* w, co
           long long plane, hipStream_t st, int* form = nullptr)
 {
     const long long M = (long long)d.B * d.Tp;
-    XWindow<TI> a{(const TI*)x, (int)M, d.T, d.Tp, d.Cin, d.k, d.s, d.p, d.x_pitch, d.x_halo};
-    WRows<TI> b{(const TI*)w, d.Cout, d.k * d.Cin};
+    const XWindow<TI> a = fwd_a<TI>(d, x);
+    const WRows<TI> b = fwd_b<TI>(d, w);
     StoreRows<TO> ep{y, bias, d.Cout, d.Tp, 0, 1, pitch, halo, plane};
     return launch_any(pl, a, b, ep, M, d.Cout, (long long)d.k * d.Cin, st, nullptr, 0, a.fast() && b.fast(), form);
 }
@@ -959,8 +967,8 @@ int dgrad_t(const ConvDesc& d, const AnyPlan& pl, const void* dy, const void* w,
     const int phases = d.s < d.T ? d.s : d.T, most = 65535 / pl.splits;  // (that have frames; that a grid takes)
     for (int f = 0; f < phases; f += most) {
         const Phase q = DyWindow<TDY>::phase(f, d.T, d.k, d.s, d.p);  // of the launch, the one with the most frames
-        DyWindow<TDY> a{(const TDY*)dy, d.B, d.T, d.Tp, d.Cout, d.k, d.s, d.p, d.y_pitch, d.y_halo, f, q};
-        WCols<TW> b{(const TW*)w, d.Cin, d.Cout, d.k, d.s, q};
+        const DyWindow<TDY> a = dgrad_a<TDY>(d, dy, f, q);
+        const WCols<TW> b = dgrad_b<TW>(d, w, q);
         StoreRows<TO> ep{dx, nullptr, d.Cin, q.count, q.first, d.s, pitch, halo, plane};
         const int rc = launch_any(pl, a, b, ep, (long long)d.B * q.count, d.Cin, (long long)q.taps * d.Cout, st, nullptr, 0, a.fast() && b.fast(),
                                   form, phases - f < most ? phases - f : most);
@@ -972,8 +980,8 @@ template <typename TX, typename TDY>
 int wgrad_t(const ConvDesc& d, const AnyPlan& pl, const void* x, const void* dy, float* dw, float* dbias, int accumulate, long long plane,
             hipStream_t st, int* form = nullptr)
 {
-    DyT<TDY> a{(const TDY*)dy, d.Tp, d.Cout, d.y_pitch, d.y_halo};
-    XShift<TX> b{(const TX*)x, d.T, d.Tp, d.Cin, d.k, d.s, d.p, d.x_pitch, d.x_halo};
+    const DyT<TDY> a = wgrad_a<TDY>(d, dy);
+    const XShift<TX> b = wgrad_b<TX>(d, x);
     StoreAcc ep{dw, d.k * d.Cin, accumulate, plane};
     // with x and dy in one haloed layout the reduction runs straight through its frames: dy is zero in the halo
     // frames, and in the slack that the last panel reads into
@@ -1160,18 +1168,29 @@ AnyPlan dgrad_plan(const ConvDesc& d, size_t budget, double fin, bool f32)
     return any_plan((long long)d.B * ((d.T + d.s - 1) / d.s), d.Cin, (long long)((d.k + d.s - 1) / d.s) * d.Cout, budget, fin,
                     (long long)d.B * d.T * d.Cin, phases < d.T ? phases : d.T, f32);
 }
+constexpr long long MOST_WALK = 1LL << 30;
+long long walk_frames(const ConvDesc& d) { return (long long)d.B * (d.Tp + 2 * LAYOUT_HALO); }
 AnyPlan wgrad_plan(const ConvDesc& d, size_t budget, bool f32)
 {
     // the reduction as long as the walk through the haloed layout makes it (where that is no more frames than an entry
     // point takes: a run's end has to stay below 2^31)
-    const long long walk = (long long)d.B * (d.Tp + 2 * LAYOUT_HALO);
-    return any_plan(d.Cout, (long long)d.k * d.Cin, walk <= 1LL << 30 ? walk : (long long)d.B * d.Tp, budget, FINISH_OWN,
+    const long long walk = walk_frames(d);
+    return any_plan(d.Cout, (long long)d.k * d.Cin, walk <= MOST_WALK ? walk : (long long)d.B * d.Tp, budget, FINISH_OWN,
                     (long long)d.Cout * d.k * d.Cin, 1, f32);
 }
-// Passes whose operands gemm_split_k takes, given the haloed layout (the fast() of their operands)
-bool fwd_splits(const ConvDesc& d, int dt) { return dt == W2L_F32 && d.Cin % 4 == 0 && d.k * (long long)d.Cin % 32 == 0; }
-bool dgrad_splits(const ConvDesc& d, int dt) { return dt == W2L_F32 && d.s == 1 && d.Cin % 4 == 0 && d.Cout % 32 == 0; }
-bool wgrad_splits(const ConvDesc& d, int dt) { return dt == W2L_F32 && d.s == 1 && d.Cin % 4 == 0 && d.Cout % 4 == 0; }
+// Passes that gemm_split_k may take: fp32, every window plain memory in the layout at hand (operands aligned: the entry
+// points ask for that).  The others are planned by the costs of the fp32 instruction, which they run on (13 x 1063 frames at a stride
+// of 2, k = 5, 512 -> 256: 107.5 us with the runs that gemm_split_k would take, 3, and 102.0 with 4).
+bool fwd_splits(const ConvDesc& d, int dt) { return dt == W2L_F32 && fwd_a<float>(d, nullptr).fast() && fwd_b<float>(d, nullptr).fast(); }
+bool dgrad_splits(const ConvDesc& d, int dt)
+{
+    const Phase q = DyWindow<float>::phase(0, d.T, d.k, d.s, d.p);
+    return dt == W2L_F32 && dgrad_a<float>(d, nullptr, 0, q).fast() && dgrad_b<float>(d, nullptr, q).fast();
+}
+bool wgrad_splits(const ConvDesc& d, int dt)
+{
+    return dt == W2L_F32 && wgrad_a<float>(d, nullptr).fast() && wgrad_b<float>(d, nullptr).fast() && wgrad_walks(d) && walk_frames(d) <= MOST_WALK;
+}
 size_t part_bytes(int splits, long long rows, long long cols) { return splits > 1 ? round_up((size_t)splits * rows * cols * 4, 256) : 0; }
 }  // namespace
 

@@ -64,3 +64,13 @@ def test_networks_on_two_streams_reserve_no_planes():
     import workloads as W
     n = P.w2l_train_step_workspace_bytes(W.layers_105m(), 8, 1500, 93, P.W2L_BF16)
     assert 460e6 < n < 490e6, n
+
+
+@pytest.mark.parametrize("pass_, shape, splits", [
+    (FWD, (13, 1063, 512, 256, 5, 2), 4), (FWD, (3, 900, 512, 512, 7, 2), 4), (FWD, (8, 1063, 256, 512, 5, 2), 2),   # strided: dense operands
+    (FWD, (2, 700, 512, 512, 19, 1), 7), (BWD_DATA, (2, 700, 512, 512, 19, 1), 7), (BWD_WEIGHT, (5, 1505, 80, 832, 19, 1), 4),  # a window wider than the halo
+], ids=str)
+def test_runs_fit_the_kernel_that_is_launched(pass_, shape, splits):
+    """fp32 layers that are not brought into the haloed layout run on the fp32 instruction, and are split for its cost: the
+    runs that their times were fitted with, not those of the kernel for haloed operands."""
+    assert P.w2l_conv1d_launch_config(pass_, *shape, F32) == (CHUNKS, splits)
