@@ -393,6 +393,14 @@ __global__ __launch_bounds__(64 * WAVES512) void logmel512_k(const float* __rest
                 const float4 wk = w[16 * k], q = p[k];
                 acc = fmaf(wk.w, q.w, fmaf(wk.z, q.z, fmaf(wk.y, q.y, fmaf(wk.x, q.x, acc))));
             }
+            if (__builtin_expect(__any(acc != acc), 0)) {  // a power beyond fp32 met a zero weight: the bands' own bins alone
+                acc = 0.f;
+#pragma unroll 1
+                for (int k = 0; k < 4 * n; ++k) {
+                    const float wk = reinterpret_cast<const float*>(w + 16 * (k >> 2))[k & 3];
+                    acc = wk > 0.f ? fmaf(wk, reinterpret_cast<const float*>(p)[k], acc) : acc;
+                }
+            }
             if (c < d.F && f.t < d.Tmax) store_as(out + c, f.t < f.T ? logf(fmaxf(acc, d.floor)) : 0.f);
         }
         __builtin_amdgcn_wave_barrier();

@@ -87,6 +87,31 @@ def test_logmel_512_edges(P, kw):
     check(feat, flen, cfg["wav"], cfg["wav_len"], n_mels, nfft=512, **kw)
 
 
+@pytest.mark.parametrize("n_mels", [40, 80, 255])
+def test_logmel_512_powers_beyond_fp32(P, n_mels):
+    """A tone so loud that the powers of its bins overflow: bands without such bins are as accurate as ever (zero weights
+    that bands of one sixteen, or a band's last four bins, have for them count nothing), bands over them are infinite."""
+    n = np.arange(1000, dtype=np.float64)
+    wav = (2e18 * np.cos(2 * np.pi * 1000.0 * n / 16000.0 + 0.3))[None, :].astype(np.float32)   # bin 32 of 512
+    feat, flen = run_logmel(P, wav, [1000], 4, n_mels, nfft=512)
+    ref, rlen = oracle.logmel(wav.astype(np.float64), [1000], n_mels=n_mels, Tmax=4)
+    assert flen[0] == rlen[0] == 4
+    feat, ref = feat[0], ref[0]
+    win = 0.54 - 0.46 * np.cos(2 * np.pi * np.arange(400) / 399)
+    power = np.stack([np.abs(np.fft.rfft(wav[0, t * 160:t * 160 + 400].astype(np.float64) * win, 512)) ** 2 for t in range(4)])
+    pts = 700 * (10 ** (np.linspace(0, np.log10(1 + 8000 / 700), n_mels + 2)) - 1) / 31.25    # in bins
+    k = np.arange(257)
+    weight = np.clip(np.minimum((k - pts[:-2, None]) / (pts[1:-1] - pts[:-2])[:, None], (pts[2:, None] - k) / (pts[2:] - pts[1:-1])[:, None]), 0, None)
+    near = ((k > pts[:-2, None] - 0.01) & (k < pts[2:, None] + 0.01))[None]                   # bins that may have a weight
+    whole = ((power[:, None] < 1e38) | ~near).all(-1) & (weight.max(1) > 0.01)                # ... none of them large
+    loud = ((power[:, None] > 1e39) & (weight > 0.01)[None]).any(-1)
+    assert whole.sum() > 60 and loud.sum() >= 8
+    depth_db = (ref.max(axis=1, keepdims=True) - ref) * (10.0 / np.log(10.0))
+    allowed = 4 * (1.2e-6 * 10 ** (depth_db / 20.0) + 1e-5)
+    assert np.isposinf(feat[loud]).all()
+    assert (np.abs(feat - ref)[whole] <= allowed[whole]).all()
+
+
 def test_logmel_benchmark_shape_and_bf16(P):
     """The shape bench.py times (B=8, up to 240240 samples -> 1500 frames of 80 bands): every
     element against the oracle; then the bf16 output the train step would read."""
