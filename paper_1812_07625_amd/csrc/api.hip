@@ -1,29 +1,11 @@
 // C-ABI entry points for the temporal convolution and the library's bookkeeping calls.
 // Argument checks happen here, on the host, before any launch; the kernels assume
 // the shapes they are given.
-#include <map>
-#include <mutex>
-#include <utility>
 #include "common.h"
 
 namespace w2l {
 static thread_local int g_last_hip_error = 0;
 void note_hip_error(hipError_t e) { g_last_hip_error = (int)e; }
-
-int set_lds_once(const void* kern, int bytes)
-{
-    static std::mutex mu;
-    static std::map<std::pair<int, const void*>, int> done;  // largest size already granted
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) dev = -1;
-    std::lock_guard<std::mutex> lock(mu);
-    int& have = done[std::make_pair(dev, kern)];
-    if (dev >= 0 && have >= bytes) return W2L_OK;
-    hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (e != hipSuccess) { note_hip_error(e); return W2L_ERR_LAUNCH; }
-    have = bytes;
-    return W2L_OK;
-}
 }  // namespace w2l
 
 using namespace w2l;

@@ -10,8 +10,6 @@ namespace w2l {
 typedef unsigned short bf16_t;  // raw bits: upper half of an IEEE float
 
 void note_hip_error(hipError_t e);
-// Raise a kernel's dynamic-LDS limit: once per (device, kernel), remembered afterwards.
-int set_lds_once(const void* kern, int bytes);
 // status of the launch just made on this thread
 inline int launch_status() {
     hipError_t e = hipGetLastError();

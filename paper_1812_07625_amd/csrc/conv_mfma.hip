@@ -39,7 +39,10 @@
 // window is then plain in-bounds memory, the per-lane byte offsets are loop invariants, the
 // panel advance is a scalar add on the base pointer, and a load costs three instructions.
 #include <cmath>
+#include <map>
 #include <type_traits>
+#include <mutex>
+#include <utility>
 #include "common.h"
 
 namespace w2l {
@@ -1375,6 +1378,21 @@ __global__ __launch_bounds__(512) void conv_bwd_k(BwdJobs a)
     else dgrad_tile<256, 128, 64, 3, 2, 1, true, bf16_t>(lds, bx, by, a.dy, a.w, dxb, a.dg, a.dper, 0);
 }
 
+// Raise a kernel's dynamic-LDS limit: once per (device, kernel), remembered afterwards.
+int set_lds_once(const void* kern, int bytes)
+{
+    static std::mutex mu;
+    static std::map<std::pair<int, const void*>, int> done;  // largest size already granted
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) dev = -1;
+    std::lock_guard<std::mutex> lock(mu);
+    int& have = done[std::make_pair(dev, kern)];
+    if (dev >= 0 && have >= bytes) return W2L_OK;
+    hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e != hipSuccess) { note_hip_error(e); return W2L_ERR_LAUNCH; }
+    have = bytes;
+    return W2L_OK;
+}
 template <class K>
 int set_lds(K kern, int bytes) { return set_lds_once((const void*)kern, bytes); }
 

@@ -557,8 +557,8 @@ extern "C" int w2l_logmel_fwd(const float* wav, const int* wav_len, void* feat, 
     const void* fn = fast ? (bf ? (const void*)logmel512_k<bf16_t> : (const void*)logmel512_k<float>)
                           : (bf ? (const void*)logmel_k<bf16_t> : (const void*)logmel_k<float>);
     if (lds > 48 * 1024) {
-        const int rc = set_lds_once(fn, (int)lds);
-        if (rc) return rc;
+        hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) { note_hip_error(e); return W2L_ERR_LAUNCH; }
     }
     if (fast && bf) hipLaunchKernelGGL(logmel512_k<bf16_t>, grid, block, lds, st, wav, wav_len, (bf16_t*)feat, feat_len, d);
     else if (fast) hipLaunchKernelGGL(logmel512_k<float>, grid, block, lds, st, wav, wav_len, (float*)feat, feat_len, d);
