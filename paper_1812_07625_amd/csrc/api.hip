@@ -243,7 +243,7 @@ extern "C" size_t w2l_conv1d_bwd_data_workspace_bytes(int B, int T, int Cin, int
     const size_t copy = stage_dgrad_f32(Cin, Cout, k, stride, dtype) ? haloed_bytes(B, T, 2 * Cout) : 0;
     ConvDesc d = dense_desc(B, T, Cin, Cout, k, stride);
     if (copy) staged_y(d);
-    const size_t a = conv_dgrad_scratch(d, dtype, dtype), b = conv_dgrad_scratch(d, dtype, W2L_F32);
+    const size_t a = conv_dgrad_scratch(d, dtype, dtype), b = dtype == W2L_F32 ? a : conv_dgrad_scratch(d, dtype, W2L_F32);
     return copy + (a > b ? a : b);
 }
 
@@ -286,6 +286,13 @@ static size_t wgrad_copies(int B, int T, int Cin, int Cout, int k, int stride, i
     return stage_wgrad_folded(B, T, Cin, Cout, k, stride, dtype, f) ? haloed_bytes(B, f.T, f.Cin) + haloed_bytes(B, f.T, Cout) : 0;
 }
 
+// and an fp32 one's, which are taken where there is room for them
+static size_t wgrad_all_copies(int B, int T, int Cin, int Cout, int k, int stride, int dtype)
+{
+    return wgrad_copies(B, T, Cin, Cout, k, stride, dtype) +
+           (stage_wgrad_f32(Cin, Cout, k, stride, dtype) ? haloed_bytes(B, T, 2 * Cin) + haloed_bytes(B, T, 2 * Cout) : 0);
+}
+
 // scratch of the kernels: fp32 layers in the layout of their copies
 static size_t wgrad_split_scratch(int B, int T, int Cin, int Cout, int k, int stride, int dtype)
 {
@@ -299,8 +306,7 @@ extern "C" size_t w2l_conv1d_bwd_weight_workspace_bytes(int B, int T, int Cin, i
 {
     if (check_conv_shape(B, T, Cin, Cout, k, stride)) return 0;
     if (!valid_dtype(dtype)) return 0;
-    return wgrad_split_scratch(B, T, Cin, Cout, k, stride, dtype) + wgrad_copies(B, T, Cin, Cout, k, stride, dtype) +
-           (stage_wgrad_f32(Cin, Cout, k, stride, dtype) ? haloed_bytes(B, T, 2 * Cin) + haloed_bytes(B, T, 2 * Cout) : 0);
+    return wgrad_split_scratch(B, T, Cin, Cout, k, stride, dtype) + wgrad_all_copies(B, T, Cin, Cout, k, stride, dtype);
 }
 
 extern "C" int w2l_conv1d_bwd_weight(const void* x, const void* dy, float* dw, float* dbias, int B, int T,
@@ -318,7 +324,7 @@ extern "C" int w2l_conv1d_bwd_weight(const void* x, const void* dy, float* dw, f
     // room for the bf16 copies and the bias sums has to be there; a split reduction and fp32 copies where there is room
     // for all of it (an fp32 dy of bf16 operands splits as far as the scratch of a bf16 one takes it)
     const size_t split = wgrad_split_scratch(B, T, Cin, Cout, k, stride, dtype), least = Cout <= 32 ? split : wgrad_dbias_scratch(d);
-    const bool all = ws_ok(workspace, ws_bytes, w2l_conv1d_bwd_weight_workspace_bytes(B, T, Cin, Cout, k, stride, dtype));
+    const bool all = ws_ok(workspace, ws_bytes, split + wgrad_all_copies(B, T, Cin, Cout, k, stride, dtype));
     const size_t scratch = all ? split : least;
     if (!all && !ws_ok(workspace, ws_bytes, least + wgrad_copies(B, T, Cin, Cout, k, stride, dtype))) return W2L_ERR_WORKSPACE;
     unsigned char* ws = static_cast<unsigned char*>(workspace);

@@ -882,20 +882,27 @@ __global__ __launch_bounds__(256, BM == TILE ? 4 : OA::K_LINES ? 3 : 2) void gem
 struct AnyPlan { int splits, per, rows; bool terms; };  // rows: of a tile; terms: gemm_split_k
 struct TileCost { int rows; double cycles, fill[3], fixed; };  // of a panel; the rate with one, two, or more workgroups on a CU
 constexpr TileCost TILES[3] = {{64, 1024, {0.67, 0.72, 0.76}, 12000}, {64, 800, {0.62, 0.70, 0.76}, 14400}, {128, 1470, {0.50, 0.62, 0.78}, 14400}};
-// values: of a plane; problems: that share a launch, each M x N x R (the phases of a stride)
+// values: of a plane; problems: that share a launch, each M x N x R (the phases of a stride).
+// Every call plans its passes, so the search leaves out what cannot be the best: with all CUs at work to the last panel,
+// a tile shape takes `least` (less the rounding of sums), and whatever adds to that adds more with every further run.
 AnyPlan any_plan(long long M, long long N, long long R, size_t budget, double finish_cycles, long long values, int problems, bool f32)
 {
     AnyPlan best{1, 0, TILE, false};
     double best_t = -1;
+    const long long columns = problems * ((N + TILE - 1) / TILE), panels = (R + PANEL - 1) / PANEL;
     for (int v = 0; v < (f32 ? 3 : 1); ++v) {
         const TileCost& c = TILES[v];
-        const long long tiles = problems * ((M + c.rows - 1) / c.rows) * ((N + TILE - 1) / TILE), panels = (R + PANEL - 1) / PANEL;
+        const long long tiles = columns * ((M + c.rows - 1) / c.rows);
+        const double least = (double)tiles * panels / 256 * c.cycles / c.fill[2] * (1 - 1e-9) + c.fixed;
         for (int s = 1; s <= 16; ++s) {
-            const long long per = (panels + s - 1) / s;
-            if (s > 1 && (per * (s - 1) >= panels || per < 2 || (size_t)s * values * 4 > budget)) continue;
+            const double planes = s > 1 ? 8.0 * s * values / 2500 + finish_cycles : 0;
+            if (best_t >= 0 && least + planes >= best_t) break;
+            const long long per = s > 1 ? (panels + s - 1) / s : panels;
+            if (s > 1 && (per < 2 || (size_t)s * values * 4 > budget)) break;
+            if (s > 1 && per * (s - 1) >= panels) continue;
             const long long load = (tiles * s + 255) / 256;
             double t = load * per * c.cycles / c.fill[load > 2 ? 2 : load > 1 ? 1 : 0] + c.fixed;
-            if (s > 1) t += 8.0 * s * values / 2500 + finish_cycles;
+            if (s > 1) t += planes;
             if (best_t < 0 || t < best_t) {
                 best_t = t;
                 best = AnyPlan{s, (int)(per * PANEL), c.rows, v > 0};
