@@ -120,6 +120,11 @@ int w2l_conv1d_bwd_weight(const void *x, const void *dy, float *dw, float *dbias
  * sum up (forms 1 to 4; 0 for form 0).  For tests and tuning; launches nothing.  Errors as the pass itself. */
 int w2l_conv1d_launch_config(int pass, int B, int T, int Cin, int Cout, int k, int stride, int dtype,
                              int with_workspace, int *form, int *splits);
+/* Of the same launch, where it is one of the kernels for any shape and type (forms 1 to 3): rows of its workgroups' tiles
+ * (64 or 128), and whether form 3 makes its products from bf16 terms of the floats (1) or with the fp32 matrix instruction
+ * (0).  0 and 0 for the other forms. */
+int w2l_conv1d_launch_tile(int pass, int B, int T, int Cin, int Cout, int k, int stride, int dtype,
+                           int with_workspace, int *rows, int *terms);
 
 /* ---- gated linear unit (the gated convnet of Sec. 4.1) -----------------------------
  * y: [rows,Cout], Cout even.  Value half a = y[:, :Cout/2], gate half g = y[:, Cout/2:].

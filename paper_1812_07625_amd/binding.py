@@ -19,7 +19,8 @@ _LIB_PATH = os.environ.get("W2L_LIB") or os.path.join(_HERE, "libw2l.so")
 __all__ = [
     "W2L_F32", "W2L_BF16", "W2LError", "w2l_layer", "w2l_version", "w2l_status_str", "w2l_last_hip_error",
     "w2l_conv1d_fwd", "w2l_conv1d_bwd_data", "w2l_conv1d_bwd_weight", "w2l_conv1d_fwd_workspace_bytes",
-    "w2l_conv1d_bwd_data_workspace_bytes", "w2l_conv1d_bwd_weight_workspace_bytes", "w2l_conv1d_launch_config", "w2l_glu_fwd", "w2l_glu_bwd",
+    "w2l_conv1d_bwd_data_workspace_bytes", "w2l_conv1d_bwd_weight_workspace_bytes", "w2l_conv1d_launch_config",
+    "w2l_conv1d_launch_tile", "w2l_glu_fwd", "w2l_glu_bwd",
     "w2l_logsoftmax_fwd", "w2l_logsoftmax_bwd", "w2l_ctc_workspace_bytes", "w2l_ctc_fwd_bwd", "w2l_ctc_fwd_bwd_noalloc",
     "w2l_ctc_check_targets_host", "w2l_ctc_launch_config", "w2l_asg_launch_config", "w2l_asg_workspace_bytes", "w2l_asg_fwd_bwd", "w2l_asg_check_targets_host",
     "w2l_logmel_num_frames", "w2l_logmel_fwd",
@@ -62,6 +63,7 @@ def _load():
         "w2l_conv1d_bwd_data": (i, [vp, vp, vp] + [i] * 8 + [vp, sz, vp]),
         "w2l_conv1d_bwd_weight": (i, [vp, vp, vp, vp] + [i] * 9 + [vp, sz, vp]),
         "w2l_conv1d_launch_config": (i, [i] * 9 + [C.POINTER(C.c_int)] * 2),
+        "w2l_conv1d_launch_tile": (i, [i] * 9 + [C.POINTER(C.c_int)] * 2),
         "w2l_glu_fwd": (i, [vp, vp, ll, i, i, vp]),
         "w2l_glu_bwd": (i, [vp, vp, vp, ll, i, i, vp]),
         "w2l_logsoftmax_fwd": (i, [vp, vp, ll, i, i, vp]),
@@ -193,6 +195,14 @@ def w2l_conv1d_launch_config(pass_, B, T, Cin, Cout, k, stride, dtype, with_work
     out = [C.c_int() for _ in range(2)]
     _check(raw.w2l_conv1d_launch_config(pass_, B, T, Cin, Cout, k, stride, dtype, int(with_workspace), *[C.byref(o) for o in out]),
            "w2l_conv1d_launch_config")
+    return tuple(o.value for o in out)
+
+
+def w2l_conv1d_launch_tile(pass_, B, T, Cin, Cout, k, stride, dtype, with_workspace=True):
+    """(rows, terms) of the same launch; host only."""
+    out = [C.c_int() for _ in range(2)]
+    _check(raw.w2l_conv1d_launch_tile(pass_, B, T, Cin, Cout, k, stride, dtype, int(with_workspace), *[C.byref(o) for o in out]),
+           "w2l_conv1d_launch_tile")
     return tuple(o.value for o in out)
 
 

@@ -353,33 +353,55 @@ extern "C" int w2l_conv1d_bwd_weight(const void* x, const void* dy, float* dw, f
     return conv_wgrad(d, x, dy, dw, dbias, dtype, dy_dtype, accumulate, workspace, scratch, st);
 }
 
-extern "C" int w2l_conv1d_launch_config(int pass, int B, int T, int Cin, int Cout, int k, int stride, int dtype, int with_workspace, int* form,
-                                        int* splits)
+// what a pass launches; rows and terms of the kernels for any shape
+static int launch_form(int pass, int B, int T, int Cin, int Cout, int k, int stride, int dtype, int with_workspace, ConvForm* form)
 {
-    if (!form || !splits) return W2L_ERR_NULL;
     const int rc = check_conv_shape(B, T, Cin, Cout, k, stride);
     if (rc) return rc;
     if (!valid_dtype(dtype)) return W2L_ERR_DTYPE;
     ConvDesc d = dense_desc(B, T, Cin, Cout, k, stride);
-    *form = CONV_BF16;
-    *splits = 0;
+    *form = ConvForm{CONV_BF16, 0, 0, 0};
     if (pass == 0) {
         if (!conv_fwd_is_generic(d, dtype)) return W2L_OK;
         if (with_workspace && stage_fwd_f32(Cin, k, stride, dtype)) staged_x(d);
         const size_t scratch = with_workspace ? conv_fwd_scratch(d, dtype) : 0;
-        return conv_fwd_generic_form(d, dtype, scratch, form, splits);
+        return conv_fwd_generic_form(d, dtype, scratch, form);
     }
     if (pass == 1) {
         if ((with_workspace && dgrad_prep(B, T, Cin, Cout, k, stride, dtype).ok) || !conv_dgrad_is_generic(d, dtype, dtype)) return W2L_OK;
         if (with_workspace && stage_dgrad_f32(Cin, Cout, k, stride, dtype)) staged_y(d);
         const size_t scratch = with_workspace ? conv_dgrad_scratch(d, dtype, dtype) : 0;
-        return conv_dgrad_generic_form(d, dtype, scratch, form, splits);
+        return conv_dgrad_generic_form(d, dtype, scratch, form);
     }
     if (pass != 2) return W2L_ERR_SHAPE;
-    if (Cout <= 32) { *form = CONV_NARROW; *splits = SKINNY_CHUNKS; return W2L_OK; }
+    if (Cout <= 32) { *form = ConvForm{CONV_NARROW, SKINNY_CHUNKS, 0, 0}; return W2L_OK; }
     if (!wgrad_is_generic(d, dtype, dtype)) return W2L_OK;
     if (stage_wgrad_f32(Cin, Cout, k, stride, dtype)) { staged_x(d); staged_y(d); }
-    return conv_wgrad_generic_form(d, dtype, form, splits);
+    return conv_wgrad_generic_form(d, dtype, form);
+}
+
+extern "C" int w2l_conv1d_launch_config(int pass, int B, int T, int Cin, int Cout, int k, int stride, int dtype, int with_workspace, int* form,
+                                        int* splits)
+{
+    if (!form || !splits) return W2L_ERR_NULL;
+    ConvForm f{0, 0, 0, 0};
+    const int rc = launch_form(pass, B, T, Cin, Cout, k, stride, dtype, with_workspace, &f);
+    if (rc) return rc;
+    *form = f.form;
+    *splits = f.splits;
+    return W2L_OK;
+}
+
+extern "C" int w2l_conv1d_launch_tile(int pass, int B, int T, int Cin, int Cout, int k, int stride, int dtype, int with_workspace, int* rows,
+                                      int* terms)
+{
+    if (!rows || !terms) return W2L_ERR_NULL;
+    ConvForm f{0, 0, 0, 0};
+    const int rc = launch_form(pass, B, T, Cin, Cout, k, stride, dtype, with_workspace, &f);
+    if (rc) return rc;
+    *rows = f.rows;
+    *terms = f.terms;
+    return W2L_OK;
 }
 
 // ---- measurement aid: what the matrix pipe sustains with nothing else going on -----------

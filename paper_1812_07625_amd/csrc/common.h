@@ -130,9 +130,10 @@ size_t conv_dgrad_generic_scratch(const ConvDesc& d, int dt);
 size_t conv_wgrad_generic_scratch(const ConvDesc& d, int dt);
 // forms of w2l_conv1d_launch_config
 enum { CONV_BF16 = 0, CONV_REGISTERS = 1, CONV_CHUNKS = 2, CONV_PLAIN = 3, CONV_NARROW = 4 };
-int conv_fwd_generic_form(const ConvDesc& d, int dt, size_t scratch_bytes, int* form, int* splits);
-int conv_dgrad_generic_form(const ConvDesc& d, int dt, size_t scratch_bytes, int* form, int* splits);
-int conv_wgrad_generic_form(const ConvDesc& d, int dt, int* form, int* splits);
+struct ConvForm { int form, splits, rows, terms; };  // and what w2l_conv1d_launch_tile tells
+int conv_fwd_generic_form(const ConvDesc& d, int dt, size_t scratch_bytes, ConvForm* form);
+int conv_dgrad_generic_form(const ConvDesc& d, int dt, size_t scratch_bytes, ConvForm* form);
+int conv_wgrad_generic_form(const ConvDesc& d, int dt, ConvForm* form);
 int conv_fwd_generic(const ConvDesc& d, const void* x, const void* w, const float* bias, void* y, int dt, int ydt,
                      hipStream_t st, void* scratch = nullptr, size_t scratch_bytes = 0);
 int conv_dgrad_generic(const ConvDesc& d, const void* dy, const void* w, void* dx, int dt, int dydt, hipStream_t st,

@@ -914,7 +914,7 @@ AnyPlan any_plan(long long M, long long N, long long R, size_t budget, double fi
 
 template <class OA, class OB, class EP>
 int launch_any(const AnyPlan& pl, OA oa, OB ob, EP ep, long long M, long long N, long long R, hipStream_t st, float* colsum = nullptr,
-               int colsum_acc = 0, bool fast = false, int* form = nullptr, int phases = 1)
+               int colsum_acc = 0, bool fast = false, ConvForm* form = nullptr, int phases = 1)
 {
     constexpr bool f32 = std::is_same<typename OA::type, float>::value && std::is_same<typename OB::type, float>::value;
     const bool tall = f32 && fast && pl.rows > TILE && oa.tall();
@@ -923,8 +923,8 @@ int launch_any(const AnyPlan& pl, OA oa, OB ob, EP ep, long long M, long long N,
     if (M > 2147483647LL || R > 2147483647LL - 4096 || gy > 65535 || gx > 2147483647LL) return W2L_ERR_SHAPE;
     if (M <= 0) return W2L_OK;
     const bool chunks = f32 && oa.chunks() && ob.chunks();
-    if (form) {  // asked which kernel it is (w2l_conv1d_launch_config)
-        *form = !chunks ? CONV_REGISTERS : fast ? CONV_PLAIN : CONV_CHUNKS;
+    if (form) {  // asked which kernel it is
+        *form = ConvForm{!chunks ? CONV_REGISTERS : fast ? CONV_PLAIN : CONV_CHUNKS, pl.splits, rows, chunks && fast && pl.terms};
         return W2L_OK;
     }
     const dim3 g((unsigned)gx, (unsigned)gy, (unsigned)(phases * pl.splits));
@@ -959,7 +959,7 @@ bool wgrad_walks(const ConvDesc& d)
 
 template <typename TI, typename TO>
 int fwd_t(const ConvDesc& d, const AnyPlan& pl, const void* x, const void* w, const float* bias, TO* y, int pitch, int halo,
-          long long plane, hipStream_t st, int* form = nullptr)
+          long long plane, hipStream_t st, ConvForm* form = nullptr)
 {
     const long long M = (long long)d.B * d.Tp;
     const XWindow<TI> a = fwd_a<TI>(d, x);
@@ -969,7 +969,7 @@ int fwd_t(const ConvDesc& d, const AnyPlan& pl, const void* x, const void* w, co
 }
 template <typename TW, typename TDY, typename TO>
 int dgrad_t(const ConvDesc& d, const AnyPlan& pl, const void* dy, const void* w, TO* dx, int pitch, int halo, long long plane, hipStream_t st,
-            int* form = nullptr)
+            ConvForm* form = nullptr)
 {
     const int phases = d.s < d.T ? d.s : d.T, most = 65535 / pl.splits;  // (that have frames; that a grid takes)
     for (int f = 0; f < phases; f += most) {
@@ -985,7 +985,7 @@ int dgrad_t(const ConvDesc& d, const AnyPlan& pl, const void* dy, const void* w,
 }
 template <typename TX, typename TDY>
 int wgrad_t(const ConvDesc& d, const AnyPlan& pl, const void* x, const void* dy, float* dw, float* dbias, int accumulate, long long plane,
-            hipStream_t st, int* form = nullptr)
+            hipStream_t st, ConvForm* form = nullptr)
 {
     const DyT<TDY> a = wgrad_a<TDY>(d, dy);
     const XShift<TX> b = wgrad_b<TX>(d, x);
@@ -1290,26 +1290,23 @@ int conv_wgrad_generic(const ConvDesc& d, const void* x, const void* dy, float* 
     return finish_sums(part, pl.splits, plane, dw, bout, d.Cout, dbias, accumulate, st);
 }
 // Which kernel the calls below would take and into how many runs the reduction goes (operands aligned; nothing is launched)
-int conv_fwd_generic_form(const ConvDesc& d, int dt, size_t scratch_bytes, int* form, int* splits)
+int conv_fwd_generic_form(const ConvDesc& d, int dt, size_t scratch_bytes, ConvForm* form)
 {
     const AnyPlan pl = fwd_plan(d, scratch_bytes < MAX_PARTIALS ? scratch_bytes : MAX_PARTIALS, FINISH_OWN, fwd_splits(d, dt));
-    *splits = pl.splits;
     float* const y = nullptr;
     if (dt == W2L_F32) return fwd_t<float, float>(d, pl, nullptr, nullptr, nullptr, y, d.y_pitch, d.y_halo, 0, nullptr, form);
     return fwd_t<bf16_t, float>(d, pl, nullptr, nullptr, nullptr, y, d.y_pitch, d.y_halo, 0, nullptr, form);
 }
-int conv_dgrad_generic_form(const ConvDesc& d, int dt, size_t scratch_bytes, int* form, int* splits)
+int conv_dgrad_generic_form(const ConvDesc& d, int dt, size_t scratch_bytes, ConvForm* form)
 {
     const AnyPlan pl = dgrad_plan(d, scratch_bytes < MAX_PARTIALS ? scratch_bytes : MAX_PARTIALS, FINISH_OWN, dgrad_splits(d, dt));
-    *splits = pl.splits;
     float* const dx = nullptr;
     if (dt == W2L_F32) return dgrad_t<float, float, float>(d, pl, nullptr, nullptr, dx, d.x_pitch, d.x_halo, 0, nullptr, form);
     return dgrad_t<bf16_t, bf16_t, float>(d, pl, nullptr, nullptr, dx, d.x_pitch, d.x_halo, 0, nullptr, form);
 }
-int conv_wgrad_generic_form(const ConvDesc& d, int dt, int* form, int* splits)
+int conv_wgrad_generic_form(const ConvDesc& d, int dt, ConvForm* form)
 {
     const AnyPlan pl = wgrad_plan(d, MAX_PARTIALS, wgrad_splits(d, dt));
-    *splits = pl.splits;
     if (dt == W2L_F32) return wgrad_t<float, float>(d, pl, nullptr, nullptr, nullptr, nullptr, 0, 0, nullptr, form);
     return wgrad_t<bf16_t, bf16_t>(d, pl, nullptr, nullptr, nullptr, nullptr, 0, 0, nullptr, form);
 }
