@@ -90,11 +90,11 @@ size_t conv_dgrad_scratch(const ConvDesc& d, int dt, int dydt)
 // scratch of a weight gradient: column sums (in the 256 bytes a channel that a workspace has to have at least: the sums
 // take 64), then what the kernel of the shape needs
 static size_t wgrad_dbias_scratch(const ConvDesc& d) { return d.Cout <= 32 ? 0 : (size_t)256 * d.Cout; }
-size_t conv_wgrad_scratch_bytes(const ConvDesc& d, int dt, int dydt, bool split)
+size_t conv_wgrad_scratch_bytes(const ConvDesc& d, int dt, int dydt, Runs runs)
 {
     const size_t rest = d.Cout <= 32                    ? conv_wgrad_skinny_scratch(d.Cin, d.Cout, d.k)
-                        : !split                        ? 0
-                        : wgrad_is_generic(d, dt, dydt) ? conv_wgrad_generic_scratch(d, dt)
+                        : runs == Runs::WHOLE           ? 0
+                        : wgrad_is_generic(d, dt, dydt) ? conv_wgrad_generic_scratch(d, dt, runs == Runs::ALONE)
                                                         : conv_wgrad_mfma_scratch(d);
     return wgrad_dbias_scratch(d) + rest;
 }
@@ -106,13 +106,13 @@ bool conv_wgrad_fuses_dbias(const ConvDesc& d, int dt, int dydt)
 }
 
 int conv_wgrad(const ConvDesc& d, const void* x, const void* dy, float* dw, float* dbias, int dt, int dydt,
-               int accumulate, void* scratch, size_t scratch_bytes, hipStream_t st, bool split)
+               int accumulate, void* scratch, size_t scratch_bytes, hipStream_t st, Runs runs)
 {
     float* dbias_scratch = static_cast<float*>(scratch);
     unsigned char* rest = static_cast<unsigned char*>(scratch) + wgrad_dbias_scratch(d);
-    const size_t rest_bytes = split && scratch_bytes > wgrad_dbias_scratch(d) ? scratch_bytes - wgrad_dbias_scratch(d) : 0;
+    const size_t rest_bytes = runs != Runs::WHOLE && scratch_bytes > wgrad_dbias_scratch(d) ? scratch_bytes - wgrad_dbias_scratch(d) : 0;
     if (wgrad_is_generic(d, dt, dydt))
-        return conv_wgrad_generic(d, x, dy, dw, dbias, dt, dydt, accumulate, st, rest, rest_bytes);
+        return conv_wgrad_generic(d, x, dy, dw, dbias, dt, dydt, accumulate, st, rest, rest_bytes, runs == Runs::ALONE);
     if (d.Cout <= 32) return conv_wgrad_skinny(d, x, dy, dw, dbias, dt, dydt, accumulate, reinterpret_cast<float*>(rest), st);
     if (dbias && conv_wgrad_fuses_dbias(d, dt, dydt)) return conv_wgrad_mfma(d, x, dy, dw, dbias, accumulate, st, rest, rest_bytes);
     if (dbias) {
@@ -298,7 +298,7 @@ static size_t wgrad_split_scratch(int B, int T, int Cin, int Cout, int k, int st
 {
     ConvDesc d = dense_desc(B, T, Cin, Cout, k, stride);
     if (stage_wgrad_f32(Cin, Cout, k, stride, dtype)) { staged_x(d); staged_y(d); }
-    return conv_wgrad_scratch_bytes(d, dtype, dtype);
+    return conv_wgrad_scratch_bytes(d, dtype, dtype, Runs::ALONE);
 }
 
 extern "C" size_t w2l_conv1d_bwd_weight_workspace_bytes(int B, int T, int Cin, int Cout, int k, int stride,
@@ -336,7 +336,7 @@ extern "C" int w2l_conv1d_bwd_weight(const void* x, const void* dy, float* dw, f
         if (rc) return rc;
         staged_x(f);
         staged_y(f);
-        return conv_wgrad(f, xp, dyp, dw, dbias, dtype, dy_dtype, accumulate, workspace, scratch, st);
+        return conv_wgrad(f, xp, dyp, dw, dbias, dtype, dy_dtype, accumulate, workspace, scratch, st, Runs::ALONE);
     }
     const bool f32 = all && stage_wgrad_f32(Cin, Cout, k, stride, dtype);
     if (f32 || (dy_dtype == W2L_BF16 && stage_wgrad(Cin, Cout, k, stride, dtype))) {
@@ -350,7 +350,7 @@ extern "C" int w2l_conv1d_bwd_weight(const void* x, const void* dy, float* dw, f
         x = xp;
         dy = dyp;
     }
-    return conv_wgrad(d, x, dy, dw, dbias, dtype, dy_dtype, accumulate, workspace, scratch, st);
+    return conv_wgrad(d, x, dy, dw, dbias, dtype, dy_dtype, accumulate, workspace, scratch, st, Runs::ALONE);
 }
 
 // what a pass launches; rows and terms of the kernels for any shape

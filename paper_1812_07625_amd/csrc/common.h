@@ -105,12 +105,13 @@ int conv_dgrad(const ConvDesc& d, const void* dy, const void* w, void* dx, int d
                void* scratch = nullptr, size_t scratch_bytes = 0);
 size_t conv_dgrad_scratch_bytes(const ConvDesc& d);
 size_t conv_dgrad_pair_bytes(const ConvDesc& d);  // of conv_dgrad_glu (0: no use for any)
-// scratch: conv_wgrad_scratch_bytes() bytes of device memory; split = false: the reduction stays whole
-size_t conv_wgrad_scratch_bytes(const ConvDesc& d, int dt, int dydt, bool split = true);
+// scratch: conv_wgrad_scratch_bytes() bytes of device memory
+enum class Runs { WHOLE, IN_STEP, ALONE };  // of the reduction: not split; split as fits inside a train step, or a launch by itself
+size_t conv_wgrad_scratch_bytes(const ConvDesc& d, int dt, int dydt, Runs runs);
 // true where conv_wgrad() produces dbias inside the weight-gradient launch (no separate column-sum kernels)
 bool conv_wgrad_fuses_dbias(const ConvDesc& d, int dt, int dydt);
 int conv_wgrad(const ConvDesc& d, const void* x, const void* dy, float* dw, float* dbias, int dt, int dydt,
-               int accumulate, void* scratch, size_t scratch_bytes, hipStream_t st, bool split = true);
+               int accumulate, void* scratch, size_t scratch_bytes, hipStream_t st, Runs runs);
 
 constexpr size_t MAX_PARTIALS = 96u << 20;  // bytes of partial sums that a split reduction may leave (they stay in the memory-side cache)
 // Planes of fp32 sums that the pass leaves in front of the GLU pass that adds them up (1: the pass is not split), the
@@ -127,7 +128,7 @@ size_t conv_dgrad_scratch(const ConvDesc& d, int dt, int dydt);
 // with too few tiles for the chip splits its reduction and adds the fp32 sums in a finishing launch
 size_t conv_fwd_generic_scratch(const ConvDesc& d, int dt);
 size_t conv_dgrad_generic_scratch(const ConvDesc& d, int dt);
-size_t conv_wgrad_generic_scratch(const ConvDesc& d, int dt);
+size_t conv_wgrad_generic_scratch(const ConvDesc& d, int dt, bool alone);
 // forms of w2l_conv1d_launch_config
 enum { CONV_BF16 = 0, CONV_REGISTERS = 1, CONV_CHUNKS = 2, CONV_PLAIN = 3, CONV_NARROW = 4 };
 struct ConvForm { int form, splits, rows, terms; };  // and what w2l_conv1d_launch_tile tells
@@ -139,7 +140,7 @@ int conv_fwd_generic(const ConvDesc& d, const void* x, const void* w, const floa
 int conv_dgrad_generic(const ConvDesc& d, const void* dy, const void* w, void* dx, int dt, int dydt, hipStream_t st,
                        void* scratch = nullptr, size_t scratch_bytes = 0);
 int conv_wgrad_generic(const ConvDesc& d, const void* x, const void* dy, float* dw, float* dbias, int dt, int dydt, int accumulate,
-                       hipStream_t st, void* scratch = nullptr, size_t scratch_bytes = 0);
+                       hipStream_t st, void* scratch, size_t scratch_bytes, bool alone);
 // The same, leaving the *_parts() planes of fp32 sums ([parts][B * frames][channels], dense) to the finish_* pass that
 // the caller fuses with its next elementwise step.
 int conv_fwd_generic_parts(const ConvDesc& d, int dt);

@@ -871,27 +871,32 @@ __global__ __launch_bounds__(256, BM == TILE ? 4 : OA::K_LINES ? 3 : 2) void gem
 // cycles: panels at 16 instructions of 64 cycles, one after the other for the workgroups that share a CU (at 0.67 of
 // the rate if there is one, 0.76 from three on: measured, 4 x 400 frames, k = 11, 256 -> 512, forward: 200 workgroups
 // of 88 panels 61 us, 1000 of 18 panels 46 us), about 12000 to fill and to drain, and for a split the partial sums'
-// way to memory and back (2500 bytes per cycle) plus the finishing launch.  64 x 64 outputs per workgroup everywhere:
-// 128 x 128 was slower on the largest problems as well (16 x 1600 frames, k = 11, 512 -> 1024: forward 2.30 against
+// way to memory and back (2500 bytes per cycle) plus the finishing launch.  64 x 64 outputs per workgroup with the fp32
+// instruction: 128 x 128 was slower on the largest problems as well (16 x 1600 frames, k = 11, 512 -> 1024: forward 2.30 against
 // 2.18 ms, data gradient 2.69 against 2.38, weight gradient 3.06 against 2.45), four small workgroups on a CU
 // covering each other's barriers better than two large ones.
 // fp32 operands in haloed tensors choose between gemm_f32_k and gemm_split_k's tiles of 64 or 128 rows: 800 and 1470 cycles a
-// panel for the matrix instructions and the splits, at rates fitted to the layers named there with either tile, and 2400 more
-// for the exchange of sums and the longer code.  So runs of up to about ten panels that leave CUs idle keep the fp32
-// instruction (2 x 100 frames, 64 -> 128, k = 5, forward / data gradient: 6.1 / 6.2 us against 7.1 / 7.4).
+// panel for the matrix instructions and the splits, the rates and what is added (the exchange of sums, the look at the
+// magnitudes, the longer code) fitted twice.  Inside a train step the passes before and behind, and the other gradient on
+// its second stream, cover a launch's ends.  A pass called by itself has them in the open, and short runs keep the fp32
+// instruction.  250 layers of up to 27 GFLOP a pass, each pass by either kernel in every split that the rule may pick, times of the
+// whole layer: by the step's figures 72 of 750 passes cost their layer more than 2 % against the fp32 instruction (up to 6.4 %) and the
+// mean layer gains 0.1 % a pass; by those for passes alone 4 (up to 4 %), and 0.7 %.  The steps of 25 networks the other way round: by
+// the figures for passes alone 9 are more than 2 % slower than by their own (up to 9 %), none is more than 2 % faster.
 struct AnyPlan { int splits, per, rows; bool terms; };  // rows: of a tile; terms: gemm_split_k
 struct TileCost { int rows; double cycles, fill[3], fixed; };  // of a panel; the rate with one, two, or more workgroups on a CU
-constexpr TileCost TILES[3] = {{64, 1024, {0.67, 0.72, 0.76}, 12000}, {64, 800, {0.62, 0.70, 0.76}, 14400}, {128, 1470, {0.50, 0.62, 0.78}, 14400}};
-// values: of a plane; problems: that share a launch, each M x N x R (the phases of a stride).
+constexpr TileCost TILES[2][3] = {{{64, 1024, {0.67, 0.72, 0.76}, 12000}, {64, 800, {0.62, 0.70, 0.76}, 14400}, {128, 1470, {0.50, 0.62, 0.78}, 14400}},
+                                  {{64, 1024, {0.67, 0.72, 0.76}, 12000}, {64, 800, {0.53, 0.73, 0.75}, 23000}, {128, 1470, {0.54, 0.81, 0.84}, 27000}}};
+// values: of a plane; problems: that share a launch, each M x N x R (the phases of a stride); alone: not part of a train step.
 // Every call plans its passes, so the search leaves out what cannot be the best: with all CUs at work to the last panel,
 // a tile shape takes `least` (less the rounding of sums), and whatever adds to that adds more with every further run.
-AnyPlan any_plan(long long M, long long N, long long R, size_t budget, double finish_cycles, long long values, int problems, bool f32)
+AnyPlan any_plan(long long M, long long N, long long R, size_t budget, double finish_cycles, long long values, int problems, bool f32, bool alone)
 {
     AnyPlan best{1, 0, TILE, false};
     double best_t = -1;
     const long long columns = problems * ((N + TILE - 1) / TILE), panels = (R + PANEL - 1) / PANEL;
     for (int v = 0; v < (f32 ? 3 : 1); ++v) {
-        const TileCost& c = TILES[v];
+        const TileCost& c = TILES[alone][v];
         const long long tiles = columns * ((M + c.rows - 1) / c.rows);
         const double least = (double)tiles * panels / 256 * c.cycles / c.fill[2] * (1 - 1e-9) + c.fixed;
         for (int s = 1; s <= 16; ++s) {
@@ -1166,24 +1171,24 @@ constexpr double FINISH_OWN = 12000, FINISH_FREE = 2000;
 AnyPlan fwd_plan(const ConvDesc& d, size_t budget, double fin, bool f32)
 {
     const long long M = (long long)d.B * d.Tp;
-    return any_plan(M, d.Cout, (long long)d.k * d.Cin, budget, fin, M * d.Cout, 1, f32);
+    return any_plan(M, d.Cout, (long long)d.k * d.Cin, budget, fin, M * d.Cout, 1, f32, fin == FINISH_OWN);
 }
 AnyPlan dgrad_plan(const ConvDesc& d, size_t budget, double fin, bool f32)
 {
     // of a stride's phases, the one with the most taps, as often as there are any with taps; a plane takes all of them
     const int phases = d.s < d.k ? d.s : d.k;
     return any_plan((long long)d.B * ((d.T + d.s - 1) / d.s), d.Cin, (long long)((d.k + d.s - 1) / d.s) * d.Cout, budget, fin,
-                    (long long)d.B * d.T * d.Cin, phases < d.T ? phases : d.T, f32);
+                    (long long)d.B * d.T * d.Cin, phases < d.T ? phases : d.T, f32, fin == FINISH_OWN);
 }
 constexpr long long MOST_WALK = 1LL << 30;
 long long walk_frames(const ConvDesc& d) { return (long long)d.B * (d.Tp + 2 * LAYOUT_HALO); }
-AnyPlan wgrad_plan(const ConvDesc& d, size_t budget, bool f32)
+AnyPlan wgrad_plan(const ConvDesc& d, size_t budget, bool f32, bool alone)
 {
     // the reduction as long as the walk through the haloed layout makes it (where that is no more frames than an entry
     // point takes: a run's end has to stay below 2^31)
     const long long walk = walk_frames(d);
     return any_plan(d.Cout, (long long)d.k * d.Cin, walk <= MOST_WALK ? walk : (long long)d.B * d.Tp, budget, FINISH_OWN,
-                    (long long)d.Cout * d.k * d.Cin, 1, f32);
+                    (long long)d.Cout * d.k * d.Cin, 1, f32, alone);
 }
 // Passes that gemm_split_k may take: fp32, every window plain memory in the layout at hand (operands aligned: the entry
 // points ask for that).  The others are planned by the costs of the fp32 instruction, which they run on (13 x 1063 frames at a stride
@@ -1209,9 +1214,9 @@ size_t conv_dgrad_generic_scratch(const ConvDesc& d, int dt)
 {
     return part_bytes(dgrad_plan(d, MAX_PARTIALS, FINISH_OWN, dgrad_splits(d, dt)).splits, (long long)d.B * d.T, d.Cin);
 }
-size_t conv_wgrad_generic_scratch(const ConvDesc& d, int dt)
+size_t conv_wgrad_generic_scratch(const ConvDesc& d, int dt, bool alone)
 {
-    return part_bytes(wgrad_plan(d, MAX_PARTIALS, wgrad_splits(d, dt)).splits, d.Cout, (long long)d.k * d.Cin + 1);
+    return part_bytes(wgrad_plan(d, MAX_PARTIALS, wgrad_splits(d, dt), alone).splits, d.Cout, (long long)d.k * d.Cin + 1);
 }
 int conv_fwd_generic_parts(const ConvDesc& d, int dt) { return fwd_plan(d, MAX_PARTIALS, FINISH_FREE, fwd_splits(d, dt)).splits; }
 int conv_dgrad_generic_parts(const ConvDesc& d, int dt) { return dgrad_plan(d, MAX_PARTIALS, FINISH_FREE, dgrad_splits(d, dt)).splits; }
@@ -1267,15 +1272,15 @@ int conv_dgrad_generic(const ConvDesc& d, const void* dy, const void* w, void* d
     return dgrad_t<bf16_t, float, bf16_t>(d, pl, dy, w, (bf16_t*)dx, d.x_pitch, d.x_halo, 0, st);
 }
 int conv_wgrad_generic(const ConvDesc& d, const void* x, const void* dy, float* dw, float* dbias, int dt, int dydt, int accumulate,
-                       hipStream_t st, void* scratch, size_t scratch_bytes)
+                       hipStream_t st, void* scratch, size_t scratch_bytes, bool alone)
 {
     if (dt == W2L_F32 && dydt != W2L_F32) return W2L_ERR_DTYPE;
     // (the bias sums of the splits lie behind the weight sums: one more column)
     const long long n = (long long)d.k * d.Cin, plane = d.Cout * n;
-    AnyPlan pl = wgrad_plan(d, MAX_PARTIALS, wgrad_splits(d, dt));
+    AnyPlan pl = wgrad_plan(d, MAX_PARTIALS, wgrad_splits(d, dt), alone);
     if (!scratch || scratch_bytes < part_bytes(pl.splits, d.Cout, n + 1)) {
         const size_t bias = (size_t)17 * d.Cout * 4;  // (room for the bias sums of 16 splits, rounded up)
-        pl = wgrad_plan(d, scratch && scratch_bytes > bias ? scratch_bytes - bias : 0, wgrad_splits(d, dt));
+        pl = wgrad_plan(d, scratch && scratch_bytes > bias ? scratch_bytes - bias : 0, wgrad_splits(d, dt), alone);
     }
     float* part = static_cast<float*>(scratch);
     const bool split = pl.splits > 1;
@@ -1306,7 +1311,7 @@ int conv_dgrad_generic_form(const ConvDesc& d, int dt, size_t scratch_bytes, Con
 }
 int conv_wgrad_generic_form(const ConvDesc& d, int dt, ConvForm* form)
 {
-    const AnyPlan pl = wgrad_plan(d, MAX_PARTIALS, wgrad_splits(d, dt));
+    const AnyPlan pl = wgrad_plan(d, MAX_PARTIALS, wgrad_splits(d, dt), true);
     if (dt == W2L_F32) return wgrad_t<float, float>(d, pl, nullptr, nullptr, nullptr, nullptr, 0, 0, nullptr, form);
     return wgrad_t<bf16_t, bf16_t>(d, pl, nullptr, nullptr, nullptr, nullptr, 0, 0, nullptr, form);
 }

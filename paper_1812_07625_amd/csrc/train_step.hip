@@ -95,7 +95,7 @@ size_t planes_bytes(int parts, size_t values) { return parts > 1 ? parts * value
 // a second stream takes: these stay on the caller's stream (unless the second stream is there anyway).
 bool main_wgrad(const Plan& p, const w2l_layer& l, int i) { return i == 0 || (l.cout <= 32 && !p.crowded); }
 // whether a weight gradient may cut its reduction
-bool cut_wgrad(const Plan& p, int dydt) { return !(p.crowded && dydt == W2L_BF16); }
+Runs wgrad_runs(const Plan& p, int dydt) { return p.crowded && dydt == W2L_BF16 ? Runs::WHOLE : Runs::IN_STEP; }
 bool same_layer(const w2l_layer& a, const w2l_layer& b) { return a.k == b.k && a.stride == b.stride && a.cin == b.cin && a.cout == b.cout && a.glu == b.glu; }
 
 Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int criterion)
@@ -164,7 +164,7 @@ Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int
         const ConvDesc d = i ? layer_bwd_desc(p, L, B, i) : dense_desc(B, T, l.cin, l.cout, l.k, l.stride);
         size_t& bytes = p.bwd[i].ok || main_wgrad(p, l, i) ? p.conv0_bytes : p.conv_bytes;
         const int dydt = i == n - 1 ? W2L_F32 : dtype;
-        bytes = max_of(bytes, p.bwd[i].ok ? p.bwd[i].wscratch : conv_wgrad_scratch_bytes(d, dtype, dydt, cut_wgrad(p, dydt)));
+        bytes = max_of(bytes, p.bwd[i].ok ? p.bwd[i].wscratch : conv_wgrad_scratch_bytes(d, dtype, dydt, wgrad_runs(p, dydt)));
     }
     p.Tlast = t;
     p.C = L[n - 1].cout;
@@ -428,7 +428,7 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
         // the shorter chain
         const bool fused_dbias = dbiases[i] && conv_wgrad_fuses_dbias(d, dtype, dy_dt);
         rc = conv_wgrad(d, xin, dy, dweights[i], (fused_dbias || !side) ? dbiases[i] : nullptr, dtype, dy_dt, 0,
-                        ws + (on_main ? p.conv0 : p.conv), on_main ? p.conv0_bytes : p.conv_bytes, wst, cut_wgrad(p, dy_dt));
+                        ws + (on_main ? p.conv0 : p.conv), on_main ? p.conv0_bytes : p.conv_bytes, wst, wgrad_runs(p, dy_dt));
         if (rc) return rc;
         if (on_side) {
             if (!hip_ok(hipEventRecord(side->done[i], wst))) return W2L_ERR_LAUNCH;

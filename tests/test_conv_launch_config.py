@@ -74,3 +74,16 @@ def test_runs_fit_the_kernel_that_is_launched(pass_, shape, splits):
     """fp32 layers that are not brought into the haloed layout run on the fp32 instruction, and are split for its cost: the
     runs that their times were fitted with, not those of the kernel for haloed operands."""
     assert P.w2l_conv1d_launch_config(pass_, *shape, F32) == (CHUNKS, splits)
+
+
+@pytest.mark.parametrize("pass_, shape, tile", [
+    # a few panels a workgroup: what the kernel for bf16 terms adds to a launch is more than it saves
+    (FWD, (9, 63, 64, 768, 11), (64, 0)), (FWD, (9, 1431, 64, 592, 1), (64, 0)), (BWD_DATA, (4, 1062, 160, 128, 3), (64, 0)),
+    (BWD_DATA, (6, 249, 256, 448, 1), (64, 0)), (BWD_WEIGHT, (3, 148, 160, 384, 5), (64, 0)), (BWD_WEIGHT, (1, 583, 96, 512, 7), (64, 0)),
+    # longer ones, few and many tiles
+    (FWD, (4, 400, 256, 512, 11), (64, 1)), (BWD_DATA, (4, 400, 256, 512, 11), (64, 1)), (BWD_WEIGHT, (4, 200, 256, 512, 11), (64, 1)),
+    (FWD, (16, 800, 256, 512, 11), (128, 1)), (BWD_DATA, (16, 800, 256, 512, 11), (128, 1)), (BWD_WEIGHT, (16, 800, 256, 512, 11), (128, 1)),
+], ids=str)
+def test_fp32_passes_alone_take_bf16_terms_where_that_is_faster(pass_, shape, tile):
+    """By the times of either kernel, 6 to 24 % of a pass in the first group (the weight gradients: 5 % of their layer)."""
+    assert P.w2l_conv1d_launch_tile(pass_, *shape, 1, F32) == tile
