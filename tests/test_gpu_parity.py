@@ -140,7 +140,9 @@ def test_glu(P, rows, Cout, dtype):
     check_one_kernel(to_host(dy), oracle.glu_bwd(y, dh), dtype, "dy")
 
 
-@pytest.mark.parametrize("rows,Cc", [(24000, 29), (100, 1), (37, 100), (9, 4096)])
+@pytest.mark.parametrize("rows,Cc", [(24000, 29), (100, 1), (37, 100), (9, 4096),
+                                     # sixteen lanes a row: their edges, the last class of that kernel, more rows than a grid
+                                     (53, 15), (50, 16), (49, 17), (47, 48), (33, 49), (31, 63), (30, 64), (29, 65), (140_001, 5)])
 def test_logsoftmax(P, rows, Cc):
     rng = np.random.default_rng(rows)
     z = (rng.standard_normal((rows, Cc)) * 3).astype(np.float32)
@@ -263,9 +265,12 @@ def test_ctc_from_logprobs_scale_blank_and_edges(P):
     _check_ctc(loss, grad, loss_o, 0.25 * g_o)
 
 
-def test_ctc_large_alphabet_gathers_scores_per_lane(P):
-    # 600 classes: the class rows of a block of frames do not fit the workgroup's score table
-    cfg = W.config2(seed=21, B=3, T=80, in_lo=60, in_hi=80, l_lo=5, l_hi=20, Cc=600)
+@pytest.mark.parametrize("Lmax,gathers", [(20, False), (200, True)])
+def test_ctc_large_alphabet_gathers_scores_per_lane(P, Lmax, gathers):
+    # 600 classes: a row for each of a short target's positions fits the score table, for each of a long one's it does not
+    T = 60 + 2 * Lmax
+    cfg = W.config2(seed=21, B=3, T=T, in_lo=T - 20, in_hi=T, l_lo=3 * Lmax // 4, l_hi=Lmax, Cc=600)
+    assert (P.w2l_ctc_launch_config(600, cfg["targets"].shape[1])[1] == 0) == gathers
     loss, grad = _run_ctc(P, cfg["logits"], 1, cfg["targets"], cfg["in_len"], cfg["tgt_len"], 0, 1.0)
     loss_o, _, dz_o = oracle.ctc_from_logits(cfg["logits"].astype(np.float64), cfg["targets"], cfg["in_len"],
                                              cfg["tgt_len"])

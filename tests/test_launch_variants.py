@@ -1,11 +1,11 @@
-"""Host-only: every lattice-kernel variant the criterion entry points can dispatch to, and every form of the train
-step's shared gradient launch, is the variant of at least one GPU parity case (tests/variant_cases.py).  The set of
+"""Host-only: every lattice-kernel variant the criterion entry points can dispatch to, every form of the train
+step's shared gradient launch, and every kernel that an fp32 convolution takes over haloed operands, is the variant of at least one GPU parity case (tests/variant_cases.py).  The set of
 reachable variants is found by asking the library's launch-configuration query for every size it accepts (gradients:
 for layers all over the range)."""
 import random
 
 import paper_1812_07625_amd as P
-from variant_cases import ASG_CASES, BWD_CASES, CTC_CASES, asg_variant, bwd_variant, ctc_variant
+from variant_cases import ASG_CASES, BWD_CASES, CTC_CASES, F32_CASES, asg_variant, bwd_variant, ctc_variant, f32_variants
 
 
 def _reachable(query, classes, lmax_max):
@@ -46,6 +46,21 @@ def test_gradient_cases_cover_every_reachable_form():
     covered = {bwd_variant(P, *c) for c in BWD_CASES}
     missing = {v: eg for v, eg in reach.items() if v not in covered and v != (0, 0)}
     assert not missing, "forms (data gradient, weight tile) of the shared launch with no parity case; e.g. (B, T, k, cin, cout): %r" % missing
+
+
+def test_fp32_cases_cover_every_kernel():
+    rng, reach = random.Random(6), {}
+    for _ in range(12000):
+        unit = rng.choice((32, 32, 4))
+        wide = lambda most: max(unit, int(2 ** rng.uniform(5.1, most) / unit) * unit)
+        case = (int(2 ** rng.uniform(0, 5.3)), int(2 ** rng.uniform(0, 10.7)), wide(10.5), wide(11), rng.choice((1, 3, 5, 7, 9, 11, 13)))
+        for p, v in enumerate(f32_variants(P, *case)):
+            if v:
+                reach.setdefault((p,) + v, case)
+    assert set(reach) == {(p, rows, terms, split) for p in (0, 1, 2) for rows, terms in ((64, 0), (64, 1), (128, 1)) for split in (False, True)}, sorted(reach)
+    covered = {(p,) + v for c in F32_CASES for p, v in enumerate(f32_variants(P, *c)) if v}
+    missing = {v: eg for v, eg in reach.items() if v not in covered}
+    assert not missing, "kernels (pass, rows, terms, split) with no parity case; e.g. (B, T, Cin, Cout, k): %r" % missing
 
 
 def test_launch_config_rejects_what_the_entry_points_reject():

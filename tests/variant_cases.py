@@ -6,7 +6,8 @@ the function the entry points dispatch through."""
 
 # CTC: (pairs per lane, frames per block) follows Lmax + 1 pairs: <= 208 -> (1,16), <= 220 -> (1,12),
 # <= 416 -> (2,16), <= 440 -> (2,12), <= 832 -> (4,16), <= 880 -> (4,12), more -> (4,16) on more wavefronts;
-# the score-table values per thread follow frames per block * C against the workgroup size.
+# the score-table values per staging thread follow frames per block * the table's rows -- the classes, or one more than the
+# longest target if that is fewer -- against the staging threads (256 beside up to four wavefronts, else all).
 CTC_LMAX = [200, 215, 400, 436, 800, 870, 1100]
 CTC_CLASSES = [29, 50, 100, 200]
 CTC_CASES = [(c, l) for l in CTC_LMAX for c in CTC_CLASSES] + [(29, 60), (600, 20)]
@@ -27,6 +28,25 @@ BWD_CASES = [
     (4, 33, 1, 64, 64), (1, 1299, 1, 1456, 192), (4, 449, 1, 1208, 192), (3, 1206, 1, 752, 1024),     # form 5
     (16, 1109, 1, 144, 64), (16, 339, 1, 704, 192), (16, 233, 1, 1328, 64), (16, 292, 1, 1024, 1024), # form 6
 ]
+
+
+# fp32 layers (B, T, Cin, Cout, k) whose passes between them take every kernel for haloed operands (rows of its tile,
+# products from bf16 terms or not, reduction split or not) in every pass, as w2l_conv1d_launch_tile names them; utterances
+# of a few frames, of less than a panel of 32, and of several; few multiplications for the fp64 oracle.
+F32_CASES = [
+    (35, 2, 1088, 1600, 5), (22, 158, 352, 96, 7), (28, 76, 96, 1696, 3), (17, 31, 96, 1824, 7), (20, 1273, 92, 96, 3),
+    (26, 24, 1280, 36, 13), (15, 3, 1216, 216, 11), (39, 6, 1120, 96, 9),   # weight gradients over short utterances
+    (2, 1321, 32, 3104, 1), (3, 701, 512, 1088, 1), (2, 450, 1024, 96, 9), (1, 130, 1100, 1600, 3),
+]
+
+
+def f32_variants(P, B, T, cin, cout, k):
+    """(rows, terms, split) of the three passes, None where the operands are not haloed."""
+    out = []
+    for p in (0, 1, 2):
+        form, splits = P.w2l_conv1d_launch_config(p, B, T, cin, cout, k, 1, P.W2L_F32)
+        out.append(P.w2l_conv1d_launch_tile(p, B, T, cin, cout, k, 1, P.W2L_F32) + (splits > 1,) if form == 3 else None)
+    return out
 
 
 def bwd_network(k, cin, cout):
