@@ -75,7 +75,9 @@ int w2l_last_hip_error(void);
  * halo around every utterance (one extra bandwidth-bound pass), run the faster unpredicated
  * kernel, and where a problem's tiles would leave compute units idle cut the reduction into runs
  * whose fp32 sums (96 MB at most) a last pass adds up in a fixed order.  So results with and without workspace may
- * differ in the rounding of the fp32 sums; either is bit-reproducible.  A smaller workspace is
+ * differ in the rounding of the fp32 sums; either is bit-reproducible.  fp32 layers may form their products from three
+ * bf16 terms of either operand, leaving out what lies below 2^-25 of a product: other roundings than the fp32
+ * instruction's, no further from the exact sums; operands that such terms do not carry take the fp32 instruction.  A smaller workspace is
  * taken as one that has no room for such sums and for fp32 copies, down to the haloed copies of
  * bf16 layers; a non-NULL workspace smaller than those is W2L_ERR_WORKSPACE. */
 size_t w2l_conv1d_fwd_workspace_bytes(int B, int T, int Cin, int Cout, int k, int stride, int dtype);

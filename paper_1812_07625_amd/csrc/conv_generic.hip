@@ -609,7 +609,7 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
 // towards minus infinity, 5e-8 of the result's rms in its mean, which adds up where many outputs are summed (a bias
 // gradient over the frames came out at twice its distance from 64 bits): so one wavefront of a pair adds up the products
 // and the other one their negatives, and the difference of the two sums has the mean error of the fp32 instruction (1e-9).
-// Distance from 64 bits against that instruction, 12 layers and 8 steps of random sizes: 0.47 to 1.0 and 0.60 to 0.96 of it.
+// Distance from 64 bits against that instruction: 28 layers 0.47 to 1.00 of it (a single pass up to 1.014), 8 steps 0.60 to 0.96.
 //
 // Six of these instructions take 192 cycles where the fp32 ones take 512 for the same 16 steps; what bounds the kernel is the
 // vector instructions of the splits, 5.5 an element, beside them.  So every wavefront takes 64 rows (two operand blocks of A to
@@ -626,8 +626,10 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_k(OA oa, OB ob, EP ep, int M,
 // The look at the magnitudes, one instruction for two operands in one of the wavefronts that split them, costs 3 % (the
 // 10M-parameter network's step 889 -> 914 us); a test of every third term for bits below the smallest bf16 cost 5 %.
 // Panels and outputs as gemm_f32_k's over FAST lines.  Measured, layers of 256 -> 512, k = 11, forward and backward, this
-// kernel against gemm_f32_k over the same lines: 4 x 400 frames 162 -> 147 us, 16 x 800 981 -> 798; 512 -> 1024, k = 3, 8 x 501
-// frames 357 -> 314; the 10M-parameter network's step 999 -> 861.
+// kernel against gemm_f32_k over the same lines: 4 x 400 frames 162 -> 160 us, 16 x 800 973 -> 847; 512 -> 1024, k = 3, 8 x 501
+// frames 354 -> 330; the 10M-parameter network's step 1006 -> 892 (996 .. 1006 -> 874 .. 918 by box).
+// The method -- an fp32 operand as three bf16 ones, the smallest products left out -- is Henry, Tang and Heinecke's ("Leveraging the
+// bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations", 2019).
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;

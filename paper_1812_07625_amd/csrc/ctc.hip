@@ -130,11 +130,11 @@ __global__ __launch_bounds__(1024) void ctc_lattice(const float* __restrict__ lp
     constexpr bool TABLE = NQ > 0;
     constexpr int HALO_LANES = BLK;             // lanes of a wavefront that mirror the wavefront on its left
     constexpr int OWN_LANES = 64 - HALO_LANES;  // lanes whose states a wavefront owns (and stores)
-    constexpr int TABLE_PITCH = BLK + 1;        // table entries per class (one of padding against bank conflicts)
+    constexpr int TABLE_PITCH = BLK + 1;        // table entries per row (one of padding against bank conflicts)
     __shared__ float xbuf[2][16][HALO_LANES][4 * PPT];  // [block parity][wavefront][lane - OWN_LANES][v, e of blank, label]
     __shared__ int bad_len, bad;
     extern __shared__ __align__(16) unsigned char dyn_smem[];
-    float2* const tbl = reinterpret_cast<float2*>(dyn_smem);  // TABLE: [2][C][TABLE_PITCH] (pm, q)
+    float2* const tbl = reinterpret_cast<float2*>(dyn_smem);  // TABLE: [2][trows][TABLE_PITCH] (pm, q)
     const int dir = blockIdx.x, b = blockIdx.y;
     const int tid = threadIdx.x, NT = blockDim.x, lane = tid & 63, wave = tid >> 6;
     const int T = crit_len(in_len[b], d.len_div), L = tgt_len[b];
@@ -296,8 +296,8 @@ __global__ __launch_bounds__(1024) void ctc_lattice(const float* __restrict__ lp
     };
 
     if constexpr (TABLE) {
-        // element e of a block: step k = e / rows of the block, table row r = e % rows.  Its address is the block's base plus a
-        // per-thread constant; steps past the last frame are clamped to it (whatever they read only feeds the spare rows).
+        // element e of a block: step k = e / rows of the block, table row r = e % rows; its score is that of frame tb BLK + k (past the
+        // last frame the last one's, which only feeds the spare rows), in the row's class.
         const bool shared = NT == 64 * d.waves;  // the recursion's wavefronts are the stagers
         const int nst = NT > 64 * d.waves ? NT - 64 * d.waves : NT, sid = tid - (NT - nst);
         const int nel = BLK * d.trows, per_buf = d.trows * TABLE_PITCH;
@@ -561,7 +561,8 @@ size_t grad_lds_bytes(int Lmax, int C)
 // every further one.  The step is bound by instruction issue, so a wavefront wants a SIMD of its own: the
 // smallest PPT that fits four wavefronts, with blocks of 16 frames if that fits (208 lanes) and of 12 (220
 // lanes) otherwise; targets beyond 220 * 4 pairs take four pairs per lane on as many wavefronts as they need.
-// NQ > 0 (score table in LDS): a block's score rows must fit 8 elements per stager and, in two buffers, 64 KB.
+// NQ > 0 (score table in LDS): a block's score rows must fit 8 elements per stager -- 128 rows of 16 frames or 170 of 12 for the
+// four stagers -- and, in two buffers, 64 KB, which binds where the recursion's wavefronts stage.
 constexpr int STAGERS = 4;
 struct CtcLaunch { int ppt, blk, waves, nt, nq, trows; size_t lds; };
 CtcLaunch ctc_launch_config(int C, int Lmax)

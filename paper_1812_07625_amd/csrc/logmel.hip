@@ -24,7 +24,7 @@ namespace {
 
 struct LogmelDims {
     int B, Nmax, Tmax, F, sr, win, hop, nfft;
-    int fpw;  // frames per workgroup (a multiple of 4)
+    int fpw;  // of a workgroup: frames, a multiple of 4 (logmel_k), or groups of four frames (logmel512_k)
     float fmin, fmax, floor;
     double mlo, mhi;  // the mel scale's ends
     int chunks;       // logmel512_k: room for the band weights
