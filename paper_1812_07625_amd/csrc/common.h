@@ -237,6 +237,12 @@ int finish_glu_bwd(const float* part, int parts, const void* y, void* dy, int B,
 int finish_sums(const float* part, int parts, long long n, float* out, const float* bpart, int nb, float* bout, int accumulate,
                 hipStream_t st);
 
+// Data gradient of a 1x1 layer with C <= 64 outputs (dz: dense fp32 [B*Tp, C]; w [C][H]) and the GLU backward of the layer
+// below (y: dense [B*Tp, 2H]; dy as in glu_bwd_layout) in one launch, where class_bwd_glu_ok()
+bool class_bwd_glu_ok(int B, int pitch, int slack, int C, int H, int dtype);
+int class_bwd_glu(const float* dz, const void* w, const void* y, void* dy, int B, int Tp, int C, int H, int dtype, int pitch, int halo, int slack,
+                  hipStream_t st);
+
 // dense bf16 [B*Tp, C] (C % 8 == 0) -> layout with the given pitch / halo / slack, zeros outside the real frames
 // (and `nclear` integers at `clear` set to zero on the way)
 int pad_layout_bf16(const void* src, void* dst, int B, int Tp, int C, int pitch, int halo, int slack, hipStream_t st,

@@ -271,6 +271,122 @@ __global__ __launch_bounds__(256) void finish_glu_bwd_k(const float* __restrict_
         store_vec<T, V>(dy + (size_t)f * 2 * H + H + c, dg);
     }
 }
+// Data gradient of a narrow 1x1 layer and the GLU backward of the layer below it, in one pass: the classes' layer of a
+// network, whose reduction is too short for matrix tiles.  dh[r][c] = sum_q dz[r][q] w[q][c] over C <= 64 outputs, in fp32,
+// then dy as in glu_bwd_k.  Bound: the bytes of y and dy (C = 29: 30 multiply-adds a value of dh, about as long as they
+// take).  A thread holds four frames of 16 bytes of channels, so that a step of the sum costs two 16-byte LDS reads (dz:
+// the same for the frames' threads) for 16 or 32 multiply-adds.  As four launches (dz cast and padded, w padded, matrix
+// product, GLU) it took 20 us for 4 x 619 frames of 512 channels, 30 for 16 x 800; now 9
+// and 19 (the last: 10 for the bytes, 6 for the products, which a chip full of workgroups that started together takes in
+// turn).
+template <typename T, int V, int CS>  // CS channel groups of V channels (16 bytes) and 256 / CS groups of four frames
+__global__ __launch_bounds__(256) void class_bwd_glu_k(const float* __restrict__ dz, const T* __restrict__ w, const T* __restrict__ y,
+                                                       T* __restrict__ dy, unsigned out_rows, int H, int C, RowMap map)
+{
+    constexpr int R = 4, FR = 256 / CS * R, DP = FR + 4;  // (rows of dz 16 bytes apart from a multiple of all banks)
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    float* const sz = reinterpret_cast<float*>(smem_raw);                      // [C][DP]
+    uint4* const sw = reinterpret_cast<uint4*>(smem_raw + (size_t)C * DP * 4);  // [C][CS]
+    const int tid = threadIdx.x, tx = tid % CS, ty = tid / CS;
+    const unsigned f0 = blockIdx.x * FR;
+    const int c0 = blockIdx.y * CS * V, c = c0 + tx * V;
+    const bool live = c < H;
+    long long r[R];
+    uint4 ya[R], yg[R];
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+        const unsigned f = f0 + ty * R + u;
+        r[u] = f < out_rows ? map.src(f) : -1;
+        ya[u] = yg[u] = make_uint4(0, 0, 0, 0);
+        if (live && r[u] >= 0) {
+            ya[u] = *reinterpret_cast<const uint4*>(y + r[u] * 2 * H + c);
+            yg[u] = *reinterpret_cast<const uint4*>(y + r[u] * 2 * H + H + c);
+        }
+    }
+    // dz and w on their way into LDS: all of a thread's loads in flight together
+    constexpr int TPR = 256 / FR, NZ = 64 / TPR, NW = 64 * CS / 256;
+    const bool wide = (reinterpret_cast<uintptr_t>(w) & 15) == 0;  // (the caller's weights may lie anywhere)
+    const int fr = tid / TPR, q0 = tid % TPR;
+    const long long row = f0 + fr < out_rows ? map.src(f0 + fr) : -1;
+    float z[NZ];
+    uint4 wr[NW];
+#pragma unroll
+    for (int i = 0; i < NZ; ++i) z[i] = row >= 0 && q0 + TPR * i < C ? dz[row * C + q0 + TPR * i] : 0.f;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+        const int e = tid + 256 * i, ch = c0 + e % CS * V;
+        const T* const src = w + (size_t)(e / CS) * H + ch;
+        wr[i] = make_uint4(0, 0, 0, 0);
+        if (e < C * CS && ch < H) {
+            if (wide) wr[i] = *reinterpret_cast<const uint4*>(src);
+            else {
+                T t[V];
+#pragma unroll
+                for (int j = 0; j < V; ++j) t[j] = src[j];
+                __builtin_memcpy(&wr[i], t, 16);
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < NZ; ++i)
+        if (q0 + TPR * i < C) sz[(q0 + TPR * i) * DP + fr] = z[i];
+#pragma unroll
+    for (int i = 0; i < NW; ++i)
+        if (tid + 256 * i < C * CS) sw[tid + 256 * i] = wr[i];
+    __syncthreads();
+    auto widen = [](const uint4& q, float (&o)[V]) {
+        const unsigned* b = &q.x;
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            if constexpr (sizeof(T) == 4) o[j] = __uint_as_float(b[j]);
+            else o[j] = __uint_as_float((j & 1) ? b[j / 2] & 0xffff0000u : b[j / 2] << 16);
+        }
+    };
+    float acc[R][V];
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+#pragma unroll
+        for (int j = 0; j < V; ++j) acc[u][j] = 0.f;
+#pragma unroll 4
+    for (int q = 0; q < C; ++q) {
+        const float4 d4 = *reinterpret_cast<const float4*>(sz + q * DP + ty * R);
+        const float* const d = &d4.x;
+        float wv[V];
+        widen(sw[q * CS + tx], wv);
+#pragma unroll
+        for (int u = 0; u < R; ++u)
+#pragma unroll
+            for (int j = 0; j < V; ++j) acc[u][j] = __builtin_fmaf(d[u], wv[j], acc[u][j]);
+    }
+    if (!live) return;
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+        const unsigned f = f0 + ty * R + u;
+        if (f >= out_rows) continue;
+        float a[V], g[V], da[V], dg[V];
+        widen(ya[u], a);
+        widen(yg[u], g);
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            const float sg = sigmoidf_(g[j]);
+            da[j] = r[u] >= 0 ? acc[u][j] * sg : 0.f;
+            dg[j] = r[u] >= 0 ? acc[u][j] * a[j] * sg * (1.f - sg) : 0.f;
+        }
+        auto narrow = [](const float (&v)[V]) {
+            uint4 q;
+            unsigned* const b = &q.x;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if constexpr (sizeof(T) == 4) b[j] = __float_as_uint(v[j]);
+                else b[j] = (unsigned)f32_to_bf16(v[2 * j]) | ((unsigned)f32_to_bf16(v[2 * j + 1]) << 16);
+            }
+            return q;
+        };
+        T* const o = dy + (size_t)f * 2 * H + c;
+        *reinterpret_cast<uint4*>(o) = narrow(da);
+        *reinterpret_cast<uint4*>(o + H) = narrow(dg);
+    }
+}
 template <int V>
 __global__ __launch_bounds__(256) void finish_sums_k(const float* __restrict__ part, int parts, long long n, float* __restrict__ out,
                                                      const float* __restrict__ bpart, int nb, float* __restrict__ bout, int accumulate)
@@ -613,6 +729,32 @@ int finish_glu_bwd(const float* part, int parts, const void* y, void* dy, int B,
     if (dtype == W2L_BF16) { if (vec) W2L_FIN(bf16_t, 4); else W2L_FIN(bf16_t, 1); }
     else { if (vec) W2L_FIN(float, 4); else W2L_FIN(float, 1); }
 #undef W2L_FIN
+    return launch_status();
+}
+// 64 classes: their products take about twice as long as the bytes; beyond, the matrix kernels (conv_dgrad) are for it
+bool class_bwd_glu_ok(int B, int pitch, int slack, int C, int H, int dtype)
+{
+    return C <= 64 && H % (dtype == W2L_BF16 ? 8 : 4) == 0 && (long long)B * pitch + slack < (1LL << 31);
+}
+int class_bwd_glu(const float* dz, const void* w, const void* y, void* dy, int B, int Tp, int C, int H, int dtype, int pitch, int halo, int slack,
+                  hipStream_t st)
+{
+    if (!class_bwd_glu_ok(B, pitch, slack, C, H, dtype)) return W2L_ERR_SHAPE;
+    const unsigned out_rows = (unsigned)((long long)B * pitch + slack);
+    const RowMap map{Tp, pitch, halo, (long long)B * pitch};
+    const bool bf16 = dtype == W2L_BF16;
+    const int groups = H / (bf16 ? 8 : 4);
+    // 32 groups of channels and 32 frames a workgroup, or 16 and 64 where a row has fewer
+#define W2L_CLS(T_, V_, CS_)                                                                                                    \
+    {                                                                                                                           \
+        constexpr int FR = 256 / CS_ * 4;                                                                                       \
+        const dim3 g((out_rows + FR - 1) / FR, (unsigned)((groups + CS_ - 1) / CS_));                                           \
+        hipLaunchKernelGGL((class_bwd_glu_k<T_, V_, CS_>), g, dim3(256), (size_t)C * ((FR + 4) * 4 + CS_ * 16), st, dz,         \
+                           (const T_*)w, (const T_*)y, (T_*)dy, out_rows, H, C, map);                                           \
+    }
+    if (bf16) { if (groups > 16) W2L_CLS(bf16_t, 8, 32) else W2L_CLS(bf16_t, 8, 16) }
+    else { if (groups > 16) W2L_CLS(float, 4, 32) else W2L_CLS(float, 4, 16) }
+#undef W2L_CLS
     return launch_status();
 }
 int finish_sums(const float* part, int parts, long long n, float* out, const float* bpart, int nb, float* bout, int accumulate,

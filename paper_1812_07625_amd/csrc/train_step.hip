@@ -64,7 +64,8 @@ struct Plan {
     size_t ctc_bytes = 0, conv_bytes = 0, conv0_bytes = 0, dgs_bytes = 0, part_bytes = 0;  // part: sums of split reductions on the caller's stream
     size_t xfold = 0;      // haloed copy of x with the first layer's stride folded into the channels (0 bytes if unused)
     bool fold0 = false;
-    size_t cls = 0;        // operands of the last layer's data gradient prepared for the MFMA kernels (its dy is fp32)
+    bool cls_glu = false;  // the last layer's data gradient and the GLU backward below it share a launch (class_bwd_glu)
+    size_t cls = 0;        // otherwise: operands of that data gradient prepared for the MFMA kernels (its dy is fp32)
     DgradPrep cls_prep;
     std::vector<ConvBwdPlan> bwd;  // per layer: both gradients in one launch, where that can be done
     bool crowded = false;
@@ -142,7 +143,9 @@ Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int
         // sums of split reductions: the geometries that the step's passes will have
         const ConvDesc fd = layer_desc(p, L, B, i), bd = layer_bwd_desc(p, L, B, i);
         p.part_bytes = max_of(p.part_bytes, l.glu ? planes_bytes(conv_fwd_parts(fd, dtype), (size_t)B * to * l.cout) : conv_fwd_scratch(fd, dtype));
-        if (i > 0) {
+        if (i > 0 && i == n - 1)
+            p.cls_glu = l.k == 1 && l.stride == 1 && L[i - 1].glu && class_bwd_glu_ok(B, t + 2 * HALO, SLACK_ZERO, l.cout, l.cin, dtype);
+        if (i > 0 && !p.cls_glu) {
             const int dydt = i == n - 1 ? W2L_F32 : dtype;
             p.part_bytes = max_of(p.part_bytes, L[i - 1].glu ? planes_bytes(conv_dgrad_parts(bd, dtype, dydt), (size_t)B * t * l.cin)
                                                              : conv_dgrad_scratch(bd, dtype, dydt));
@@ -193,7 +196,7 @@ Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int
         p.xfold = off;
         if (p.fold0) off += round_up(haloed_bytes(B, f0.T, f0.Cin, es), 256);
     }
-    if (n > 1) {
+    if (n > 1 && !p.cls_glu) {
         const w2l_layer& ll = L[n - 1];
         p.cls_prep = dgrad_prep(B, p.Tin[n - 1], ll.cin, ll.cout, ll.k, ll.stride, dtype);
         p.cls = off;
@@ -440,6 +443,13 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
             rc = dbias_reduce(dy, dbiases[i], (long long)d.B * d.y_pitch, d.Cout, 0,
                               reinterpret_cast<float*>(ws + p.dbias), st);
             if (rc) return rc;
+        }
+        if (i > 0 && i == n - 1 && p.cls_glu) {
+            rc = class_bwd_glu(dz, weights[i], ws + p.pre[i - 1], ws + p.gdy[(i - 1) % 3], B, p.Tout[i - 1], l.cout, l.cin, dtype,
+                               p.Tout[i - 1] + 2 * HALO, HALO, SLACK_ZERO, st);
+            if (rc) return rc;
+            dy_ready = true;
+            continue;
         }
         if (i > 0) {
             const bool prepared = i == n - 1 && dy_dt == W2L_F32 && p.cls_prep.ok;

@@ -63,6 +63,32 @@ def test_bias_gradients_not_wanted(P):
         check_train_step(got, ref, "bf16")
 
 
+@pytest.mark.parametrize("classes, H, dtype", [
+    (29, 8, "bf16"), (30, 72, "bf16"), (64, 128, "bf16"), (63, 136, "bf16"), (29, 264, "bf16"), (33, 520, "bf16"),  # 1 .. 16 groups of 8 channels, 17 ..
+    (65, 64, "bf16"), (29, 44, "bf16"),                                        # matrix kernels: a class or channels too many
+    (29, 4, "f32"), (29, 60, "f32"), (64, 64, "f32"), (30, 68, "f32"), (31, 132, "f32"), (65, 64, "f32"), (29, 42, "f32"),
+])
+@pytest.mark.parametrize("misaligned", [False, True])
+def test_class_layer_backward(P, classes, H, dtype, misaligned):
+    """The gradient through the classes' layer into the layer below: one launch up to 64 classes of whole 16-byte groups
+    of channels, over blocks of 32 and 64 frames that end in the middle, also where the weights lie off a 16-byte
+    address (fp32 steps; the bf16 kernels of other passes read theirs in 16-byte pieces).  Bounds: a whole step's."""
+    if misaligned and dtype == "bf16":
+        pytest.skip("bf16 weights are read in 16-byte pieces")
+    layers = [dict(k=3, stride=1, cin=16, cout=2 * H, glu=1), dict(k=1, stride=1, cin=H, cout=classes, glu=0)]
+    cfg = W.small_model(100 + H, 3, 50, 61, 16, layers, dtype == "bf16", 2, 8)
+
+    class Shifted:  # the binding, with the classes' weights 4 bytes behind where an allocation starts
+        def __getattr__(self, name): return getattr(P, name)
+        def w2l_train_step(self, layers, w, *rest):
+            import torch
+            room = torch.empty(w[-1].numel() + 1, dtype=w[-1].dtype, device=w[-1].device)
+            room[1:] = w[-1].reshape(-1)
+            return P.w2l_train_step(layers, w[:-1] + [room[1:].view(w[-1].shape)], *rest)
+
+    check_train_step(run_train_step(Shifted() if misaligned else P, cfg), oracle_train_step(cfg), dtype)
+
+
 @pytest.mark.parametrize("net, dtype", [("shared", "bf16"), ("two streams", "bf16"), ("shared", "f32")])
 def test_captured_step_replays_the_eager_one(P, net, dtype):
     """A train step recorded into a HIP graph leaves the eager step's bits at every replay, with eager work of the same
