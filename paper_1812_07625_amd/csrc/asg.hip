@@ -51,6 +51,7 @@ struct AsgDims {
     int B, Tp, C, Lmax;
     int Sp;   // FAL lattice row pitch = Lmax + 4 (the last four are spare slots); Tp + 1 rows per utterance
     int nch;  // frame chunks per utterance
+    int len_div;  // in_len[] counts frames before the network's total stride: the criterion sees ceil(in_len / len_div)
 };
 
 // workspace pointers
@@ -682,7 +683,7 @@ __global__ __launch_bounds__(MAXT) void asg_lattice(const float* __restrict__ em
     __shared__ int bad;
     const int kind = blockIdx.x >> 1, dir = blockIdx.x & 1, b = blockIdx.y;
     const int tid = threadIdx.x, NT = blockDim.x;
-    const int T = in_len[b], L = tgt_len[b];
+    const int T = crit_len(in_len[b], d.len_div), L = tgt_len[b];
     const bool bad_len = T < 0 || T > d.Tp || L < 0 || L > d.Lmax;  // uniform
     if (tid == 0) bad = 0;
     __syncthreads();
@@ -754,7 +755,7 @@ __global__ __launch_bounds__(256) void asg_grad_em(const float* __restrict__ em,
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     float* gb = grad + (size_t)b * d.Tp * d.C;
     const int status = w.status[b];
-    const int T = in_len[b];
+    const int T = crit_len(in_len[b], d.len_div);
     const double fcc2 = w.terms[2 * b], fal2 = w.terms[2 * b + 1];
     if (blockIdx.x == 0 && tid == 0)
         loss[b] = status == 2 ? NAN : (status == 1 ? INFINITY : (float)((fcc2 - fal2) * LN2));
@@ -865,7 +866,7 @@ __global__ __launch_bounds__(256) void asg_trans_partial(const float* __restrict
     const int C2 = d.C * d.C;
     float* pF = w.partF + ((size_t)b * d.nch + ch) * C2;
     float* pA = w.partA + ((size_t)b * d.nch + ch) * 2 * d.Lmax;
-    const int T = in_len[b], L = tgt_len[b];
+    const int T = crit_len(in_len[b], d.len_div), L = tgt_len[b];
     const int t0 = ch * CHUNK;
     const int tlo = t0 < 1 ? 1 : t0, thi = t0 + CHUNK < T ? t0 + CHUNK : T;  // frames [tlo, thi)
     if (w.status[b] != 0 || tlo >= thi) {
@@ -1142,18 +1143,19 @@ extern "C" int w2l_asg_check_targets_host(const int* targets, const int* in_len,
     return W2L_OK;
 }
 
-extern "C" int w2l_asg_fwd_bwd(const float* emissions, const float* trans, const int* targets, const int* in_len,
-                               const int* tgt_len, float* loss, float* grad_emissions, float* grad_trans, int B, int Tp,
-                               int C, int Lmax, float grad_scale, void* workspace, size_t ws_bytes, void* stream)
+namespace w2l {
+int asg_fwd_bwd_strided(const float* emissions, const float* trans, const int* targets, const int* in_len, const int* tgt_len,
+                        float* loss, float* grad_emissions, float* grad_trans, int B, int Tp, int C, int Lmax, float grad_scale,
+                        void* workspace, size_t ws_bytes, void* stream, int len_div)
 {
     if (!emissions || !trans || !targets || !in_len || !tgt_len || !loss || !grad_emissions) return W2L_ERR_NULL;
-    if (B <= 0 || Tp <= 0 || C <= 0 || C > CP || Lmax <= 0 || Lmax > 3000 || B > 65535) return W2L_ERR_SHAPE;
+    if (B <= 0 || Tp <= 0 || C <= 0 || C > CP || Lmax <= 0 || Lmax > 3000 || B > 65535 || len_div < 1) return W2L_ERR_SHAPE;
     if (!aligned16(emissions) || !aligned16(targets) || !aligned16(grad_emissions)) return W2L_ERR_ALIGN;
     const WsLayout l = ws_layout(B, Tp, C, Lmax);
     if (!workspace || ws_bytes < l.total || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return W2L_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     unsigned char* ws = static_cast<unsigned char*>(workspace);
-    AsgDims d{B, Tp, C, Lmax, Lmax + 4, (Tp + CHUNK - 1) / CHUNK};
+    AsgDims d{B, Tp, C, Lmax, Lmax + 4, (Tp + CHUNK - 1) / CHUNK, len_div};
     AsgWs w;
     for (int q = 0; q < 2; ++q) {
         w.fal[q] = reinterpret_cast<float*>(ws + l.fal[q]);
@@ -1206,4 +1208,13 @@ extern "C" int w2l_asg_fwd_bwd(const float* emissions, const float* trans, const
     if (rc) return rc;
     hipLaunchKernelGGL(asg_trans_reduce, dim3((C * C + 63) / 64), dim3(64), 0, st, grad_trans, w, d, grad_scale);
     return launch_status();
+}
+}  // namespace w2l
+
+extern "C" int w2l_asg_fwd_bwd(const float* emissions, const float* trans, const int* targets, const int* in_len,
+                               const int* tgt_len, float* loss, float* grad_emissions, float* grad_trans, int B, int Tp,
+                               int C, int Lmax, float grad_scale, void* workspace, size_t ws_bytes, void* stream)
+{
+    return asg_fwd_bwd_strided(emissions, trans, targets, in_len, tgt_len, loss, grad_emissions, grad_trans, B, Tp, C, Lmax, grad_scale,
+                               workspace, ws_bytes, stream, 1);
 }

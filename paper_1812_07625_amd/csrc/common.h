@@ -28,6 +28,9 @@ __device__ __forceinline__ float bf16_to_f32(bf16_t v) { return __uint_as_float(
 // compiler selects for this cast and pairs up for neighbouring values): one instruction instead of six.
 __device__ __forceinline__ bf16_t f32_to_bf16(float f) { return __builtin_bit_cast(bf16_t, (__bf16)f); }
 
+// frames that a criterion sees of an utterance counted before the network's total stride
+__device__ __forceinline__ int crit_len(int n, int div) { return (n < 0 || div <= 1) ? n : (n + div - 1) / div; }
+
 // the hardware reciprocal (1 ulp) instead of an IEEE division: a quarter of the GLU kernels' instructions
 __device__ __forceinline__ float sigmoidf_(float u) { return __builtin_amdgcn_rcpf(1.f + __expf(-u)); }
 
@@ -214,6 +217,10 @@ int conv_bwd(const ConvBwdPlan& p, const ConvDesc& d, const void* dy, const void
 // w2l_ctc_fwd_bwd with in_len counted before a total stride len_div (ctc.hip): the criterion sees ceil(in_len / len_div)
 int ctc_fwd_bwd_strided(const float* input, int is_logits, const int* targets, const int* in_len, const int* tgt_len,
                         float* loss, float* grad, int B, int Tp, int C, int Lmax, int blank, float grad_scale,
+                        void* workspace, size_t ws_bytes, void* stream, int len_div);
+// and w2l_asg_fwd_bwd (asg.hip)
+int asg_fwd_bwd_strided(const float* emissions, const float* trans, const int* targets, const int* in_len, const int* tgt_len,
+                        float* loss, float* grad_emissions, float* grad_trans, int B, int Tp, int C, int Lmax, float grad_scale,
                         void* workspace, size_t ws_bytes, void* stream, int len_div);
 
 // GLU with an explicit output layout (elementwise.hip).  y (and dh) are dense [B*Tp, Cout]

@@ -37,7 +37,6 @@ struct CtcDims {
     int trows; // rows of the score table: the classes, or (fewer) the blank and the positions of the target
 };
 
-__device__ __forceinline__ int crit_len(int n, int div) { return (n < 0 || div <= 1) ? n : (n + div - 1) / div; }
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
 

@@ -60,7 +60,7 @@ struct Plan {
     int n = 0, C = 0, Tlast = 0, tot_stride = 1;
     std::vector<int> Tin, Tout, outch;
     std::vector<size_t> pre, post;  // workspace offsets of conv output (dense) and GLU output (haloed) per layer
-    size_t dlogits = 0, crit_len = 0, gdy[3] = {0, 0, 0}, gdh[2] = {0, 0}, ctc = 0, conv = 0, conv0 = 0, dbias = 0, dgs = 0, part = 0, total = 0;
+    size_t dlogits = 0, gdy[3] = {0, 0, 0}, gdh[2] = {0, 0}, ctc = 0, conv = 0, conv0 = 0, dbias = 0, dgs = 0, part = 0, total = 0;
     size_t ctc_bytes = 0, conv_bytes = 0, conv0_bytes = 0, dgs_bytes = 0, part_bytes = 0;  // part: sums of split reductions on the caller's stream
     size_t xfold = 0;      // haloed copy of x with the first layer's stride folded into the channels (0 bytes if unused)
     bool fold0 = false;
@@ -172,7 +172,6 @@ Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int
     p.Tlast = t;
     p.C = L[n - 1].cout;
     p.dlogits = off; off += round_up((size_t)B * p.Tlast * p.C * 4, 256);
-    p.crit_len = off; off += round_up((size_t)B * 4, 256);
     for (int q = 0; q < 3; ++q) { p.gdy[q] = off; off += round_up(dymax, 256); }
     for (int q = 0; q < 2; ++q) { p.gdh[q] = off; off += round_up(dhmax, 256); }
     p.ctc_bytes = criterion == CRIT_ASG ? w2l_asg_workspace_bytes(B, p.Tlast, p.C, Lmax) : w2l_ctc_workspace_bytes(B, p.Tlast, p.C, Lmax);
@@ -204,15 +203,6 @@ Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int
     }
     p.total = off;
     return p;
-}
-
-__global__ void crit_len_k(const int* in_len, int* out, int B, int tot_stride)
-{
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b < B) {
-        const int n = in_len[b];
-        out[b] = n < 0 ? n : (n + tot_stride - 1) / tot_stride;
-    }
 }
 
 }  // namespace
@@ -271,6 +261,9 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
     const int n = n_layers;
     int rc;
 
+    // the last layer writes the caller's logits where it can (the entry points' alignment), and the criterion reads them there
+    float* const z = logits && aligned16(logits) ? logits : reinterpret_cast<float*>(ws + p.pre[n - 1]);
+
     // ---- network forward: y_i = conv(h_{i-1}) + bias (dense), h_i = GLU(y_i) (haloed)
     const void* h = x;
     for (int i = 0; i < n; ++i) {
@@ -294,7 +287,7 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
             h = ws + p.post[i];
             continue;
         }
-        rc = conv_fwd(fd, h, weights[i], biases[i], ws + p.pre[i], dtype, ydt, st, part, p.part_bytes);
+        rc = conv_fwd(fd, h, weights[i], biases[i], i == n - 1 ? (void*)z : ws + p.pre[i], dtype, ydt, st, part, p.part_bytes);
         if (rc) return rc;
         if (l.glu) {
             rc = glu_fwd_layout(ws + p.pre[i], ws + p.post[i], B, p.Tout[i], l.cout, dtype, p.Tout[i] + 2 * HALO, HALO,
@@ -307,8 +300,7 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
         }
         h = ws + p.post[i];
     }
-    const float* z = reinterpret_cast<const float*>(ws + p.pre[n - 1]);
-    if (logits) {
+    if (logits && z != logits) {
         hipError_t e = hipMemcpyAsync(logits, z, (size_t)B * p.Tlast * p.C * 4, hipMemcpyDeviceToDevice, st);
         if (e != hipSuccess) { note_hip_error(e); return W2L_ERR_LAUNCH; }
     }
@@ -316,12 +308,8 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
     // ---- criterion: frames seen = ceil(in_len / total stride)
     float* dz = reinterpret_cast<float*>(ws + p.dlogits);
     if (criterion == CRIT_ASG) {
-        int* clen = reinterpret_cast<int*>(ws + p.crit_len);
-        hipLaunchKernelGGL(crit_len_k, dim3((B + 255) / 256), dim3(256), 0, st, in_len, clen, B, p.tot_stride);
-        rc = launch_status();
-        if (rc) return rc;
-        rc = w2l_asg_fwd_bwd(z, trans, targets, clen, tgt_len, loss, dz, dtrans, B, p.Tlast, p.C, Lmax, grad_scale,
-                             ws + p.ctc, p.ctc_bytes, stream);
+        rc = asg_fwd_bwd_strided(z, trans, targets, in_len, tgt_len, loss, dz, dtrans, B, p.Tlast, p.C, Lmax, grad_scale,
+                                 ws + p.ctc, p.ctc_bytes, stream, p.tot_stride);
     } else {
         rc = ctc_fwd_bwd_strided(z, 1, targets, in_len, tgt_len, loss, dz, B, p.Tlast, p.C, Lmax, blank, grad_scale,
                                  ws + p.ctc, p.ctc_bytes, stream, p.tot_stride);
