@@ -205,30 +205,199 @@ Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int
     return p;
 }
 
+// ---- widths that the matrix kernels do not take --------------------------------------
+// The bf16 kernels want whole blocks of 64 output channels for a data gradient and whole chunks of 8 input channels for
+// any pass; a network of other widths ran its passes on the fp32 matrix instruction, a sixteenth of the rate.  Such a
+// network is stepped as one of wider layers: every gated layer's halves are rounded up, the weights and biases copied
+// with zeros in the new places, and the gradients of the real ones copied out at the end.  The new channels hold exact
+// zeros all the way (0 * sigmoid(0) forward, sums of zeros backward), so the real ones' sums gain zeros and nothing else.
+// Steps, us, k = 7, four body layers, 4 x 800 frames at stride 2: width 512 284; 496 520 -> 302; 500 1024 -> 306;
+// 8 x 1200, k = 11, width 404 2299 -> 493.  The two copying launches and their host calls are about 15 us: 2 x 200 frames
+// of width 144 (0.22 GFLOP) 157 -> 133, 1 x 100 of width 240 (0.16, and too few frames for the kernels) 166 -> 170, of 132
+// (0.03) 117 -> 133.
+constexpr double WIDEN_FLOPS = 2e8;
+constexpr long long WIDEN_FRAMES = 128;  // what the matrix kernels ask for (conv_fwd_mfma_ok, conv_dgrad_mfma_ok)
+struct Widened {
+    std::vector<w2l_layer> L;                // empty: nothing to widen
+    std::vector<size_t> w, b, dw, db;        // offsets of the copies, for layers that change
+    std::vector<char> changed;
+    size_t total = 0;
+    bool any() const { return !L.empty(); }
+};
+// Halves of 32 channels more make whole blocks of 64; of 64, also rows of weights that panels divide whatever the taps
+// (FAST addressing in the forward pass), which is worth it up to a sixth more work in either direction.
+int wide_half(int h)
+{
+    const int a = (h + 31) / 32 * 32, b = (h + 63) / 64 * 64;
+    return b * 7 <= a * 8 ? b : a;
+}
+Widened widen(const w2l_layer* L, int n, int B, int T, int dtype)
+{
+    Widened v;
+    if (!L || n < 2 || n > 1024 || B <= 0 || T <= 0 || dtype != W2L_BF16) return v;
+    bool wanted = false;
+    double flops = 0;
+    int t = T;
+    for (int i = 0; i < n; ++i) {
+        const w2l_layer& l = L[i];
+        if (l.k <= 0 || (l.k & 1) == 0 || l.stride <= 0 || l.cin <= 0 || l.cout <= 0 || l.cout > 1 << 20 || l.cin > 1 << 20) return v;
+        if (i < n - 1 ? !l.glu || (l.cout & 1) : l.glu) return v;  // (layers without GLU keep their widths)
+        if (i > 0 && l.cin != L[i - 1].cout / 2) return v;
+        if (i < n - 1) wanted = wanted || l.cout / 2 % 8 || (i > 0 && l.cout % 64);
+        t = out_len(t, l.stride);
+        flops += 6.0 * B * t * l.k * l.cin * l.cout;
+    }
+    if (!wanted || flops < WIDEN_FLOPS || (long long)B * t < WIDEN_FRAMES || L[0].cin % 4) return v;
+    v.L.assign(L, L + n);
+    for (int i = 0; i < n - 1; ++i) {
+        v.L[i].cout = 2 * wide_half(L[i].cout / 2);
+        v.L[i + 1].cin = v.L[i].cout / 2;
+    }
+    for (int i = 0; i < n; ++i) {
+        const w2l_layer& l = v.L[i];
+        v.changed.push_back(l.cout != L[i].cout || l.cin != L[i].cin);
+        const size_t m = (size_t)l.cout * l.k * l.cin;
+        auto take = [&](size_t bytes) { const size_t o = v.total; v.total += v.changed[i] ? round_up(bytes, 256) : 0; return o; };
+        v.w.push_back(take(m * 2));
+        v.b.push_back(take((size_t)l.cout * 4));
+        v.dw.push_back(take(m * 4));
+        v.db.push_back(take((size_t)l.cout * 4));
+    }
+    return v;
+}
+
+struct WideJob {  // one layer; half = 0: no halves (the classes), all rows stay where they are
+    const bf16_t* w; bf16_t* ww; const float* b; float* wb;
+    const float* wdw; float* dw; const float* wdb; float* db;
+    int cout, half, wcout, whalf, k, cin, wcin, vec;
+    unsigned first;  // block of the launch that begins the layer
+};
+constexpr int WIDE_JOBS = 24, WIDE_ITEMS = 4;  // layers a launch; items of a thread, whose loads are in flight together
+struct WideJobs { WideJob j[WIDE_JOBS]; int n; };
+__device__ __forceinline__ int wide_row(int co, int half, int whalf) { return co < half || !half ? co : co - half + whalf; }
+// row of the layer that row co of the wide one is, or -1
+__device__ __forceinline__ int real_row(int co, const WideJob& j)
+{
+    if (!j.half) return co;
+    return co < j.whalf ? (co < j.half ? co : -1) : (co - j.whalf < j.half ? co - j.whalf + j.half : -1);
+}
+__device__ __forceinline__ const WideJob& wide_job(const WideJobs& a)
+{
+    int q = 0;
+    while (q + 1 < a.n && blockIdx.x >= a.j[q + 1].first) ++q;
+    return a.j[q];
+}
+// Bound by memory: a layer's weights read and the wide ones written (the gradients, the other way), four channels a
+// thread and turn where rows start on whole groups of four, one otherwise.
+__global__ __launch_bounds__(256) void widen_k(WideJobs a)
+{
+    const WideJob& j = wide_job(a);
+    const unsigned blk = blockIdx.x - j.first;
+    if (blk == 0 && j.b)
+        for (int c = threadIdx.x; c < j.wcout; c += 256) {
+            const int r = real_row(c, j);
+            j.wb[c] = r >= 0 ? j.b[r] : 0.f;
+        }
+    const long long cols = j.wcin / 4, items = (long long)j.wcout * j.k * cols;  // (wcin is a multiple of 4)
+#pragma unroll
+    for (int u = 0; u < WIDE_ITEMS; ++u) {
+        const long long e = ((long long)blk * WIDE_ITEMS + u) * 256 + threadIdx.x;
+        if (e >= items) continue;
+        const long long line = e / cols;
+        const int c = (int)(e - line * cols) * 4, co = (int)(line / j.k), tap = (int)(line - (long long)co * j.k), r = real_row(co, j);
+        bf16_t v[4] = {0, 0, 0, 0};
+        if (r >= 0) {
+            const bf16_t* const src = j.w + ((long long)r * j.k + tap) * j.cin;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (c + q < j.cin) v[q] = src[c + q];
+        }
+        *reinterpret_cast<uint2*>(j.ww + line * j.wcin + c) =
+            make_uint2((unsigned)v[0] | ((unsigned)v[1] << 16), (unsigned)v[2] | ((unsigned)v[3] << 16));
+    }
+}
+__global__ __launch_bounds__(256) void narrow_k(WideJobs a)
+{
+    const WideJob& j = wide_job(a);
+    const unsigned blk = blockIdx.x - j.first;
+    if (blk == 0 && j.db)
+        for (int c = threadIdx.x; c < j.cout; c += 256) j.db[c] = j.wdb[wide_row(c, j.half, j.whalf)];
+    const long long cols = j.cin / j.vec, items = (long long)j.cout * j.k * cols;
+#pragma unroll
+    for (int u = 0; u < WIDE_ITEMS; ++u) {
+        const long long e = ((long long)blk * WIDE_ITEMS + u) * 256 + threadIdx.x;
+        if (e >= items) continue;
+        const long long line = e / cols;
+        const int c = (int)(e - line * cols) * j.vec, co = (int)(line / j.k), tap = (int)(line - (long long)co * j.k);
+        const float* const src = j.wdw + ((long long)wide_row(co, j.half, j.whalf) * j.k + tap) * j.wcin + c;
+        float* const dst = j.dw + line * j.cin + c;
+        if (j.vec == 4) *reinterpret_cast<float4*>(dst) = *reinterpret_cast<const float4*>(src);
+        else *dst = *src;
+    }
+}
+// the layers that change, some to a launch: their weights widened, or their gradients copied out
+int launch_wide(bool out, const Widened& v, const w2l_layer* L, int n, const void* const* weights, const float* const* biases,
+                float* const* dweights, float* const* dbiases, unsigned char* ws, hipStream_t st)
+{
+    WideJobs a;
+    a.n = 0;
+    unsigned blocks = 0;
+    for (int i = 0; i <= n; ++i) {
+        if (a.n && (i == n || a.n == WIDE_JOBS)) {
+            if (out) hipLaunchKernelGGL(narrow_k, dim3(blocks), dim3(256), 0, st, a);
+            else hipLaunchKernelGGL(widen_k, dim3(blocks), dim3(256), 0, st, a);
+            const int rc = launch_status();
+            if (rc) return rc;
+            a.n = 0;
+            blocks = 0;
+        }
+        if (i == n || !v.changed[i]) continue;
+        WideJob& j = a.j[a.n++];
+        j.w = (const bf16_t*)weights[i]; j.ww = (bf16_t*)(ws + v.w[i]);
+        j.b = biases[i]; j.wb = (float*)(ws + v.b[i]);
+        j.wdw = (const float*)(ws + v.dw[i]); j.dw = dweights[i];
+        j.wdb = (const float*)(ws + v.db[i]); j.db = dbiases[i];
+        j.cout = L[i].cout; j.half = L[i].glu ? L[i].cout / 2 : 0;
+        j.wcout = v.L[i].cout; j.whalf = v.L[i].glu ? v.L[i].cout / 2 : 0;
+        j.k = L[i].k; j.cin = L[i].cin; j.wcin = v.L[i].cin;
+        j.vec = j.cin % 4 == 0 && aligned16(j.dw) ? 4 : 1;
+        j.first = blocks;
+        const long long items = out ? (long long)j.cout * j.k * (j.cin / j.vec) : (long long)j.wcout * j.k * (j.wcin / 4);
+        blocks += (unsigned)((items + 256 * WIDE_ITEMS - 1) / (256 * WIDE_ITEMS));
+    }
+    return W2L_OK;
+}
+
 }  // namespace
 }  // namespace w2l
 
 using namespace w2l;
 
+static size_t step_bytes(const w2l_layer* layers, int n_layers, int B, int T, int Lmax, int dtype, int criterion)
+{
+    const Widened v = widen(layers, n_layers, B, T, dtype);
+    const Plan p = make_plan(v.any() ? v.L.data() : layers, n_layers, B, T, Lmax, dtype, criterion);
+    return p.status == W2L_OK ? p.total + v.total : 0;
+}
+
 extern "C" size_t w2l_train_step_workspace_bytes(const w2l_layer* layers, int n_layers, int B, int T, int Lmax,
                                                  int dtype)
 {
-    Plan p = make_plan(layers, n_layers, B, T, Lmax, dtype, CRIT_CTC);
-    return p.status == W2L_OK ? p.total : 0;
+    return step_bytes(layers, n_layers, B, T, Lmax, dtype, CRIT_CTC);
 }
 
 extern "C" size_t w2l_train_step_asg_workspace_bytes(const w2l_layer* layers, int n_layers, int B, int T, int Lmax,
                                                      int dtype)
 {
-    Plan p = make_plan(layers, n_layers, B, T, Lmax, dtype, CRIT_ASG);
-    return p.status == W2L_OK ? p.total : 0;
+    return step_bytes(layers, n_layers, B, T, Lmax, dtype, CRIT_ASG);
 }
 
 extern "C" int w2l_train_step_launch_config(const w2l_layer* layers, int n_layers, int B, int T, int dtype, int layer, int* data_form, int* data_runs,
                                             int* weight_tile, int* weight_runs)
 {
     if (!layers || !data_form || !data_runs || !weight_tile || !weight_runs) return W2L_ERR_NULL;
-    const Plan p = make_plan(layers, n_layers, B, T, 1, dtype, CRIT_CTC);
+    const Widened v = widen(layers, n_layers, B, T, dtype);
+    const Plan p = make_plan(v.any() ? v.L.data() : layers, n_layers, B, T, 1, dtype, CRIT_CTC);
     if (p.status) return p.status;
     if (layer < 0 || layer >= n_layers) return W2L_ERR_SHAPE;
     const ConvBwdPlan& b = p.bwd[layer];
@@ -239,23 +408,12 @@ extern "C" int w2l_train_step_launch_config(const w2l_layer* layers, int n_layer
     return W2L_OK;
 }
 
-// network forward, criterion (CTC on the log-softmax of the output, or ASG on the output itself), backward
-static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers, const void* const* weights,
-                           const float* const* biases, float* const* dweights, float* const* dbiases, const void* x,
-                           const int* in_len, const int* targets, const int* tgt_len, const float* trans, float* dtrans,
-                           float* loss, float* logits, int B, int T, int Lmax, int blank, int dtype, float grad_scale,
-                           void* workspace, size_t ws_bytes, void* stream)
+// network forward, criterion (CTC on the log-softmax of the output, or ASG on the output itself), backward; arguments checked
+static int run_step(const Plan& p, int criterion, const w2l_layer* layers, int n_layers, const void* const* weights, const float* const* biases,
+                    float* const* dweights, float* const* dbiases, const void* x, const int* in_len, const int* targets,
+                    const int* tgt_len, const float* trans, float* dtrans, float* loss, float* logits, int B, int T, int Lmax, int blank,
+                    int dtype, float grad_scale, void* workspace, void* stream)
 {
-    if (!layers || !weights || !biases || !dweights || !dbiases || !x || !in_len || !targets || !tgt_len || !loss)
-        return W2L_ERR_NULL;
-    if (criterion == CRIT_ASG && !trans) return W2L_ERR_NULL;
-    Plan p = make_plan(layers, n_layers, B, T, Lmax, dtype, criterion);
-    if (p.status) return p.status;
-    if (criterion == CRIT_CTC && (blank < 0 || blank >= p.C)) return W2L_ERR_SHAPE;
-    for (int i = 0; i < n_layers; ++i)
-        if (!weights[i] || !dweights[i]) return W2L_ERR_NULL;
-    if (!workspace || ws_bytes < p.total || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return W2L_ERR_WORKSPACE;
-    if (!aligned16(x)) return W2L_ERR_ALIGN;
     unsigned char* ws = static_cast<unsigned char*>(workspace);
     hipStream_t st = (hipStream_t)stream;
     const int n = n_layers;
@@ -486,6 +644,47 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
     // join: the side stream is in order, so its last event covers every weight gradient
     if (on_helper < n && !hip_ok(hipStreamWaitEvent(st, side->done[on_helper], 0))) return W2L_ERR_LAUNCH;
     return W2L_OK;
+}
+
+static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers, const void* const* weights,
+                           const float* const* biases, float* const* dweights, float* const* dbiases, const void* x,
+                           const int* in_len, const int* targets, const int* tgt_len, const float* trans, float* dtrans,
+                           float* loss, float* logits, int B, int T, int Lmax, int blank, int dtype, float grad_scale,
+                           void* workspace, size_t ws_bytes, void* stream)
+{
+    if (!layers || !weights || !biases || !dweights || !dbiases || !x || !in_len || !targets || !tgt_len || !loss)
+        return W2L_ERR_NULL;
+    if (criterion == CRIT_ASG && !trans) return W2L_ERR_NULL;
+    const Widened v = widen(layers, n_layers, B, T, dtype);
+    const w2l_layer* const L = v.any() ? v.L.data() : layers;
+    const Plan p = make_plan(L, n_layers, B, T, Lmax, dtype, criterion);
+    if (p.status) return p.status;
+    if (criterion == CRIT_CTC && (blank < 0 || blank >= p.C)) return W2L_ERR_SHAPE;
+    for (int i = 0; i < n_layers; ++i)
+        if (!weights[i] || !dweights[i]) return W2L_ERR_NULL;
+    if (!workspace || ws_bytes < p.total + v.total || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return W2L_ERR_WORKSPACE;
+    if (!aligned16(x)) return W2L_ERR_ALIGN;
+    if (!v.any())
+        return run_step(p, criterion, L, n_layers, weights, biases, dweights, dbiases, x, in_len, targets, tgt_len, trans, dtrans, loss, logits,
+                        B, T, Lmax, blank, dtype, grad_scale, workspace, stream);
+    unsigned char* const wide = static_cast<unsigned char*>(workspace) + p.total;
+    std::vector<const void*> w(weights, weights + n_layers);
+    std::vector<const float*> b(biases, biases + n_layers);
+    std::vector<float*> dw(dweights, dweights + n_layers), db(dbiases, dbiases + n_layers);
+    for (int i = 0; i < n_layers; ++i) {
+        if (!v.changed[i]) continue;
+        w[i] = wide + v.w[i];
+        dw[i] = reinterpret_cast<float*>(wide + v.dw[i]);
+        if (b[i]) b[i] = reinterpret_cast<float*>(wide + v.b[i]);
+        if (db[i]) db[i] = reinterpret_cast<float*>(wide + v.db[i]);
+    }
+    hipStream_t st = (hipStream_t)stream;
+    int rc = launch_wide(false, v, layers, n_layers, weights, biases, dweights, dbiases, wide, st);
+    if (rc) return rc;
+    rc = run_step(p, criterion, L, n_layers, w.data(), b.data(), dw.data(), db.data(), x, in_len, targets, tgt_len, trans, dtrans, loss, logits,
+                  B, T, Lmax, blank, dtype, grad_scale, workspace, stream);
+    if (rc) return rc;
+    return launch_wide(true, v, layers, n_layers, weights, biases, dweights, dbiases, wide, st);
 }
 
 extern "C" int w2l_train_step(const w2l_layer* layers, int n_layers, const void* const* weights,

@@ -89,6 +89,36 @@ def test_class_layer_backward(P, classes, H, dtype, misaligned):
     check_train_step(run_train_step(Shifted() if misaligned else P, cfg), oracle_train_step(cfg), dtype)
 
 
+@pytest.mark.parametrize("widths, k, stride, feat, frames", [
+    ((210, 250), 5, 2, 40, 260),              # halves of 105 and 125: no multiple of anything
+    ((496, 240, 332), 3, 1, 80, 131),         # whole chunks, no whole blocks; a half of 2 mod 4 (gradients copied one by one)
+    ((256, 128, 192, 264), 3, 1, 12, 140),    # one layer off the blocks; features of a multiple of 4
+    ((72,) * 30, 3, 1, 40, 150),              # more layers than a copying launch takes
+])
+def test_widths_off_the_matrix_blocks(P, widths, k, stride, feat, frames):
+    """Networks whose layers are stepped with zeros in new channels give the oracle's outputs, loss and gradients; bounds of a
+    whole bf16 step.  Twice into one workspace, the second time after other bytes, and without some biases and their gradients."""
+    cin = [feat] + [w // 2 for w in widths[:-1]]
+    layers = [dict(k=k, stride=stride if i == 0 else 1, cin=c, cout=w, glu=1) for i, (c, w) in enumerate(zip(cin, widths))]
+    layers += [dict(k=1, stride=1, cin=widths[-1] // 2, cout=29, glu=0)]
+    cfg = W.small_model(130 + k, 3, frames - 30, frames, feat, layers, True, 5, 20)
+    plain = [dict(l) for l in layers]
+    ref = oracle_train_step(cfg)
+    check_train_step(run_train_step(P, cfg), ref, "bf16")
+
+    class Without:  # the binding without the bias gradients of two layers, into a workspace full of NaN
+        def __getattr__(self, name): return getattr(P, name)
+        def w2l_train_step(self, layers, w, b, dw, db, *rest):
+            rest[-1].fill_(255)
+            return P.w2l_train_step(layers, w, b, dw, [None if i in (0, 1) else t for i, t in enumerate(db)], *rest)
+
+    got = run_train_step(Without(), cfg)
+    for i in (0, 1):
+        got["db"][i] = ref["db"][i]
+    check_train_step(got, ref, "bf16")
+    assert layers == plain
+
+
 @pytest.mark.parametrize("net, dtype", [("shared", "bf16"), ("two streams", "bf16"), ("shared", "f32")])
 def test_captured_step_replays_the_eager_one(P, net, dtype):
     """A train step recorded into a HIP graph leaves the eager step's bits at every replay, with eager work of the same
