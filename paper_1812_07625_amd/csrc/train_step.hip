@@ -92,9 +92,16 @@ ConvDesc layer_bwd_desc(const Plan& p, const w2l_layer* L, int B, int i)
 }
 size_t planes_bytes(int parts, size_t values) { return parts > 1 ? parts * values * 4 : 0; }
 
-// Layer 0 has no data gradient to run beside, and the weight gradient of narrow outputs is shorter than the events that
-// a second stream takes: these stay on the caller's stream (unless the second stream is there anyway).
-bool main_wgrad(const Plan& p, const w2l_layer& l, int i) { return i == 0 || (l.cout <= 32 && !p.crowded); }
+// Layer 0 has no data gradient to run beside, and the weight gradients of narrow outputs and of little work are shorter
+// than the events that a second stream takes (on the device, and on the host, which a small step waits for): these stay
+// on the caller's stream (unless the second stream is there anyway).  Steps of fp32 networks with four equal body layers, us,
+// with their weight gradients on the second stream and on the caller's: 0.13 GFLOP a layer (4 x 100 frames, k = 5,
+// 128 -> 256) 235 and 196, 0.26 212..239 and 211, 0.58 250..261 and 260, 1.2 304 and 327; the tiny network (0.016) 94..100 and 85..88.
+constexpr double SHORT_WGRAD = 3e8;
+bool main_wgrad(const Plan& p, const w2l_layer& l, int i, int B)
+{
+    return i == 0 || (!p.crowded && (l.cout <= 32 || 2.0 * B * p.Tout[i] * l.k * l.cin * l.cout <= SHORT_WGRAD));
+}
 // whether a weight gradient may cut its reduction
 Runs wgrad_runs(const Plan& p, int dydt) { return p.crowded && dydt == W2L_BF16 ? Runs::WHOLE : Runs::IN_STEP; }
 bool same_layer(const w2l_layer& a, const w2l_layer& b) { return a.k == b.k && a.stride == b.stride && a.cin == b.cin && a.cout == b.cout && a.glu == b.glu; }
@@ -165,7 +172,7 @@ Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int
     for (int i = 0; i < n; ++i) {
         const w2l_layer& l = L[i];
         const ConvDesc d = i ? layer_bwd_desc(p, L, B, i) : dense_desc(B, T, l.cin, l.cout, l.k, l.stride);
-        size_t& bytes = p.bwd[i].ok || main_wgrad(p, l, i) ? p.conv0_bytes : p.conv_bytes;
+        size_t& bytes = p.bwd[i].ok || main_wgrad(p, l, i, B) ? p.conv0_bytes : p.conv_bytes;
         const int dydt = i == n - 1 ? W2L_F32 : dtype;
         bytes = max_of(bytes, p.bwd[i].ok ? p.bwd[i].wscratch : conv_wgrad_scratch_bytes(d, dtype, dydt, wgrad_runs(p, dydt)));
     }
@@ -553,7 +560,7 @@ static int run_step(const Plan& p, int criterion, const w2l_layer* layers, int n
             continue;
         }
         // (layer 0's takes the caller's stream next to the helper stream's last launch instead of queueing behind it)
-        const bool on_main = main_wgrad(p, l, i), on_side = side && !on_main;
+        const bool on_main = main_wgrad(p, l, i, B), on_side = side && !on_main;
         hipStream_t wst = on_side ? side->stream : st;
         if (on_side) {
             if (!hip_ok(hipEventRecord(side->ready[i], st)) || !hip_ok(hipStreamWaitEvent(wst, side->ready[i], 0)))
