@@ -11,8 +11,8 @@
 //   wgrad  m=co      n=(j,ci)  r=(b,t')   A = dy (m-contiguous)         B = x window (n-contiguous)
 //
 // One workgroup computes a BM x BN tile with one or two groups of 4 wavefronts (2x2).  Two
-// groups put two wavefronts on every SIMD, which then work in opposite phases (one multiplies
-// while the other moves data, see run_pingpong); each wavefront may then use 256 registers, i.e.
+// groups put two wavefronts on every SIMD (in opposite phases where that pays -- one multiplies
+// while the other moves data -- see run_ring); each wavefront may then use 256 registers, i.e.
 // hold a 96x96 or 128x64 block of accumulators.  The groups either split the reduction (KG = 2:
 // alternate 16-element sub-steps of every panel, accumulators summed through LDS at the end;
 // tiles up to 192x192 / 256x128) or the tile's columns (GN = 2: group g owns columns
@@ -221,6 +221,7 @@ struct PanelMN {
 template <int BM, int BN, int BKT, int KG, int GN, class PA, class PB>
 struct Core {
     static_assert(KG * GN <= 2, "at most two groups of wavefronts");
+    static constexpr bool COLUMN_GROUPS = GN == 2;
     static constexpr int WTN = BN / (2 * GN);              // columns per wavefront (wn = 0 .. 2 GN - 1)
     static constexpr int TM = BM / 2 / 32, TN = WTN / 32;  // 32x32 blocks per wavefront
     f32x16 acc[TM][TN];
@@ -286,7 +287,7 @@ struct Core {
             mfmas(u, hook);
         }
     }
-    // Ping-pong form (KG == 2): a wavefront first reads all its fragments of a panel, then
+    // Ping-pong form: a wavefront first reads all its fragments of a panel, then
     // multiplies them; the two groups do this in opposite phases (see run_pingpong).
     __device__ __forceinline__ void read_panel(const unsigned char* la, const unsigned char* lb, int kg, int wm, int wn,
                                                int lane, int arow = 0)
@@ -522,7 +523,7 @@ __device__ __forceinline__ void run_pipeline(CoreT& core, unsigned char* lds, in
     wait_vmcnt<0>();  // the trailing panels must land before LDS is reused or released
 }
 
-// Ping-pong schedule for two groups of wavefronts (KG == 2).  Time is cut into phases with one
+// Ping-pong schedule for two groups of wavefronts.  Time is cut into phases with one
 // workgroup barrier between consecutive phases.  In a "read" phase R(st) a wavefront starts its
 // share of the loads of panel st+2, reads all its fragments of panel st from LDS and waits for
 // its loads of panel st+1; in a "multiply" phase M(st) it only issues the MFMAs of panel st.
@@ -584,11 +585,17 @@ __device__ __forceinline__ void run_pingpong(CoreT& core, unsigned char* lds, in
     wait_vmcnt<0>();  // the trailing panels must land before LDS is reused or released
 }
 
+// Which schedule: two groups that share a panel's reduction read all of it between them and multiply for half as long, so
+// that LDS is what they wait for (128x128: 768 of about 1300 cycles a panel in ping-pong), and phases that wait for each
+// other's barriers add to that; with the reads between the multiplications and one barrier a panel, us a pass before and
+// after: shared launch of both gradients, 4 x 619 frames, k = 11, 256 -> 512 29.2 and 26.5 (its step 532 and 515), layer of
+// 16 x 800 frames, k = 11, 512 -> 1024 472 and 467, step of the 10M network, 16 x 1600 993 and 983, no shape slower.  The
+// groups of a 256x256 tile, with columns of their own, keep the phases (without: 105M step 3367 and 3389..3425).
 template <int STAGES, int GROUPS, int NL, int STAGE_BYTES, int A_BYTES, class CoreT, class Issue>
 __device__ __forceinline__ void run_ring(CoreT& core, unsigned char* lds, int nsteps, Issue issue, int grp, int kg, int wm,
                                          int wn, int lane)
 {
-    if constexpr (GROUPS == 2) {
+    if constexpr (GROUPS == 2 && CoreT::COLUMN_GROUPS) {
         run_pingpong<STAGES, NL, STAGE_BYTES, A_BYTES>(core, lds, nsteps, issue, grp, kg, wm, wn, lane);
     } else {
         run_pipeline<STAGES, NL, STAGE_BYTES, A_BYTES>(core, lds, nsteps, issue, kg, wm, wn, lane);
