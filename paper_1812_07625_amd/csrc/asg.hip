@@ -25,11 +25,10 @@
 //      range a log-domain recursion with a full log-sum-exp per state takes over.
 //   2. asg_grad_em: per frame, node occupancies of both lattices, each normalised per frame;
 //      FAL positions are summed per class in a fixed order ((class, position) sort).
-//   3. asg_trans_partial: per (utterance, 32 frames), edge occupancies summed over the frames:
-//      FCC per class pair, FAL per target position (stay / advance).
-//   4. asg_trans_utt: per utterance, FCC edge sums minus FAL edge sums as a C x C table (the FAL
-//      sums are scattered with 64-bit fixed-point integer atomics, which are order-independent).
-//   5. asg_trans_reduce: sum over utterances in a fixed order.
+//   3. asg_trans_partial: per (utterance, 32 frames), edge occupancies summed over the frames as a
+//      C x C table, FCC minus FAL (the sums of the FAL positions, stay / advance, are scattered
+//      with 64-bit fixed-point integer atomics, which are order-independent).
+//   4. asg_trans_reduce: sum over these tables in a fixed order.
 #include <type_traits>
 #include "common.h"
 
@@ -61,7 +60,7 @@ struct AsgWs {
     double* terms;                   // [B][2]: FCC, FAL in base-2 units
     int* status;                     // [B]: 0 live, 1 no alignment, 2 invalid
     float *izf, *iza;                // [B][Tp] inverse per-frame normalisers of the node occupancies
-    float *partF, *partA, *tabD;     // [B][nch][C*C], [B][nch][2][Lmax], [B][C*C] (per-utterance d loss / d g)
+    float *part;                     // [B][nch][C*C]: a chunk of frames' share of d loss / d g
     int *order, *cstart;             // [B][Lmax] target positions sorted by (class, position); [B][C+1] start of every class in it
 };
 
@@ -850,11 +849,15 @@ __global__ __launch_bounds__(256) void asg_grad_em(const float* __restrict__ em,
     }
 }
 
-// Edge occupancies summed over a chunk of frames.  Workgroup (chunk, utterance).
-//   FCC: partF[i*C+j] = sum_t P_fcc(pi_t = i, pi_{t-1} = j)
-//   FAL: partA[0][s]  = sum_t P_fal(position s at t-1 and at t),  partA[1][s] = sum_t P_fal(s-1 at t-1, s at t)
+// Edge occupancies summed over a chunk of frames, as its share of d loss / d g.  Workgroup (chunk, utterance).
+//   part[i*C+j] = sum_t P_fcc(pi_t = i, pi_{t-1} = j) - P_fal(pi_t = i, pi_{t-1} = j)
 // An edge's weight is exp2( fwd_{t-1}[source] + g + bwd_t[destination] - total ), normalised by the
-// node normaliser of frame t (the edge occupancies of a frame sum to the same 1).
+// node normaliser of frame t (the edge occupancies of a frame sum to the same 1).  The aligned ones are sums per target
+// position (it stays, or it is entered), scattered over the class pairs in LDS as 64-bit fixed-point numbers: integer
+// addition does not depend on the order, so the result is reproducible.
+// A chain of latencies, like asg_grad_em.  (The scatter used to be a launch of its own behind this one, a workgroup an
+// utterance, and the sum over the utterances another: B = 32, T = 750, C = 28 8.7 + 4.8 us, and now 3.9 for the sum.)
+constexpr double FIXED_ONE = 4294967296.0;  // 2^32: occupancies up to 2^31 frames, resolved to 2.3e-10
 __global__ __launch_bounds__(256) void asg_trans_partial(const float* __restrict__ trans, const int* __restrict__ targets,
                                                          const int* __restrict__ in_len, const int* __restrict__ tgt_len,
                                                          AsgWs w, AsgDims d)
@@ -864,16 +867,17 @@ __global__ __launch_bounds__(256) void asg_trans_partial(const float* __restrict
     __shared__ float wF[CHUNK], wA[CHUNK];
     const int ch = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
     const int C2 = d.C * d.C;
-    float* pF = w.partF + ((size_t)b * d.nch + ch) * C2;
-    float* pA = w.partA + ((size_t)b * d.nch + ch) * 2 * d.Lmax;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    unsigned long long* const fal = reinterpret_cast<unsigned long long*>(smem_raw);  // [C*C]
+    float* const part = w.part + ((size_t)b * d.nch + ch) * C2;
     const int T = crit_len(in_len[b], d.len_div), L = tgt_len[b];
     const int t0 = ch * CHUNK;
     const int tlo = t0 < 1 ? 1 : t0, thi = t0 + CHUNK < T ? t0 + CHUNK : T;  // frames [tlo, thi)
     if (w.status[b] != 0 || tlo >= thi) {
-        for (int p = tid; p < C2; p += 256) pF[p] = 0.f;
-        for (int s = tid; s < 2 * d.Lmax; s += 256) pA[s] = 0.f;
+        for (int p = tid; p < C2; p += 256) part[p] = 0.f;
         return;
     }
+    for (int p = tid; p < C2; p += 256) fal[p] = 0ull;
     const size_t rowb = (size_t)b * (d.Tp + 1);
     const double fcc2 = w.terms[2 * b], fal2 = w.terms[2 * b + 1];
     // everything the chunk reads of the lattices is requested at once: the FCC rows in 16-byte pieces on their way into
@@ -928,15 +932,20 @@ __global__ __launch_bounds__(256) void asg_trans_partial(const float* __restrict
     }
     __syncthreads();
     const float log2e = (float)LOG2E;
-    // four source classes a thread: one 16-byte LDS read a frame for them (frames that do not count have wF = log zero)
+    // four source classes a thread and turn: one 16-byte LDS read a frame for them (frames that do not count have wF = log zero)
     const int quads = (d.C + 3) / 4;
-    for (int p = tid; p < d.C * quads; p += 256) {
+    constexpr int TURNS = CP * CP / 4 / 256;
+    float acc[TURNS][4];
+#pragma unroll
+    for (int n = 0; n < TURNS; ++n) {
+        const int p = tid + 256 * n;
+        if (p >= d.C * quads) continue;
         const int i = p / quads, j = (p - i * quads) * 4;
-        float g2[4], acc[4];
+        float g2[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             g2[u] = trans[i * d.C + min(j + u, d.C - 1)] * log2e;
-            acc[u] = 0.f;
+            acc[n][u] = 0.f;
         }
 #pragma unroll 8
         for (int r = 0; r < CHUNK; ++r) {
@@ -944,91 +953,72 @@ __global__ __launch_bounds__(256) void asg_trans_partial(const float* __restrict
             const float* av = &a4.x;
             const float bv = sB[r][i], wv = wF[r];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) acc[u] += fast_exp2((av[u] + bv) + (g2[u] + wv));
+            for (int u = 0; u < 4; ++u) acc[n][u] += fast_exp2((av[u] + bv) + (g2[u] + wv));
         }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (j + u < d.C) pF[i * d.C + j + u] = acc[u];
     }
-    for (int s = tid; s < d.Lmax; s += 256) {
+    for (int s = tid; s < L; s += 256) {
         float stay = 0.f, adv = 0.f;
-        if (s < L) {
-            const int c = lab[s];
-            const float gs = trans[(size_t)c * d.C + c] * log2e;
-            const float ga = s >= 1 ? trans[(size_t)c * d.C + lab[s - 1]] * log2e : NEG;
-            for (int t = tlo; t < thi; t += FAL_AHEAD) {
-                if (s != tid || t != tlo) fetch(s, t);
+        const int c = lab[s], left = s >= 1 ? lab[s - 1] : 0;
+        const float gs = trans[(size_t)c * d.C + c] * log2e;
+        const float ga = s >= 1 ? trans[(size_t)c * d.C + left] * log2e : NEG;
+        for (int t = tlo; t < thi; t += FAL_AHEAD) {
+            if (s != tid || t != tlo) fetch(s, t);
 #pragma unroll
-                for (int u = 0; u < FAL_AHEAD; ++u) {
-                    if (t + u < thi) {
-                        const float bv = y[u] + wA[t + u - t0];
-                        stay += fast_exp2((x0[u] + bv) + gs);
-                        adv += fast_exp2(((s >= 1 ? x1[u] : NEG) + bv) + ga);
-                    }
+            for (int u = 0; u < FAL_AHEAD; ++u) {
+                if (t + u < thi) {
+                    const float bv = y[u] + wA[t + u - t0];
+                    stay += fast_exp2((x0[u] + bv) + gs);
+                    adv += fast_exp2(((s >= 1 ? x1[u] : NEG) + bv) + ga);
                 }
             }
         }
-        pA[s] = stay;
-        pA[d.Lmax + s] = adv;
-    }
-}
-
-// Per utterance: d loss_b / d g as a C x C table.  FAL edge sums (added over the chunks in
-// order) are scattered into the table as 64-bit fixed-point numbers with integer atomics -- integer
-// addition does not depend on the order, so the result is reproducible -- and subtracted from
-// the FCC edge sums (added over the chunks in order).
-constexpr double FIXED_ONE = 4294967296.0;  // 2^32: occupancies up to 2^31 frames, resolved to 2.3e-10
-constexpr int UTT_THREADS = 1024;
-__global__ __launch_bounds__(UTT_THREADS) void asg_trans_utt(const int* __restrict__ targets, const int* __restrict__ tgt_len,
-                                                     AsgWs w, AsgDims d)
-{
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    const int b = blockIdx.x, tid = threadIdx.x, C2 = d.C * d.C;
-    float* tab = w.tabD + (size_t)b * C2;
-    if (w.status[b] != 0) {
-        for (int p = tid; p < C2; p += UTT_THREADS) tab[p] = 0.f;
-        return;
-    }
-    const int L = tgt_len[b];
-    unsigned long long* fal = reinterpret_cast<unsigned long long*>(smem_raw);  // [C*C]
-    for (int p = tid; p < C2; p += UTT_THREADS) fal[p] = 0ull;
-    __syncthreads();
-    const int* lab = targets + (size_t)b * d.Lmax;
-    const float* pA = w.partA + (size_t)b * d.nch * 2 * d.Lmax;
-    for (int s = tid; s < L; s += UTT_THREADS) {
-        float stay = 0.f, adv = 0.f;
-#pragma unroll 16
-        for (int ch = 0; ch < d.nch; ++ch) {
-            stay += pA[(size_t)ch * 2 * d.Lmax + s];
-            adv += pA[(size_t)ch * 2 * d.Lmax + d.Lmax + s];
-        }
-        const int c = lab[s];
         atomicAdd(&fal[c * d.C + c], (unsigned long long)(long long)__double2ll_rn((double)stay * FIXED_ONE));
-        if (s >= 1)
-            atomicAdd(&fal[c * d.C + lab[s - 1]], (unsigned long long)(long long)__double2ll_rn((double)adv * FIXED_ONE));
+        if (s >= 1) atomicAdd(&fal[c * d.C + left], (unsigned long long)(long long)__double2ll_rn((double)adv * FIXED_ONE));
     }
     __syncthreads();
-    const float* pF = w.partF + (size_t)b * d.nch * C2;
-    for (int p = tid; p < C2; p += UTT_THREADS) {
-        float f = 0.f;
-#pragma unroll 16
-        for (int ch = 0; ch < d.nch; ++ch) f += pF[(size_t)ch * C2 + p];
-        tab[p] = f - (float)((double)(long long)fal[p] * (1.0 / FIXED_ONE));
+#pragma unroll
+    for (int n = 0; n < TURNS; ++n) {
+        const int p = tid + 256 * n;
+        if (p >= d.C * quads) continue;
+        const int i = p / quads, j = (p - i * quads) * 4;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (j + u < d.C) {
+                const int e = i * d.C + j + u;
+                part[e] = (float)((double)acc[n][u] - (double)(long long)fal[e] * (1.0 / FIXED_ONE));
+            }
     }
 }
 
-//   grad_trans[p] = grad_scale * sum_b tabD[b][p], added in the order b = 0, 1, ...
-__global__ __launch_bounds__(64) void asg_trans_reduce(float* __restrict__ grad_trans, AsgWs w, AsgDims d, float grad_scale)
+//   grad_trans[p] = grad_scale * sum over utterances and chunks of part[..][p], in a fixed order: REDUCE_RUNS runs of planes
+// by as many threads, then the runs.  Bound by the latency of its loads, which a thread has all in flight up to 1024 planes
+// (24 a thread, the last eight one by one: 8.8 us; 12 at once: 3.9).
+constexpr int REDUCE_PAIRS = 16, REDUCE_RUNS = 64;
+__global__ __launch_bounds__(REDUCE_PAIRS * REDUCE_RUNS) void asg_trans_reduce(float* __restrict__ grad_trans, AsgWs w, AsgDims d, float grad_scale)
 {
-    const int p = blockIdx.x * 64 + threadIdx.x, C2 = d.C * d.C;
-    if (p >= C2) return;
-    float acc = 0.f;
-#pragma unroll 32
-    for (int b = 0; b < d.B; ++b) acc += w.tabD[(size_t)b * C2 + p];
-    grad_trans[p] = grad_scale * acc;
+    __shared__ double run[REDUCE_RUNS][REDUCE_PAIRS];
+    const int C2 = d.C * d.C, q = threadIdx.x % REDUCE_PAIRS, g = threadIdx.x / REDUCE_PAIRS, p = blockIdx.x * REDUCE_PAIRS + q;
+    const long long planes = (long long)d.B * d.nch, per = (planes + REDUCE_RUNS - 1) / REDUCE_RUNS;
+    const long long lo = g * per, hi = lo + per < planes ? lo + per : planes;
+    double acc = 0.0;
+    constexpr int BATCH = 16;  // planes whose loads are in flight together
+    for (long long z = lo; z < hi && p < C2; z += BATCH) {
+        float v[BATCH];
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) v[u] = w.part[(z + u < hi ? z + u : z) * C2 + p];
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) acc += z + u < hi ? (double)v[u] : 0.0;
+    }
+    run[g][q] = acc;
+    __syncthreads();
+    if (g == 0 && p < C2) {
+#pragma unroll
+        for (int r = 1; r < REDUCE_RUNS; ++r) acc += run[r][q];
+        grad_trans[p] = (float)(grad_scale * acc);
+    }
 }
 
-struct WsLayout { size_t fal[2], fcc[2], faloff[2], fccoff[2], terms, status, izf, iza, partF, partA, tabD, order, cstart, total; };
+struct WsLayout { size_t fal[2], fcc[2], faloff[2], fccoff[2], terms, status, izf, iza, part, order, cstart, total; };
 WsLayout ws_layout(int B, int Tp, int C, int Lmax)
 {
     WsLayout w;
@@ -1043,9 +1033,7 @@ WsLayout ws_layout(int B, int Tp, int C, int Lmax)
     w.status = off; off += round_up((size_t)B * 4, 256);
     w.izf = off; off += round_up((size_t)B * Tp * 4, 256);
     w.iza = off; off += round_up((size_t)B * Tp * 4, 256);
-    w.partF = off; off += round_up((size_t)B * nch * C * C * 4, 256);
-    w.partA = off; off += round_up((size_t)B * nch * 2 * Lmax * 4, 256);
-    w.tabD = off; off += round_up((size_t)B * C * C * 4, 256);
+    w.part = off; off += round_up((size_t)B * nch * C * C * 4, 256);
     w.order = off; off += round_up((size_t)B * Lmax * 4, 256);
     w.cstart = off; off += round_up((size_t)B * (C + 1) * 4, 256);
     w.total = off;
@@ -1167,14 +1155,11 @@ int asg_fwd_bwd_strided(const float* emissions, const float* trans, const int* t
     w.status = reinterpret_cast<int*>(ws + l.status);
     w.izf = reinterpret_cast<float*>(ws + l.izf);
     w.iza = reinterpret_cast<float*>(ws + l.iza);
-    w.partF = reinterpret_cast<float*>(ws + l.partF);
-    w.partA = reinterpret_cast<float*>(ws + l.partA);
-    w.tabD = reinterpret_cast<float*>(ws + l.tabD);
+    w.part = reinterpret_cast<float*>(ws + l.part);
     w.order = reinterpret_cast<int*>(ws + l.order);
     w.cstart = reinterpret_cast<int*>(ws + l.cstart);
 
     const size_t lds_em = (size_t)4 * (2 * Lmax + C + 1) + (size_t)4 * 4 * (Lmax + 4);
-    const size_t lds_tab = (size_t)8 * C * C;
     if (lds_em > 160 * 1024) return W2L_ERR_SHAPE;
     if (lds_em > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void*)asg_grad_em, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_em);
@@ -1200,13 +1185,11 @@ int asg_fwd_bwd_strided(const float* emissions, const float* trans, const int* t
                        in_len, tgt_len, loss, grad_emissions, w, d, rows_per_wg, grad_scale);
     rc = launch_status();
     if (rc || !grad_trans) return rc;
-    hipLaunchKernelGGL(asg_trans_partial, dim3(d.nch, B), dim3(256), 0, st, trans, targets, in_len, tgt_len, w, d);
+    hipLaunchKernelGGL(asg_trans_partial, dim3(d.nch, B), dim3(256), (size_t)8 * C * C, st, trans, targets, in_len, tgt_len, w, d);
     rc = launch_status();
     if (rc) return rc;
-    hipLaunchKernelGGL(asg_trans_utt, dim3(B), dim3(UTT_THREADS), lds_tab, st, targets, tgt_len, w, d);
-    rc = launch_status();
-    if (rc) return rc;
-    hipLaunchKernelGGL(asg_trans_reduce, dim3((C * C + 63) / 64), dim3(64), 0, st, grad_trans, w, d, grad_scale);
+    hipLaunchKernelGGL(asg_trans_reduce, dim3((C * C + REDUCE_PAIRS - 1) / REDUCE_PAIRS), dim3(REDUCE_PAIRS * REDUCE_RUNS), 0, st, grad_trans,
+                       w, d, grad_scale);
     return launch_status();
 }
 }  // namespace w2l
