@@ -69,6 +69,7 @@ struct Plan {
     DgradPrep cls_prep;
     std::vector<ConvBwdPlan> bwd;  // per layer: both gradients in one launch, where that can be done
     bool crowded = false;
+    bool long_wgrad = false;  // a weight gradient that is worth the helper stream
     int status = W2L_OK;
 };
 
@@ -94,13 +95,15 @@ size_t planes_bytes(int parts, size_t values) { return parts > 1 ? parts * value
 
 // Layer 0 has no data gradient to run beside, and the weight gradients of narrow outputs and of little work are shorter
 // than the events that a second stream takes (on the device, and on the host, which a small step waits for): these stay
-// on the caller's stream (unless the second stream is there anyway).  Steps of fp32 networks with four equal body layers, us,
+// on the caller's stream (unless the second stream is there anyway: beside a body of 0.57 GFLOP, a head of 0.22 on the
+// caller's stream 242 -> 255).  Steps of fp32 networks with four equal body layers, us,
 // with their weight gradients on the second stream and on the caller's: 0.13 GFLOP a layer (4 x 100 frames, k = 5,
 // 128 -> 256) 235 and 196, 0.26 212..239 and 211, 0.58 250..261 and 260, 1.2 304 and 327; the tiny network (0.016) 94..100 and 85..88.
 constexpr double SHORT_WGRAD = 3e8;
+bool short_wgrad(const Plan& p, const w2l_layer& l, int i, int B) { return 2.0 * B * p.Tout[i] * l.k * l.cin * l.cout <= SHORT_WGRAD; }
 bool main_wgrad(const Plan& p, const w2l_layer& l, int i, int B)
 {
-    return i == 0 || (!p.crowded && (l.cout <= 32 || 2.0 * B * p.Tout[i] * l.k * l.cin * l.cout <= SHORT_WGRAD));
+    return i == 0 || (!p.crowded && (l.cout <= 32 || (!p.long_wgrad && short_wgrad(p, l, i, B))));
 }
 // whether a weight gradient may cut its reduction
 Runs wgrad_runs(const Plan& p, int dydt) { return p.crowded && dydt == W2L_BF16 ? Runs::WHOLE : Runs::IN_STEP; }
@@ -168,6 +171,7 @@ Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int
     // A network with layers whose gradients fill the chip from two streams keeps those streams for all of them, and cuts no
     // bf16 weight gradient: their workgroups take turns with the other stream's as it is (105M step, 8 x 1500 frames, mixed with shared launches and cut: 1.3 % slower).
     if (p.crowded) p.bwd.assign(n, ConvBwdPlan{});
+    for (int i = 1; i < n; ++i) p.long_wgrad = p.long_wgrad || (!p.bwd[i].ok && L[i].cout > 32 && !short_wgrad(p, L[i], i, B));
     // scratch of the weight gradients: on the caller's stream, or on the helper stream beside it
     for (int i = 0; i < n; ++i) {
         const w2l_layer& l = L[i];
