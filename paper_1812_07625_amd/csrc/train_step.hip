@@ -236,7 +236,7 @@ struct Widened {
     bool any() const { return !L.empty(); }
 };
 // Halves of 32 channels more make whole blocks of 64; of 64, also rows of weights that panels divide whatever the taps
-// (FAST addressing in the forward pass), which is worth it up to a sixth more work in either direction.
+// (FAST addressing in the forward pass), which is worth it up to a seventh more channels.
 int wide_half(int h)
 {
     const int a = (h + 31) / 32 * 32, b = (h + 63) / 64 * 64;
