@@ -109,7 +109,8 @@ bool main_wgrad(const Plan& p, const w2l_layer& l, int i, int B)
 Runs wgrad_runs(const Plan& p, int dydt) { return p.crowded && dydt == W2L_BF16 ? Runs::WHOLE : Runs::IN_STEP; }
 bool same_layer(const w2l_layer& a, const w2l_layer& b) { return a.k == b.k && a.stride == b.stride && a.cin == b.cin && a.cout == b.cout && a.glu == b.glu; }
 
-Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int criterion)
+// real: the caller's layers, of which L may be wider ones (widen)
+Plan make_plan(const w2l_layer* L, const w2l_layer* real, int n, int B, int T, int Lmax, int dtype, int criterion)
 {
     Plan p;
     p.n = n;
@@ -207,8 +208,10 @@ Plan make_plan(const w2l_layer* L, int n, int B, int T, int Lmax, int dtype, int
         if (p.fold0) off += round_up(haloed_bytes(B, f0.T, f0.Cin, es), 256);
     }
     if (n > 1 && !p.cls_glu) {
+        // (it rounds the criterion's fp32 gradient to bf16, so only a layer that takes it at the caller's own width does)
         const w2l_layer& ll = L[n - 1];
-        p.cls_prep = dgrad_prep(B, p.Tin[n - 1], ll.cin, ll.cout, ll.k, ll.stride, dtype);
+        if (dgrad_prep(B, p.Tin[n - 1], real[n - 1].cin, ll.cout, ll.k, ll.stride, dtype).ok)
+            p.cls_prep = dgrad_prep(B, p.Tin[n - 1], ll.cin, ll.cout, ll.k, ll.stride, dtype);
         p.cls = off;
         if (p.cls_prep.ok) off += round_up(p.cls_prep.total(), 256);
     }
@@ -387,7 +390,7 @@ using namespace w2l;
 static size_t step_bytes(const w2l_layer* layers, int n_layers, int B, int T, int Lmax, int dtype, int criterion)
 {
     const Widened v = widen(layers, n_layers, B, T, dtype);
-    const Plan p = make_plan(v.any() ? v.L.data() : layers, n_layers, B, T, Lmax, dtype, criterion);
+    const Plan p = make_plan(v.any() ? v.L.data() : layers, layers, n_layers, B, T, Lmax, dtype, criterion);
     return p.status == W2L_OK ? p.total + v.total : 0;
 }
 
@@ -408,7 +411,7 @@ extern "C" int w2l_train_step_launch_config(const w2l_layer* layers, int n_layer
 {
     if (!layers || !data_form || !data_runs || !weight_tile || !weight_runs) return W2L_ERR_NULL;
     const Widened v = widen(layers, n_layers, B, T, dtype);
-    const Plan p = make_plan(v.any() ? v.L.data() : layers, n_layers, B, T, 1, dtype, CRIT_CTC);
+    const Plan p = make_plan(v.any() ? v.L.data() : layers, layers, n_layers, B, T, 1, dtype, CRIT_CTC);
     if (p.status) return p.status;
     if (layer < 0 || layer >= n_layers) return W2L_ERR_SHAPE;
     const ConvBwdPlan& b = p.bwd[layer];
@@ -668,7 +671,7 @@ static int train_step_impl(int criterion, const w2l_layer* layers, int n_layers,
     if (criterion == CRIT_ASG && !trans) return W2L_ERR_NULL;
     const Widened v = widen(layers, n_layers, B, T, dtype);
     const w2l_layer* const L = v.any() ? v.L.data() : layers;
-    const Plan p = make_plan(L, n_layers, B, T, Lmax, dtype, criterion);
+    const Plan p = make_plan(L, layers, n_layers, B, T, Lmax, dtype, criterion);
     if (p.status) return p.status;
     if (criterion == CRIT_CTC && (blank < 0 || blank >= p.C)) return W2L_ERR_SHAPE;
     for (int i = 0; i < n_layers; ++i)

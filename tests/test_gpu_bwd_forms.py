@@ -119,6 +119,23 @@ def test_widths_off_the_matrix_blocks(P, widths, k, stride, feat, frames):
     assert layers == plain
 
 
+@pytest.mark.parametrize("width, classes", [(250, 100), (250, 29), (256, 29)])
+def test_class_gradient_is_not_rounded(P, width, classes):
+    """Where the class layer's weights are the same for all classes, the criterion's gradient, whose classes add up to zero in
+    every frame, leaves nothing for the layers below: what arrives there is the error of that sum.  In fp32 that is about 1e-6
+    of what unequal weights pass on; a gradient rounded to bf16 (2^-9 a class) leaves about 1e-3.  (250: a width that the
+    step rounds up; 256 with more than 64 classes does round it.)"""
+    import numpy as np
+    layers = [dict(k=3, stride=1, cin=40, cout=width, glu=1), dict(k=3, stride=1, cin=width // 2, cout=width, glu=1),
+              dict(k=1, stride=1, cin=width // 2, cout=classes, glu=0)]
+    cfg = W.small_model(140, 4, 160, 200, 40, layers, True, 5, 20)
+    unequal = run_train_step(P, cfg)
+    cfg["weights"][-1] = np.broadcast_to(cfg["weights"][-1][:1], cfg["weights"][-1].shape).copy()
+    equal = run_train_step(P, cfg)
+    for i in range(2):
+        assert np.linalg.norm(equal["dw"][i]) <= 5e-5 * np.linalg.norm(unequal["dw"][i]), i
+
+
 @pytest.mark.parametrize("net, dtype", [("shared", "bf16"), ("two streams", "bf16"), ("shared", "f32")])
 def test_captured_step_replays_the_eager_one(P, net, dtype):
     """A train step recorded into a HIP graph leaves the eager step's bits at every replay, with eager work of the same
