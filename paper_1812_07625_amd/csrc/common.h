@@ -31,6 +31,15 @@ __device__ __forceinline__ bf16_t f32_to_bf16(float f) { return __builtin_bit_ca
 // frames that a criterion sees of an utterance counted before the network's total stride
 __device__ __forceinline__ int crit_len(int n, int div) { return (n < 0 || div <= 1) ? n : (n + div - 1) / div; }
 
+// the first n of eight bf16 values, and zeros
+__device__ __forceinline__ uint4 first_bf16(uint4 v, int n)
+{
+    unsigned* const q = &v.x;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) q[j] = n > 2 * j + 1 ? q[j] : n > 2 * j ? q[j] & 0xffffu : 0u;
+    return v;
+}
+
 // the hardware reciprocal (1 ulp) instead of an IEEE division: a quarter of the GLU kernels' instructions
 __device__ __forceinline__ float sigmoidf_(float u) { return __builtin_amdgcn_rcpf(1.f + __expf(-u)); }
 
@@ -64,6 +73,8 @@ struct ConvDesc {
     int B, T, Tp, Cin, Cout, k, s, p;
     int x_pitch, x_halo, y_pitch, y_halo, slack;
     int xcd_m = 0;  // set by the launchers: how the tile grid is cut over the 8 XCDs (see tile_of_block)
+    int x_live = 0, h_live = 0;  // of Cin and of the Cout / 2 channels behind a GLU, those that are there (0: all).  The others fill a
+                                 // row up to what the kernels take: their GLU outputs and gradients are zeros whatever the sums hold
     int w_cols = 0; // weight gradient only: columns of a dw row that exist (0: all k * Cin).  A strided layer
                     // folded into a stride-1 one (fold_stride) has k * Cin rounded up to whole folded frames.
 };
@@ -225,11 +236,11 @@ int asg_fwd_bwd_strided(const float* emissions, const float* trans, const int* t
 
 // GLU with an explicit output layout (elementwise.hip).  y (and dh) are dense [B*Tp, Cout]
 // ([B*Tp, Cout/2]); the output is written with the given pitch and halo, halo and slack
-// frames included (as zeros).
+// frames included (as zeros).  live, here and below: as ConvDesc::h_live.
 int glu_fwd_layout(const void* y, void* h, int B, int Tp, int Cout, int dtype, int pitch, int halo, int slack,
-                   hipStream_t st);
+                   hipStream_t st, int live = 0);
 int glu_bwd_layout(const void* y, const void* dh, void* dy, int B, int Tp, int Cout, int dtype, int pitch, int halo,
-                   int slack, hipStream_t st);
+                   int slack, hipStream_t st, int live = 0);
 
 // Finishing passes of a split reduction: part holds `parts` planes of fp32 sums, added in order (elementwise.hip).
 //   rows: + bias -> y in the given layout;  glu_fwd: + bias -> y (dense) and h = GLU(y) as in glu_fwd_layout;
@@ -238,9 +249,9 @@ int glu_bwd_layout(const void* y, const void* dh, void* dy, int B, int Tp, int C
 int finish_rows(const float* part, int parts, const float* bias, void* y, int dtype, int B, int frames, int N, int pitch, int halo,
                 hipStream_t st);
 int finish_glu_fwd(const float* part, int parts, const float* bias, void* y, void* h, int B, int Tp, int Cout, int dtype, int pitch,
-                   int halo, int slack, hipStream_t st);
+                   int halo, int slack, hipStream_t st, int live = 0);
 int finish_glu_bwd(const float* part, int parts, const void* y, void* dy, int B, int Tp, int Cout, int dtype, int pitch, int halo,
-                   int slack, hipStream_t st);
+                   int slack, hipStream_t st, int live = 0);
 int finish_sums(const float* part, int parts, long long n, float* out, const float* bpart, int nb, float* bout, int accumulate,
                 hipStream_t st);
 
@@ -248,7 +259,7 @@ int finish_sums(const float* part, int parts, long long n, float* out, const flo
 // below (y: dense [B*Tp, 2H]; dy as in glu_bwd_layout) in one launch, where class_bwd_glu_ok()
 bool class_bwd_glu_ok(int B, int pitch, int slack, int C, int H, int dtype);
 int class_bwd_glu(const float* dz, const void* w, const void* y, void* dy, int B, int Tp, int C, int H, int dtype, int pitch, int halo, int slack,
-                  hipStream_t st);
+                  hipStream_t st, int live = 0);
 
 // dense bf16 [B*Tp, C] (C % 8 == 0) -> layout with the given pitch / halo / slack, zeros outside the real frames
 // (and `nclear` integers at `clear` set to zero on the way)

@@ -910,7 +910,7 @@ __global__ __launch_bounds__(256 * KG) void conv_fwd_slab_k(const bf16_t* __rest
         core.stage_bf16(lds, bv, 0, kg, wm, wn, lane);
         __syncthreads();
         const long long zero_end = (long long)g.B * g.x_pitch + LAYOUT_SLACK_ZERO;  // h is zero up to here outside real frames
-        const int ch0 = tn * (BN / 2);
+        const int ch0 = tn * (BN / 2), live = g.h_live ? g.h_live : H;
 #pragma unroll 2
         for (int c = threadIdx.x; c < BM * CPH; c += NTHR) {
             const int row = c / CPH, cc = c - row * CPH;
@@ -935,6 +935,7 @@ __global__ __launch_bounds__(256 * KG) void conv_fwd_slab_k(const bf16_t* __rest
                     }
                     qh[q] = r2;
                 }
+                if (ch0 + cc * 8 + 8 > live) oh = first_bf16(oh, live - ch0 - cc * 8);
             }
             if (f < zero_end || ro >= 0) *reinterpret_cast<uint4*>(h + (size_t)f * H + ch0 + cc * 8) = oh;
         }
@@ -1157,6 +1158,7 @@ __device__ __forceinline__ void dgrad_slab_tile(unsigned char* lds, int bx, int 
     core.stage_bf16(lds, zero, 0, kg, wm, wn, lane);
     __syncthreads();
     const long long alloc_frames = (long long)g.B * g.y_pitch + g.slack;
+    const int live = g.x_live ? g.x_live : N;
 #pragma unroll 2
     for (int c = threadIdx.x; c < BM * CPRW; c += NTHR) {
         const int row = c / CPRW, cc = c - row * CPRW;
@@ -1184,6 +1186,10 @@ __device__ __forceinline__ void dgrad_slab_tile(unsigned char* lds, int bx, int 
                 }
                 qa[q] = ra;
                 qg[q] = rg;
+            }
+            if (n + 8 > live) {
+                oa = first_bf16(oa, live - n);
+                og = first_bf16(og, live - n);
             }
         }
         bf16_t* o = dx + (size_t)f * 2 * N + n;

@@ -55,6 +55,15 @@ template <> struct Vec8<float> {
 struct RowMap {
     int Tp, pitch, halo;
     long long real_frames;  // B * pitch
+    int live = 1 << 30;     // channels behind the GLU that are there; the others are written as zeros
+    // v, values of channels c .., with zeros in those that are not there
+    template <int V>
+    __device__ __forceinline__ void clear(int c, float (&v)[V]) const
+    {
+        if (c + V <= live) return;
+#pragma unroll
+        for (int j = 0; j < V; ++j) v[j] = c + j < live ? v[j] : 0.f;
+    }
     // IDX: long long, or unsigned where every frame index fits (the 64-bit division is slow)
     template <typename IDX>
     __device__ __forceinline__ long long src(IDX f) const
@@ -91,6 +100,7 @@ __global__ __launch_bounds__(256) void glu_fwd_k(const T* __restrict__ y, T* __r
             }
 #pragma unroll
             for (int j = 0; j < V; ++j) o[j] = a[j] * sigmoidf_(g[j]);
+            map.clear(c, o);
         } else {
 #pragma unroll
             for (int j = 0; j < V; ++j) o[j] = 0.f;
@@ -128,6 +138,8 @@ __global__ __launch_bounds__(256) void glu_bwd_k(const T* __restrict__ y, const 
                 da[j] = d[j] * sg;
                 dg[j] = d[j] * a[j] * sg * (1.f - sg);
             }
+            map.clear(c, da);
+            map.clear(c, dg);
         } else {
 #pragma unroll
             for (int j = 0; j < V; ++j) { da[j] = 0.f; dg[j] = 0.f; }
@@ -233,6 +245,7 @@ __global__ __launch_bounds__(256) void finish_glu_fwd_k(const float* __restrict_
                 if (bias) { a.v[j] += bias[c + j]; g.v[j] += bias[H + c + j]; }
                 o[j] = as_stored<T>(a.v[j]) * sigmoidf_(as_stored<T>(g.v[j]));
             }
+            map.clear(c, o);
             store_vec<T, V>(y + r * 2 * H + c, a.v);
             store_vec<T, V>(y + r * 2 * H + H + c, g.v);
         } else {
@@ -263,6 +276,8 @@ __global__ __launch_bounds__(256) void finish_glu_bwd_k(const float* __restrict_
                 da[j] = d * sg;
                 dg[j] = d * a[j] * sg * (1.f - sg);
             }
+            map.clear(c, da);
+            map.clear(c, dg);
         } else {
 #pragma unroll
             for (int j = 0; j < V; ++j) { da[j] = 0.f; dg[j] = 0.f; }
@@ -372,6 +387,8 @@ __global__ __launch_bounds__(256) void class_bwd_glu_k(const float* __restrict__
             da[j] = r[u] >= 0 ? acc[u][j] * sg : 0.f;
             dg[j] = r[u] >= 0 ? acc[u][j] * a[j] * sg * (1.f - sg) : 0.f;
         }
+        map.clear(c, da);
+        map.clear(c, dg);
         auto narrow = [](const float (&v)[V]) {
             uint4 q;
             unsigned* const b = &q.x;
@@ -643,12 +660,12 @@ void launch_glu_bwd(dim3 g, hipStream_t st, const void* y, const void* dh, void*
 }  // namespace
 
 int glu_fwd_layout(const void* y, void* h, int B, int Tp, int Cout, int dtype, int pitch, int halo, int slack,
-                   hipStream_t st)
+                   hipStream_t st, int live)
 {
     const int H = Cout / 2;
     const bool vec = (H % 8) == 0;
     const long long out_rows = (long long)B * pitch + slack;
-    const RowMap map{Tp, pitch, halo, (long long)B * pitch};
+    const RowMap map{Tp, pitch, halo, (long long)B * pitch, live > 0 ? live : H};
     const long long items = vec ? out_rows * (H / 8) : out_rows * H;
     const dim3 g(grid_for(items));
     const bool small = items < (1LL << 31);  // 32-bit element indices
@@ -667,12 +684,12 @@ int glu_fwd_layout(const void* y, void* h, int B, int Tp, int Cout, int dtype, i
 }
 
 int glu_bwd_layout(const void* y, const void* dh, void* dy, int B, int Tp, int Cout, int dtype, int pitch, int halo,
-                   int slack, hipStream_t st)
+                   int slack, hipStream_t st, int live)
 {
     const int H = Cout / 2;
     const bool vec = (H % 8) == 0;
     const long long out_rows = (long long)B * pitch + slack;
-    const RowMap map{Tp, pitch, halo, (long long)B * pitch};
+    const RowMap map{Tp, pitch, halo, (long long)B * pitch, live > 0 ? live : H};
     const long long items = vec ? out_rows * (H / 8) : out_rows * H;
     const dim3 g(grid_for(items));
     const bool small = items < (1LL << 31);
@@ -706,12 +723,12 @@ int finish_rows(const float* part, int parts, const float* bias, void* y, int dt
     return launch_status();
 }
 int finish_glu_fwd(const float* part, int parts, const float* bias, void* y, void* h, int B, int Tp, int Cout, int dtype, int pitch,
-                   int halo, int slack, hipStream_t st)
+                   int halo, int slack, hipStream_t st, int live)
 {
     const int H = Cout / 2;
     const bool vec = H % 4 == 0;
     const unsigned out_rows = (unsigned)B * pitch + slack;
-    const RowMap map{Tp, pitch, halo, (long long)B * pitch};
+    const RowMap map{Tp, pitch, halo, (long long)B * pitch, live > 0 ? live : H};
     const long long plane = (long long)B * Tp * Cout;
     const dim3 g(grid_for((long long)out_rows * (vec ? H / 4 : H))), b(256);
 #define W2L_FIN(T_, V_) hipLaunchKernelGGL((finish_glu_fwd_k<T_, V_>), g, b, 0, st, part, parts, bias, (T_*)y, (T_*)h, out_rows, H, map, plane)
@@ -721,12 +738,12 @@ int finish_glu_fwd(const float* part, int parts, const float* bias, void* y, voi
     return launch_status();
 }
 int finish_glu_bwd(const float* part, int parts, const void* y, void* dy, int B, int Tp, int Cout, int dtype, int pitch, int halo,
-                   int slack, hipStream_t st)
+                   int slack, hipStream_t st, int live)
 {
     const int H = Cout / 2;
     const bool vec = H % 4 == 0;
     const unsigned out_rows = (unsigned)B * pitch + slack;
-    const RowMap map{Tp, pitch, halo, (long long)B * pitch};
+    const RowMap map{Tp, pitch, halo, (long long)B * pitch, live > 0 ? live : H};
     const long long plane = (long long)B * Tp * H;
     const dim3 g(grid_for((long long)out_rows * (vec ? H / 4 : H))), b(256);
 #define W2L_FIN(T_, V_) hipLaunchKernelGGL((finish_glu_bwd_k<T_, V_>), g, b, 0, st, part, parts, (const T_*)y, (T_*)dy, out_rows, H, map, plane)
@@ -741,11 +758,11 @@ bool class_bwd_glu_ok(int B, int pitch, int slack, int C, int H, int dtype)
     return C <= 64 && H % (dtype == W2L_BF16 ? 8 : 4) == 0 && (long long)B * pitch + slack < (1LL << 31);
 }
 int class_bwd_glu(const float* dz, const void* w, const void* y, void* dy, int B, int Tp, int C, int H, int dtype, int pitch, int halo, int slack,
-                  hipStream_t st)
+                  hipStream_t st, int live)
 {
     if (!class_bwd_glu_ok(B, pitch, slack, C, H, dtype)) return W2L_ERR_SHAPE;
     const unsigned out_rows = (unsigned)((long long)B * pitch + slack);
-    const RowMap map{Tp, pitch, halo, (long long)B * pitch};
+    const RowMap map{Tp, pitch, halo, (long long)B * pitch, live > 0 ? live : H};
     const bool bf16 = dtype == W2L_BF16;
     const int groups = H / (bf16 ? 8 : 4);
     // 32 groups of channels and 32 frames a workgroup, or 16 and 64 where a row has fewer

@@ -59,6 +59,7 @@ enum { CRIT_CTC = 0, CRIT_ASG = 1 };
 struct Plan {
     int n = 0, C = 0, Tlast = 0, tot_stride = 1;
     std::vector<int> Tin, Tout, outch;
+    std::vector<int> live;          // channels behind a layer's GLU that the caller's network has (widen)
     std::vector<size_t> pre, post;  // workspace offsets of conv output (dense) and GLU output (haloed) per layer
     size_t dlogits = 0, gdy[3] = {0, 0, 0}, gdh[2] = {0, 0}, ctc = 0, conv = 0, conv0 = 0, dbias = 0, dgs = 0, part = 0, total = 0;
     size_t ctc_bytes = 0, conv_bytes = 0, conv0_bytes = 0, dgs_bytes = 0, part_bytes = 0;  // part: sums of split reductions on the caller's stream
@@ -81,7 +82,8 @@ size_t haloed_bytes(int B, int frames, int ch, size_t es) { return ((size_t)B * 
 ConvDesc layer_desc(const Plan& p, const w2l_layer* L, int B, int i)
 {
     ConvDesc d = dense_desc(B, p.Tin[i], L[i].cin, L[i].cout, L[i].k, L[i].stride);
-    if (i > 0) { d.x_pitch = p.Tin[i] + 2 * HALO; d.x_halo = HALO; d.slack = SLACK; }
+    if (i > 0) { d.x_pitch = p.Tin[i] + 2 * HALO; d.x_halo = HALO; d.slack = SLACK; d.x_live = p.live[i - 1]; }
+    d.h_live = p.live[i];
     return d;
 }
 ConvDesc layer_bwd_desc(const Plan& p, const w2l_layer* L, int B, int i)
@@ -130,6 +132,7 @@ Plan make_plan(const w2l_layer* L, const w2l_layer* real, int n, int B, int T, i
         p.Tin.push_back(t);
         p.Tout.push_back(to);
         p.outch.push_back(l.glu ? l.cout / 2 : l.cout);
+        p.live.push_back(l.glu ? real[i].cout / 2 : 0);
         p.tot_stride *= l.stride;
         const size_t oes = (i == n - 1) ? 4 : es;  // logits are fp32
         p.pre.push_back(off);
@@ -223,8 +226,9 @@ Plan make_plan(const w2l_layer* L, const w2l_layer* real, int n, int B, int T, i
 // The bf16 kernels want whole blocks of 64 output channels for a data gradient and whole chunks of 8 input channels for
 // any pass; a network of other widths ran its passes on the fp32 matrix instruction, a sixteenth of the rate.  Such a
 // network is stepped as one of wider layers: every gated layer's halves are rounded up, the weights and biases copied
-// with zeros in the new places, and the gradients of the real ones copied out at the end.  The new channels hold exact
-// zeros all the way (0 * sigmoid(0) forward, sums of zeros backward), so the real ones' sums gain zeros and nothing else.
+// with zeros in the new places, and the gradients of the real ones copied out at the end.  Behind every GLU and every GLU
+// backward the new channels hold zeros (written as such: 0 times an infinity of a real channel is none), so the real ones'
+// sums gain zeros and nothing else.
 // Steps, us, k = 7, four body layers, 4 x 800 frames at stride 2: width 512 284; 496 520 -> 302; 500 1024 -> 306;
 // 8 x 1200, k = 11, width 404 2299 -> 493.  The two copying launches and their host calls are about 15 us: 2 x 200 frames
 // of width 144 (0.22 GFLOP) 157 -> 133, 1 x 100 of width 240 (0.16, and too few frames for the kernels) 166 -> 170, of 132
@@ -448,7 +452,7 @@ static int run_step(const Plan& p, int criterion, const w2l_layer* layers, int n
             rc = conv_fwd_partial(fd, h, weights[i], dtype, part, st);  // the GLU pass adds the parts up
             if (rc) return rc;
             rc = finish_glu_fwd(part, parts, biases[i], ws + p.pre[i], ws + p.post[i], B, p.Tout[i], l.cout, dtype,
-                                p.Tout[i] + 2 * HALO, HALO, SLACK_ZERO, st);
+                                p.Tout[i] + 2 * HALO, HALO, SLACK_ZERO, st, p.live[i]);
             if (rc) return rc;
             h = ws + p.post[i];
             continue;
@@ -463,7 +467,7 @@ static int run_step(const Plan& p, int criterion, const w2l_layer* layers, int n
         if (rc) return rc;
         if (l.glu) {
             rc = glu_fwd_layout(ws + p.pre[i], ws + p.post[i], B, p.Tout[i], l.cout, dtype, p.Tout[i] + 2 * HALO, HALO,
-                                SLACK_ZERO, st);
+                                SLACK_ZERO, st, p.live[i]);
             if (rc) return rc;
         } else if (i < n - 1) {
             rc = pad_layout(ws + p.pre[i], ws + p.post[i], B, p.Tout[i], l.cout, dtype, p.Tout[i] + 2 * HALO, HALO,
@@ -527,7 +531,7 @@ static int run_step(const Plan& p, int criterion, const w2l_layer* layers, int n
             if (!dy_ready) {
                 if (!wait_wgrad(i + 3)) return W2L_ERR_LAUNCH;
                 rc = glu_bwd_layout(ws + p.pre[i], dh, gdy, B, p.Tout[i], l.cout, dtype, p.Tout[i] + 2 * HALO, HALO,
-                                    SLACK_ZERO, st);
+                                    SLACK_ZERO, st, p.live[i]);
                 if (rc) return rc;
             }
             dy = gdy;
@@ -555,7 +559,7 @@ static int run_step(const Plan& p, int criterion, const w2l_layer* layers, int n
             if (rc) return rc;
             if (planes) {
                 rc = finish_glu_bwd(reinterpret_cast<float*>(ws + p.part), both.dparts, ws + p.pre[i - 1], dyb, B, p.Tout[i - 1],
-                                    layers[i - 1].cout, dtype, p.Tout[i - 1] + 2 * HALO, HALO, SLACK_ZERO, st);
+                                    layers[i - 1].cout, dtype, p.Tout[i - 1] + 2 * HALO, HALO, SLACK_ZERO, st, p.live[i - 1]);
                 if (rc) return rc;
             }
             dy_ready = below;
@@ -606,7 +610,7 @@ static int run_step(const Plan& p, int criterion, const w2l_layer* layers, int n
         }
         if (i > 0 && i == n - 1 && p.cls_glu) {
             rc = class_bwd_glu(dz, weights[i], ws + p.pre[i - 1], ws + p.gdy[(i - 1) % 3], B, p.Tout[i - 1], l.cout, l.cin, dtype,
-                               p.Tout[i - 1] + 2 * HALO, HALO, SLACK_ZERO, st);
+                               p.Tout[i - 1] + 2 * HALO, HALO, SLACK_ZERO, st, p.live[i - 1]);
             if (rc) return rc;
             dy_ready = true;
             continue;
@@ -620,7 +624,7 @@ static int run_step(const Plan& p, int criterion, const w2l_layer* layers, int n
                 rc = conv_dgrad_partial(d, dy, weights[i], dtype, dy_dt, part, st);
                 if (rc) return rc;
                 rc = finish_glu_bwd(part, parts, ws + p.pre[i - 1], ws + p.gdy[(i - 1) % 3], B, p.Tout[i - 1],
-                                    layers[i - 1].cout, dtype, p.Tout[i - 1] + 2 * HALO, HALO, SLACK_ZERO, st);
+                                    layers[i - 1].cout, dtype, p.Tout[i - 1] + 2 * HALO, HALO, SLACK_ZERO, st, p.live[i - 1]);
                 if (rc) return rc;
                 dy_ready = true;
                 continue;

@@ -136,6 +136,68 @@ def test_class_gradient_is_not_rounded(P, width, classes):
         assert np.linalg.norm(equal["dw"][i]) <= 5e-5 * np.linalg.norm(unequal["dw"][i]), i
 
 
+@pytest.mark.parametrize("widths, k, frames", [
+    ((250,) * 3, 3, 200),       # planes of sums finished by the GLU passes
+    ((250,) * 3, 1, 200),       # GLU passes of their own
+    ((750, 760, 700), 3, 3000), # GLU and GLU backward in the epilogues of the tiles
+])
+def test_infinities_stay_where_they_are(P, widths, k, frames):
+    """A network of positive weights, stepped at rounded-up widths, carries an infinite feature to the logits of the frames
+    around it as infinities of its real channels (0 times infinity in a new channel would make them NaN); the others are
+    finite and right, within the rounding of a bf16 step's activations."""
+    import numpy as np
+    import oracle
+    cin = [40] + [w // 2 for w in widths[:-1]]
+    layers = [dict(k=k, stride=1, cin=c, cout=w, glu=1) for c, w in zip(cin, widths)] + [dict(k=1, stride=1, cin=widths[-1] // 2, cout=29, glu=0)]
+    B = 4
+    cfg = W.small_model(150 + k, B, frames, frames, 40, layers, True, 3, 10)
+    cfg["x"] = np.abs(cfg["x"])
+    cfg["weights"] = [np.abs(w) for w in cfg["weights"]]
+    cfg["x"][1, frames // 2, 7] = np.inf
+    h = cfg["x"][1].astype(np.float64)[None, frames // 2 - 20:frames // 2 + 20]   # (the frames that it can reach, and some more)
+    for L, w, b in zip(layers, cfg["weights"], cfg["biases"]):
+        h = oracle.conv1d_fwd(h, w.astype(np.float64), b.astype(np.float64), L["stride"])
+        if L["glu"]:
+            h = oracle.glu_fwd(h)
+    got = run_train_step(P, cfg)["logits"]
+    assert np.isfinite(np.delete(got, 1, 0)).all()
+    reach = slice(frames // 2 - 10, frames // 2 + 10)
+    got, ref = got[1, reach], h[0, 10:30]
+    assert np.isposinf(ref).any() and np.isfinite(ref).any()
+    np.testing.assert_array_equal(np.isposinf(got), np.isposinf(ref))
+    assert not np.isnan(got).any()
+    fin = np.isfinite(ref)
+    assert np.linalg.norm(got[fin] - ref[fin]) <= 2e-2 * np.linalg.norm(ref[fin])
+
+
+@pytest.mark.parametrize("widths, k, frames", [((250,) * 3, 3, 200), ((250,) * 3, 1, 200), ((750, 760, 700), 3, 3000)])
+def test_infinite_gradients_stay_where_they_are(P, widths, k, frames):
+    """The same on the way back: with positive weights and features and a class that no target has, whose gradient times its
+    weights overflows in some frames, every term of the layers' gradients is positive, so they overflow but are no NaN."""
+    import numpy as np
+    cin = [40] + [w // 2 for w in widths[:-1]]
+    layers = [dict(k=k, stride=1, cin=c, cout=w, glu=1) for c, w in zip(cin, widths)] + [dict(k=1, stride=1, cin=widths[-1] // 2, cout=29, glu=0)]
+    cfg = W.small_model(160 + k, 4, frames, frames, 40, layers, True, 3, 10, zero_bias=True)
+    assert cfg["targets"].max() <= 28
+    cfg["targets"] = np.where(cfg["targets"] == 28, 1, cfg["targets"]).astype(np.int32)
+    x = 0.5 + 0.5 * np.abs(cfg["x"]) / np.abs(cfg["x"]).max()
+    mid = slice(frames // 2 - 5, frames // 2 + 5)
+    x[:, mid] *= 4                                                   # gates stay far from where their slope is 0
+    cfg["x"] = W.round_to_bf16(x.astype(np.float32))
+    mean = lambda w: np.abs(w) / np.abs(w).sum((1, 2), keepdims=True)  # a layer's values are means of the last one's
+    w = [mean(w) for w in cfg["weights"][:-1]]
+    w[-1] = 0.002 * w[-1]
+    last = np.zeros(cfg["weights"][-1].shape)
+    last[28] = 10.0 / (0.0027 * last.shape[2])
+    cfg["weights"] = [W.round_to_bf16(a.astype(np.float32)) for a in w + [last]]
+    cfg["biases"][-1][28] = -5
+    got = run_train_step(P, cfg, grad_scale=3e38)
+    assert np.isfinite(got["logits"]).all() and np.isfinite(got["loss"]).all()
+    for i in range(3):
+        assert np.isposinf(got["dw"][i]).any(), i
+        assert not np.isnan(got["dw"][i]).any() and not np.isnan(got["db"][i]).any(), i
+
+
 @pytest.mark.parametrize("net, dtype", [("shared", "bf16"), ("two streams", "bf16"), ("shared", "f32")])
 def test_captured_step_replays_the_eager_one(P, net, dtype):
     """A train step recorded into a HIP graph leaves the eager step's bits at every replay, with eager work of the same
