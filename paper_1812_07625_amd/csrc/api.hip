@@ -144,7 +144,11 @@ void staged_y(ConvDesc& d) { d.y_pitch = d.Tp + 2 * ABI_HALO; d.y_halo = ABI_HAL
 // a strided layer whose stride folds into the channels (fold_stride) is staged as the stride-1 layer it folds to
 bool stage_wgrad_folded(int B, int T, int Cin, int Cout, int k, int s, int dt, ConvDesc& f)
 {
-    return s > 1 && fold_stride(dense_desc(B, T, Cin, Cout, k, s), f) && stage_wgrad(f.Cin, Cout, f.k, 1, dt);
+    if (s <= 1 || !fold_stride(dense_desc(B, T, Cin, Cout, k, s), f) || !stage_wgrad(f.Cin, Cout, f.k, 1, dt)) return false;
+    ConvDesc g = f;  // (kernels for any shape know nothing of a folded row's end)
+    staged_x(g);
+    staged_y(g);
+    return conv_wgrad_mfma_takes_dbias(g);
 }
 }  // namespace
 

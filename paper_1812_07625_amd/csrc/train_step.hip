@@ -93,6 +93,16 @@ ConvDesc layer_bwd_desc(const Plan& p, const w2l_layer* L, int B, int i)
     if (L[i].glu) { d.y_pitch = p.Tout[i] + 2 * HALO; d.y_halo = HALO; d.slack = SLACK; }
     return d;
 }
+// A strided bf16 first layer whose weight gradient runs over folded frames, x copied into the haloed layout of its dy: f, its
+// geometry.  Only where the matrix kernels take that: the others know nothing of a folded row's end (w_cols).
+bool folded_first(const Plan& p, const w2l_layer* L, int n, int B, int dtype, ConvDesc& f)
+{
+    if (dtype != W2L_BF16 || n < 2 || !L[0].glu || !fold_stride(dense_desc(B, p.Tin[0], L[0].cin, L[0].cout, L[0].k, L[0].stride), f)) return false;
+    f.x_pitch = f.y_pitch = p.Tout[0] + 2 * HALO;
+    f.x_halo = f.y_halo = HALO;
+    f.slack = SLACK;
+    return f.p <= HALO && conv_wgrad_mfma_takes_dbias(f);
+}
 size_t planes_bytes(int parts, size_t values) { return parts > 1 ? parts * values * 4 : 0; }
 
 // Layer 0 has no data gradient to run beside, and the weight gradients of narrow outputs and of little work are shorter
@@ -204,9 +214,8 @@ Plan make_plan(const w2l_layer* L, const w2l_layer* real, int n, int B, int T, i
     p.part = off; off += round_up(p.part_bytes, 256);
     {
         // a strided first layer with GLU (its dy is haloed): the weight gradient reads x folded and haloed
-        ConvDesc d0 = dense_desc(B, T, L[0].cin, L[0].cout, L[0].k, L[0].stride), f0;
-        p.fold0 = dtype == W2L_BF16 && L[0].glu && n > 1 && fold_stride(d0, f0) && f0.p <= HALO && f0.Cin % 8 == 0 &&
-                  L[0].cout >= 64;
+        ConvDesc f0;
+        p.fold0 = folded_first(p, L, n, B, dtype, f0);
         p.xfold = off;
         if (p.fold0) off += round_up(haloed_bytes(B, f0.T, f0.Cin, es), 256);
     }
@@ -581,10 +590,7 @@ static int run_step(const Plan& p, int criterion, const w2l_layer* layers, int n
             // the strided first layer as a stride-1 layer over folded frames: x copied (2 MB) into the haloed time
             // layout of dy_0, then the same dense weight-gradient kernel as every other layer, bias gradient included
             ConvDesc f;
-            fold_stride(dense_desc(B, p.Tin[0], l.cin, l.cout, l.k, l.stride), f);
-            f.x_pitch = f.y_pitch = p.Tout[0] + 2 * HALO;
-            f.x_halo = f.y_halo = HALO;
-            f.slack = SLACK;
+            folded_first(p, layers, n, B, dtype, f);
             rc = pad_layout_bf16(x, ws + p.xfold, B, f.T, f.Cin, f.x_pitch, HALO, SLACK_ZERO, st);
             if (rc) return rc;
             d = f;

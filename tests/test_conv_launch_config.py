@@ -87,3 +87,10 @@ def test_runs_fit_the_kernel_that_is_launched(pass_, shape, splits):
 def test_fp32_passes_alone_take_bf16_terms_where_that_is_faster(pass_, shape, tile):
     """By the times of either kernel, 6 to 24 % of a pass in the first group (the weight gradients: 5 % of their layer)."""
     assert P.w2l_conv1d_launch_tile(pass_, *shape, 1, F32) == tile
+
+
+def test_strides_fold_only_for_the_matrix_kernels():
+    """A strided bf16 weight gradient whose x is beyond the matrix kernels' 32-bit offsets is not copied into folded frames,
+    which the other kernels cannot read."""
+    copies = lambda T: P.w2l_conv1d_bwd_weight_workspace_bytes(64, T, 512, 64, 5, 2, P.W2L_BF16) > 64 * T * 512 * 2
+    assert copies(8000) and not copies(40000)

@@ -198,6 +198,26 @@ def test_infinite_gradients_stay_where_they_are(P, widths, k, frames):
         assert not np.isnan(got["dw"][i]).any() and not np.isnan(got["db"][i]).any(), i
 
 
+@pytest.mark.parametrize("cout, k, stride", [(100, 5, 2), (150, 13, 2), (84, 1, 2), (100, 9, 4), (128, 5, 2)])
+def test_strided_first_layer_of_any_width(P, cout, k, stride):
+    """The first layer's weight gradient, whose stride folds into the channels only where the matrix kernels take the folded
+    layer: right, and nothing written behind it.  (Too little work to be stepped at rounded-up widths.)"""
+    import torch
+    layers = [dict(k=k, stride=stride, cin=40, cout=cout, glu=1), dict(k=1, stride=1, cin=cout // 2, cout=29, glu=0)]
+    cfg = W.small_model(170 + cout + k, 3, 150, 200, 40, layers, True, 3, 10)
+    room = torch.full((cfg["weights"][0].size + 65536,), -7.0, device="cuda:0")
+
+    class Guarded:  # the binding, with room of known contents behind the first layer's weight gradient
+        def __getattr__(self, name): return getattr(P, name)
+        def w2l_train_step(self, layers, w, b, dw, db, *rest):
+            inner = room[:dw[0].numel()].view(dw[0].shape)
+            P.w2l_train_step(layers, w, b, [inner] + dw[1:], db, *rest)
+            dw[0].copy_(inner)
+
+    check_train_step(run_train_step(Guarded(), cfg), oracle_train_step(cfg), "bf16")
+    assert (room[cfg["weights"][0].size:] == -7.0).all()
+
+
 @pytest.mark.parametrize("net, dtype", [("shared", "bf16"), ("two streams", "bf16"), ("shared", "f32")])
 def test_captured_step_replays_the_eager_one(P, net, dtype):
     """A train step recorded into a HIP graph leaves the eager step's bits at every replay, with eager work of the same
