@@ -300,6 +300,12 @@ int w2l_logmel_fwd(const float *wav, const int *wav_len, void *feat, int *feat_l
  * tgt_len, loss, logits are device pointers.  With W2L_BF16, activations and
  * gradients between layers are stored as bf16, the last layer's output (logits), the
  * log-softmax and CTC are fp32.
+ * Widths: the bf16 matrix kernels take output channels in blocks of 64 and input channels in chunks of 8.
+ * A bf16 network of gated layers (all but the last; cin_0 a multiple of 4, at least 0.2 GFLOP and 128
+ * frames) with other widths is stepped with those layers' channels rounded up, where that is the quicker
+ * way: the workspace then also holds the wider weights (bf16) and their gradients (fp32), and activations
+ * of the wider layers (4 x 800 frames, width 500: 62 MB instead of 41).  Results have the caller's widths
+ * and are what they are at those, infinities and NaN included; only the order of sums differs.
  * Concurrency: weight gradients that neither share a launch with their layer's data gradient nor are
  * too short for it run on one helper stream (default priority, created on first use, one per device,
  * never destroyed) tied to `stream` by events; the step is
@@ -335,12 +341,17 @@ int w2l_train_step_asg(const w2l_layer *layers, int n_layers,
                        void *workspace, size_t ws_bytes, void *stream);
 /* Host-only query: how both train steps compute the gradients of one layer.  data_form 0: weight and data gradient are
  * launches of their own (then the others are 0 too); otherwise one launch takes both (if the layer's bias gradient is
- * wanted), the data gradient as 1: 192x192 tiles by two workgroups each, GLU backward of the layer below in their
+ * wanted; a network stepped at rounded-up widths is described at those), the data gradient as 1: 192x192 tiles by two workgroups each, GLU backward of the layer below in their
  * epilogue; 2: 256x128 tiles with that epilogue; 3 / 4: data_runs planes of sums in 128x128 / 256x128 tiles; 5 / 6: the
  * gradient of the layer below's output in 128x128 / 256x128 tiles.  weight_tile: 0: 128x128, 1: 256x128, 2: 192x192,
  * 3: 256x256, its reduction in weight_runs runs.  For tests and tuning; launches nothing. */
 int w2l_train_step_launch_config(const w2l_layer *layers, int n_layers, int B, int T, int dtype, int layer,
                                  int *data_form, int *data_runs, int *weight_tile, int *weight_runs);
+/* Host-only query: the channels with which both train steps compute a layer (cin and cout themselves, or those of a bf16
+ * network stepped at rounded-up widths: see above) and whether its weight gradient runs on the helper stream (1) if the
+ * layer's bias gradient is wanted.  For tests and tuning; launches nothing. */
+int w2l_train_step_layer_config(const w2l_layer *layers, int n_layers, int B, int T, int dtype, int layer,
+                                int *cin, int *cout, int *helper);
 
 /* ---- measurement aid (not part of the training path) -----------------------------------
  * Launches `blocks` workgroups of 4 wavefronts, each wavefront issuing 8*iters independent

@@ -25,7 +25,7 @@ __all__ = [
     "w2l_ctc_check_targets_host", "w2l_ctc_launch_config", "w2l_asg_launch_config", "w2l_asg_workspace_bytes", "w2l_asg_fwd_bwd", "w2l_asg_check_targets_host",
     "w2l_logmel_num_frames", "w2l_logmel_fwd",
     "w2l_train_step_workspace_bytes", "w2l_train_step", "w2l_train_step_asg_workspace_bytes", "w2l_train_step_asg",
-    "w2l_train_step_launch_config", "w2l_sgd_momentum_step",
+    "w2l_train_step_launch_config", "w2l_train_step_layer_config", "w2l_sgd_momentum_step",
     "w2l_probe_mfma", "raw",
     "workspace",
 ]
@@ -85,6 +85,7 @@ def _load():
         "w2l_train_step": (i, [C.POINTER(w2l_layer), i, C.POINTER(vp), C.POINTER(vp), C.POINTER(vp),
                                C.POINTER(vp), vp, vp, vp, vp, vp, vp, i, i, i, i, i, f, vp, sz, vp]),
         "w2l_train_step_launch_config": (i, [C.POINTER(w2l_layer), i, i, i, i, i] + [C.POINTER(C.c_int)] * 4),
+        "w2l_train_step_layer_config": (i, [C.POINTER(w2l_layer), i, i, i, i, i] + [C.POINTER(C.c_int)] * 3),
         "w2l_train_step_asg_workspace_bytes": (sz, [C.POINTER(w2l_layer), i, i, i, i, i]),
         "w2l_train_step_asg": (i, [C.POINTER(w2l_layer), i, C.POINTER(vp), C.POINTER(vp), C.POINTER(vp),
                                    C.POINTER(vp), vp, vp, vp, vp, vp, vp, vp, vp, i, i, i, i, f, vp, sz, vp]),
@@ -353,6 +354,14 @@ def w2l_train_step_launch_config(layers, B, T, dtype, layer):
     out = [C.c_int() for _ in range(4)]
     _check(raw.w2l_train_step_launch_config(_layer_array(layers), len(layers), B, T, dtype, layer, *[C.byref(o) for o in out]),
            "w2l_train_step_launch_config")
+    return tuple(o.value for o in out)
+
+
+def w2l_train_step_layer_config(layers, B, T, dtype, layer):
+    """(cin, cout, helper stream) with which a train step computes a layer; host only."""
+    out = [C.c_int() for _ in range(3)]
+    _check(raw.w2l_train_step_layer_config(_layer_array(layers), len(layers), B, T, dtype, layer, *[C.byref(o) for o in out]),
+           "w2l_train_step_layer_config")
     return tuple(o.value for o in out)
 
 

@@ -49,7 +49,7 @@ namespace w2l {
 
 bool conv_fwd_is_generic(const ConvDesc& d, int dt) { return !(dt == W2L_BF16 && conv_fwd_mfma_ok(d)); }
 bool conv_dgrad_is_generic(const ConvDesc& d, int dt, int dydt) { return !(dt == W2L_BF16 && dydt == W2L_BF16 && conv_dgrad_mfma_ok(d)); }
-static bool wgrad_is_generic(const ConvDesc& d, int dt, int dydt)
+bool conv_wgrad_is_generic(const ConvDesc& d, int dt, int dydt)
 {
     return d.Cout > 32 && !(dt == W2L_BF16 && dydt == W2L_BF16 && conv_wgrad_mfma_ok(d));
 }
@@ -94,14 +94,14 @@ size_t conv_wgrad_scratch_bytes(const ConvDesc& d, int dt, int dydt, Runs runs)
 {
     const size_t rest = d.Cout <= 32                    ? conv_wgrad_skinny_scratch(d.Cin, d.Cout, d.k)
                         : runs == Runs::WHOLE           ? 0
-                        : wgrad_is_generic(d, dt, dydt) ? conv_wgrad_generic_scratch(d, dt, runs == Runs::ALONE)
+                        : conv_wgrad_is_generic(d, dt, dydt) ? conv_wgrad_generic_scratch(d, dt, runs == Runs::ALONE)
                                                         : conv_wgrad_mfma_scratch(d);
     return wgrad_dbias_scratch(d) + rest;
 }
 
 bool conv_wgrad_fuses_dbias(const ConvDesc& d, int dt, int dydt)
 {
-    return d.Cout <= 32 || wgrad_is_generic(d, dt, dydt) ||
+    return d.Cout <= 32 || conv_wgrad_is_generic(d, dt, dydt) ||
            (dt == W2L_BF16 && dydt == W2L_BF16 && conv_wgrad_mfma_takes_dbias(d));
 }
 
@@ -111,7 +111,7 @@ int conv_wgrad(const ConvDesc& d, const void* x, const void* dy, float* dw, floa
     float* dbias_scratch = static_cast<float*>(scratch);
     unsigned char* rest = static_cast<unsigned char*>(scratch) + wgrad_dbias_scratch(d);
     const size_t rest_bytes = runs != Runs::WHOLE && scratch_bytes > wgrad_dbias_scratch(d) ? scratch_bytes - wgrad_dbias_scratch(d) : 0;
-    if (wgrad_is_generic(d, dt, dydt))
+    if (conv_wgrad_is_generic(d, dt, dydt))
         return conv_wgrad_generic(d, x, dy, dw, dbias, dt, dydt, accumulate, st, rest, rest_bytes, runs == Runs::ALONE);
     if (d.Cout <= 32) return conv_wgrad_skinny(d, x, dy, dw, dbias, dt, dydt, accumulate, reinterpret_cast<float*>(rest), st);
     if (dbias && conv_wgrad_fuses_dbias(d, dt, dydt)) return conv_wgrad_mfma(d, x, dy, dw, dbias, accumulate, st, rest, rest_bytes);
@@ -379,7 +379,7 @@ static int launch_form(int pass, int B, int T, int Cin, int Cout, int k, int str
     }
     if (pass != 2) return W2L_ERR_SHAPE;
     if (Cout <= 32) { *form = ConvForm{CONV_NARROW, SKINNY_CHUNKS, 0, 0}; return W2L_OK; }
-    if (!wgrad_is_generic(d, dtype, dtype)) return W2L_OK;
+    if (!conv_wgrad_is_generic(d, dtype, dtype)) return W2L_OK;
     if (stage_wgrad_f32(Cin, Cout, k, stride, dtype)) { staged_x(d); staged_y(d); }
     return conv_wgrad_generic_form(d, dtype, form);
 }

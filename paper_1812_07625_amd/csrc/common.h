@@ -113,6 +113,7 @@ inline bool fold_stride(const ConvDesc& d, ConvDesc& f)
 // gradient conv_dgrad_scratch_bytes(d); given it, shapes that would leave CUs idle split their reduction
 bool conv_fwd_is_generic(const ConvDesc& d, int dt);
 bool conv_dgrad_is_generic(const ConvDesc& d, int dt, int dydt);
+bool conv_wgrad_is_generic(const ConvDesc& d, int dt, int dydt);  // (narrow outputs: conv_wgrad_skinny, not generic)
 int conv_fwd(const ConvDesc& d, const void* x, const void* w, const float* bias, void* y, int dt, int ydt,
              hipStream_t st, void* scratch = nullptr, size_t scratch_bytes = 0);
 int conv_dgrad(const ConvDesc& d, const void* dy, const void* w, void* dx, int dt, int dydt, hipStream_t st,

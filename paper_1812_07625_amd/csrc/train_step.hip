@@ -93,6 +93,11 @@ ConvDesc layer_bwd_desc(const Plan& p, const w2l_layer* L, int B, int i)
     if (L[i].glu) { d.y_pitch = p.Tout[i] + 2 * HALO; d.y_halo = HALO; d.slack = SLACK; }
     return d;
 }
+// whether the last layer's data gradient and the GLU backward below it share a launch (class_bwd_glu)
+bool class_layer_fused(const Plan& p, const w2l_layer* L, int B, int i, int dtype)
+{
+    return L[i].k == 1 && L[i].stride == 1 && L[i - 1].glu && class_bwd_glu_ok(B, p.Tin[i] + 2 * HALO, SLACK_ZERO, L[i].cout, L[i].cin, dtype);
+}
 // A strided bf16 first layer whose weight gradient runs over folded frames, x copied into the haloed layout of its dy: f, its
 // geometry.  Only where the matrix kernels take that: the others know nothing of a folded row's end (w_cols).
 bool folded_first(const Plan& p, const w2l_layer* L, int n, int B, int dtype, ConvDesc& f)
@@ -167,8 +172,7 @@ Plan make_plan(const w2l_layer* L, const w2l_layer* real, int n, int B, int T, i
         // sums of split reductions: the geometries that the step's passes will have
         const ConvDesc fd = layer_desc(p, L, B, i), bd = layer_bwd_desc(p, L, B, i);
         p.part_bytes = max_of(p.part_bytes, l.glu ? planes_bytes(conv_fwd_parts(fd, dtype), (size_t)B * to * l.cout) : conv_fwd_scratch(fd, dtype));
-        if (i > 0 && i == n - 1)
-            p.cls_glu = l.k == 1 && l.stride == 1 && L[i - 1].glu && class_bwd_glu_ok(B, t + 2 * HALO, SLACK_ZERO, l.cout, l.cin, dtype);
+        if (i > 0 && i == n - 1) p.cls_glu = class_layer_fused(p, L, B, i, dtype);
         if (i > 0 && !p.cls_glu) {
             const int dydt = i == n - 1 ? W2L_F32 : dtype;
             p.part_bytes = max_of(p.part_bytes, L[i - 1].glu ? planes_bytes(conv_dgrad_parts(bd, dtype, dydt), (size_t)B * t * l.cin)
@@ -234,15 +238,22 @@ Plan make_plan(const w2l_layer* L, const w2l_layer* real, int n, int B, int T, i
 // ---- widths that the matrix kernels do not take --------------------------------------
 // The bf16 kernels want whole blocks of 64 output channels for a data gradient and whole chunks of 8 input channels for
 // any pass; a network of other widths ran its passes on the fp32 matrix instruction, a sixteenth of the rate.  Such a
-// network is stepped as one of wider layers: every gated layer's halves are rounded up, the weights and biases copied
+// network is stepped as one of wider layers: the halves of those gated layers are rounded up, the weights and biases copied
 // with zeros in the new places, and the gradients of the real ones copied out at the end.  Behind every GLU and every GLU
 // backward the new channels hold zeros (written as such: 0 times an infinity of a real channel is none), so the real ones'
 // sums gain zeros and nothing else.
-// Steps, us, k = 7, four body layers, 4 x 800 frames at stride 2: width 512 284; 496 520 -> 302; 500 1024 -> 306;
-// 8 x 1200, k = 11, width 404 2299 -> 493.  The two copying launches and their host calls are about 15 us: 2 x 200 frames
-// of width 144 (0.22 GFLOP) 157 -> 133, 1 x 100 of width 240 (0.16, and too few frames for the kernels) 166 -> 170, of 132
-// (0.03) 117 -> 133.
-constexpr double WIDEN_FLOPS = 2e8;
+// Steps, us, k = 7, four layers, 16 x 1600 frames at stride 2: width 40 527 -> 318, 100 559 -> 248, 240 548 -> 300, 500 3853 -> 418,
+// 1000 11649 -> 1047; 4 x 800: 40 204 -> 181, 100 230 -> 189, 240 270 -> 198, 500 785 -> 242, 1000 1526 -> 349.
+// It is done where the passes that leave the kernels for any shape save more than the two copying launches, their host calls
+// and the larger tensors take: 6 us a pass (9 a data gradient) and 15 a GFLOP against 17 us and some room for the error of
+// these, from 600 networks of 1 .. 7 layers and widths of 8 .. 1300 (three of which it makes slower, by 2, 3 and 7 %).  Below it:
+// two layers of width 100, 4 x 800 frames, 87 -> 91; widths 24 and three of 512, 8 x 1200, 320 -> 326; four of 64 and one of
+// 200, 4 x 800, 212 -> 216; tensors beyond the kernels' 32-bit offsets.  Networks with halves below 64 are quick on the other
+// kernels, where their data gradients stay (four of width 24, 16 x 1600, 240 -> 318; of 32, k = 13, 284 -> 358; seven of 36,
+// 10 x 141, 277 -> 309), so they may take 2.7 times the products (four of 36: 2.57, 570 -> 385; the three named: 5.1, 3.1, 2.8).
+// And below 0.2 GFLOP the copies cost more than they give: 1 x 100 frames of width 240 (and too few frames for the kernels)
+// 166 -> 170, of 132 (0.03) 117 -> 133.
+constexpr double WIDEN_FLOPS = 2e8, WIDEN_PASS = 6.0, WIDEN_DGRAD = 9.0, WIDEN_FLOP = 15e-9, WIDEN_COST = 24.0, WIDEN_MOST = 2.7;
 constexpr long long WIDEN_FRAMES = 128;  // what the matrix kernels ask for (conv_fwd_mfma_ok, conv_dgrad_mfma_ok)
 struct Widened {
     std::vector<w2l_layer> L;                // empty: nothing to widen
@@ -257,6 +268,28 @@ int wide_half(int h)
 {
     const int a = (h + 31) / 32 * 32, b = (h + 63) / 64 * 64;
     return b * 7 <= a * 8 ? b : a;
+}
+// a bf16 step's products, and what its passes on the kernels for any shape count for (us)
+struct StepWork { double flops = 0, any = 0; };
+StepWork step_work(const w2l_layer* L, const w2l_layer* real, int n, int B, int T)
+{
+    StepWork v;
+    Plan p;
+    for (int i = 0, t = T; i < n; ++i) {
+        p.Tin.push_back(t);
+        p.Tout.push_back(t = out_len(t, L[i].stride));
+        p.live.push_back(L[i].glu ? real[i].cout / 2 : 0);
+        const double f = 2.0 * B * t * L[i].k * L[i].cin * L[i].cout;
+        auto add = [&](bool any, double pass) { v.flops += f; v.any += any ? pass + WIDEN_FLOP * f : 0; };
+        const ConvDesc d = layer_desc(p, L, B, i), b = layer_bwd_desc(p, L, B, i);
+        const bool last = i == n - 1;
+        add(conv_fwd_is_generic(d, W2L_BF16), WIDEN_PASS);
+        add(conv_wgrad_is_generic(b, W2L_BF16, last ? W2L_F32 : W2L_BF16), WIDEN_PASS);
+        if (i == 0) continue;
+        add(last ? !class_layer_fused(p, L, B, i, W2L_BF16) && !dgrad_prep(B, p.Tin[i], real[i].cin, L[i].cout, L[i].k, L[i].stride, W2L_BF16).ok
+                 : conv_dgrad_is_generic(b, W2L_BF16, W2L_BF16), WIDEN_DGRAD);
+    }
+    return v;
 }
 Widened widen(const w2l_layer* L, int n, int B, int T, int dtype)
 {
@@ -275,11 +308,16 @@ Widened widen(const w2l_layer* L, int n, int B, int T, int dtype)
         flops += 6.0 * B * t * l.k * l.cin * l.cout;
     }
     if (!wanted || flops < WIDEN_FLOPS || (long long)B * t < WIDEN_FRAMES || L[0].cin % 4) return v;
-    v.L.assign(L, L + n);
+    std::vector<w2l_layer> wide(L, L + n);
+    bool narrow = false;
     for (int i = 0; i < n - 1; ++i) {
-        v.L[i].cout = 2 * wide_half(L[i].cout / 2);
-        v.L[i + 1].cin = v.L[i].cout / 2;
+        if (L[i].cout % 64) wide[i].cout = 2 * wide_half(L[i].cout / 2);
+        wide[i + 1].cin = wide[i].cout / 2;
+        narrow = narrow || wide[i].cout < 128;
     }
+    const StepWork now = step_work(L, L, n, B, T), then = step_work(wide.data(), L, n, B, T);
+    if ((narrow && then.flops > WIDEN_MOST * now.flops) || now.any - then.any < WIDEN_COST) return v;
+    v.L = wide;
     for (int i = 0; i < n; ++i) {
         const w2l_layer& l = v.L[i];
         v.changed.push_back(l.cout != L[i].cout || l.cin != L[i].cin);
@@ -432,6 +470,20 @@ extern "C" int w2l_train_step_launch_config(const w2l_layer* layers, int n_layer
     *data_runs = b.ok ? b.dparts : 0;
     *weight_tile = b.ok ? b.wtile : 0;
     *weight_runs = b.ok ? b.wsplits : 0;
+    return W2L_OK;
+}
+
+extern "C" int w2l_train_step_layer_config(const w2l_layer* layers, int n_layers, int B, int T, int dtype, int layer, int* cin, int* cout, int* helper)
+{
+    if (!layers || !cin || !cout || !helper) return W2L_ERR_NULL;
+    const Widened v = widen(layers, n_layers, B, T, dtype);
+    const w2l_layer* const L = v.any() ? v.L.data() : layers;
+    const Plan p = make_plan(L, layers, n_layers, B, T, 1, dtype, CRIT_CTC);
+    if (p.status) return p.status;
+    if (layer < 0 || layer >= n_layers) return W2L_ERR_SHAPE;
+    *cin = L[layer].cin;
+    *cout = L[layer].cout;
+    *helper = !p.bwd[layer].ok && !main_wgrad(p, L[layer], layer, B);
     return W2L_OK;
 }
 

@@ -94,3 +94,52 @@ def test_strides_fold_only_for_the_matrix_kernels():
     which the other kernels cannot read."""
     copies = lambda T: P.w2l_conv1d_bwd_weight_workspace_bytes(64, T, 512, 64, 5, 2, P.W2L_BF16) > 64 * T * 512 * 2
     assert copies(8000) and not copies(40000)
+
+
+def _net(widths, k, feat=40, classes=29, stride=2, head=None):
+    layers = [dict(k=k, stride=stride if i == 0 else 1, cin=c, cout=w, glu=1) for i, (c, w) in enumerate(zip([feat] + [w // 2 for w in widths[:-1]], widths))]
+    if head:
+        layers.append(dict(k=1, stride=1, cin=widths[-1] // 2, cout=head, glu=1))
+    return layers + [dict(k=1, stride=1, cin=(head or widths[-1]) // 2, cout=classes, glu=0)]
+
+
+def _widths(layers, B, T, dtype=P.W2L_BF16):
+    got = [P.w2l_train_step_layer_config(layers, B, T, dtype, i) for i in range(len(layers))]
+    for i in range(1, len(layers)):
+        assert got[i][0] == got[i - 1][1] // 2
+    assert got[0][0] == layers[0]["cin"] and got[-1][1] == layers[-1]["cout"]
+    return [g[1] for g in got[:-1]]
+
+
+@pytest.mark.parametrize("layers, B, T, widths", [
+    (_net([500] * 4, 7), 4, 800, [512] * 4),
+    (_net([210, 250], 5), 3, 260, [256, 256]),
+    (_net([496, 240, 332], 3, 80), 4, 800, [512, 256, 384]),
+    (_net([40] * 4, 7), 16, 1600, [64] * 4),                  # 2.2 times the products
+    (_net([66] * 4, 7), 4, 800, [128] * 4),                   # 3.4 times, all halves 64
+    (_net([448] * 4, 7, head=1000), 4, 800, [448] * 4 + [1024]),  # layers on the blocks keep their widths
+    (_net([500] * 4, 7, classes=100), 4, 800, [512] * 4),
+    (_net([240] * 4, 7), 2, 200, [256] * 4),                  # (data gradients only)
+    # as they are: on the blocks; features of no whole four; nothing gained; narrow; few products; few frames
+    (_net([512] * 4, 7), 4, 800, [512] * 4),
+    (_net([500] * 4, 7, feat=42), 4, 800, [500] * 4),
+    (_net([64] * 4, 7, head=200), 4, 800, [64] * 4 + [200]),
+    (_net([496], 7), 16, 1600, [496]),
+    (_net([24] * 4, 7), 16, 1600, [24] * 4),
+    (_net([32] * 4, 13), 16, 1600, [32] * 4),
+    (_net([140] * 4, 5), 1, 280, [140] * 4),
+    (_net([500] * 4, 7), 1, 254, [500] * 4),
+    # tensors beyond the matrix kernels' 32-bit offsets, at the wide width and at both
+    (_net([1100] * 4, 5, stride=1), 64, 18000, [1100] * 4),
+    (_net([1000] * 4, 5, stride=1), 64, 16600, [1000] * 4),
+], ids=str)
+def test_networks_stepped_at_rounded_up_widths(layers, B, T, widths):
+    """bf16 networks off the matrix kernels' blocks are stepped at wider widths where that moves enough work to those
+    kernels, and only there; fp32 ones, and networks with a layer without GLU, never."""
+    assert _widths(layers, B, T) == widths
+    assert _widths(layers, B, T, F32) == [l["cout"] for l in layers[:-1]]
+    if len(layers) > 3:
+        plain = [dict(l) for l in layers]
+        plain[1].update(glu=0, cout=plain[1]["cout"] // 2)
+        got = [P.w2l_train_step_layer_config(plain, B, T, P.W2L_BF16, i)[:2] for i in range(len(plain))]
+        assert got == [(l["cin"], l["cout"]) for l in plain]
