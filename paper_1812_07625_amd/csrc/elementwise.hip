@@ -293,7 +293,7 @@ __global__ __launch_bounds__(256) void finish_glu_bwd_k(const float* __restrict_
 // the same for the frames' threads) for 16 or 32 multiply-adds.  As four launches (dz cast and padded, w padded, matrix
 // product, GLU) it took 20 us for 4 x 619 frames of 512 channels, 30 for 16 x 800; now 9
 // and 19 (the last: 10 for the bytes, 6 for the products, which a chip full of workgroups that started together takes in
-// turn).
+// turn).  (What it costs at 8 to 64 classes: class_bwd_glu_ok.)
 template <typename T, int V, int CS>  // CS channel groups of V channels (16 bytes) and 256 / CS groups of four frames
 __global__ __launch_bounds__(256) void class_bwd_glu_k(const float* __restrict__ dz, const T* __restrict__ w, const T* __restrict__ y,
                                                        T* __restrict__ dy, unsigned out_rows, int H, int C, RowMap map)
@@ -752,10 +752,16 @@ int finish_glu_bwd(const float* part, int parts, const void* y, void* dy, int B,
 #undef W2L_FIN
     return launch_status();
 }
-// 64 classes: their products take about twice as long as the bytes; beyond, the matrix kernels (conv_dgrad) are for it
+// Up to 64 classes; beyond, the matrix kernels (conv_dgrad) are for it.  Steps of a network of one 1x1 layer, us, as launches of
+// their own and as one, 200 / 1600 / 12800 frames: bf16, H = 256, 8 classes 82 -> 74, 98 -> 90, 205 -> 189; 64 classes 78 -> 77, 91 -> 90,
+// 207 -> 197; H = 2048 82 -> 81, 135 -> 132, 429 -> 417.  fp32, H = 256, 48 classes 64 -> 64, 86 -> 85, 184 -> 175; 64 classes 64 -> 65,
+// 85 -> 87, 183 -> 180; H = 1024 64 -> 65, 104 -> 102, 350 -> 321; H = 64, 51200 frames 431 -> 442: of fp32, beyond 48 classes, only
+// where there is enough of dh.
 bool class_bwd_glu_ok(int B, int pitch, int slack, int C, int H, int dtype)
 {
-    return C <= 64 && H % (dtype == W2L_BF16 ? 8 : 4) == 0 && (long long)B * pitch + slack < (1LL << 31);
+    const bool bf16 = dtype == W2L_BF16;
+    const long long rows = (long long)B * pitch;
+    return C <= 64 && (bf16 || C <= 48 || (H >= 128 && rows * H >= 1 << 20)) && H % (bf16 ? 8 : 4) == 0 && rows + slack < (1LL << 31);
 }
 int class_bwd_glu(const float* dz, const void* w, const void* y, void* dy, int B, int Tp, int C, int H, int dtype, int pitch, int halo, int slack,
                   hipStream_t st, int live)

@@ -89,6 +89,15 @@ def test_class_layer_backward(P, classes, H, dtype, misaligned):
     check_train_step(run_train_step(Shifted() if misaligned else P, cfg), oracle_train_step(cfg), dtype)
 
 
+@pytest.mark.parametrize("classes, H, frames", [(64, 132, 2650), (49, 128, 2750), (64, 132, 2400), (64, 124, 2750)])
+def test_many_classes_fp32(P, classes, H, frames):
+    """fp32 networks of 49 .. 64 classes on either side of 2^20 values of dh and of 128 channels: one launch, or launches of
+    their own, through the class layer.  Bounds: a whole step's."""
+    layers = [dict(k=1, stride=1, cin=16, cout=2 * H, glu=1), dict(k=1, stride=1, cin=H, cout=classes, glu=0)]
+    cfg = W.small_model(110 + H, 3, frames - 11, frames, 16, layers, False, 2, 8)
+    check_train_step(run_train_step(P, cfg), oracle_train_step(cfg), "f32")
+
+
 @pytest.mark.parametrize("widths, k, stride, feat, frames", [
     ((210, 250), 5, 2, 40, 260),              # halves of 105 and 125: no multiple of anything
     ((496, 240, 332), 3, 1, 80, 131),         # whole chunks, no whole blocks; a half of 2 mod 4 (gradients copied one by one)
