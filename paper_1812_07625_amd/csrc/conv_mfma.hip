@@ -288,7 +288,7 @@ struct Core {
         }
     }
     // Ping-pong form: a wavefront first reads all its fragments of a panel, then
-    // multiplies them; the two groups do this in opposite phases (see run_pingpong).
+    // multiplies them; the two groups do this in opposite phases (see run_pingpong).  kg: its sub-steps of a panel.
     __device__ __forceinline__ void read_panel(const unsigned char* la, const unsigned char* lb, int kg, int wm, int wn,
                                                int lane, int arow = 0)
     {
@@ -523,9 +523,9 @@ __device__ __forceinline__ void run_pipeline(CoreT& core, unsigned char* lds, in
     wait_vmcnt<0>();  // the trailing panels must land before LDS is reused or released
 }
 
-// Ping-pong schedule for two groups of wavefronts.  Time is cut into phases with one
+// Ping-pong schedule for two groups of wavefronts that own columns of the tile each.  Time is cut into phases with one
 // workgroup barrier between consecutive phases.  In a "read" phase R(st) a wavefront starts its
-// share of the loads of panel st+2, reads all its fragments of panel st from LDS and waits for
+// share of the loads of panel st+3, reads all its fragments of panel st from LDS and waits for
 // its loads of panel st+1; in a "multiply" phase M(st) it only issues the MFMAs of panel st.
 //     phase:    0      1      2      3      4    ...
 //     group 0:  R(0)   M(0)   R(1)   M(1)   R(2) ...
@@ -537,13 +537,12 @@ __device__ __forceinline__ void run_pipeline(CoreT& core, unsigned char* lds, in
 // every barrier.  Panel st is read in phases 2st and 2st+1; its ring slot is written again by
 // loads issued in phase 2st+2 or later, and panel st+1 has landed (every wavefront waited for
 // its own share at the end of a read phase no later than phase 2st+1) before phase 2st+2.
-// grp = the group's phase offset (0 or 1); kg = which sub-steps of a panel the wavefront
-// multiplies.  With a ring of STAGES slots the loads of panel st+STAGES-1 start in R(st).
+// grp = the group's phase offset (0 or 1).  The loads of panel st+3 start in R(st) (a ring of four slots).
 template <int STAGES, int NL, int STAGE_BYTES, int A_BYTES, class CoreT, class Issue>
-__device__ __forceinline__ void run_pingpong(CoreT& core, unsigned char* lds, int nsteps, Issue issue, int grp, int kg,
-                                             int wm, int wn, int lane)
+__device__ __forceinline__ void run_pingpong(CoreT& core, unsigned char* lds, int nsteps, Issue issue, int grp, int wm, int wn,
+                                             int lane)
 {
-    static_assert(STAGES == 3 || STAGES == 4, "ring depth");
+    static_assert(STAGES == 4 && CoreT::COLUMN_GROUPS, "the 256x256 tile's ring");
     static_assert((STAGES - 2) * NL < 64, "loads in flight must fit the vmcnt counter");
     const unsigned lds0 = (unsigned)(size_t)(lds_byte*)lds;
 #pragma unroll
@@ -567,7 +566,7 @@ __device__ __forceinline__ void run_pingpong(CoreT& core, unsigned char* lds, in
         // ---- R(st)
 #pragma unroll
         for (int i = 0; i < NL; ++i) issue(i, st + STAGES - 1, dst);
-        core.read_panel(cur, cur + A_BYTES, kg, wm, wn, lane);
+        core.read_panel(cur, cur + A_BYTES, 0, wm, wn, lane);
         wait_vmcnt<(STAGES - 2) * NL>();                    // this wavefront's share of panel st+1 has landed
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // and its reads of panel st are done
         __builtin_amdgcn_s_barrier();
@@ -589,14 +588,14 @@ __device__ __forceinline__ void run_pingpong(CoreT& core, unsigned char* lds, in
 // that LDS is what they wait for (128x128: 768 of about 1300 cycles a panel in ping-pong), and phases that wait for each
 // other's barriers add to that; with the reads between the multiplications and one barrier a panel, us a pass before and
 // after: shared launch of both gradients, 4 x 619 frames, k = 11, 256 -> 512 29.2 and 26.5 (its step 532 and 515), layer of
-// 16 x 800 frames, k = 11, 512 -> 1024 472 and 467, step of the 10M network, 16 x 1600 993 and 983, no shape slower.  The
+// 16 x 800 frames, k = 11, 512 -> 1024 472 and 467, step of the 10M network, 16 x 1600 993 and 983.  The
 // groups of a 256x256 tile, with columns of their own, keep the phases (without: 105M step 3367 and 3389..3425).
 template <int STAGES, int GROUPS, int NL, int STAGE_BYTES, int A_BYTES, class CoreT, class Issue>
 __device__ __forceinline__ void run_ring(CoreT& core, unsigned char* lds, int nsteps, Issue issue, int grp, int kg, int wm,
                                          int wn, int lane)
 {
     if constexpr (GROUPS == 2 && CoreT::COLUMN_GROUPS) {
-        run_pingpong<STAGES, NL, STAGE_BYTES, A_BYTES>(core, lds, nsteps, issue, grp, kg, wm, wn, lane);
+        run_pingpong<STAGES, NL, STAGE_BYTES, A_BYTES>(core, lds, nsteps, issue, grp, wm, wn, lane);
     } else {
         run_pipeline<STAGES, NL, STAGE_BYTES, A_BYTES>(core, lds, nsteps, issue, kg, wm, wn, lane);
     }
@@ -1495,12 +1494,16 @@ bool slab_ok(const ConvDesc& d, int bm, int srows, int C, int frames, int pitch,
 // A problem whose tiles do not fill the 256 CUs (each holds one workgroup of these kernels) lasts as long as one tile's
 // reduction whatever the idle CUs could do, so the reduction is cut into runs of panels: a workgroup per tile and run,
 // a plane of fp32 sums per run, and the pass that reads the result next adds the planes up in order (finish_*).
-// Times in us, on which the choice of tile and cut rests, from kernel traces of 1000 .. 12800 frames, 64 .. 2048 channels:
-//   64 steps of the reduction on one CU 0.55 (128 x 128), 0.80 (256 x 128), 0.88 (192 x 192), 1.50 (256 x 256);
+// Times in us, on which the choice of tile and cut rests, fitted together on kernel traces of 1000 .. 12800 frames, 64 .. 2048
+// channels, when tiles whose groups share a panel still worked in phases (see run_ring):
+//   64 steps of the reduction on one CU 0.55 (128 x 128; alone it now takes 0.47), 0.80 (256 x 128), 0.88 (192 x 192), 1.50 (256 x 256);
 //   a workgroup's first panels and its way out 4; the sums' way to memory and back 4 TB/s;
 //   a finishing pass of its own with its launch 6, where a GLU pass does it about as long as that takes anyway.
 // 16 x 800 frames, k = 11, 256 -> 512, weight gradient beside the data gradient 121 -> 93 us (46 tiles of 256 x 128, five
 // runs, instead of 92 of 128 x 128), 1x1 256 -> 1024 121 -> 46 us; 4 x 619 frames, data gradient 53 -> 32 us.
+// They are costs of a plan, no longer a kernel's times one by one: with 0.47 in place of 0.55 alone, other tiles are chosen and the
+// 10M network's step of 16 x 1600 frames takes 1051 us instead of 977; with a finishing pass of 3 instead of 6, single
+// layers are 5 to 12 % quicker and others 6 % slower.
 constexpr double FINISH_OWN = 6.0, FINISH_FREE = 0.5, GLU_PASS = 5.0;
 double tile_us(int bm, int bn)
 {
