@@ -71,14 +71,14 @@ def test_bias_gradients_not_wanted(P):
 @pytest.mark.parametrize("misaligned", [False, True])
 def test_class_layer_backward(P, classes, H, dtype, misaligned):
     """The gradient through the classes' layer into the layer below: one launch up to 64 classes of whole 16-byte groups
-    of channels, over blocks of 32 and 64 frames that end in the middle, also where the weights lie off a 16-byte
-    address (fp32 steps; the bf16 kernels of other passes read theirs in 16-byte pieces).  Bounds: a whole step's."""
-    if misaligned and dtype == "bf16":
-        pytest.skip("bf16 weights are read in 16-byte pieces")
+    of channels (fp32 of so few values: up to 48), over blocks of 32 and 64 frames that end in the middle, also where the
+    weights lie off a 16-byte address (bf16: over fewer frames than the matrix kernels take, whose forward pass reads them in
+    16-byte pieces).  Bounds: a whole step's."""
     layers = [dict(k=3, stride=1, cin=16, cout=2 * H, glu=1), dict(k=1, stride=1, cin=H, cout=classes, glu=0)]
-    cfg = W.small_model(100 + H, 3, 50, 61, 16, layers, dtype == "bf16", 2, 8)
+    T = 42 if misaligned and dtype == "bf16" else 61
+    cfg = W.small_model(100 + H, 3, T - 11, T, 16, layers, dtype == "bf16", 2, 8)
 
-    class Shifted:  # the binding, with the classes' weights 4 bytes behind where an allocation starts
+    class Shifted:  # the binding, with the classes' weights one element behind where an allocation starts
         def __getattr__(self, name): return getattr(P, name)
         def w2l_train_step(self, layers, w, *rest):
             import torch
@@ -106,11 +106,14 @@ def test_many_classes_fp32(P, classes, H, frames):
 ])
 def test_widths_off_the_matrix_blocks(P, widths, k, stride, feat, frames):
     """Networks whose layers are stepped with zeros in new channels give the oracle's outputs, loss and gradients; bounds of a
-    whole bf16 step.  Twice into one workspace, the second time after other bytes, and without some biases and their gradients."""
+    whole bf16 step.  Twice, the second time in a workspace full of other bytes and without some bias gradients."""
     cin = [feat] + [w // 2 for w in widths[:-1]]
     layers = [dict(k=k, stride=stride if i == 0 else 1, cin=c, cout=w, glu=1) for i, (c, w) in enumerate(zip(cin, widths))]
     layers += [dict(k=1, stride=1, cin=widths[-1] // 2, cout=29, glu=0)]
     cfg = W.small_model(130 + k, 3, frames - 30, frames, feat, layers, True, 5, 20)
+    wide = [P.w2l_train_step_layer_config(layers, 3, frames, P.W2L_BF16, i)[1] for i in range(len(layers))]
+    assert any(w % 64 for w in widths) and wide[-1] == 29
+    assert all(b % 64 == 0 and (b > a if a % 64 else b == a) for a, b in zip(widths, wide))
     plain = [dict(l) for l in layers]
     ref = oracle_train_step(cfg)
     check_train_step(run_train_step(P, cfg), ref, "bf16")
@@ -126,6 +129,156 @@ def test_widths_off_the_matrix_blocks(P, widths, k, stride, feat, frames):
         got["db"][i] = ref["db"][i]
     check_train_step(got, ref, "bf16")
     assert layers == plain
+
+
+def test_widths_off_the_matrix_blocks_many_classes(P):
+    """The same with more classes than the class layer's own launch takes (their gradient stays on the fp32 instruction)."""
+    layers = [dict(k=3, stride=1, cin=40, cout=250, glu=1), dict(k=3, stride=1, cin=125, cout=300, glu=1), dict(k=1, stride=1, cin=150, cout=100, glu=0)]
+    assert [P.w2l_train_step_layer_config(layers, 4, 200, P.W2L_BF16, i)[1] for i in range(3)] == [256, 320, 100]
+    cfg = W.small_model(180, 4, 160, 200, 40, layers, True, 5, 20)
+    check_train_step(run_train_step(P, cfg), oracle_train_step(cfg), "bf16")
+
+
+def _asg_step(P, layers, cfg, trans, targets, dtype):
+    import torch
+    from workloads.device import empty, to_dev, to_host
+    code = P.W2L_BF16 if dtype == "bf16" else P.W2L_F32
+    B, T, Lmax = cfg["B"], cfg["T"], targets.shape[1]
+    dw, db = [empty(a.shape) for a in cfg["weights"]], [empty(a.shape) for a in cfg["biases"]]
+    dtrans, loss, logits = empty(trans.shape), empty((B,)), empty((B, -(-T // layers[0]["stride"]), layers[-1]["cout"]))
+    P.w2l_train_step_asg(layers, [to_dev(a, dtype) for a in cfg["weights"]], [to_dev(a) for a in cfg["biases"]], dw, db, to_dev(cfg["x"], dtype),
+                         to_dev(cfg["in_len"]), to_dev(targets), to_dev(cfg["tgt_len"]), to_dev(trans), dtrans, loss, logits, 1.0,
+                         P.workspace(P.w2l_train_step_asg_workspace_bytes(layers, B, T, Lmax, code)))
+    torch.cuda.synchronize()
+    return dict(loss=to_host(loss), logits=to_host(logits), dw=[to_host(t) for t in dw], db=[to_host(t) for t in db]), to_host(dtrans)
+
+
+def test_widths_off_the_matrix_blocks_asg(P):
+    """The same with the ASG criterion, at a stride, whose frame counts its kernels divide themselves."""
+    import numpy as np
+    import oracle
+    from gpu_util import rel_l2
+    layers = [dict(k=5, stride=2, cin=40, cout=250, glu=1), dict(k=5, stride=1, cin=125, cout=300, glu=1), dict(k=1, stride=1, cin=150, cout=28, glu=0)]
+    assert [P.w2l_train_step_layer_config(layers, 4, 301, P.W2L_BF16, i)[1] for i in range(3)] == [256, 320, 28]
+    cfg = W.small_model(181, 4, 200, 301, 40, layers, True, 5, 20)
+    trans = (np.random.default_rng(182).standard_normal((28, 28)) * 0.5).astype(np.float32)
+    targets = (cfg["targets"] % 28).astype(np.int32)
+    got, dtrans = _asg_step(P, layers, cfg, trans, targets, "bf16")
+    f64 = lambda a: np.asarray(a, dtype=np.float64)
+    ref = oracle.train_step(layers, [f64(w) for w in cfg["weights"]], [f64(b) for b in cfg["biases"]], f64(cfg["x"]),
+                            cfg["in_len"], targets, cfg["tgt_len"], 1.0, trans=f64(trans))
+    check_train_step(got, ref, "bf16")
+    assert rel_l2(dtrans, ref["dtrans"]) <= 2e-2
+
+
+@pytest.mark.parametrize("what", ["weights", "gradients", "logits"])
+def test_widths_off_the_matrix_blocks_off_16_bytes(P, what):
+    """Tensors that a network stepped at rounded-up widths copies element by element where they lie off a 16-byte address (the
+    layers' weights and their gradients, at widths that are whole groups of four), and the logits, which are then written in the
+    workspace and copied: the bits are those of aligned tensors."""
+    import numpy as np
+    import torch
+    layers = [dict(k=5, stride=1, cin=40, cout=232, glu=1), dict(k=5, stride=1, cin=116, cout=232, glu=1), dict(k=1, stride=1, cin=116, cout=29, glu=0)]
+    assert [P.w2l_train_step_layer_config(layers, 3, 260, P.W2L_BF16, i)[1] for i in range(3)] == [256, 256, 29]
+    cfg = W.small_model(183, 3, 200, 260, 40, layers, True, 5, 20)
+
+    def off(t, copy):  # a tensor of t's shape one element behind where an allocation starts
+        room = torch.full((t.numel() + 1,), float("nan"), dtype=t.dtype, device=t.device)[1:].view(t.shape)
+        return room.copy_(t) if copy else room
+
+    class Off:
+        def __getattr__(self, name): return getattr(P, name)
+        def w2l_train_step(self, layers, w, b, dw, db, x, n, tg, tl, loss, logits, *rest):
+            w2 = [off(t, True) for t in w] if what == "weights" else w
+            dw2 = [off(t, False) for t in dw] if what == "gradients" else dw
+            z2 = off(logits, False) if what == "logits" else logits
+            P.w2l_train_step(layers, w2, b, dw2, db, x, n, tg, tl, loss, z2, *rest)
+            for a, c in zip(dw + [logits], dw2 + [z2]):
+                a.copy_(c)
+
+    got, ref = run_train_step(Off(), cfg), run_train_step(P, cfg)
+    for a, b in zip([got["loss"], got["logits"]] + got["dw"] + got["db"], [ref["loss"], ref["logits"]] + ref["dw"] + ref["db"]):
+        assert np.isfinite(b).all()
+        np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("aligned", [True, False])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_logits_where_the_caller_wants_them(P, dtype, aligned):
+    """Written in place, or (off a 16-byte address) copied: the oracle's, and nothing behind them."""
+    import torch
+    layers = [dict(k=3, stride=2, cin=40, cout=128, glu=1), dict(k=1, stride=1, cin=64, cout=29, glu=0)]
+    cfg = W.small_model(184, 3, 100, 131, 40, layers, dtype == "bf16", 3, 10)
+    room = torch.full((3 * 66 * 29 + 64,), -7.0, device="cuda:0")[0 if aligned else 1:]
+
+    class There:
+        def __getattr__(self, name): return getattr(P, name)
+        def w2l_train_step(self, layers, w, b, dw, db, x, n, tg, tl, loss, logits, *rest):
+            z = room[:logits.numel()].view(logits.shape)
+            P.w2l_train_step(layers, w, b, dw, db, x, n, tg, tl, loss, z, *rest)
+            logits.copy_(z)
+
+    check_train_step(run_train_step(There(), cfg), oracle_train_step(cfg), dtype)
+    assert (room[3 * 66 * 29:] == -7.0).all()
+
+
+def _helpers(P, layers, B, T, dtype):
+    """which weight gradients run on the helper stream, and which layers share a launch for both"""
+    code = P.W2L_BF16 if dtype == "bf16" else P.W2L_F32
+    n = range(len(layers))
+    return ([P.w2l_train_step_layer_config(layers, B, T, code, i)[2] for i in n], [int(P.w2l_train_step_launch_config(layers, B, T, code, i)[0] > 0) for i in n])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_two_streams_layers_without_glu(P, dtype):
+    """Layers without a GLU, whose dh is their dy, beside weight gradients on the helper stream: the data gradients wait before
+    they overwrite a buffer that such a weight gradient still reads."""
+    import numpy as np
+    layers = [dict(k=5, stride=2, cin=40, cout=64, glu=0), dict(k=3, stride=1, cin=64, cout=96, glu=1),
+              dict(k=3, stride=1, cin=48, cout=256, glu=0), dict(k=11, stride=1, cin=256, cout=256, glu=0),
+              dict(k=5, stride=1, cin=256, cout=256, glu=0), dict(k=3, stride=1, cin=256, cout=64, glu=1),
+              dict(k=1, stride=1, cin=32, cout=29, glu=0)]
+    assert _helpers(P, layers, 4, 233, dtype)[0] == [0, 1, 1, 1, 1, 1, 0]
+    cfg = W.small_model(185, 4, 150, 233, 40, layers, dtype == "bf16", 5, 30)
+    ref = oracle_train_step(cfg)
+    a, b = run_train_step(P, cfg), run_train_step(P, cfg)
+    check_train_step(a, ref, dtype)
+    for u, v in zip(a["dw"] + a["db"], b["dw"] + b["db"]):
+        assert np.array_equal(u, v)
+
+
+def test_two_streams_beside_shared_launches(P):
+    """A strided layer's long weight gradient on the helper stream between layers that share a launch for both gradients, and
+    those on the helper stream too where their bias gradients are not wanted."""
+    import numpy as np
+    body = dict(k=5, stride=1, cin=128, cout=256, glu=1)
+    layers = [dict(k=5, stride=2, cin=40, cout=256, glu=1), body, dict(k=9, stride=2, cin=128, cout=512, glu=1),
+              dict(k=5, stride=1, cin=256, cout=256, glu=1), body, dict(k=1, stride=1, cin=128, cout=29, glu=0)]
+    assert _helpers(P, layers, 4, 301, "bf16") == ([0, 0, 1, 0, 0, 0], [0, 1, 0, 1, 1, 0])
+    cfg = W.small_model(186, 4, 220, 301, 40, layers, True, 4, 20)
+    ref = oracle_train_step(cfg)
+
+    class Without:
+        def __init__(self, skip): self.skip = skip
+        def __getattr__(self, name): return getattr(P, name)
+        def w2l_train_step(self, layers, w, b, dw, db, *rest):
+            return P.w2l_train_step(layers, w, b, dw, [None if i in self.skip else t for i, t in enumerate(db)], *rest)
+
+    for skip in ((), (1,), (3, 4), (1, 2, 3, 4), tuple(range(6))):
+        got = run_train_step(Without(skip), cfg)
+        for i in skip:
+            assert np.isnan(got["db"][i]).all()
+            got["db"][i] = ref["db"][i]
+        check_train_step(got, ref, "bf16")
+
+
+def test_two_streams_fp32(P):
+    """fp32 weight gradients on the helper stream, split ones and short ones among them, beside the caller's."""
+    layers = [dict(k=5, stride=2, cin=40, cout=256, glu=1), dict(k=9, stride=1, cin=128, cout=512, glu=1), dict(k=3, stride=1, cin=256, cout=140, glu=1),
+              dict(k=7, stride=1, cin=70, cout=256, glu=1), dict(k=1, stride=1, cin=128, cout=40, glu=0)]
+    assert _helpers(P, layers, 4, 301, "f32") == ([0, 1, 1, 1, 1], [0] * 5)
+    cfg = W.small_model(187, 4, 220, 301, 40, layers, False, 4, 20)
+    check_train_step(run_train_step(P, cfg), oracle_train_step(cfg), "f32")
 
 
 @pytest.mark.parametrize("width, classes", [(250, 100), (250, 29), (256, 29)])
@@ -227,15 +380,16 @@ def test_strided_first_layer_of_any_width(P, cout, k, stride):
     assert (room[cfg["weights"][0].size:] == -7.0).all()
 
 
-@pytest.mark.parametrize("net, dtype", [("shared", "bf16"), ("two streams", "bf16"), ("shared", "f32")])
+@pytest.mark.parametrize("net, dtype", [("shared", "bf16"), ("two streams", "bf16"), ("shared", "f32"), ("rounded up", "bf16")])
 def test_captured_step_replays_the_eager_one(P, net, dtype):
     """A train step recorded into a HIP graph leaves the eager step's bits at every replay, with eager work of the same
     kernels on other data, and synchronisations, in between."""
     import torch
     from workloads.device import empty, to_dev
-    widths = [(5, 128, 256)] * 3 if net == "shared" else [(3, 320, 256), (7, 128, 128), (5, 64, 128)]
+    widths = dict([("shared", [(5, 128, 256)] * 3), ("two streams", [(3, 320, 256), (7, 128, 128), (5, 64, 128)]), ("rounded up", [(5, 125, 250)] * 3)])[net]
     layers = [dict(k=5, stride=1, cin=40, cout=2 * widths[0][1], glu=1)] + [dict(k=k, stride=1, cin=a, cout=b, glu=1) for k, a, b in widths]
     layers += [dict(k=1, stride=1, cin=widths[-1][2] // 2, cout=29, glu=0)]
+    assert (P.w2l_train_step_layer_config(layers, 16, 98, P.W2L_BF16, 1)[1] != widths[0][2]) == (net == "rounded up")
 
     def state(seed):
         cfg = W.small_model(seed, 16, 70, 98, 40, layers, dtype == "bf16", 2, 8)

@@ -140,16 +140,19 @@ def test_fp32_train_step_split_and_ragged():
     check_train_step(run_train_step(P, cfg), oracle_train_step(cfg), "f32")
 
 
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_train_step_haloed_layers_off_the_chunks(dtype):
+@pytest.mark.parametrize("dtype, feat", [("f32", 40), ("bf16", 40), ("bf16", 42)])
+def test_train_step_haloed_layers_off_the_chunks(dtype, feat):
     """Gated layers on either side of 70 channels: x and dy of the weight gradient share the step's haloed layout, but
-    their lines are no whole chunks, so the reduction counts real frames (of several utterances)."""
+    their lines are no whole chunks, so the reduction counts real frames (of several utterances).  The bf16 step of 40
+    features is one of 96 channels; of 42, which is no multiple of 4, it is not."""
     import paper_1812_07625_amd as P
     from test_gpu_parity import check_train_step, oracle_train_step
     from workloads.device import run_train_step
-    layers = [dict(k=5, stride=1, cin=40, cout=140, glu=1), dict(k=5, stride=1, cin=70, cout=140, glu=1),
+    layers = [dict(k=5, stride=1, cin=feat, cout=140, glu=1), dict(k=5, stride=1, cin=70, cout=140, glu=1),
               dict(k=3, stride=1, cin=70, cout=140, glu=1), dict(k=1, stride=1, cin=70, cout=40, glu=0)]
-    cfg = W.small_model(52, 3, 120, 201, 40, layers, dtype == "bf16", 4, 20)
+    code = P.W2L_BF16 if dtype == "bf16" else P.W2L_F32
+    assert P.w2l_train_step_layer_config(layers, 3, 201, code, 1)[0] == (96 if (dtype, feat) == ("bf16", 40) else 70)
+    cfg = W.small_model(52, 3, 120, 201, feat, layers, dtype == "bf16", 4, 20)
     check_train_step(run_train_step(P, cfg), oracle_train_step(cfg), dtype)
 
 
@@ -260,6 +263,7 @@ def test_bf16_train_step_split_reductions():
     layers = [dict(k=13, stride=2, cin=40, cout=512, glu=1), dict(k=7, stride=1, cin=256, cout=512, glu=1),
               dict(k=5, stride=1, cin=256, cout=272, glu=1), dict(k=1, stride=1, cin=136, cout=512, glu=1),
               dict(k=1, stride=1, cin=256, cout=29, glu=0)]
+    assert [P.w2l_train_step_layer_config(layers, 3, 301, P.W2L_BF16, i)[1] for i in range(5)] == [512, 512, 272, 512, 29]
     cfg = W.small_model(53, 3, 200, 301, 40, layers, True, 4, 20)
     check_train_step(run_train_step(P, cfg), oracle_train_step(cfg), "bf16")
 
