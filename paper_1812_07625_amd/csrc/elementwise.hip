@@ -756,12 +756,12 @@ int finish_glu_bwd(const float* part, int parts, const void* y, void* dy, int B,
 // their own and as one, 200 / 1600 / 12800 frames: bf16, H = 256, 8 classes 82 -> 74, 98 -> 90, 205 -> 189; 64 classes 78 -> 77, 91 -> 90,
 // 207 -> 197; H = 2048 82 -> 81, 135 -> 132, 429 -> 417.  fp32, H = 256, 48 classes 64 -> 64, 86 -> 85, 184 -> 175; 64 classes 64 -> 65,
 // 85 -> 87, 183 -> 180; H = 1024 64 -> 65, 104 -> 102, 350 -> 321; H = 64, 51200 frames 431 -> 442: of fp32, beyond 48 classes, only
-// where there is enough of dh.
+// where there is enough of dh.  (A launch has fewer than 2^32 threads: 8 a frame of out_rows.)
 bool class_bwd_glu_ok(int B, int pitch, int slack, int C, int H, int dtype)
 {
     const bool bf16 = dtype == W2L_BF16;
     const long long rows = (long long)B * pitch;
-    return C <= 64 && (bf16 || C <= 48 || (H >= 128 && rows * H >= 1 << 20)) && H % (bf16 ? 8 : 4) == 0 && rows + slack < (1LL << 31);
+    return C <= 64 && (bf16 || C <= 48 || (H >= 128 && rows * H >= 1 << 20)) && H % (bf16 ? 8 : 4) == 0 && rows + slack <= (1LL << 29) - 32;
 }
 int class_bwd_glu(const float* dz, const void* w, const void* y, void* dy, int B, int Tp, int C, int H, int dtype, int pitch, int halo, int slack,
                   hipStream_t st, int live)

@@ -1,5 +1,7 @@
 """Host-only: the rules by which the convolution passes choose their kernels, asked through w2l_conv1d_launch_config
 (the functions that the entry points dispatch through)."""
+import ctypes
+
 import pytest
 
 import paper_1812_07625_amd as P
@@ -94,6 +96,15 @@ def test_strides_fold_only_for_the_matrix_kernels():
     which the other kernels cannot read."""
     copies = lambda T: P.w2l_conv1d_bwd_weight_workspace_bytes(64, T, 512, 64, 5, 2, P.W2L_BF16) > 64 * T * 512 * 2
     assert copies(8000) and not copies(40000)
+
+
+def test_class_layer_launch_has_fewer_than_2_32_threads():
+    """A thread of the class layer's launch has four frames of one group of channels, 32 groups a workgroup: networks of more
+    frames than 2^32 threads have room for keep the launches that walk."""
+    ok = P.raw._ZN3w2l16class_bwd_glu_okEiiiiii  # (B, pitch, slack, C, H, dtype)
+    ok.restype = ctypes.c_bool
+    assert ok(60000, 8940, 64, 2, 256, P.W2L_BF16) and not ok(60000, 8960, 64, 2, 256, P.W2L_BF16)
+    assert ok(1 << 10, (1 << 19) - 1, 512, 29, 128, F32) and not ok(1 << 10, 1 << 19, 0, 29, 128, F32)
 
 
 def _net(widths, k, feat=40, classes=29, stride=2, head=None):
