@@ -56,11 +56,12 @@ struct RowMap {
     int Tp, pitch, halo;
     long long real_frames;  // B * pitch
     int live = 1 << 30;     // channels behind the GLU that are there; the others are written as zeros
-    // v, values of channels c .., with zeros in those that are not there
+    // v, values of channels c .., with zeros in those that are not there.  (Rows that have such channels are whole vectors: kernels
+    // of one channel a thread go without: 0.4 us of the 81 of a layer of 3 x 731 frames, 200 -> 440, pass by pass.)
     template <int V>
     __device__ __forceinline__ void clear(int c, float (&v)[V]) const
     {
-        if (c + V <= live) return;
+        if (V == 1 || c + V <= live) return;
 #pragma unroll
         for (int j = 0; j < V; ++j) v[j] = c + j < live ? v[j] : 0.f;
     }
